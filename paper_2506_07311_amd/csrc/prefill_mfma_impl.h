@@ -1,5 +1,5 @@
 // Paged prefill (ragged packed queries, optional causal bound) for bf16 / fp16 pools with head_dim D = 128 or 64 on
-// gfx950 (and D = 256 for page sizes of 16 and more).  Internal header: the kernel templates; one translation unit
+// gfx950 (and D = 256, 80, 96, 112 for page sizes of 16 and more).  Internal header: the kernel templates; one translation unit
 // per head_dim instantiates them.  The text below describes D = 128.  D = 64 is the same kernel with half the steps: LDS rows keep their 256-byte stride and
 // swizzle, only the positions of the 8 existing 16-byte pieces are read (the fetch fills the other 8 positions
 // with repeats), the score product takes 4 steps instead of 8 and the value product covers 2 column blocks, not 4.  D = 256 doubles the
@@ -55,6 +55,13 @@ struct RowGeo {
     static constexpr int kTileB = kBN * kRowB;        // K part of a tile buffer; the V part follows
     static constexpr int kBufB = 2 * kTileB;
 };
+// head_dims 80, 96 and 112: rows hold 10, 12 or 14 pieces and the last column block of O is padded where D is not a
+// multiple of 32.  Every tile carries two-term weights: the portable kernel, which served these head_dims, keeps its
+// weights in fp32, and the second term (2^-17 of a weight) keeps the error at what the output's rounding leaves.
+// 2 prompts of 700 and 950 tokens, 32 / 32 heads, D = 96: 22 us for 9 GFLOP, bound by the start of a workgroup and its
+// heaviest row tile like every short prompt here; 1065 us on the portable kernel, which reads K and V again per row.
+template <int D>
+constexpr bool kTwoTermOnly = D % 64 != 0;
 // byte offset inside its row of logical 16-byte piece L of LDS row r
 __device__ __forceinline__ int piece_pos(int L, int r) { return 16 * ((L & 16) | ((L & 15) ^ swz(r))); }
 
@@ -170,7 +177,7 @@ struct RowMods {
 
 // M: compile-time policy of the hooks.  With score hooks the scores are first rewritten in place as
 // log2(e) * (cap(scale * s) + slope * (key - pos)) and the rest runs with a unit scale.
-template <bool MASK, bool FIRST, typename M, int T>
+template <bool MASK, bool FIRST, typename M, int KS, int T>
 __device__ __forceinline__ void half_softmax(f32x16& p, f32x16& s, f32x16 (&o)[T], float& m_ref, float& l, float sc,
                                              int32_t key0, int32_t nk, const RowMods& rm, const int32_t* docs)
 {
@@ -224,7 +231,7 @@ __device__ __forceinline__ void half_softmax(f32x16& p, f32x16& s, f32x16 (&o)[T
     if (FIRST) {
         // instruction order for the region that holds both score products and this half's softmax: the second
         // half's 8 matrix instructions are issued with the vector work of the first half's softmax in between
-        constexpr int KS = 2 * T;                             // matrix instructions per score product
+        // (KS = matrix instructions per score product)
         __builtin_amdgcn_sched_group_barrier(0x100, KS / 2, 0);
 #pragma unroll
         for (int i = 0; i < KS; ++i) {
@@ -365,29 +372,29 @@ __device__ __forceinline__ void half_scores(f32x16& s, const char* kbuf, int hal
 //     vector ALU:            softmax(h0)    softmax(h1)
 // buf = tile buffer (K rows, then V rows); key0 = first key of the tile + 4 * (lane/32); nk = keys this lane's
 // query may see (MASK only); sc = scale * log2(e) > 0.
-template <bool PRECISE, bool MASK, typename E, typename M, int T>
-__device__ __forceinline__ void attend_tile(const char* buf, const uint32_t (&kx)[2 * T], const uint32_t (&vx)[2 * T],
-                                            const uint4 (&qf)[2 * T], f32x16 (&o)[T], float& m, float& l, float sc,
+template <bool PRECISE, bool MASK, typename E, typename M, int T, int KS>
+__device__ __forceinline__ void attend_tile(const char* buf, const uint32_t (&kx)[KS], const uint32_t (&vx)[2 * T],
+                                            const uint4 (&qf)[KS], f32x16 (&o)[T], float& m, float& l, float sc,
                                             int32_t key0, int32_t nk, const RowMods& rm, const int32_t* docs)
 {
     f32x16 s0, s1, p;
     constexpr int TB = kBN * (T > 4 ? 512 : 256);
     if constexpr (T <= 4) {
         uint4 va[T], vb[T];
-        half_scores<E, 2 * T>(s0, buf, 0, kx, qf);
-        half_scores<E, 2 * T>(s1, buf, 1, kx, qf);
+        half_scores<E, KS>(s0, buf, 0, kx, qf);
+        half_scores<E, KS>(s1, buf, 1, kx, qf);
         load_v_frags<T>(va, vb, buf + TB, 0, vx);
-        half_softmax<MASK, true, M, T>(p, s0, o, m, l, sc, key0, nk, rm, docs);
+        half_softmax<MASK, true, M, KS, T>(p, s0, o, m, l, sc, key0, nk, rm, docs);
         half_pv_frags<PRECISE, E, T>(o, p, va, vb);
         load_v_frags<T>(va, vb, buf + TB, 1, vx);
-        half_softmax<MASK, false, M, T>(p, s1, o, m, l, sc, key0 + 32, nk, rm, docs + 32);
+        half_softmax<MASK, false, M, KS, T>(p, s1, o, m, l, sc, key0 + 32, nk, rm, docs + 32);
         half_pv_frags<PRECISE, E, T>(o, p, va, vb);
     } else {
-        half_scores<E, 2 * T>(s0, buf, 0, kx, qf);
-        half_scores<E, 2 * T>(s1, buf, 1, kx, qf);
-        half_softmax<MASK, true, M, T>(p, s0, o, m, l, sc, key0, nk, rm, docs);
+        half_scores<E, KS>(s0, buf, 0, kx, qf);
+        half_scores<E, KS>(s1, buf, 1, kx, qf);
+        half_softmax<MASK, true, M, KS, T>(p, s0, o, m, l, sc, key0, nk, rm, docs);
         half_pv<PRECISE, E, T>(o, p, buf + TB, 0, vx);
-        half_softmax<MASK, false, M, T>(p, s1, o, m, l, sc, key0 + 32, nk, rm, docs + 32);
+        half_softmax<MASK, false, M, KS, T>(p, s1, o, m, l, sc, key0 + 32, nk, rm, docs + 32);
         half_pv<PRECISE, E, T>(o, p, buf + TB, 1, vx);
     }
 }
@@ -404,7 +411,7 @@ __device__ __forceinline__ void prefill_body(
     const int32_t* __restrict__ seq_lens, int32_t batch, int32_t num_tiles, int32_t num_q_heads, int32_t max_blocks,
     float scale, int32_t causal, const PrefillPlan& plan, int32_t precise_keys, const OwnLengths& own)
 {
-    constexpr int KS = D / 16, T = D / 32;               // steps of a score product, 32-column blocks of O
+    constexpr int KS = D / 16, T = (D + 31) / 32;        // steps of a score product, 32-column blocks of O
     constexpr int RB = RowGeo<D>::kRowB;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -450,7 +457,7 @@ __device__ __forceinline__ void prefill_body(
     int32_t n_first = len;                                   // keys the tile's first row sees
     if (causal) n_first = min(len, len - q_len + (m0 >> lg) + 1);
     if (window > 0) n_first = min(n_first, causal ? window : 2 * window - 1);
-    const bool few_keys = n_first <= precise_keys ||
+    const bool few_keys = kTwoTermOnly<D> || n_first <= precise_keys ||
                           (M::kScore && plan.mods.alibi_slopes != nullptr) || (M::kDoc && plan.mods.doc_ids != nullptr) ||
                           M::kUser;
     if (few_keys != PRECISE) return;                        // the other instantiation handles this tile
@@ -551,10 +558,12 @@ __device__ __forceinline__ void prefill_body(
     }
     // fetch role of this lane.  256-byte rows: position lane%16 of rows 16*i + frow holds logical piece
     // (lane%16) ^ swz(frow) (a row of head_dim 64 has 8 pieces: the other 8 positions receive repeats that nobody
-    // reads).  512-byte rows: position lane%32 of rows 8*i + frow; the swizzle of that row depends on the parity of i.
+    // reads; head_dims 80, 96 and 112 repeat their first pieces likewise, and the columns of O beyond D that are computed
+    // from repeats are not stored).  512-byte rows: position lane%32 of rows 8*i + frow; the swizzle of that row depends on the parity of i.
     const int frow = D > 128 ? 2 * wave + (lane >> 5) : 4 * wave + (lane >> 4);
     const uint32_t head_off = (uint32_t)(kvh * cache.head_stride * 2);
-    const uint32_t lane_off = head_off + 16 * (((lane & 15) ^ swz(frow)) & (D / 8 - 1));
+    const int piece = (lane & 15) ^ swz(frow);
+    const uint32_t lane_off = head_off + 16 * (D <= 128 && piece >= D / 8 ? piece - D / 8 : piece);
     uint32_t lane_off2[2];
 #pragma unroll
     for (int par = 0; par < 2; ++par)
@@ -662,6 +671,7 @@ __device__ __forceinline__ void prefill_body(
         for (int t = 0; t < T; ++t)
 #pragma unroll
             for (int a = 0; a < 4; ++a) {
+                if (32 * t + 8 * a >= D) continue;           // columns that pad the last block
                 float4 w;
                 w.x = o[t][4 * a + 0] * inv;
                 w.y = o[t][4 * a + 1] * inv;
@@ -677,6 +687,7 @@ __device__ __forceinline__ void prefill_body(
     for (int t = 0; t < T; ++t)
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
+            if (32 * t + 8 * a >= D) continue;
             uint2 w;
             w.x = E::pack(o[t][4 * a + 0] * inv, o[t][4 * a + 1] * inv);
             w.y = E::pack(o[t][4 * a + 2] * inv, o[t][4 * a + 3] * inv);
@@ -709,11 +720,14 @@ __global__ __launch_bounds__(kThreads, D > 128 ? 1 : 2) void paged_prefill_mfma_
         own.q_end = cu_q_lens[s + 1];
         own.len = seq_lens[s];
     }
-    const int32_t precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal,
-                                                   (M::kWindow && plan.mods.window > 0) ? plan.mods.window : 0,
-                                                   (int)(threadIdx.x & 63));
-    prefill_body<false, UNIFORM, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, cu_q_lens, block_table, seq_lens, batch, num_tiles,
-                                 num_q_heads, max_blocks, scale, causal, plan, precise_keys, own);
+    int32_t precise_keys = 0;
+    if constexpr (!kTwoTermOnly<D>) {
+        precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal,
+                                         (M::kWindow && plan.mods.window > 0) ? plan.mods.window : 0,
+                                         (int)(threadIdx.x & 63));
+        prefill_body<false, UNIFORM, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, cu_q_lens, block_table, seq_lens, batch,
+                                     num_tiles, num_q_heads, max_blocks, scale, causal, plan, precise_keys, own);
+    }
     prefill_body<true, UNIFORM, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, cu_q_lens, block_table, seq_lens, batch, num_tiles,
                                 num_q_heads, max_blocks, scale, causal, plan, precise_keys, own);
 }
@@ -726,6 +740,15 @@ pa_status launch_prefill_mfma_dim(const AttnArgs& a, const PrefillPlan& plan, in
                                   hipStream_t stream)
 {
     const dim3 grid((uint32_t)blocks, 1, 1);
+    if constexpr (kTwoTermOnly<D>) {   // (prefill_mfma_supported takes no hooks and no pages below 16 tokens here)
+        if (a.has_mods || a.cache.page_size < 16) return PA_ERR_UNSUPPORTED;
+        auto kern = a.dtype == PA_DTYPE_BF16 ? paged_prefill_mfma_kernel<true, ElemBf16, NoMods, D>
+                                             : paged_prefill_mfma_kernel<true, ElemF16, NoMods, D>;
+        hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, stream, a.cache, (const uint16_t*)a.q, (uint16_t*)a.out, a.lse,
+                           a.cu_q_lens, a.block_table, a.seq_lens, a.batch, (int32_t)tiles, a.num_q_heads, a.max_blocks,
+                           a.scale, a.causal, plan);
+        return launch_status();
+    } else {
     // page sizes of 16 and more make the page of a 16-key group wave-uniform (scalar page translation)
     const bool uniform = a.cache.page_size >= 16;
     if (D > 128 && !uniform) return PA_ERR_UNSUPPORTED;   // 512-byte rows: two rows per load must share a page
@@ -768,6 +791,7 @@ pa_status launch_prefill_mfma_dim(const AttnArgs& a, const PrefillPlan& plan, in
                        a.cu_q_lens, a.block_table, a.seq_lens, a.batch, (int32_t)tiles, a.num_q_heads, a.max_blocks,
                        a.scale, a.causal, plan);
     return launch_status();
+    }
 }
 
 }  // namespace pa
