@@ -102,6 +102,10 @@ pa_status paged_kv_gather(const pa_kv_cache_desc* cache, void* out_k, void* out_
  * decode (the bound then covers the decode entry points only; a prefill call
  * with total_q <= batch that is not plain decode keeps its few-query sequences
  * on the prefill kernel when the workspace has no room for their partials).
+ * For calls of several sequences with contexts of 4096 tokens and more it
+ * includes the room in which a jagged call cuts its long contexts evenly over
+ * the GPU (about 135 MB at head_dim 128); a workspace without that room is
+ * accepted and such calls run on the plain grid.
  * Always a multiple of 256; never 0.  Depends on the calling thread's
  * pa_set_option knobs and on the current device's compute-unit count.
  */

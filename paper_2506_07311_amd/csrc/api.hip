@@ -316,6 +316,57 @@ size_t part_lse_bytes(int64_t rows, int32_t hq, int32_t nsplit)
     return align256((size_t)rows * hq * nsplit * sizeof(float));
 }
 
+// Partials of the prefill kernel's work-list mode.
+size_t list_bytes(int32_t d)
+{
+    return align256(prefill_list_slots() * prefill_list_slot_floats(d) * sizeof(float)) +
+           align256((size_t)prefill_list_slots() * 128 * sizeof(float));
+}
+
+// Can a call of these sizes take the work-list mode?  (More than one sequence, a context long enough to cut.)
+bool list_possible(int32_t batch, int32_t total_q, int32_t max_seq_len)
+{
+    return g_opt.prefill_chunk_tokens == 0 && batch > 1 && total_q > batch && max_seq_len >= prefill_list_min_context() &&
+           max_seq_len < (1 << 28);
+}
+
+// The work-list mode replaces the plain grid where that is unbalanced: sequences with different query counts, contexts at
+// least twice as long as the longest query range (chunks of long prompts, not whole prompts, whose heaviest-first grid
+// balances itself: 4 x 2048 loses 2-3 % in sequence order), and too few row tiles to average the lengths out --
+// estimated as if the queries sat in as few sequences as max_q_len allows, since the host knows no lengths.
+constexpr int64_t kListMaxWGs = 2048;
+
+bool list_pays(const AttnArgs& a, int32_t log2_pack)
+{
+    if (!list_possible(a.batch, a.total_q, a.max_seq_len) || !prefill_list_supported(a)) return false;
+    if ((int64_t)a.batch * a.max_q_len == a.total_q || a.max_seq_len / 2 < a.max_q_len) return false;
+    const int64_t live = (a.total_q + a.max_q_len - 1) / (a.max_q_len > 0 ? a.max_q_len : 1);
+    return ((((int64_t)a.total_q << log2_pack) / 128) + live) * (a.num_q_heads >> log2_pack) < kListMaxWGs;
+}
+
+// What a call's workspace has to hold.  (paged_attention_workspace_bytes adds the room of the prefill kernel's
+// work-list mode, an optimisation that a smaller workspace does without.)
+size_t required_workspace_bytes(int32_t batch, int32_t num_q_heads, int32_t head_dim, int32_t total_q,
+                                int32_t max_seq_len)
+{
+    if (batch <= 0 || num_q_heads <= 0 || head_dim <= 0 || total_q <= 0) return 256;
+    if (total_q <= batch) {
+        // decode: partials of the portable kernel's chunks, or of the tile stream's workgroups
+        const int32_t ns = nsplit_bound(max_seq_len);
+        const size_t chunked = part_o_bytes(batch, num_q_heads, head_dim, ns) + part_lse_bytes(batch, num_q_heads, ns);
+        const size_t stream = stream_workspace_bytes(batch, num_q_heads, head_dim,
+                                                     stream_wgs_bound(batch, num_q_heads, max_seq_len));
+        const size_t split = short_split_workspace_bytes(batch, num_q_heads, head_dim);
+        const size_t need = chunked > stream ? chunked : stream;
+        return need > split ? need : split;
+    }
+    // prefill: partials of the context split, when the sizes make it split, and of the few-query route
+    const int32_t np = prefill_nsplit_bound(batch, num_q_heads, total_q, max_seq_len);
+    const size_t split = np > 1 ? part_o_bytes(total_q, num_q_heads, head_dim, np) + part_lse_bytes(total_q, num_q_heads, np)
+                                : 0;
+    return split + small_route_workspace_bytes(batch, num_q_heads, head_dim);
+}
+
 // The workspace of a call.  The public entry points promise the bound paged_attention_workspace_bytes() and are
 // checked against it (bound = true); the entry point that brings its own scratch array is checked against what the
 // call's plan really uses.
@@ -355,7 +406,7 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
         m.doc_stride = mods->doc_ids ? mods->doc_stride : 0;
     }
     if (ws.bound) {
-        const size_t need = paged_attention_workspace_bytes(batch, num_q_heads, cache->head_dim, total_q, max_seq_len);
+        const size_t need = required_workspace_bytes(batch, num_q_heads, cache->head_dim, total_q, max_seq_len);
         if (!ws.ptr || ws.bytes < need) return PA_ERR_WORKSPACE_TOO_SMALL;
     }
     if ((uintptr_t)ws.ptr & 255) return PA_ERR_INVALID_ARG;
@@ -387,6 +438,8 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
     a.stream_split = 0;
     a.num_wgs = 0;
     a.seg_first = a.seg_last = nullptr;
+    a.list_items = 0;
+    a.list_o = a.list_lse = nullptr;
     a.skip_small = 0;
     a.mods = m;
     a.has_mods = m.window > 0 || m.softcap > 0.f || m.alibi_slopes || m.doc_ids || m.user_mod != 0;
@@ -459,11 +512,22 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
         const bool uniform_q = (int64_t)batch * max_q_len == total_q;      // every sequence has max_q_len queries
         bool may_have_small = !g_opt.no_small_q_route && decode_mfma_supported(a) && G <= 16 &&
                               !(uniform_q && (int64_t)max_q_len * G > 16);
-        const SplitPlan pp = plan_prefill(batch, num_q_heads, prefill_mfma_log2_pack(num_q_heads, cache->num_kv_heads),
-                                          total_q, max_seq_len, cache->page_size);
-        const size_t split_bytes =
+        const int32_t lg = prefill_mfma_log2_pack(num_q_heads, cache->num_kv_heads);
+        SplitPlan pp = plan_prefill(batch, num_q_heads, lg, total_q, max_seq_len, cache->page_size);
+        size_t split_bytes =
             pp.nsplit > 1 ? part_o_bytes(total_q, num_q_heads, d, pp.nsplit) + part_lse_bytes(total_q, num_q_heads, pp.nsplit)
                           : 0;
+        // (a workspace that holds what is required and not the list's partials as well keeps the plain grid)
+        int64_t list_items = 0;
+        if (list_pays(a, lg) &&
+            ws.bytes >= required_workspace_bytes(batch, num_q_heads, d, total_q, max_seq_len) + list_bytes(d))
+            list_items = prefill_list_items(a);
+        if (list_items * (num_q_heads >> lg) > 0x7fffffffLL) list_items = 0;
+        if (list_items > 0) {
+            pp.chunk = max_seq_len;
+            pp.nsplit = 1;
+            split_bytes = list_bytes(d);
+        }
         int32_t small_wgs = 0;
         if (may_have_small) {
             const int32_t head_groups = cache->num_kv_heads / decode_mfma_heads_per_wg(cache->num_kv_heads, d);
@@ -483,8 +547,16 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
             b.plan = pp;
             b.part_o = reinterpret_cast<float*>(base);
             b.part_lse = reinterpret_cast<float*>(base + part_o_bytes(total_q, num_q_heads, d, pp.nsplit));
+            if (list_items > 0) {
+                a.list_items = b.list_items = (int32_t)list_items;
+                a.list_o = b.list_o = reinterpret_cast<float*>(base);
+                a.list_lse = b.list_lse = reinterpret_cast<float*>(
+                    base + align256(prefill_list_slots() * prefill_list_slot_floats(d) * sizeof(float)));
+                a.skip_small = b.skip_small;
+            }
             st = launch_prefill_mfma(b, s);
             if (st != PA_OK) return st;
+            if (list_items > 0 && !may_have_small) return launch_merge(a, s);
         }
         if (may_have_small) {
             AttnArgs b = a;
@@ -602,22 +674,9 @@ pa_status pa_debug_check(const pa_kv_cache_desc* cache, const int32_t* block_tab
 size_t paged_attention_workspace_bytes(int32_t batch, int32_t num_q_heads, int32_t head_dim, int32_t total_q,
                                        int32_t max_seq_len)
 {
-    if (batch <= 0 || num_q_heads <= 0 || head_dim <= 0 || total_q <= 0) return 256;
-    if (total_q <= batch) {
-        // decode: partials of the portable kernel's chunks, or of the tile stream's workgroups
-        const int32_t ns = nsplit_bound(max_seq_len);
-        const size_t chunked = part_o_bytes(batch, num_q_heads, head_dim, ns) + part_lse_bytes(batch, num_q_heads, ns);
-        const size_t stream = stream_workspace_bytes(batch, num_q_heads, head_dim,
-                                                     stream_wgs_bound(batch, num_q_heads, max_seq_len));
-        const size_t split = short_split_workspace_bytes(batch, num_q_heads, head_dim);
-        const size_t need = chunked > stream ? chunked : stream;
-        return need > split ? need : split;
-    }
-    // prefill: partials of the context split, when the sizes make it split, and of the few-query route
-    const int32_t np = prefill_nsplit_bound(batch, num_q_heads, total_q, max_seq_len);
-    const size_t split = np > 1 ? part_o_bytes(total_q, num_q_heads, head_dim, np) + part_lse_bytes(total_q, num_q_heads, np)
-                                : 0;
-    return split + small_route_workspace_bytes(batch, num_q_heads, head_dim);
+    const size_t need = required_workspace_bytes(batch, num_q_heads, head_dim, total_q, max_seq_len);
+    const bool sized = batch > 0 && num_q_heads > 0 && head_dim > 0 && head_dim <= 256 && total_q > 0;
+    return need + (sized && list_possible(batch, total_q, max_seq_len) ? list_bytes(head_dim) : 0);
 }
 
 pa_status paged_attention_decode(const pa_kv_cache_desc* cache, const void* q, void* out, float* lse,

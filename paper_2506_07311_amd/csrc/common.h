@@ -150,6 +150,10 @@ struct AttnArgs {
     int32_t num_wgs;
     int32_t* seg_first;
     int32_t* seg_last;
+    int32_t list_items;      // prefill kernel: > 0 = work-list mode with at most this many (tile, chunk) items per head
+                             // group (see prefill_tiles.h); partials by slot in list_o / list_lse
+    float* list_o;
+    float* list_lse;
     int32_t skip_small;      // prefill kernel: leave sequences with q_len * G <= 16 to the decode kernel
     ModArgs mods;
     bool has_mods;
@@ -183,7 +187,15 @@ constexpr int32_t kShortMaxUnits = 4096;   // (sequence, KV head, slice) units o
 bool prefill_mfma_supported(const AttnArgs& a);
 int32_t prefill_mfma_log2_pack(int32_t num_q_heads, int32_t num_kv_heads);
 pa_status launch_prefill_mfma(const AttnArgs& a, hipStream_t stream);
-// LSE merge of the split partials into out / lse.
+// Its work-list mode (prefill_tiles.h): partial slots and floats per slot (plus 128 LSEs), the shortest context it may
+// cut, and the (tile, chunk) items per head group of a call.
+bool prefill_list_supported(const AttnArgs& a);
+int32_t prefill_list_slots();
+size_t prefill_list_slot_floats(int32_t head_dim);
+int32_t prefill_list_min_context();
+int64_t prefill_list_items(const AttnArgs& a);
+// LSE merge of the split partials into out / lse: those of the plan's chunks, of the tile stream (stream_split), of the
+// prefill kernel's work list (list_items > 0), or of the last two in one launch.
 pa_status launch_merge(const AttnArgs& a, hipStream_t stream);
 
 // ---------------------------------------------------------------------------------------------

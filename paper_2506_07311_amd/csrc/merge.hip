@@ -2,7 +2,7 @@
 // With partial c holding the normalised output o_c and lse_c = log sum_j exp(score_j) over its keys,
 //   M = max_c lse_c,  w_c = exp(lse_c - M),  out = sum_c w_c o_c / sum_c w_c,  lse = M + log sum_c w_c.
 // Only the ceil(n_keys / chunk) chunks that hold keys are read; a row without keys gets out = 0, lse = -inf.
-#include "common.h"
+#include "prefill_tiles.h"
 
 namespace pa {
 
@@ -89,6 +89,68 @@ __global__ __launch_bounds__(256) void paged_attention_merge_kernel(
 // with independent loads (eight in flight), so the kernel costs a few memory latencies, not one per partial.
 constexpr int kMergeThreads = 128;
 
+// Partials of the prefill kernel's work list (prefill_tiles.h): blocks [0, blocks) of the launch.
+struct ListMerge {
+    const float* part_o;
+    const float* part_lse;
+    int32_t blocks;          // a multiple of 8; 0 = no work list
+    int32_t batch, heads, log2_pack, small_group, unit, causal;
+};
+
+// Eight workgroups of two waves share a row tile of a sequence that is cut: 32 rows each and every second pair of a lane's
+// 16-byte accumulator pieces, so that a few hundred tiles fill the machine; consecutive lanes read consecutive 16 bytes.
+// Bound by reading the partials once (21 us for the 67 MB of four 512-token chunks on 2.7k to 31k tokens).
+template <int OUT>
+__device__ void merge_list(const ListMerge& p, int32_t block, void* __restrict__ out, float* __restrict__ lse,
+                           const int32_t* __restrict__ cu_q_lens, const int32_t* __restrict__ seq_lens,
+                           int32_t num_q_heads, int32_t d)
+{
+    using namespace prefill;
+    const int lane = threadIdx.x & 63;
+    const int32_t quarter = block & 3, piece = (block >> 1 & 2) + (int32_t)(threadIdx.x >> 6);
+    const int32_t lg = p.log2_pack, T = (d + 31) / 32;
+    const WorkList list = make_list(cu_q_lens, seq_lens, p.batch, lg, p.small_group, p.heads, p.unit, lane);
+    for (int32_t index = block >> 3;; index += p.blocks >> 3) {
+        const int32_t hg = index % p.heads;
+        ListItem it;
+        if (!list_locate<true>(it, list, cu_q_lens, seq_lens, index / p.heads, lane)) return;
+        const int32_t q_begin = cu_q_lens[it.s], q_len = cu_q_lens[it.s + 1] - q_begin, len = seq_lens[it.s];
+        const int32_t n_rows = q_len << lg, m0 = it.tile * kBM;
+        const int32_t row = m0 + 32 * quarter + (lane & 31);
+        // the chunks that hold keys of this row tile (the others left nothing behind)
+        int32_t nk = len;
+        if (p.causal) nk = min(len, len - q_len + ((min(m0 + kBM, n_rows) - 1) >> lg) + 1);
+        const int32_t n = (max(nk, 0) + list.chunk - 1) / list.chunk;
+        if (row >= n_rows) continue;                          // (nothing below is shared between lanes)
+        const float* pl = p.part_lse + 32 * quarter + (lane & 31);
+        float M = -INFINITY;
+        for (int32_t c = 0; c < n; ++c) M = fmaxf(M, pl[(int64_t)list_slot(it, c, p.heads, hg) * kBM]);
+        const bool none = M == -INFINITY;
+        float wsum = 0.f;
+        for (int32_t c = 0; c < n && !none; ++c) wsum += expf(pl[(int64_t)list_slot(it, c, p.heads, hg) * kBM] - M);
+        const int64_t o_row = (int64_t)(q_begin + (row >> lg)) * num_q_heads + (hg << lg) + (row & ((1 << lg) - 1));
+        const float4* po = reinterpret_cast<const float4*>(p.part_o) + quarter * (T * 256) + piece * 64 + lane;
+        for (int32_t t = 0; t < T; ++t) {
+            const int32_t col = 32 * t + 8 * piece + 4 * (lane >> 5);
+            if (col >= d) break;
+            float4 acc = float4{0.f, 0.f, 0.f, 0.f};
+            for (int32_t c = 0; c < n && !none; ++c) {
+                const int64_t slot = list_slot(it, c, p.heads, hg);
+                const float w = expf(pl[slot * kBM] - M);
+                const float4 v = po[slot * (T * 1024) + t * 256];
+                acc.x = fmaf(w, v.x, acc.x);
+                acc.y = fmaf(w, v.y, acc.y);
+                acc.z = fmaf(w, v.z, acc.z);
+                acc.w = fmaf(w, v.w, acc.w);
+            }
+            const float4 r = none ? float4{0.f, 0.f, 0.f, 0.f}
+                                  : float4{acc.x / wsum, acc.y / wsum, acc.z / wsum, acc.w / wsum};
+            store_out4<OUT>(out, o_row * d + col, r);
+        }
+        if (lse && piece == 0 && lane < 32) lse[o_row] = none ? -INFINITY : M + logf(wsum);
+    }
+}
+
 // RAGGED (the few-query sequences of a prefill call): one workgroup per (sequence, KV head, column); column
 // c of the 16 is query c / G, head c % G of the group; partials are 16 rows per KV head; sequences that did not
 // take that path (q_len * G > 16) are skipped.
@@ -97,14 +159,19 @@ __global__ __launch_bounds__(kMergeThreads) void paged_attention_merge_stream_ke
     const float* __restrict__ part_o, const float* __restrict__ part_lse, void* __restrict__ out,
     float* __restrict__ lse, const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ seg_first,
     const int32_t* __restrict__ seg_last, int32_t num_q_heads, int32_t d, const int32_t* __restrict__ cu_q_lens,
-    int32_t num_kv_heads)
+    int32_t num_kv_heads, ListMerge list)
 {
+    if (RAGGED && (int32_t)blockIdx.x < list.blocks) {
+        merge_list<OUT>(list, blockIdx.x, out, lse, cu_q_lens, seq_lens, num_q_heads, d);
+        return;
+    }
+    const int32_t block = RAGGED ? (int32_t)blockIdx.x - list.blocks : (int32_t)blockIdx.x;
     __shared__ float w_s[kMaxDecodeWGs + 1];
     __shared__ float red[4];
     const int32_t rows = RAGGED ? num_kv_heads * 16 : num_q_heads;   // partial rows per (workgroup, sequence)
-    const int32_t s = blockIdx.x / rows;
-    const int32_t h = blockIdx.x % rows;
-    int64_t o_idx = blockIdx.x;
+    const int32_t s = block / rows;
+    const int32_t h = block % rows;
+    int64_t o_idx = block;
     if (RAGGED) {
         const int32_t G = num_q_heads / num_kv_heads;
         const int32_t q_len = cu_q_lens[s + 1] - cu_q_lens[s];
@@ -169,12 +236,29 @@ pa_status launch_merge(const AttnArgs& a, hipStream_t stream)
 {
     const int64_t blocks = (int64_t)a.total_q * a.num_q_heads;
     if (blocks > 0x7fffffffLL) return PA_ERR_UNSUPPORTED;
-    ProfileScope prof("paged_attention_merge_kernel", stream);
-    if (a.stream_split) {
+    ProfileScope prof(a.list_items > 0 ? "paged_attention_merge_list_kernel" : "paged_attention_merge_kernel", stream);
+    if (a.stream_split || a.list_items > 0) {
         // tile-stream partials of the MFMA decode kernel (16-bit pools only); with cu_q_lens: the few-query
         // sequences of a prefill call
         const bool ragged = a.cu_q_lens != nullptr;
-        const int64_t sblocks = ragged ? (int64_t)a.batch * a.cache.num_kv_heads * 16 : blocks;
+        // (stream and list partials of one call are merged by one launch: 4 us less than two on a mixed batch)
+        ListMerge list = {};
+        if (a.list_items > 0) {
+            const int32_t G = a.num_q_heads / a.cache.num_kv_heads;
+            list.part_o = a.list_o;
+            list.part_lse = a.list_lse;
+            list.batch = a.batch;
+            list.log2_pack = prefill_mfma_log2_pack(a.num_q_heads, a.cache.num_kv_heads);
+            list.heads = a.num_q_heads >> list.log2_pack;
+            list.small_group = a.skip_small ? G : prefill::kNoSmallGroup;
+            list.unit = a.cache.page_size > prefill::kBN ? a.cache.page_size : prefill::kBN;
+            list.causal = a.causal;
+            // row tiles of the sequences that are cut: each has more keys than a chunk
+            const int64_t most = prefill::kListTarget / list.heads + 1;
+            const int64_t eighths = 8 * list.heads * (most < a.list_items ? most : a.list_items);
+            list.blocks = (int32_t)(eighths < prefill::kListMergeGrid ? eighths : prefill::kListMergeGrid);
+        }
+        const int64_t sblocks = list.blocks + (!a.stream_split ? 0 : ragged ? (int64_t)a.batch * a.cache.num_kv_heads * 16 : blocks);
         if (sblocks > 0x7fffffffLL || a.dtype == PA_DTYPE_F32) return PA_ERR_UNSUPPORTED;
         auto kern = a.dtype == PA_DTYPE_BF16
                         ? (ragged ? paged_attention_merge_stream_kernel<PA_DTYPE_BF16, true>
@@ -183,7 +267,7 @@ pa_status launch_merge(const AttnArgs& a, hipStream_t stream)
                                   : paged_attention_merge_stream_kernel<PA_DTYPE_F16, false>);
         hipLaunchKernelGGL(kern, dim3((uint32_t)sblocks), dim3(kMergeThreads), 0, stream, a.part_o, a.part_lse, a.out,
                            a.lse, a.seq_lens, a.seg_first, a.seg_last, a.num_q_heads, a.cache.head_dim, a.cu_q_lens,
-                           a.cache.num_kv_heads);
+                           a.cache.num_kv_heads, list);
         return launch_status();
     }
     auto kern = a.dtype == PA_DTYPE_BF16  ? paged_attention_merge_kernel<PA_DTYPE_BF16>

@@ -46,9 +46,28 @@ int32_t prefill_mfma_log2_pack(int32_t num_q_heads, int32_t num_kv_heads)
     return (1 << lg) == g ? lg : 0;
 }
 
+int32_t prefill_list_slots() { return 2 * kListTarget; }
+size_t prefill_list_slot_floats(int32_t head_dim) { return list_slot_floats(head_dim); }
+int32_t prefill_list_min_context() { return 2 * kListMinTiles * kBN; }
+
+// (the work list has no instantiations with hooks or for pages below 16 tokens)
+bool prefill_list_supported(const AttnArgs& a) { return !a.has_mods && a.cache.page_size >= 16; }
+
+// Items: every chunk holds at least 1 / kListTarget of the call's work, plus one rounded-up chunk per row tile.
+int64_t prefill_list_items(const AttnArgs& a)
+{
+    const int32_t lg = prefill_mfma_log2_pack(a.num_q_heads, a.cache.num_kv_heads);
+    return kListTarget / (a.num_q_heads >> lg) + (((int64_t)a.total_q << lg) / kBM) +
+           (a.batch < a.total_q ? a.batch : a.total_q) + 1;
+}
+
 pa_status launch_prefill_mfma(const AttnArgs& a, hipStream_t stream)
 {
     PrefillPlan plan;
+    plan.list_items = a.list_items;
+    plan.list_o = a.list_o;
+    plan.list_lse = a.list_lse;
+    plan.list_unit = a.cache.page_size > kBN ? a.cache.page_size : kBN;
     plan.log2_pack = prefill_mfma_log2_pack(a.num_q_heads, a.cache.num_kv_heads);
     plan.chunk = a.plan.chunk;
     plan.nsplit = a.plan.nsplit;
@@ -59,7 +78,9 @@ pa_status launch_prefill_mfma(const AttnArgs& a, hipStream_t stream)
     if (plan.nsplit > 1 && (plan.chunk % kBN != 0 || plan.chunk % a.cache.page_size != 0)) return PA_ERR_INVALID_ARG;
     const int64_t tiles = (((int64_t)a.max_q_len << plan.log2_pack) + kBM - 1) / kBM;
     if (tiles <= 0) return PA_OK;
-    const int64_t blocks = tiles * plan.nsplit * (a.num_q_heads >> plan.log2_pack) * a.batch;
+    const int32_t heads = a.num_q_heads >> plan.log2_pack;
+    int64_t blocks = plan.list_items > 0 ? (int64_t)plan.list_items * heads : tiles * plan.nsplit * heads * a.batch;
+    if (plan.list_items > 0 && blocks > kListGrid) blocks = kListGrid;
     if (blocks > 0x7fffffffLL) return PA_ERR_UNSUPPORTED;
     {
         ProfileScope prof("paged_prefill_mfma_kernel", stream);
@@ -72,7 +93,7 @@ pa_status launch_prefill_mfma(const AttnArgs& a, hipStream_t stream)
             case 256: st = launch_prefill_mfma_dim<256>(a, plan, blocks, tiles, stream); break;
             default: st = launch_prefill_mfma_dim<128>(a, plan, blocks, tiles, stream); break;
         }
-        if (st != PA_OK || plan.nsplit == 1) return st;
+        if (st != PA_OK || plan.nsplit == 1) return st;    // (a work list is merged by launch_merge)
     }
     return launch_merge(a, stream);
 }

@@ -399,41 +399,33 @@ __device__ __forceinline__ void attend_tile(const char* buf, const uint32_t (&kx
     }
 }
 
-// Query range and context length of the sequence a workgroup works on.
-struct OwnLengths {
-    int32_t q_begin, q_end, len;
+// What a workgroup works on: sequence, its query range and context length, row tile, head group, and its chunk of the
+// context (chunks == 1: all of it).
+struct WorkItem {
+    int32_t s, q_begin, q_end, len;
+    int32_t tile, hg;
+    int32_t split, chunks, chunk;
+    int32_t slot;            // work-list mode: where a partial goes (-1: the plain layout)
 };
 
-template <bool PRECISE, bool UNIFORM, typename E, typename M, int D>
+template <bool PRECISE, bool UNIFORM, bool LIST, typename E, typename M, int D>
 __device__ __forceinline__ void prefill_body(
     char* buf0, char* buf1, int32_t* docs0, int32_t* docs1, const CacheView& cache, const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float* __restrict__ lse,
-    const int32_t* __restrict__ cu_q_lens, const int32_t* __restrict__ block_table,
-    const int32_t* __restrict__ seq_lens, int32_t batch, int32_t num_tiles, int32_t num_q_heads, int32_t max_blocks,
-    float scale, int32_t causal, const PrefillPlan& plan, int32_t precise_keys, const OwnLengths& own)
+    const int32_t* __restrict__ block_table, int32_t num_q_heads, int32_t max_blocks, float scale, int32_t causal, const PrefillPlan& plan, int32_t precise_keys,
+    const WorkItem& own, const int tid)
 {
     constexpr int KS = D / 16, T = (D + 31) / 32;        // steps of a score product, 32-column blocks of O
     constexpr int RB = RowGeo<D>::kRowB;
-    const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int ql = lane & 31, hh = lane >> 5;
     // Rows of a workgroup's 128-row tile are (query, head) pairs: the 2^log2_pack query heads packed into a tile
     // share one KV head, row r of a sequence is query r >> log2_pack, packed head r & (pack - 1).
     const int32_t lg = plan.log2_pack;
-    const int32_t heads = num_q_heads >> lg;                 // head groups along the grid
-    // Workgroups are dispatched in blockIdx.x order: the row-tile index is the slowest-varying part and runs
-    // backwards, so the whole grid is handed out heaviest (latest causal tiles) first; the context chunks of a
-    // tile follow each other.
-    const int32_t hb = heads * batch;
-    const int32_t slow = (int32_t)(blockIdx.x / hb);
-    const int32_t tile = num_tiles - 1 - slow / plan.nsplit;
-    const int32_t split = slow % plan.nsplit;
-    const int32_t rest = blockIdx.x % hb;
-    const int32_t s = rest / heads;
-    const int32_t hg = rest % heads;
+    const int32_t s = own.s, hg = own.hg, split = own.split;
     const int32_t q_begin = own.q_begin;                     // (this sequence's lengths: fetched by the kernel ahead of
     const int32_t q_len = own.q_end - own.q_begin;           //  everything else, see there)
     const int32_t n_rows = q_len << lg;
-    const int32_t m0 = tile * kBM;
+    const int32_t m0 = own.tile * kBM;
     if (m0 >= n_rows) return;
     if (plan.skip_small && q_len * (num_q_heads / cache.num_kv_heads) <= 16) return;
     const int32_t len = own.len;
@@ -465,9 +457,9 @@ __device__ __forceinline__ void prefill_body(
     // reads only the chunks that hold keys of a row)
     // (without a causal bound a window also cuts the END of a row's range, which the merge does not know: those
     // chunks must leave explicit empty partials, so the workgroup goes on with zero tiles)
-    if (plan.nsplit > 1 && split * plan.chunk >= nk_wg && !(window > 0 && !causal)) return;
-    const int32_t k_begin = max(split * plan.chunk, k_lo);
-    const int32_t k_end = min(nk_wg, split * plan.chunk + plan.chunk);
+    if (own.chunks > 1 && split * own.chunk >= nk_wg && !(window > 0 && !causal)) return;
+    const int32_t k_begin = max(split * own.chunk, k_lo);
+    const int32_t k_end = min(nk_wg, split * own.chunk + own.chunk);
 
     const int32_t G = num_q_heads / cache.num_kv_heads;
     const int32_t* table = block_table + (int64_t)s * max_blocks;
@@ -663,7 +655,22 @@ __device__ __forceinline__ void prefill_body(
     if (!q_valid) return;
     const float inv = l > 0.f ? 1.f / l : 0.f;
     // o[t][r]: column 32*t + 8*(r/4) + 4*hh + r%4 of this lane's query
-    if (plan.nsplit > 1) {
+    if (LIST && own.slot >= 0) {
+        // work-list mode: normalised accumulators lane by lane (whole cache lines per store), LSE per row
+        float4* po = reinterpret_cast<float4*>(plan.list_o) + (int64_t)own.slot * (list_slot_floats(D) / 4) +
+                     wave * (T * 4 * 64) + lane;
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+                po[(4 * t + a) * 64] = float4{o[t][4 * a + 0] * inv, o[t][4 * a + 1] * inv, o[t][4 * a + 2] * inv,
+                                              o[t][4 * a + 3] * inv};
+        if (hh == 0)
+            plan.list_lse[(int64_t)own.slot * kBM + 32 * wave + ql] =
+                l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
+        return;
+    }
+    if (!LIST && own.chunks > 1) {
         // partial of this chunk: normalised output in fp32 and the natural-log LSE over the chunk's keys
         const int64_t pidx = row * plan.nsplit + split;
         float* prow = plan.part_o + pidx * D;
@@ -698,7 +705,8 @@ __device__ __forceinline__ void prefill_body(
 
 // Both instantiations live in one kernel as two separate code paths (each with its own tile loop); a
 // workgroup runs exactly one of them, decided by its context length.
-template <bool UNIFORM, typename E, typename M, int D>
+// LIST: the work-list mode of prefill_tiles.h.
+template <bool UNIFORM, typename E, typename M, int D, bool LIST = false>
 __global__ __launch_bounds__(kThreads, D > 128 ? 1 : 2) void paged_prefill_mfma_kernel(
     CacheView cache, const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float* __restrict__ lse,
     const int32_t* __restrict__ cu_q_lens, const int32_t* __restrict__ block_table,
@@ -712,24 +720,68 @@ __global__ __launch_bounds__(kThreads, D > 128 ? 1 : 2) void paged_prefill_mfma_
     // The workgroup's own lengths are requested first (scalar loads), the scan of every sequence's lengths for the
     // two-term rule right behind them (vector loads): one round trip to memory instead of three in a row in front
     // of the query and block-table loads that depend on them.
-    OwnLengths own;
-    {
-        const int32_t heads = num_q_heads >> plan.log2_pack;
-        const int32_t s = (int32_t)(blockIdx.x % (uint32_t)(heads * batch)) / heads;
-        own.q_begin = cu_q_lens[s];
-        own.q_end = cu_q_lens[s + 1];
-        own.len = seq_lens[s];
+    WorkItem own;
+    const int32_t heads = num_q_heads >> plan.log2_pack;
+    if constexpr (LIST) {
+        // A workgroup steps over the list by the size of the grid.  Between two items nothing has to be waited for: a
+        // tile loop ends with the barrier behind its last read of LDS.  The thread index is made opaque for each item:
+        // what the body derives from it would otherwise be kept in registers across the loop, which spills.
+        const WorkList list = make_list(cu_q_lens, seq_lens, batch, plan.log2_pack,
+                                        plan.skip_small ? num_q_heads / cache.num_kv_heads : kNoSmallGroup, heads,
+                                        plan.list_unit, (int)(threadIdx.x & 63));
+        int32_t precise_keys = 0;
+        if constexpr (!kTwoTermOnly<D>)
+            precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal, 0, (int)(threadIdx.x & 63));
+        for (uint32_t index = blockIdx.x;; index += gridDim.x) {
+            int tid = threadIdx.x;
+            asm volatile("" : "+v"(tid));
+            ListItem it;
+            if (!list_locate<false>(it, list, cu_q_lens, seq_lens, (int32_t)(index / (uint32_t)heads), tid & 63)) return;
+            own.s = it.s;
+            own.hg = (int32_t)(index % (uint32_t)heads);
+            own.tile = it.tile;
+            own.split = it.split;
+            own.chunks = it.chunks;
+            own.chunk = list.chunk;
+            own.slot = it.chunks > 1 ? list_slot(it, it.split, heads, own.hg) : -1;
+            own.q_begin = cu_q_lens[it.s];
+            own.q_end = cu_q_lens[it.s + 1];
+            own.len = seq_lens[it.s];
+            if constexpr (!kTwoTermOnly<D>)
+                prefill_body<false, UNIFORM, LIST, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
+                                                            num_q_heads, max_blocks, scale, causal, plan, precise_keys, own,
+                                                            tid);
+            prefill_body<true, UNIFORM, LIST, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table, num_q_heads,
+                                                       max_blocks, scale, causal, plan, precise_keys, own, tid);
+        }
+    } else {
+        // Workgroups are dispatched in blockIdx.x order: the row-tile index is the slowest-varying part and runs
+        // backwards, so the whole grid is handed out heaviest (latest causal tiles) first; the context chunks of a
+        // tile follow each other.
+        const int32_t hb = heads * batch;
+        const int32_t slow = (int32_t)(blockIdx.x / (uint32_t)hb);
+        const int32_t rest = (int32_t)(blockIdx.x % (uint32_t)hb);
+        own.s = rest / heads;
+        own.hg = rest % heads;
+        own.tile = num_tiles - 1 - slow / plan.nsplit;
+        own.split = slow % plan.nsplit;
+        own.chunks = plan.nsplit;
+        own.chunk = plan.chunk;
+        own.slot = -1;
+        own.q_begin = cu_q_lens[own.s];
+        own.q_end = cu_q_lens[own.s + 1];
+        own.len = seq_lens[own.s];
+        int32_t precise_keys = 0;
+        if constexpr (!kTwoTermOnly<D>) {
+            precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal,
+                                             (M::kWindow && plan.mods.window > 0) ? plan.mods.window : 0,
+                                             (int)(threadIdx.x & 63));
+            prefill_body<false, UNIFORM, LIST, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table, num_q_heads,
+                                                        max_blocks, scale, causal, plan, precise_keys, own, (int)threadIdx.x);
+        }
+        prefill_body<true, UNIFORM, LIST, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table, num_q_heads,
+                                                   max_blocks, scale, causal, plan, precise_keys, own, (int)threadIdx.x);
     }
-    int32_t precise_keys = 0;
-    if constexpr (!kTwoTermOnly<D>) {
-        precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal,
-                                         (M::kWindow && plan.mods.window > 0) ? plan.mods.window : 0,
-                                         (int)(threadIdx.x & 63));
-        prefill_body<false, UNIFORM, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, cu_q_lens, block_table, seq_lens, batch,
-                                     num_tiles, num_q_heads, max_blocks, scale, causal, plan, precise_keys, own);
-    }
-    prefill_body<true, UNIFORM, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, cu_q_lens, block_table, seq_lens, batch, num_tiles,
-                                num_q_heads, max_blocks, scale, causal, plan, precise_keys, own);
 }
 
 }  // namespace
@@ -742,8 +794,11 @@ pa_status launch_prefill_mfma_dim(const AttnArgs& a, const PrefillPlan& plan, in
     const dim3 grid((uint32_t)blocks, 1, 1);
     if constexpr (kTwoTermOnly<D>) {   // (prefill_mfma_supported takes no hooks and no pages below 16 tokens here)
         if (a.has_mods || a.cache.page_size < 16) return PA_ERR_UNSUPPORTED;
-        auto kern = a.dtype == PA_DTYPE_BF16 ? paged_prefill_mfma_kernel<true, ElemBf16, NoMods, D>
-                                             : paged_prefill_mfma_kernel<true, ElemF16, NoMods, D>;
+        auto kern = a.dtype == PA_DTYPE_BF16
+                        ? (plan.list_items > 0 ? paged_prefill_mfma_kernel<true, ElemBf16, NoMods, D, true>
+                                               : paged_prefill_mfma_kernel<true, ElemBf16, NoMods, D>)
+                        : (plan.list_items > 0 ? paged_prefill_mfma_kernel<true, ElemF16, NoMods, D, true>
+                                               : paged_prefill_mfma_kernel<true, ElemF16, NoMods, D>);
         hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, stream, a.cache, (const uint16_t*)a.q, (uint16_t*)a.out, a.lse,
                            a.cu_q_lens, a.block_table, a.seq_lens, a.batch, (int32_t)tiles, a.num_q_heads, a.max_blocks,
                            a.scale, a.causal, plan);
@@ -754,7 +809,11 @@ pa_status launch_prefill_mfma_dim(const AttnArgs& a, const PrefillPlan& plan, in
     if (D > 128 && !uniform) return PA_ERR_UNSUPPORTED;   // 512-byte rows: two rows per load must share a page
     typedef Mods<true, true, false> WindowScore;
     auto kern = paged_prefill_mfma_kernel<true, ElemBf16, NoMods, D>;
-    if (a.mods.user_mod) {                                // a user modification: one instantiation per listed struct
+    if (plan.list_items > 0) {                            // (prefill_list_supported)
+        if (a.has_mods || !uniform) return PA_ERR_UNSUPPORTED;
+        kern = a.dtype == PA_DTYPE_BF16 ? paged_prefill_mfma_kernel<true, ElemBf16, NoMods, D, true>
+                                        : paged_prefill_mfma_kernel<true, ElemF16, NoMods, D, true>;
+    } else if (a.mods.user_mod) {                         // a user modification: one instantiation per listed struct
         bool found = false;
 #define PA_USER_CASE(U)                                                                                     \
         if (a.mods.user_mod == U::kId) {                                                                    \

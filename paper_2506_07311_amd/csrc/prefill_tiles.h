@@ -77,10 +77,162 @@ struct PrefillPlan {
     int32_t chunk;        // context tokens per workgroup (multiple of 64 and of the page size when nsplit > 1)
     int32_t nsplit;       // chunks along the grid; > 1: partials go to part_o / part_lse for the merge kernel
     int32_t skip_small;   // 1: sequences with q_len * G <= 16 are computed by the decode kernel, not here
+    int32_t list_items;   // > 0: work-list mode (below); at most list_items x head groups items, the grid steps over them
+    float* list_o;        // its partials: [slot][wave][16 bytes of a lane][lane]
+    float* list_lse;      // [slot][row]
+    int32_t list_unit;    // chunks are multiples of this many tokens (a tile and a page)
     float* part_o;        // [total_q, Hq, nsplit, head_dim]
     float* part_lse;      // [total_q, Hq, nsplit]
     ModArgs mods;         // mask / score hooks (used by the instantiations that have them)
 };
+
+// ---------------------------------------------------------------------------------------------------
+// Work-list mode.  A jagged call (a few chunks of long prompts among decode rows) has neither of the shapes the plain
+// grid serves: most of its (tile, sequence) pairs are empty, and the host, which knows no lengths, cannot see that a
+// handful of workgroups would walk the longest contexts alone (60 decode rows + 4 chunks of 512 tokens, contexts
+// of 2.7k to 31k tokens: 128 workgroups of 490 tiles each set the time, 1510 us, with three quarters of the machine
+// idle).  Here every wave derives the same list from cu_q_lens and seq_lens: row tiles of the live sequences only, the
+// context of a sequence cut into chunks of one length, chosen so that the call has about kListTarget work items
+// (two per workgroup slot; none shorter than kListMinTiles, where a workgroup's start and its partial begin to show).
+// Item order: sequence, chunk, row tile from last to first, head group -- the workgroups that run together on a
+// chiplet walk the same keys, so a chunk's K/V comes from HBM once per head.  Same call: prefill kernel
+// 1510 -> 460 us (410 GFLOP: 0.9 PFLOP/s) + 10 us of merging; the whole call 1690 -> 655 us.
+// ---------------------------------------------------------------------------------------------------
+constexpr int32_t kListTarget = 1024;
+constexpr int32_t kListMinTiles = 32;
+// ... except that chunks may be as short as kListShortTiles while all items fit the workgroup slots of the machine (two
+// per compute unit): one chunk of 512 tokens on 2787 among 16 sequences 73 us against 86 with 32 tiles, but six chunks of
+// 200 tokens on up to 3508, whose 728 items of 16 tiles need a second round, 134 against 123.
+constexpr int32_t kListShortTiles = 16;
+constexpr int32_t kListSlots = 512;
+// Workgroups of the launch and of its merge (an eighth of a row tile each).  Items beyond the grid are taken by
+// stepping over the list: the host can only bound the number of items, and a workgroup that finds none still costs its
+// slot for the 3 us that finding out takes (60 sequences with three short chunks of 200 tokens: 147 us with a workgroup
+// for every possible item and quarter, 129 like this, 131 on the plain grid).
+constexpr int32_t kListGrid = 2048;
+constexpr int32_t kListMergeGrid = 2048;
+
+// small_group = query heads per KV head when sequences with q_len * G <= 16 are left to the decode kernel, kNoSmallGroup
+// when none is.
+constexpr int32_t kNoSmallGroup = 17;
+
+// One lane's sequence of a block of 64: row tiles (0: no queries, or left to the decode kernel) and key tiles.
+struct ListSeq {
+    int32_t tiles, len;
+};
+__device__ __forceinline__ ListSeq list_seq(const int32_t* __restrict__ cu_q_lens, const int32_t* __restrict__ seq_lens,
+                                            int32_t batch, int32_t i, int32_t log2_pack, int32_t small_group)
+{
+    ListSeq q = {0, 0};
+    if (i < batch) {
+        const int32_t q_len = cu_q_lens[i + 1] - cu_q_lens[i];
+        q.len = seq_lens[i];
+        if (q_len > 0 && q_len * small_group > 16) q.tiles = ((q_len << log2_pack) + kBM - 1) / kBM;
+    }
+    return q;
+}
+
+// The list of a call, as one wave sees it: the chunk length (the same on every wave: fixed order of the sums) and, for
+// batches of up to 64 sequences, this lane's sequence, so that finding an item needs no further load.
+struct WorkList {
+    int32_t chunk;
+    int32_t small_group, log2_pack, heads, batch;
+    ListSeq own;
+};
+__device__ __forceinline__ WorkList make_list(const int32_t* __restrict__ cu_q_lens,
+                                              const int32_t* __restrict__ seq_lens, int32_t batch, int32_t log2_pack,
+                                              int32_t small_group, int32_t heads, int32_t unit, int lane)
+{
+    WorkList w;
+    w.small_group = small_group;
+    w.log2_pack = log2_pack;
+    w.heads = heads;
+    w.batch = batch;
+    w.own = list_seq(cu_q_lens, seq_lens, batch, lane, log2_pack, small_group);
+    float work = (float)w.own.tiles * (float)((w.own.len + kBN - 1) / kBN);   // (row tile, key tile) pairs per head group
+    for (int32_t i = lane + 64; i < batch; i += 64) {
+        const ListSeq q = list_seq(cu_q_lens, seq_lens, batch, i, log2_pack, small_group);
+        work += (float)q.tiles * (float)((q.len + kBN - 1) / kBN);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) work += __shfl_xor(work, o, 64);
+    int32_t tiles = max(kListMinTiles, (int32_t)(work * (float)heads * (1.f / kListTarget)) + 1);
+    if (tiles == kListMinTiles) {
+        // little work: shorter chunks, if all items still run at once
+#pragma unroll 1
+        for (int32_t c = kListShortTiles; c < kListMinTiles; c += 8) {
+            int32_t n = 0;
+            for (int32_t i = lane; i < batch; i += 64) {
+                const ListSeq q = i < 64 ? w.own : list_seq(cu_q_lens, seq_lens, batch, i, log2_pack, small_group);
+                n += min(q.tiles * ((max(q.len, 1) + c * kBN - 1) / (c * kBN)), 2 * kListSlots);
+            }
+            n = min(n, 1 << 20);
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
+            if ((int64_t)n * heads <= kListSlots) {
+                tiles = c;
+                break;
+            }
+        }
+        tiles = __builtin_amdgcn_readfirstlane(tiles);
+    }
+    w.chunk = __builtin_amdgcn_readfirstlane((min(tiles, 1 << 22) * kBN + unit - 1) / unit * unit);
+    return w;
+}
+
+// Item (or, SPLIT_TILES: the idx-th row tile of the sequences that are cut) number idx of the list; false = no such item.
+struct ListItem {
+    int32_t s;           // sequence
+    int32_t tile;        // row tile
+    int32_t split;       // chunk of the context
+    int32_t tiles;       // row tiles of the sequence
+    int32_t chunks;      // chunks of the sequence; 1 = the item writes its rows, > 1 = a partial
+    int32_t slot;        // partial of chunk 0 of the sequence's last row tile, per head group
+};
+template <bool SPLIT_TILES>
+__device__ __forceinline__ bool list_locate(ListItem& it, const WorkList& w, const int32_t* __restrict__ cu_q_lens,
+                                            const int32_t* __restrict__ seq_lens, int32_t idx, int lane)
+{
+    int32_t items_before = 0, slots_before = 0;
+    for (int32_t blk = 0; blk < w.batch; blk += 64) {
+        const ListSeq q = blk == 0 ? w.own : list_seq(cu_q_lens, seq_lens, w.batch, blk + lane, w.log2_pack, w.small_group);
+        const int32_t chunks = max((q.len + w.chunk - 1) / w.chunk, 1);
+        const int32_t slots = chunks > 1 ? q.tiles * chunks : 0;
+        const int32_t n = !SPLIT_TILES ? q.tiles * chunks : chunks > 1 ? q.tiles : 0;
+        int32_t inc = n, sinc = slots;                        // inclusive scans over the 64 lanes
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int32_t t = __shfl_up(inc, o, 64), u = __shfl_up(sinc, o, 64);
+            if (lane >= o) {
+                inc += t;
+                sinc += u;
+            }
+        }
+        const uint64_t hit = __ballot(items_before + inc > idx);
+        if (hit) {
+            const int first = __ffsll((unsigned long long)hit) - 1;
+            it.s = blk + first;
+            it.tiles = __builtin_amdgcn_readlane(q.tiles, first);
+            it.chunks = __builtin_amdgcn_readlane(chunks, first);
+            it.slot = slots_before + __builtin_amdgcn_readlane(sinc, first) - __builtin_amdgcn_readlane(slots, first);
+            const int32_t rest = idx - (items_before + __builtin_amdgcn_readlane(inc, first) -
+                                        __builtin_amdgcn_readlane(n, first));
+            it.split = rest / it.tiles;
+            it.tile = it.tiles - 1 - rest % it.tiles;
+            return true;
+        }
+        items_before += __builtin_amdgcn_readlane(inc, 63);
+        slots_before += __builtin_amdgcn_readlane(sinc, 63);
+    }
+    return false;
+}
+// slot of chunk `split` of row tile `tile`, head group hg
+__device__ __forceinline__ int32_t list_slot(const ListItem& it, int32_t split, int32_t heads, int32_t hg)
+{
+    return (it.slot + split * it.tiles + it.tiles - 1 - it.tile) * heads + hg;
+}
+// floats of a slot's accumulators: 128 rows x the 32-column blocks of head_dim
+__host__ __device__ constexpr int32_t list_slot_floats(int32_t d) { return kBM * ((d + 31) / 32 * 32); }
 
 struct PageIds {
     int32_t p0, p1, p2, p3;

@@ -1,0 +1,74 @@
+"""GPU parity of the prefill kernel's work-list mode: jagged calls whose long contexts are cut into chunks on the device."""
+import pytest
+import torch
+
+from paper_2506_07311_amd import workloads as W
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def pa():
+    import paper_2506_07311_amd as pa_mod
+    pa_mod.load_library()
+    return pa_mod
+
+
+# chunks of 2048 keys at the least: contexts on, one below and one above its multiples; sequences without queries, without
+# keys, left to the decode kernel, not cut; more sequences than lanes
+LENS = [4096, 2048, 0, 4097, 6143, 70, 2049, 300, 1]
+Q_LENS = [130, 64, 0, 1, 257, 33, 40, 0, 1]
+CASES = [  # lens, q_lens, Hq, Hkv, d, P, dtype, causal, hooks
+    (LENS, Q_LENS, 8, 2, 128, 16, torch.bfloat16, True, None),
+    (LENS, Q_LENS, 6, 2, 64, 128, torch.float16, False, None),
+    (LENS, Q_LENS, 2, 2, 256, 16, torch.bfloat16, True, None),
+    (LENS, Q_LENS, 2, 1, 96, 16, torch.bfloat16, True, None),
+    (LENS, Q_LENS, 4, 4, 128, 4, torch.bfloat16, True, dict(alibi=True, softcap=30.0)),
+    ([40] * 70 + LENS + [9], [1] * 70 + Q_LENS + [9], 4, 1, 128, 16, torch.bfloat16, True, None),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"Hq{c[2]}-Hkv{c[3]}-d{c[4]}-P{c[5]}-n{len(c[0])}")
+def test_jagged_calls_with_long_contexts(pa, oracle, case):
+    from paper_2506_07311_amd import binding
+    from tests.test_gpu_parity import build_mods
+    lens, q_lens, Hq, Hkv, d, P, dtype, causal, hooks = case
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=P,
+                        dtype=dtype, causal=causal, seed=211, device=DEV)
+    mods = build_mods(hooks, Hq, lens) if hooks else None
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        parity.check_step(pa, oracle, w, f"{case[2:]}", mods=mods)
+        listed = hooks is None and P >= 16                    # (hooks and smaller pages keep the plain grid)
+        assert binding.pa_profile_read("paged_attention_merge_list")[0] == (1 if listed else 0)
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
+
+
+def test_a_workspace_of_the_smaller_size_is_accepted_and_keeps_the_plain_grid(pa):
+    """The list's partials are room on top of what a call requires: without it the plain grid runs, with the same results
+    up to the merge's rounding (bf16 outputs one step apart at most)."""
+    from paper_2506_07311_amd import binding
+    w = W.make_workload("t", seq_lens=LENS, q_lens=Q_LENS, num_q_heads=8, num_kv_heads=2, head_dim=128, page_size=16,
+                        dtype=torch.bfloat16, causal=True, seed=212, device=DEV)
+    pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
+    full = pa.paged_attention_workspace_bytes(w.batch, 8, 128, w.total_q, w.max_seq_len)
+    outs = []
+    for nbytes in (full, full - 256):
+        ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device=DEV)
+        binding.pa_profile_reset()
+        binding.pa_profile_enable(True)
+        try:
+            out = pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, w.cu_q_lens, w.max_q_len, w.block_table,
+                                             w.seq_lens, w.max_seq_len, w.scale, True, workspace=ws)
+            torch.cuda.synchronize()
+            assert binding.pa_profile_read("paged_attention_merge_list")[0] == (1 if nbytes == full else 0)
+        finally:
+            binding.pa_profile_enable(False)
+            binding.pa_profile_reset()
+        outs.append(out.float())
+    assert ((outs[0] - outs[1]).abs() <= 2.0 ** -7 * outs[1].abs() + 2e-3).all()
