@@ -256,6 +256,24 @@ size_t short_split_workspace_bytes(int32_t batch, int32_t hq, int32_t d)
     return align256(decode_short_part_floats(wgs, d) * sizeof(float));
 }
 
+// Workgroups per (sequence, KV head) of the fp32 decode kernel: one per compute unit (its eight waves take the register
+// file of one), at least one tile for every slot of its waves, and no more than the workspace holds partials for.
+int32_t plan_f32_splits(const AttnArgs& a, size_t ws_bytes)
+{
+    const int64_t units = (int64_t)a.batch * a.cache.num_kv_heads;
+    if (units > kShortMaxUnits) return 1;
+    int64_t n = device_cus() / units;
+    if (g_opt.decode_chunk_tokens > 0) {
+        n = (a.max_seq_len + g_opt.decode_chunk_tokens - 1) / g_opt.decode_chunk_tokens;
+    } else {
+        const int64_t by_keys = (a.max_seq_len + 15) / 16 / decode_f32_tile_slots(a);
+        if (n > by_keys) n = by_keys;
+    }
+    if (n > kF32MaxSplit) n = kF32MaxSplit;
+    while (n > 1 && decode_f32_part_floats(a, (int32_t)n) * sizeof(float) > ws_bytes) --n;
+    return n < 1 ? 1 : (int32_t)n;
+}
+
 size_t stream_workspace_bytes(int32_t batch, int32_t hq, int32_t d, int32_t wgs)
 {
     const size_t parts = (size_t)wgs + batch;
@@ -463,6 +481,7 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
         b.seg_last = reinterpret_cast<int32_t*>(p);
     };
 
+    const bool f32 = !g_opt.force_generic && attention_f32_supported(a);
     if (decode) {
         if (!g_opt.force_generic && g_opt.decode_short >= 0 && decode_short_supported(a)) {
             const int32_t nsplit = plan_short_splits(a);
@@ -496,9 +515,15 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
         const size_t po = part_o_bytes(batch, num_q_heads, d, a.plan.nsplit);
         if (a.plan.nsplit > 1 && ws.bytes < po + part_lse_bytes(batch, num_q_heads, a.plan.nsplit))
             return PA_ERR_WORKSPACE_TOO_SMALL;
+        // (behind the check above: a workspace or scratch array that was too small for the chunks' partials stays too small)
+        if (f32 && decode_f32_supported(a)) {
+            a.short_nsplit = plan_f32_splits(a, ws.bytes);
+            a.short_part = reinterpret_cast<float*>(base);
+            return launch_decode_f32(a, s);
+        }
         a.part_o = reinterpret_cast<float*>(base);
         a.part_lse = reinterpret_cast<float*>(base + po);
-        st = launch_attention_generic(a, s);
+        st = f32 ? launch_attention_f32(a, s) : launch_attention_generic(a, s);
         if (st != PA_OK) return st;
         if (a.plan.nsplit > 1) st = launch_merge(a, s);
         return st;
@@ -569,7 +594,7 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
         }
         return st;
     }
-    return launch_attention_generic(a, s);
+    return f32 ? launch_attention_f32(a, s) : launch_attention_generic(a, s);
 }
 
 // Device address of this GPU's copy of `scratch`, looked up once per device with that device current.

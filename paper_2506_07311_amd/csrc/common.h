@@ -170,6 +170,20 @@ struct AttnArgs {
 
 // Portable VALU kernel: any dtype / head_dim / page size / group size; decode and ragged prefill.
 pa_status launch_attention_generic(const AttnArgs& a, hipStream_t stream);
+// fp32 pools on the double-precision matrix cores: head_dim 64 / 128, no hooks, pages of 16 tokens and more; decode (with
+// the same chunks and merge as the portable kernel) and ragged prefill.
+bool attention_f32_supported(const AttnArgs& a);
+pa_status launch_attention_f32(const AttnArgs& a, hipStream_t stream);
+// The decode form for up to kF32MaxGroup heads of a KV head: one launch, short_nsplit workgroups per (sequence, KV head)
+// merging through short_part (this many floats); a workgroup's waves attend to `tile_slots` tiles of 16 keys at a time.
+constexpr int32_t kF32MaxSplit = 64;
+constexpr int32_t kF32MaxGroup = 4;
+int32_t decode_f32_tile_slots(const AttnArgs& a);
+bool decode_f32_supported(const AttnArgs& a);
+size_t decode_f32_part_floats(const AttnArgs& a, int32_t nsplit);
+pa_status launch_decode_f32(const AttnArgs& a, hipStream_t stream);
+// `units` arrival counters (all zero, left zero by the kernel) for one launch on the current device.
+pa_status arrival_window(int32_t units, uint32_t** out);
 // MFMA decode kernel: bf16, head_dim 128, group size <= 16.
 bool decode_mfma_supported(const AttnArgs& a);
 int32_t decode_mfma_heads_per_wg(int32_t num_kv_heads, int32_t head_dim);

@@ -21,7 +21,8 @@ std::mutex g_arrive_mutex;
 uint32_t* g_arrive_ptr[64] = {};
 std::atomic<uint32_t> g_arrive_cursor{0};
 
-// `units` counters (all zero) for one launch on the current device.
+}  // namespace
+
 pa_status arrival_window(int32_t units, uint32_t** out)
 {
     if (units < 1 || units > kShortMaxUnits) return PA_ERR_INVALID_ARG;
@@ -41,8 +42,6 @@ pa_status arrival_window(int32_t units, uint32_t** out)
     *out = base + (size_t)window * kShortMaxUnits;
     return PA_OK;
 }
-
-}  // namespace
 
 template void launch_decode_mfma_dim<128>(const AttnArgs&, hipStream_t);
 extern template void launch_decode_mfma_dim<64>(const AttnArgs&, hipStream_t);

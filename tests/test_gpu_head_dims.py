@@ -68,3 +68,51 @@ def test_prefill_at_padded_head_dims_equals_the_portable_kernel(pa, d):
     for out, lse in outs[1:]:
         assert ((out - ref).abs() <= 2.0 ** -7 * ref.abs() + 1e-4).all()
         assert (lse - ref_lse).abs().max() <= 2e-5
+
+
+# ----------------------------------------------------------------------------- fp32 pools on the fp64 matrix cores
+F32_CASES = [  # lens, q_lens (None: decode), Hq, Hkv, d, P, causal
+    ([1, 15, 16, 17, 0, 129, 777, 33], [1, 15, 16, 17, 0, 100, 200, 33], 4, 4, 64, 16, True),
+    ([1, 15, 16, 300], [1, 15, 16, 50], 6, 2, 128, 32, True),
+    ([40, 200], [7, 33], 40, 2, 64, 64, False),                  # 20 heads a group: row tiles that straddle queries
+    ([1, 16, 0, 129, 2049, 255], None, 8, 8, 64, 16, False),     # 2049 keys: chunks of 256 and the merge kernel
+    ([700, 3, 128], None, 40, 2, 128, 128, False),
+]
+
+
+@pytest.mark.parametrize("case", F32_CASES, ids=lambda c: f"Hq{c[2]}-Hkv{c[3]}-d{c[4]}-P{c[5]}-{'prefill' if c[1] else 'decode'}")
+def test_fp32_on_the_matrix_cores(pa, oracle, case):
+    """Against the fp64 oracle at 2e-6 max-abs / 1e-5 max-rel: fp64 products and sums leave the exponential (one fp32 ulp, 6e-8
+    of a weight), the fp32 partials (6e-8) and the output's rounding (6e-8) of values below 4."""
+    from paper_2506_07311_amd import binding
+    lens, q_lens, Hq, Hkv, d, P, causal = case
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=P,
+                        dtype=torch.float32, causal=causal, seed=203, device=DEV)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        parity.check_step(pa, oracle, w, f"fp32 {case[2:]}", tol=(2e-6, 1e-5), step_call=q_lens is None)
+        assert binding.pa_profile_read("paged_attention_f32")[0] == 1
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
+
+
+@pytest.mark.parametrize("d,dtype", [(64, torch.float32), (128, torch.float32)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_values_that_are_not_finite_stay_with_the_rows_that_see_them(pa, d, dtype, bad):
+    """A later token of a prompt with a NaN or an infinity in V (or K) must not reach the queries in front of it."""
+    n, at, P = 50, 20, 16
+    w = W.make_workload("t", seq_lens=[n], q_lens=[n], num_q_heads=2, num_kv_heads=2, head_dim=d, page_size=P, dtype=dtype,
+                        causal=True, seed=204, device=DEV)
+    outs = []
+    for value in (0.5, bad):
+        w.v_new[at, :, 3] = value
+        pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
+        outs.append(pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, w.cu_q_lens, w.max_q_len, w.block_table,
+                                               w.seq_lens, w.max_seq_len, w.scale, True))
+    good, got = outs
+    assert (got[:at] - good[:at]).abs().max() <= 1e-6
+    other = [c for c in range(d) if c != 3]
+    assert (got[at:, :, other] - good[at:, :, other]).abs().max() <= 1e-6
+    assert not got[at:, :, 3].isfinite().any()
