@@ -869,31 +869,58 @@ __global__ __launch_bounds__(NW * 64) void paged_decode_short_kernel(
     }
     __syncthreads();
     if (sm_last == 0u) return;
+    // Every load of the merge is in flight at once, instead of one round trip past the caches per partial (step of
+    // 1 x 8192, 32 / 8 heads, 16 partials: 20.3 -> 14.2 us; 1 x 2048, 8 partials: 11.8 -> 9.0; 8 x 2048, 4: 17.2 -> 16.5): the statistics by one thread each, weights into LDS, then the rows four partials at a time.
     const float* const unit_part = part + unit * nsplit * kPartFloats;
+    float* const sm_w = sm_o;                                // [nsplit][16] maxima, then weights (the wave partials are merged)
+    float* const sm_s = sm_o + 16 * kShortMaxSplit;          // [nsplit][16] sums
+    for (int i = threadIdx.x; i < 32 * nsplit; i += NW * 64) {
+        const int k = i >> 5, r = i & 31;
+        (r < 16 ? sm_w : sm_s - 16)[k * 16 + r] =
+            __hip_atomic_load(unit_part + k * kPartFloats + 16 * kD + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (threadIdx.x < 16) {
+        const int r = threadIdx.x;
+        float mx = -INFINITY;
+        for (int p = 0; p < nsplit; ++p) mx = fmaxf(mx, sm_w[p * 16 + r]);
+        float sum = 0.f;
+        for (int p = 0; p < nsplit; ++p) {
+            const float mp = sm_w[p * 16 + r];
+            const float wgt = mp == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mp - mx);
+            sum = __builtin_fmaf(wgt, sm_s[p * 16 + r], sum);
+            sm_w[p * 16 + r] = wgt;
+        }
+        sm_m[r] = mx;
+        sm_l[r] = sum;
+    }
+    __syncthreads();
     for (int it = threadIdx.x; it < 16 * (kD / 4); it += NW * 64) {
         const int row = it / (kD / 4), c4 = it % (kD / 4);
         if (row >= rows) continue;
-        float mx = -INFINITY;
-        for (int p = 0; p < nsplit; ++p)
-            mx = fmaxf(mx, __hip_atomic_load(unit_part + p * kPartFloats + 16 * kD + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        float sum = 0.f;
         float4 acc = float4{0.f, 0.f, 0.f, 0.f};
-        for (int p = 0; p < nsplit; ++p) {
-            const float* pp = unit_part + p * kPartFloats;
-            const float mp = __hip_atomic_load(pp + 16 * kD + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const float wgt = mp == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mp - mx);
-            float4 v;
-            const float* pv = pp + row * (kD / 4) + c4;
-            v.x = __hip_atomic_load(pv + 0 * 4 * kD, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            v.y = __hip_atomic_load(pv + 1 * 4 * kD, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            v.z = __hip_atomic_load(pv + 2 * 4 * kD, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            v.w = __hip_atomic_load(pv + 3 * 4 * kD, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            sum = __builtin_fmaf(wgt, __hip_atomic_load(pp + 16 * kD + 16 + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), sum);
-            acc.x = __builtin_fmaf(wgt, v.x, acc.x);
-            acc.y = __builtin_fmaf(wgt, v.y, acc.y);
-            acc.z = __builtin_fmaf(wgt, v.z, acc.z);
-            acc.w = __builtin_fmaf(wgt, v.w, acc.w);
+        const float* const pv = unit_part + it;
+        for (int p0 = 0; p0 < nsplit; p0 += 4) {
+            float4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float* pp = pv + min(p0 + u, nsplit - 1) * kPartFloats;
+                v[u].x = __hip_atomic_load(pp + 0 * 4 * kD, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                v[u].y = __hip_atomic_load(pp + 1 * 4 * kD, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                v[u].z = __hip_atomic_load(pp + 2 * 4 * kD, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                v[u].w = __hip_atomic_load(pp + 3 * 4 * kD, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (p0 + u >= nsplit) break;
+                const float wgt = sm_w[(p0 + u) * 16 + row];
+                acc.x = __builtin_fmaf(wgt, v[u].x, acc.x);
+                acc.y = __builtin_fmaf(wgt, v[u].y, acc.y);
+                acc.z = __builtin_fmaf(wgt, v[u].z, acc.z);
+                acc.w = __builtin_fmaf(wgt, v[u].w, acc.w);
+            }
         }
+        const float sum = sm_l[row], mx = sm_m[row];
         const float inv = sum > 0.f ? 1.f / sum : 0.f;
         uint2 wv;
         wv.x = E::pack(acc.x * inv, acc.y * inv);
