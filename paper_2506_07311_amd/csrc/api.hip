@@ -208,15 +208,25 @@ int32_t plan_stream_wgs(int32_t batch, int32_t max_seq_len, int32_t head_groups,
 // workgroup of the one-launch kernel streams its share of a (sequence, KV head) at about 55 GB/s, so its time is
 // about 4 us + 9 us per 512 KB, against a floor of 12-16 us for tile stream + merge.  With few sequences the
 // kernel puts several workgroups on a (sequence, KV head) -- as many as fill the machine once (a compute unit holds
-// one workgroup of this kernel: its eight waves take the whole register file), at least 256 keys each -- which
+// one workgroup of this kernel: its eight waves take the whole register file), at least 128 keys each at head_dim 128 -- which
 // merge through the workspace inside the same launch; the route is taken while a workgroup's share stays within
 // 512 KB of K and V rows (1024 tokens at head_dim <= 128, 512 at head_dim 256: rows twice as long).  Beyond that
-// the tile stream's whole-row reads and equal split use the memory system better.  Measured, 32 / 8 heads, one box:
-// 8 x 1024 tokens 10.6 us with 4 workgroups per (sequence, KV head) against 14.3 with one (15.5 tile stream + merge),
-// 8 x 2048 16.9 against 23.6 (20.7), 8 x 4096 26.7 against 41.9 (29.5), 1 x 8192 19.9 against 75 (20.2).
+// the tile stream's whole-row reads and equal split use the memory system better.  Measured, steps, 32 / 8 heads, one box,
+// workgroups per (sequence, KV head): 4 x 700 tokens 8.2 us with 4, 9.9 with 2, 11.2 with one (15.0 tile stream + merge);
+// 8 x 4096 26.1 with 4, 43.3 with one (29.5); 2 x 1000 at head_dim 256 11.0 with 8, 13.0 with 4 (17.9); 1 x 30000 with
+// 8 / 1 heads 19.9 with 32, 25.4 with 16 (32.9).  More than 16 pay only where the units are few: 1 x 8192 with 8 KV heads
+// 13.9 with 16, 15.5 with 32.  At least 16384 / head_dim keys to a workgroup, half its waves' tiles: below that the merge
+// costs more than the tiles (1 x 128: 7.0 with 2, 5.2 with one; 8 x 300 with 8 / 1 heads at head_dim 64: 7.3 and 6.3).
 constexpr int64_t kShortMaxRowBytes = 1024 * 512;   // context tokens x bytes of a K row and a V row (>= 512) per workgroup
+// A single sequence has no lengths to balance, and its split reads at what the memory gives: the tile stream's slower start
+// and second launch are worth it only beyond this many bytes of K and V (32 / 8 heads: 32768 tokens 30.0 us against 37.9,
+// 65536 62.0 against 56.1; 8 / 1 heads, 131072 tokens = 67 MB, 48 against 66; 32 / 32, 16384 = 268 MB, 48.0 against 48.5).
+constexpr int64_t kShortMaxSingleBytes = (int64_t)160 << 20;
 constexpr int64_t kShortMaxWGsPerCU = 2;
-constexpr int32_t kShortMinSplitKeys = 256;
+constexpr int32_t kShortMinSplitElems = 16384;   // keys x head_dim
+// The plan that paged_attention_decode_static's scratch limit is stated for (see run_attention).
+constexpr int32_t kScratchMaxSplit = 16;
+constexpr int32_t kScratchMinSplitKeys = 256;
 
 int64_t short_units(const AttnArgs& a)
 {
@@ -224,16 +234,19 @@ int64_t short_units(const AttnArgs& a)
 }
 
 // Workgroups per (sequence, KV head, slice of 16 heads) of the one-launch kernel.
-int32_t plan_short_splits(const AttnArgs& a)
+int32_t plan_short_splits(const AttnArgs& a, int32_t min_keys = 0, int32_t max_split = 0)
 {
     const int64_t units = short_units(a);
     if (units > kShortMaxUnits) return 1;
     int64_t n = g_opt.decode_short_splits;
     if (n <= 0) {
         n = device_cus() / units;
-        const int64_t by_keys = a.max_seq_len / kShortMinSplitKeys;
+        if (min_keys <= 0) min_keys = kShortMinSplitElems / a.cache.head_dim;
+        if (max_split <= 0) max_split = units < 8 ? kShortMaxSplit : kScratchMaxSplit;
+        const int64_t by_keys = a.max_seq_len / min_keys;
         if (n > by_keys) n = by_keys;
     }
+    if (max_split > 0 && n > max_split) n = max_split;
     if (n > kShortMaxSplit) n = kShortMaxSplit;
     return n < 1 ? 1 : (int32_t)n;
 }
@@ -243,7 +256,9 @@ bool short_decode_pays(const AttnArgs& a, int32_t nsplit)
     if (g_opt.decode_workgroups > 0) return false;     // the caller shapes the tile stream: keep it
     const int64_t row_bytes = 4LL * (a.cache.head_dim > 128 ? a.cache.head_dim : 128);
     const int64_t share = ((int64_t)a.max_seq_len + nsplit - 1) / nsplit;
-    return share * row_bytes <= kShortMaxRowBytes && short_units(a) * nsplit <= kShortMaxWGsPerCU * device_cus();
+    const bool single = a.batch == 1 && nsplit > 1 &&
+                        4LL * a.max_seq_len * a.cache.num_kv_heads * a.cache.head_dim <= kShortMaxSingleBytes;
+    return (single || share * row_bytes <= kShortMaxRowBytes) && short_units(a) * nsplit <= kShortMaxWGsPerCU * device_cus();
 }
 
 // Partials of the one-launch kernel's workgroups when a call splits: at most kShortMaxWGsPerCU per compute unit
@@ -482,10 +497,22 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
     };
 
     const bool f32 = !g_opt.force_generic && attention_f32_supported(a);
+    auto plan_stream = [&]() -> int32_t {
+        const int32_t head_groups = cache->num_kv_heads / decode_mfma_heads_per_wg(cache->num_kv_heads, d);
+        return plan_stream_wgs(batch, max_seq_len, head_groups, cache->num_kv_heads, (num_q_heads / cache->num_kv_heads + 15) / 16);
+    };
+    auto tile_stream_bytes = [&]() { return stream_workspace_bytes(batch, num_q_heads, d, plan_stream()); };
+
     if (decode) {
         if (!g_opt.force_generic && g_opt.decode_short >= 0 && decode_short_supported(a)) {
             const int32_t nsplit = plan_short_splits(a);
             if (g_opt.decode_short > 0 || short_decode_pays(a, nsplit)) {
+                // A call that the static scratch array was too small for stays refused, although this kernel now takes it with
+                // less: the limit is that of the tile stream wherever a split of 16 or of 256 keys would have left it that.
+                if (!ws.bound && g_opt.decode_short == 0 &&
+                    !short_decode_pays(a, plan_short_splits(a, kScratchMinSplitKeys, kScratchMaxSplit)) &&
+                    ws.bytes < tile_stream_bytes())
+                    return PA_ERR_WORKSPACE_TOO_SMALL;
                 a.short_nsplit = nsplit;
                 a.short_part = reinterpret_cast<float*>(base);
                 if (nsplit > 1 &&
@@ -496,11 +523,9 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
         }
         const bool stream_route = !g_opt.force_generic && decode_mfma_supported(a);
         if (stream_route) {
-            const int32_t head_groups = cache->num_kv_heads / decode_mfma_heads_per_wg(cache->num_kv_heads, d);
             a.stream_split = 1;
-            a.num_wgs = plan_stream_wgs(batch, max_seq_len, head_groups, cache->num_kv_heads,
-                                        (num_q_heads / cache->num_kv_heads + 15) / 16);
-            if (ws.bytes < stream_workspace_bytes(batch, num_q_heads, d, a.num_wgs)) return PA_ERR_WORKSPACE_TOO_SMALL;
+            a.num_wgs = plan_stream();
+            if (ws.bytes < tile_stream_bytes()) return PA_ERR_WORKSPACE_TOO_SMALL;
             place_stream(a, base, ((size_t)a.num_wgs + batch) * num_q_heads);
             if (a.k_new && g_opt.step_append_kernel) {     // append as a launch of its own, then attend
                 st = launch_kv_append_last(cache, k_new, v_new, seq_lens, block_table, batch, max_blocks, s);
@@ -818,7 +843,7 @@ pa_status pa_set_option(const char* name, int64_t value)
         return PA_OK;
     }
     if (!strcmp(name, "decode_short_splits")) {
-        if (value < 0 || value > kShortMaxSplit) return PA_ERR_INVALID_ARG;
+        if (value < 0 || value > 16) return PA_ERR_INVALID_ARG;
         g_opt.decode_short_splits = value;
         return PA_OK;
     }

@@ -195,7 +195,7 @@ pa_status launch_decode_short(const AttnArgs& a, hipStream_t stream);
 // Floats of the partials of that kernel for `wgs` workgroups (several per sequence and KV head), and the most
 // workgroups one call may split into.
 inline size_t decode_short_part_floats(int64_t wgs, int32_t head_dim) { return (size_t)wgs * (16 * (size_t)head_dim + 32); }
-constexpr int32_t kShortMaxSplit = 16;
+constexpr int32_t kShortMaxSplit = 32;
 constexpr int32_t kShortMaxUnits = 4096;   // (sequence, KV head, slice) units of a split call: one arrival counter each
 // MFMA prefill kernel: bf16, head_dim 128.
 bool prefill_mfma_supported(const AttnArgs& a);
