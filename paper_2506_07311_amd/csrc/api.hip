@@ -559,9 +559,17 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
         // others go to the prefill kernel.  Both kernels decide per sequence from cu_q_lens on the device; the
         // host only skips a launch that cannot find work.
         const int32_t G = num_q_heads / cache->num_kv_heads;
-        const bool uniform_q = (int64_t)batch * max_q_len == total_q;      // every sequence has max_q_len queries
-        bool may_have_small = !g_opt.no_small_q_route && decode_mfma_supported(a) && G <= 16 &&
-                              !(uniform_q && (int64_t)max_q_len * G > 16);
+        // Where it cannot pay, its two launches are left out.  That is when no sequence can have so few queries (the others
+        // have at most max_q_len), and when the call is whole prompts in the main (no context longer than the longest
+        // query range, half of that range on average): a few-query sequence among those walks no more keys than the
+        // longest prompt's last row tile does beside it.  Append + prefill, with / without: 2 prompts of 300 .. 900 tokens
+        // 31.1 / 27.5 us, 16 of 60 .. 170 with 8 / 1 heads 17.3 / 13.1, 4 of 700 .. 2000 122 / 118; 24 prompts of 300 ..
+        // 1000 among 8 single queries 240 / 234.  Below that average it does pay: one prompt of 2048 tokens among 15 single
+        // queries on 1000 .. 2048 keys 175 / 186, one of 4000 among 7 447 / 495.
+        const int64_t least_q = (int64_t)total_q - (int64_t)(batch - 1) * max_q_len;
+        const bool whole_prompts = max_seq_len <= max_q_len && 2LL * total_q >= (int64_t)batch * max_q_len;
+        bool may_have_small = !g_opt.no_small_q_route && decode_mfma_supported(a) && G <= 16 && least_q * G <= 16 &&
+                              !whole_prompts;
         const int32_t lg = prefill_mfma_log2_pack(num_q_heads, cache->num_kv_heads);
         SplitPlan pp = plan_prefill(batch, num_q_heads, lg, total_q, max_seq_len, cache->page_size);
         size_t split_bytes =

@@ -449,7 +449,8 @@ __device__ __forceinline__ void prefill_body(
     int32_t n_first = len;                                   // keys the tile's first row sees
     if (causal) n_first = min(len, len - q_len + (m0 >> lg) + 1);
     if (window > 0) n_first = min(n_first, causal ? window : 2 * window - 1);
-    const bool few_keys = kTwoTermOnly<D> || n_first <= precise_keys ||
+    // (sequences with few queries carry two terms as they do on the decode kernel)
+    const bool few_keys = kTwoTermOnly<D> || n_first <= precise_keys || q_len * (num_q_heads / cache.num_kv_heads) <= 16 ||
                           (M::kScore && plan.mods.alibi_slopes != nullptr) || (M::kDoc && plan.mods.doc_ids != nullptr) ||
                           M::kUser;
     if (few_keys != PRECISE) return;                        // the other instantiation handles this tile

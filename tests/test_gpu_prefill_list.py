@@ -72,3 +72,20 @@ def test_a_workspace_of_the_smaller_size_is_accepted_and_keeps_the_plain_grid(pa
             binding.pa_profile_reset()
         outs.append(out.float())
     assert ((outs[0] - outs[1]).abs() <= 2.0 ** -7 * outs[1].abs() + 2e-3).all()
+
+
+@pytest.mark.parametrize("q_lens,launches", [([200, 1, 150, 190], 0),     # whole prompts in the main: one launch, all sequences
+                                             ([200, 5, 1, 3], 1),         # mostly few queries: they take the decode kernel
+                                             ([200, 20], 0)])             # no sequence can have few queries
+def test_the_few_query_launches_are_left_out_of_ragged_prompts(pa, oracle, q_lens, launches):
+    from paper_2506_07311_amd import binding
+    w = W.make_workload("t", seq_lens=[200, 133, 150, 190][:len(q_lens)], q_lens=q_lens, num_q_heads=8, num_kv_heads=2, head_dim=128,
+                        page_size=16, dtype=torch.bfloat16, causal=True, seed=213, device=DEV)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        parity.check_step(pa, oracle, w, f"{q_lens}")
+        assert binding.pa_profile_read("paged_decode_mfma")[0] == launches
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
