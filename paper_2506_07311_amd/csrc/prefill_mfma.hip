@@ -25,7 +25,7 @@ bool prefill_mfma_supported(const AttnArgs& a)
     const int32_t d = a.cache.head_dim;
     // head_dims 80, 96, 112 without hooks, pages of 16 tokens and more: faster than the portable kernel at every size
     // (append + prefill, portable / this kernel): 1 x 8 tokens 8.6 / 7.2 us, 1 x 100 with 32 heads 20.1 / 9.7, 2 x 300
-    // 138 / 13.0, 2 prompts of 700 and 950 tokens with 32 / 32 heads at D = 96 1075 / 33; 2 rows behind 4000 cached
+    // 138 / 13.0, 2 prompts of 700 and 950 tokens with 32 / 32 heads at D = 96 1075 / 36; 2 rows behind 4000 cached
     // tokens 83.5 / 33.3.  Hooks and smaller pages stay on the portable kernel: instantiations for them do not exist.
     const bool odd = (d == 80 || d == 96 || d == 112) && !a.has_mods && a.cache.page_size >= 16;
     if (d != 128 && d != 64 && !(d == 256 && a.cache.page_size >= 16) && !odd) return false;

@@ -58,7 +58,7 @@ struct RowGeo {
 // head_dims 80, 96 and 112: rows hold 10, 12 or 14 pieces and the last column block of O is padded where D is not a
 // multiple of 32.  Every tile carries two-term weights: the portable kernel, which served these head_dims, keeps its
 // weights in fp32, and the second term (2^-17 of a weight) keeps the error at what the output's rounding leaves.
-// 2 prompts of 700 and 950 tokens, 32 / 32 heads, D = 96: 22 us for 9 GFLOP, bound by the start of a workgroup and its
+// 2 prompts of 700 and 950 tokens, 32 / 32 heads, D = 96: 25 us for 9 GFLOP, bound by the start of a workgroup and its
 // heaviest row tile like every short prompt here; 1065 us on the portable kernel, which reads K and V again per row.
 template <int D>
 constexpr bool kTwoTermOnly = D % 64 != 0;
@@ -334,6 +334,53 @@ __device__ __forceinline__ void half_pv_frags(f32x16 (&o)[T], const f32x16& s, c
     }
 }
 
+// Does a lane's share of the half tile's V hold a value that is not finite (exponent all ones)?
+template <typename E, int T>
+__device__ __forceinline__ bool not_finite(const uint4 (&va)[T], const uint4 (&vb)[T])
+{
+    constexpr uint32_t kExp = E::kDtype == PA_DTYPE_BF16 ? 0x7f80u : 0x7c00u;
+    bool odd = false;
+    auto test = [&](uint32_t w) { odd |= (w & kExp) == kExp || (w & (kExp << 16)) == kExp << 16; };
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        test(va[t].x), test(va[t].y), test(va[t].z), test(va[t].w);
+        test(vb[t].x), test(vb[t].y), test(vb[t].z), test(vb[t].w);
+    }
+    return odd;
+}
+
+// The same product for a half tile at a causal edge whose V holds such values: weights of masked keys are exact zeros, but
+// zero times infinity is not.  One key at a time (the other contraction slots zeroed on both sides), added only to the
+// rows that see it.  base = first key of the half tile; weight r of lane half hh is key base + 8 (r / 4) + 4 hh + r % 4.
+template <typename E, int T>
+__device__ __forceinline__ void half_pv_by_key(f32x16 (&o)[T], const f32x16& s, const uint4 (&va)[T], const uint4 (&vb)[T],
+                                               int32_t base, int32_t nk, int hh)
+{
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+        uint4 w, wl;
+        pack_weights<true, E>(w, wl, s, 8 * st);
+#pragma unroll 1
+        for (int i = 0; i < 16; ++i) {
+            const int e = i >> 1, h = i & 1;
+            const bool seen = base + 8 * (2 * st + (e >> 2)) + 4 * h + (e & 3) < nk;
+            const uint32_t half = hh != h ? 0u : (e & 1) ? 0xffff0000u : 0xffffu;
+            const uint4 keep = {e >> 1 == 0 ? half : 0u, e >> 1 == 1 ? half : 0u, e >> 1 == 2 ? half : 0u, e >> 1 == 3 ? half : 0u};
+            auto cut = [&](const uint4& v) { return uint4{v.x & keep.x, v.y & keep.y, v.z & keep.z, v.w & keep.w}; };
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const uint4 v = cut(st ? vb[t] : va[t]);
+                f32x16 one = (f32x16)(0.f);
+                one = E::mfma32(v, cut(w), one);
+                one = E::mfma32(v, cut(wl), one);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[t][r] = seen ? o[t][r] + one[r] : o[t][r];
+                __builtin_amdgcn_sched_barrier(0);           // (one block's accumulators at a time)
+            }
+        }
+    }
+}
+
 // O^T += V^T P^T for the 32 keys of half tile `half` (two 16-key steps), head_dim 256: the second step's fragments
 // take the place of the first step's as those are consumed (the 8 column blocks leave no room to hold both).
 // vbuf = V part of the tile buffer.
@@ -390,6 +437,7 @@ __device__ __forceinline__ void attend_tile(const char* buf, const uint32_t (&kx
                                             int32_t key0, int32_t nk, const RowMods& rm, const int32_t* docs)
 {
     f32x16 s0, s1, p;
+    const int hh = (int)(threadIdx.x >> 5) & 1;
     constexpr int TB = kBN * (T > 4 ? 512 : 256);
     if constexpr (T <= 4) {
         uint4 va[T], vb[T];
@@ -397,10 +445,14 @@ __device__ __forceinline__ void attend_tile(const char* buf, const uint32_t (&kx
         half_scores<E, KS>(s1, buf, 1, kx, qf);
         load_v_frags<T>(va, vb, buf + TB, 0, vx);
         half_softmax<MASK, true, M, KS, T>(p, s0, o, m, l, sc, key0, nk, rm, docs);
-        half_pv_frags<PRECISE, E, T>(o, p, va, vb);
+        // (head_dims 80, 96, 112: what the portable kernel, which never touches a key a row does not see, gave them)
+        constexpr bool kGuard = MASK && KS % 4 != 0;
+        if (kGuard && __any(not_finite<E, T>(va, vb))) half_pv_by_key<E, T>(o, p, va, vb, key0 - 4 * hh, nk, hh);
+        else half_pv_frags<PRECISE, E, T>(o, p, va, vb);
         load_v_frags<T>(va, vb, buf + TB, 1, vx);
         half_softmax<MASK, false, M, KS, T>(p, s1, o, m, l, sc, key0 + 32, nk, rm, docs + 32);
-        half_pv_frags<PRECISE, E, T>(o, p, va, vb);
+        if (kGuard && __any(not_finite<E, T>(va, vb))) half_pv_by_key<E, T>(o, p, va, vb, key0 + 32 - 4 * hh, nk, hh);
+        else half_pv_frags<PRECISE, E, T>(o, p, va, vb);
     } else {
         half_scores<E, KS>(s0, buf, 0, kx, qf);
         half_scores<E, KS>(s1, buf, 1, kx, qf);

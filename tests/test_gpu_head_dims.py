@@ -98,11 +98,13 @@ def test_fp32_on_the_matrix_cores(pa, oracle, case):
         binding.pa_profile_reset()
 
 
-@pytest.mark.parametrize("d,dtype", [(64, torch.float32), (128, torch.float32)])
+@pytest.mark.parametrize("d,dtype", [(64, torch.float32), (128, torch.float32), (80, torch.bfloat16), (96, torch.float16),
+                                     (112, torch.bfloat16)])
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
 def test_values_that_are_not_finite_stay_with_the_rows_that_see_them(pa, d, dtype, bad):
     """A later token of a prompt with a NaN or an infinity in V (or K) must not reach the queries in front of it."""
-    n, at, P = 50, 20, 16
+    n, at, P = 150, 70, 16
+    eps = 1e-6 if dtype == torch.float32 else 4e-3 if dtype == torch.float16 else 3e-2     # one rounding step of values below 4
     w = W.make_workload("t", seq_lens=[n], q_lens=[n], num_q_heads=2, num_kv_heads=2, head_dim=d, page_size=P, dtype=dtype,
                         causal=True, seed=204, device=DEV)
     outs = []
@@ -112,7 +114,7 @@ def test_values_that_are_not_finite_stay_with_the_rows_that_see_them(pa, d, dtyp
         outs.append(pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, w.cu_q_lens, w.max_q_len, w.block_table,
                                                w.seq_lens, w.max_seq_len, w.scale, True))
     good, got = outs
-    assert (got[:at] - good[:at]).abs().max() <= 1e-6
+    assert (got[:at] - good[:at]).abs().max() <= eps
     other = [c for c in range(d) if c != 3]
-    assert (got[at:, :, other] - good[at:, :, other]).abs().max() <= 1e-6
+    assert (got[at:, :, other] - good[at:, :, other]).abs().max() <= eps
     assert not got[at:, :, 3].isfinite().any()
