@@ -2,6 +2,7 @@
 // Nothing here touches device memory; every check is a host check made before the first launch.
 #include <string.h>
 
+#include <atomic>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -237,7 +238,6 @@ int64_t short_units(const AttnArgs& a)
 int32_t plan_short_splits(const AttnArgs& a, int32_t min_keys = 0, int32_t max_split = 0)
 {
     const int64_t units = short_units(a);
-    if (units > kShortMaxUnits) return 1;
     int64_t n = g_opt.decode_short_splits;
     if (n <= 0) {
         n = device_cus() / units;
@@ -261,14 +261,38 @@ bool short_decode_pays(const AttnArgs& a, int32_t nsplit)
     return (single || share * row_bytes <= kShortMaxRowBytes) && short_units(a) * nsplit <= kShortMaxWGsPerCU * device_cus();
 }
 
-// Partials of the one-launch kernel's workgroups when a call splits: at most kShortMaxWGsPerCU per compute unit
-// (or the forced number per unit), 16 rows of head_dim floats plus maxima and sums each.
+// What a split call of the one-launch kernel keeps in the workspace: the workgroups' partials (16 rows of head_dim floats
+// plus maxima and sums each), then the units' arrival counters.
+size_t short_split_bytes(int64_t units, int32_t nsplit, int32_t d)
+{
+    return align256(decode_short_part_floats(units * nsplit, d) * sizeof(float)) + arrival_bytes(units);
+}
+
+// Its bound.  The heuristic splits only while one workgroup per compute unit is not reached, so the counters fit the room
+// of the second one.
 size_t short_split_workspace_bytes(int32_t batch, int32_t hq, int32_t d)
 {
     // units <= batch * hq (group size 1, one slice); the heuristic never exceeds two workgroups per compute unit
-    int64_t wgs = kShortMaxWGsPerCU * device_cus();
-    if (g_opt.decode_short_splits > 1) wgs = (int64_t)batch * hq * g_opt.decode_short_splits;
-    return align256(decode_short_part_floats(wgs, d) * sizeof(float));
+    if (g_opt.decode_short_splits > 1)
+        return short_split_bytes((int64_t)batch * hq, (int32_t)g_opt.decode_short_splits, d);
+    return align256(decode_short_part_floats(kShortMaxWGsPerCU * device_cus(), d) * sizeof(float));
+}
+
+// What a call's arrival counters count in: a scrambled call number (the 64-bit finalizer of MurmurHash3), made odd so that
+// its first 2^64 multiples differ.
+uint64_t next_arrival_step()
+{
+    static std::atomic<uint64_t> calls{0};
+    uint64_t x = calls.fetch_add(1, std::memory_order_relaxed) + 0x9e3779b97f4a7c15ull;
+    x = (x ^ (x >> 33)) * 0xff51afd7ed558ccdull;
+    x = (x ^ (x >> 33)) * 0xc4ceb9fe1a85ec53ull;
+    return (x ^ (x >> 33)) | 1;
+}
+
+// Partials and arrival counters of a split call of the fp32 decode kernel.
+size_t f32_split_bytes(const AttnArgs& a, int32_t nsplit)
+{
+    return align256(decode_f32_part_floats(a, nsplit) * sizeof(float)) + arrival_bytes((int64_t)a.batch * a.cache.num_kv_heads);
 }
 
 // Workgroups per (sequence, KV head) of the fp32 decode kernel: one per compute unit (its eight waves take the register
@@ -276,7 +300,6 @@ size_t short_split_workspace_bytes(int32_t batch, int32_t hq, int32_t d)
 int32_t plan_f32_splits(const AttnArgs& a, size_t ws_bytes)
 {
     const int64_t units = (int64_t)a.batch * a.cache.num_kv_heads;
-    if (units > kShortMaxUnits) return 1;
     int64_t n = device_cus() / units;
     if (g_opt.decode_chunk_tokens > 0) {
         n = (a.max_seq_len + g_opt.decode_chunk_tokens - 1) / g_opt.decode_chunk_tokens;
@@ -285,7 +308,7 @@ int32_t plan_f32_splits(const AttnArgs& a, size_t ws_bytes)
         if (n > by_keys) n = by_keys;
     }
     if (n > kF32MaxSplit) n = kF32MaxSplit;
-    while (n > 1 && decode_f32_part_floats(a, (int32_t)n) * sizeof(float) > ws_bytes) --n;
+    while (n > 1 && f32_split_bytes(a, (int32_t)n) > ws_bytes) --n;
     return n < 1 ? 1 : (int32_t)n;
 }
 
@@ -481,6 +504,7 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
     a.short_nsplit = 1;
     a.short_part = nullptr;
     a.short_arrive = nullptr;
+    a.short_step = 0;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     char* const base = reinterpret_cast<char*>(ws.ptr);
     const int32_t d = cache->head_dim;
@@ -494,6 +518,13 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
         b.seg_first = reinterpret_cast<int32_t*>(p);
         p += align256((size_t)batch * sizeof(int32_t));
         b.seg_last = reinterpret_cast<int32_t*>(p);
+    };
+
+    // a split call of a one-launch kernel: partials from the start of the workspace, counters at the end of `bytes`
+    auto place_split = [&](size_t bytes, int64_t units) {
+        a.short_part = reinterpret_cast<float*>(base);
+        a.short_arrive = reinterpret_cast<uint64_t*>(base + bytes - arrival_bytes(units));
+        a.short_step = next_arrival_step();
     };
 
     const bool f32 = !g_opt.force_generic && attention_f32_supported(a);
@@ -514,10 +545,11 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
                     ws.bytes < tile_stream_bytes())
                     return PA_ERR_WORKSPACE_TOO_SMALL;
                 a.short_nsplit = nsplit;
-                a.short_part = reinterpret_cast<float*>(base);
-                if (nsplit > 1 &&
-                    ws.bytes < decode_short_part_floats(short_units(a) * nsplit, d) * sizeof(float))
-                    return PA_ERR_WORKSPACE_TOO_SMALL;
+                if (nsplit > 1) {
+                    const size_t need = short_split_bytes(short_units(a), nsplit, d);
+                    if (ws.bytes < need) return PA_ERR_WORKSPACE_TOO_SMALL;
+                    place_split(need, short_units(a));
+                }
                 return launch_decode_short(a, s);          // with k_new / v_new: the append happens in this launch
             }
         }
@@ -543,7 +575,8 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
         // (behind the check above: a workspace or scratch array that was too small for the chunks' partials stays too small)
         if (f32 && decode_f32_supported(a)) {
             a.short_nsplit = plan_f32_splits(a, ws.bytes);
-            a.short_part = reinterpret_cast<float*>(base);
+            if (a.short_nsplit > 1)
+                place_split(f32_split_bytes(a, a.short_nsplit), (int64_t)batch * cache->num_kv_heads);
             return launch_decode_f32(a, s);
         }
         a.part_o = reinterpret_cast<float*>(base);

@@ -370,8 +370,8 @@ __global__ __launch_bounds__(NW * 64) void paged_attention_f32_kernel(
 // quad), a 4-lane sum, and for P.V four keys times a lane's columns per row.  A wave holds R rows (two
 // at head_dim 64, one at 128: more spill); the `groups` (a power of two) waves that share a tile take other rows each and read it through the cache.
 // Everything else -- tiles, loads, LDS merge -- is as above, plus the context split: nsplit workgroups share a (sequence, KV head), leave their merged partial
-// in `part`, and the one that arrives last merges them in split order and sets the counter back to zero (the scheme of
-// the one-launch decode kernel of the 16-bit pools).  One launch, whatever the context; bound by launch and memory
+// in `part`, and the one that arrives last merges them in split order (the scheme of the one-launch decode kernel of the
+// 16-bit pools).  One launch, whatever the context; bound by launch and memory
 // round trips while a wave has a tile or two, by the stream of K and V beyond.
 // Portable kernel / this one, us: 1 x 16 tokens 8 / 8 heads, head_dim 64 6.0 / 4.7; 1 x 128 7.9 / 5.7; 1 x 2048 16.6 / 11.6;
 // 8 x 2048 at head_dim 128 50 / 27 (134 MB), with 32 / 8 heads 99 / 47; 8 x 100 with 32 / 8 heads, head_dim 64 7.7 / 7.7.  With
@@ -382,7 +382,7 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
     CacheView cache, const float* __restrict__ q, float* __restrict__ out, float* __restrict__ lse,
     const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_lens, int32_t num_q_heads,
     int32_t max_blocks, float scale, int32_t log2_groups, int32_t nsplit, float* __restrict__ part,
-    uint32_t* __restrict__ arrive, const float* __restrict__ k_new, const float* __restrict__ v_new)
+    uint64_t* __restrict__ arrive, uint64_t arrive_step, const float* __restrict__ k_new, const float* __restrict__ v_new)
 {
     constexpr int kHeads = HEADS;                            // rows a workgroup has room for
     constexpr int kParts = kHeads * (D + 4);
@@ -402,6 +402,9 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
     const int64_t row0 = (int64_t)s * num_q_heads + (int64_t)kvh * G;
 
     // lengths and queries are requested together
+    const int64_t unit = (int64_t)s * gridDim.y + kvh;
+    uint64_t* const counter = arrive + unit * kArrivalStride;
+    uint64_t seen = 0;
     const int32_t len = seq_lens[s];
     const int group = kHeads == 1 ? 0 : wave & ((1 << log2_groups) - 1);          // this wave's rows: R * group ..
     const int slot = kHeads == 1 ? wave : wave >> log2_groups, slots = kHeads == 1 ? kWaves : kWaves >> log2_groups;
@@ -519,6 +522,8 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
     TileRegs<D> ta, tc;
     if (tb + slot < te) fetch(ta, tb + slot);
     __syncthreads();                                         // q is in LDS
+    // (looked at behind the first tile's loads, so that nothing waits for it; opened when the loop is done)
+    if (nsplit > 1 && threadIdx.x == 0) seen = arrival_peek(counter);
     for (int32_t t = tb + slot; t < te; t += 2 * slots) {
         if (t + slots < te) fetch(tc, t + slots);
         attend(ta, t);
@@ -526,6 +531,7 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
         if (t + 2 * slots < te) fetch(ta, t + 2 * slots);
         attend(tc, t + slots);
     }
+    if (nsplit > 1 && threadIdx.x == 0) arrival_open(counter, seen, arrive_step, nsplit);
 
     // the wave's partial: sums over the quads (keys) of the accumulators, over 16 lanes (keys) of the weights
 #pragma unroll
@@ -547,7 +553,6 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
     __syncthreads();
 
     // merge: thread -> (row, 4 columns)
-    const int64_t unit = (int64_t)s * gridDim.y + kvh;
     for (int it = threadIdx.x; it < kHeads * (D / 4); it += kWaves * 64) {
         const int g = it / (D / 4), c4 = it % (D / 4);
         if (g >= G) continue;
@@ -589,12 +594,7 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
     // caches that are not coherent across the chip, after its counting has returned.
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t before = __hip_atomic_fetch_add(arrive + unit, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint32_t is_last = before == (uint32_t)(nsplit - 1) ? 1u : 0u;
-        if (is_last) __hip_atomic_store(arrive + unit, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sm_last = is_last;
-    }
+    if (threadIdx.x == 0) sm_last = arrival_count(counter, arrive_step, nsplit) ? 1u : 0u;
     __syncthreads();
     if (sm_last == 0u) return;
     // all partials at once: a thread adds up every J-th partial of its row and columns, J threads per piece of the output
@@ -637,6 +637,7 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
 #pragma unroll
     for (int e = 0; e < 4; ++e) sm_a[e * (kWaves * 64) + threadIdx.x] = acc[e];
     __syncthreads();
+    if (threadIdx.x == 0) arrival_clear(counter);
     if ((int)threadIdx.x >= pieces) return;
     for (int k = 1; k < J; ++k)
 #pragma unroll
@@ -657,7 +658,8 @@ void launch_decode_f32_dim(const AttnArgs& a, hipStream_t stream)
     auto kern = G == 1 ? paged_decode_f32_kernel<D, 1, 1> : paged_decode_f32_kernel<D, R, kF32MaxGroup>;
     hipLaunchKernelGGL(kern, dim3((uint32_t)(a.batch * a.short_nsplit), (uint32_t)a.cache.num_kv_heads), dim3(kWaves * 64), 0,
                        stream, a.cache, (const float*)a.q, (float*)a.out, a.lse, a.block_table, a.seq_lens, a.num_q_heads,
-                       a.max_blocks, a.scale, log2_groups, a.short_nsplit, a.short_part, a.short_arrive, (const float*)a.k_new,
+                       a.max_blocks, a.scale, log2_groups, a.short_nsplit, a.short_part, a.short_arrive,
+                       a.short_step, (const float*)a.k_new,
                        (const float*)a.v_new);
 }
 
@@ -691,16 +693,9 @@ size_t decode_f32_part_floats(const AttnArgs& a, int32_t nsplit)
     return nsplit > 1 ? (size_t)a.batch * a.cache.num_kv_heads * nsplit * heads * (a.cache.head_dim + 4) : 0;
 }
 
-pa_status launch_decode_f32(const AttnArgs& args, hipStream_t stream)
+pa_status launch_decode_f32(const AttnArgs& a, hipStream_t stream)
 {
-    AttnArgs a = args;
-    a.short_arrive = nullptr;
-    if (a.short_nsplit > 1) {
-        const int64_t units = (int64_t)a.batch * a.cache.num_kv_heads;
-        if (units > kShortMaxUnits || a.short_nsplit > kF32MaxSplit || !a.short_part) return PA_ERR_INVALID_ARG;
-        const pa_status st = arrival_window((int32_t)units, &a.short_arrive);
-        if (st != PA_OK) return st;
-    }
+    if (a.short_nsplit > 1 && (a.short_nsplit > kF32MaxSplit || !a.short_part || !a.short_arrive)) return PA_ERR_INVALID_ARG;
     ProfileScope prof("paged_decode_f32_kernel", stream);
     if (a.cache.head_dim == 64) launch_decode_f32_dim<64>(a, stream);
     else launch_decode_f32_dim<128>(a, stream);

@@ -650,15 +650,16 @@ __global__ __launch_bounds__(NW * 64) void paged_decode_mfma_kernel(
 // would stream its context through a single compute unit): nsplit workgroups share a (sequence, KV head, slice), each
 // takes a contiguous share of the tiles, leaves its merged partial (unnormalised accumulator rows, maxima, sums) in
 // `part` and counts itself in on the unit's arrival counter; the workgroup that arrives last merges the nsplit
-// partials in split order -- the result does not depend on who that is -- and sets the counter back to zero, so the
-// counters are zero again when the kernel ends: still one launch, no merge kernel, nothing to clear beforehand.
-// part: nsplit blocks of 16 * D + 32 floats per unit; arrive: one counter per unit, zero on entry.
+// partials in split order -- the result does not depend on who that is: still one launch, no merge kernel, nothing
+// to clear beforehand (kArrivalStride in common.h).
+// part: nsplit blocks of 16 * D + 32 floats per unit; arrive: one counter per unit, anything on entry.
 template <int NW, bool UNIFORM, bool FUSED, typename E, typename M, typename GE>
 __global__ __launch_bounds__(NW * 64) void paged_decode_short_kernel(
     CacheView cache, const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float* __restrict__ lse,
     const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_lens, int32_t num_q_heads,
     int32_t max_blocks, float scale, ModArgs mods, const uint16_t* __restrict__ k_new,
-    const uint16_t* __restrict__ v_new, int32_t nsplit, float* __restrict__ part, uint32_t* __restrict__ arrive)
+    const uint16_t* __restrict__ v_new, int32_t nsplit, float* __restrict__ part, uint64_t* __restrict__ arrive,
+    uint64_t arrive_step)
 {
     constexpr int kD = GE::kD;
     constexpr int kTileKeys = GE::kTileKeys;
@@ -690,6 +691,10 @@ __global__ __launch_bounds__(NW * 64) void paged_decode_short_kernel(
     const int32_t c0 = key0 + t_begin * kTileKeys;
     const int32_t c1 = min(len, key0 + t_end * kTileKeys);
     const int32_t pos = len - 1;
+
+    const int64_t unit = ((int64_t)s * gridDim.y + kvh) * gridDim.z + blockIdx.z;
+    uint64_t* const counter = arrive + unit * kArrivalStride;
+    uint64_t seen = 0;
 
     State<GE> st;
 #pragma unroll
@@ -774,6 +779,9 @@ __global__ __launch_bounds__(NW * 64) void paged_decode_short_kernel(
         }
         Tile<GE> ta, tb;
         load_tile<UNIFORM, M, GE, FUSED, true>(ta, a, c0, c1);
+        // (the unit's arrival counter is looked at behind the first tile's loads, so that nothing waits for it, and opened
+        // when the loop is done)
+        if (nsplit > 1 && threadIdx.x == 0) seen = arrival_peek(counter);
         for (int32_t t0 = c0; t0 < c1; t0 += 2 * kTileKeys) {
             const int32_t t1 = t0 + kTileKeys;
             if (t1 < c1) load_tile<UNIFORM, M, GE, FUSED, true>(tb, a, t1, c1);
@@ -782,7 +790,10 @@ __global__ __launch_bounds__(NW * 64) void paged_decode_short_kernel(
             if (t1 + kTileKeys < c1) load_tile<UNIFORM, M, GE, FUSED, true>(ta, a, t1 + kTileKeys, c1);
             compute_tile<false, E, M, GE>(st, tb, qf, sc, t1, c1, c1, quad, rm);
         }
+    } else if (nsplit > 1 && threadIdx.x == 0) {
+        seen = arrival_peek(counter);
     }
+    if (nsplit > 1 && threadIdx.x == 0) arrival_open(counter, seen, arrive_step, nsplit);
 
     // publish the wave's partial: unnormalised accumulator, running maximum (log2 domain), sum
     float l = st.l;
@@ -808,7 +819,6 @@ __global__ __launch_bounds__(NW * 64) void paged_decode_short_kernel(
 
     // merge: thread -> (row, 4 columns); weights 2^(m_p - M), a partial without any visible key weighs nothing
     const int64_t out_row0 = (int64_t)s * num_q_heads + kvh * G + h0;
-    const int64_t unit = ((int64_t)s * gridDim.y + kvh) * gridDim.z + blockIdx.z;
     constexpr int kPartFloats = 16 * kD + 32;                // accumulator rows, then 16 maxima, then 16 sums
     float* const my_part = part + (unit * nsplit + split) * kPartFloats;
     for (int it = threadIdx.x; it < 16 * (kD / 4); it += NW * 64) {
@@ -857,16 +867,11 @@ __global__ __launch_bounds__(NW * 64) void paged_decode_short_kernel(
     // or invalidation -- a release fence per workgroup costs about as much here as the context split gains -- only
     // order: every wave waits until its stores have been acknowledged, the barrier collects the waves, then one thread
     // counts the workgroup in; the workgroup that finds nsplit - 1 earlier arrivals reads the partials after its
-    // counting has returned.  It merges them in split order and hands the counter back as it found it.  (Every
-    // workgroup of the unit gets here exactly once, with or without tiles.)
+    // counting has returned, and merges them in split order.  (Every workgroup of the unit gets here exactly once, with
+    // or without tiles.)
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t before = __hip_atomic_fetch_add(arrive + unit, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint32_t last = before == (uint32_t)(nsplit - 1) ? 1u : 0u;
-        if (last) __hip_atomic_store(arrive + unit, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sm_last = last;
-    }
+    if (threadIdx.x == 0) sm_last = arrival_count(counter, arrive_step, nsplit) ? 1u : 0u;
     __syncthreads();
     if (sm_last == 0u) return;
     // Every load of the merge is in flight at once, instead of one round trip past the caches per partial (step of
@@ -895,6 +900,7 @@ __global__ __launch_bounds__(NW * 64) void paged_decode_short_kernel(
         sm_l[r] = sum;
     }
     __syncthreads();
+    if (threadIdx.x == 0) arrival_clear(counter);
     for (int it = threadIdx.x; it < 16 * (kD / 4); it += NW * 64) {
         const int row = it / (kD / 4), c4 = it % (kD / 4);
         if (row >= rows) continue;
@@ -943,7 +949,8 @@ void launch_short_nw(const AttnArgs& a, hipStream_t stream)
                                    : paged_decode_short_kernel<NW, false, false, E, M, GE>);
     hipLaunchKernelGGL(kern, grid, dim3(NW * 64), 0, stream, a.cache, (const uint16_t*)a.q, (uint16_t*)a.out, a.lse,
                        a.block_table, a.seq_lens, a.num_q_heads, a.max_blocks, a.scale, a.mods,
-                       (const uint16_t*)a.k_new, (const uint16_t*)a.v_new, nsplit, a.short_part, a.short_arrive);
+                       (const uint16_t*)a.k_new, (const uint16_t*)a.v_new, nsplit, a.short_part, a.short_arrive,
+                       a.short_step);
 }
 
 template <int NW, typename E, typename M, typename GE>
