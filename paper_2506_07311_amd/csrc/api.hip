@@ -295,21 +295,41 @@ size_t f32_split_bytes(const AttnArgs& a, int32_t nsplit)
     return align256(decode_f32_part_floats(a, nsplit) * sizeof(float)) + arrival_bytes((int64_t)a.batch * a.cache.num_kv_heads);
 }
 
-// Workgroups per (sequence, KV head) of the fp32 decode kernel: one per compute unit (its eight waves take the register
-// file of one), at least one tile for every slot of its waves, and no more than the workspace holds partials for.
-int32_t plan_f32_splits(const AttnArgs& a, size_t ws_bytes)
+// Workgroups per (sequence, KV head) of the fp32 decode kernel.  `fill`: what fills the machine, one workgroup per compute
+// unit (its eight waves take the register file of one), while each slot of its waves has a tile; every sequence is cut that
+// far.  `nsplit`: what a long context among others is cut into, so that no workgroup walks more than kF32MaxShare keys (40
+// us and more) while the machine idles; a sequence takes as many as it has shares of `chunk` tiles.  The others leave at
+// once but cost their slot for about a microsecond, so there are at most kF32MaxWGs in all: beyond that the batch itself
+// averages the lengths out.  Not more than the workspace holds partials for.  us with the chunks of the portable
+// kernel / with `fill` alone / like this: 32 sequences of 64 .. 32768 tokens, 32 / 8 heads, head_dim 128 1460 / 1910 / 888; 64
+// of them at head_dim 64 1322 / 1099 / 842, 8 / 8 heads - / 793 / 417; 32 of 64 .. 131072 at head_dim 64 2399 / 2800 / 1718;
+// 256 of 64 .. 8192, 8 / 8 heads, head_dim 64 - / 416 / 395 (with shares of 1024 keys and 8192 workgroups 445).
+constexpr int64_t kF32MaxShare = 2048;
+constexpr int64_t kF32MaxWGs = 4096;
+
+void plan_f32_splits(AttnArgs& a, size_t ws_bytes)
 {
     const int64_t units = (int64_t)a.batch * a.cache.num_kv_heads;
-    int64_t n = device_cus() / units;
+    const int64_t tiles = ((int64_t)a.max_seq_len + 15) / 16;
+    auto fits = [&](int64_t n) { return n <= 1 || f32_split_bytes(a, (int32_t)n) <= ws_bytes; };
+    int64_t fill = device_cus() / units;
+    int64_t n = 0;
     if (g_opt.decode_chunk_tokens > 0) {
-        n = (a.max_seq_len + g_opt.decode_chunk_tokens - 1) / g_opt.decode_chunk_tokens;
+        fill = (a.max_seq_len + g_opt.decode_chunk_tokens - 1) / g_opt.decode_chunk_tokens;
     } else {
-        const int64_t by_keys = (a.max_seq_len + 15) / 16 / decode_f32_tile_slots(a);
-        if (n > by_keys) n = by_keys;
+        const int64_t by_keys = tiles / decode_f32_tile_slots(a);
+        if (fill > by_keys) fill = by_keys;
+        if (a.batch > 1) n = (a.max_seq_len + kF32MaxShare - 1) / kF32MaxShare;
+        if (n > kF32MaxWGs / units) n = kF32MaxWGs / units;
     }
+    if (n < fill) n = fill;
     if (n > kF32MaxSplit) n = kF32MaxSplit;
-    while (n > 1 && f32_split_bytes(a, (int32_t)n) > ws_bytes) --n;
-    return n < 1 ? 1 : (int32_t)n;
+    while (!fits(n)) --n;
+    if (n < 1) n = 1;
+    if (fill > n) fill = n;
+    a.short_nsplit = (int32_t)n;
+    a.short_fill = fill < 1 ? 1 : (int32_t)fill;
+    a.short_chunk = tiles > n ? (int32_t)((tiles + n - 1) / n) : 1;
 }
 
 size_t stream_workspace_bytes(int32_t batch, int32_t hq, int32_t d, int32_t wgs)
@@ -501,7 +521,8 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
     a.has_mods = m.window > 0 || m.softcap > 0.f || m.alibi_slopes || m.doc_ids || m.user_mod != 0;
     a.k_new = k_new;
     a.v_new = v_new;
-    a.short_nsplit = 1;
+    a.short_nsplit = a.short_fill = 1;
+    a.short_chunk = 0;
     a.short_part = nullptr;
     a.short_arrive = nullptr;
     a.short_step = 0;
@@ -574,7 +595,7 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
             return PA_ERR_WORKSPACE_TOO_SMALL;
         // (behind the check above: a workspace or scratch array that was too small for the chunks' partials stays too small)
         if (f32 && decode_f32_supported(a)) {
-            a.short_nsplit = plan_f32_splits(a, ws.bytes);
+            plan_f32_splits(a, ws.bytes);
             if (a.short_nsplit > 1)
                 place_split(f32_split_bytes(a, a.short_nsplit), (int64_t)batch * cache->num_kv_heads);
             return launch_decode_f32(a, s);

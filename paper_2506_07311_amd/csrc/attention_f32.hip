@@ -369,8 +369,9 @@ __global__ __launch_bounds__(NW * 64) void paged_attention_f32_kernel(
 // the same fp64 rate, so the products run there: a lane's piece of a K row against rows of q (held in LDS, one address per
 // quad), a 4-lane sum, and for P.V four keys times a lane's columns per row.  A wave holds R rows (two
 // at head_dim 64, one at 128: more spill); the `groups` (a power of two) waves that share a tile take other rows each and read it through the cache.
-// Everything else -- tiles, loads, LDS merge -- is as above, plus the context split: nsplit workgroups share a (sequence, KV head), leave their merged partial
-// in `part`, and the one that arrives last merges them in split order (the scheme of the one-launch decode kernel of the
+// Everything else -- tiles, loads, LDS merge -- is as above, plus the context split: several workgroups share a (sequence,
+// KV head), as many as its length asks for, leave their merged partial in `part`, and the one that arrives last merges them
+// in split order (the scheme of the one-launch decode kernel of the
 // 16-bit pools).  One launch, whatever the context; bound by launch and memory
 // round trips while a wave has a tile or two, by the stream of K and V beyond.
 // Portable kernel / this one, us: 1 x 16 tokens 8 / 8 heads, head_dim 64 6.0 / 4.7; 1 x 128 7.9 / 5.7; 1 x 2048 16.6 / 11.6;
@@ -381,7 +382,7 @@ template <int D, int R, int HEADS>
 __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
     CacheView cache, const float* __restrict__ q, float* __restrict__ out, float* __restrict__ lse,
     const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_lens, int32_t num_q_heads,
-    int32_t max_blocks, float scale, int32_t log2_groups, int32_t nsplit, float* __restrict__ part,
+    int32_t max_blocks, float scale, int32_t log2_groups, int32_t max_split, int32_t fill, int32_t chunk, float* __restrict__ part,
     uint64_t* __restrict__ arrive, uint64_t arrive_step, const float* __restrict__ k_new, const float* __restrict__ v_new)
 {
     constexpr int kHeads = HEADS;                            // rows a workgroup has room for
@@ -395,8 +396,8 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int r16 = lane & 15, quad = lane >> 4;
-    const int32_t s = (int32_t)blockIdx.x / nsplit;
-    const int32_t split = (int32_t)blockIdx.x - s * nsplit;
+    const int32_t s = (int32_t)blockIdx.x / max_split;
+    const int32_t split = (int32_t)blockIdx.x - s * max_split;
     const int32_t kvh = blockIdx.y;
     const int32_t G = num_q_heads / cache.num_kv_heads;
     const int64_t row0 = (int64_t)s * num_q_heads + (int64_t)kvh * G;
@@ -406,10 +407,15 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
     uint64_t* const counter = arrive + unit * kArrivalStride;
     uint64_t seen = 0;
     const int32_t len = seq_lens[s];
+    const int32_t nt = (len + kKeys - 1) / kKeys;
     const int group = kHeads == 1 ? 0 : wave & ((1 << log2_groups) - 1);          // this wave's rows: R * group ..
     const int slot = kHeads == 1 ? wave : wave >> log2_groups, slots = kHeads == 1 ? kWaves : kWaves >> log2_groups;
     for (int i = threadIdx.x; i < kHeads * D; i += kWaves * 64)
         sm_q[i] = i < G * D ? (double)q[row0 * D + i] * ((double)scale * kLog2e) : 0.0;
+    // the workgroups of this sequence: a round of tiles for each up to `fill`, more where they would get beyond `chunk`
+    const uint32_t rounds = (uint32_t)nt >> (kHeads == 1 ? 3 : 3 - log2_groups), shares = (uint32_t)(nt + chunk - 1) / (uint32_t)chunk;
+    const int32_t nsplit = (int32_t)min(max(min((uint32_t)fill, rounds), max(shares, 1u)), (uint32_t)max_split);
+    if (split >= nsplit) return;
 
     Rows a;
     a.table = block_table + (int64_t)s * max_blocks;
@@ -423,8 +429,8 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
     a.new_pos = -1;
     const int32_t last = len - 1;
     // this workgroup's tiles, dealt to its waves in turn
-    const int32_t nt = (len + kKeys - 1) / kKeys;
-    const int32_t tb = (int32_t)((int64_t)split * nt / nsplit), te = (int32_t)((int64_t)(split + 1) * nt / nsplit);
+    const int32_t each = (int32_t)((uint32_t)nt / (uint32_t)nsplit), more = nt - each * nsplit;   // the first `more` take one more
+    const int32_t tb = split * each + min(split, more), te = tb + each + (split < more ? 1 : 0);
     if (k_new) {
         const int64_t off = ((int64_t)s * cache.num_kv_heads + kvh) * D;
         a.knew = reinterpret_cast<const char*>(k_new + off);
@@ -571,7 +577,7 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
         }
         if (nsplit > 1) {
             // component-major, device-scope stores: see the arrival below
-            float* po = part + (unit * nsplit + split) * kParts;
+            float* po = part + (unit * max_split + split) * kParts;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 __hip_atomic_store(po + e * (kHeads * D / 4) + it, (float)acc[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -598,7 +604,7 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
     __syncthreads();
     if (sm_last == 0u) return;
     // all partials at once: a thread adds up every J-th partial of its row and columns, J threads per piece of the output
-    const float* pu = part + unit * nsplit * kParts;
+    const float* pu = part + unit * max_split * kParts;
     __shared__ double sm_w[kF32MaxSplit * kHeads];
     __shared__ double sm_s[kHeads], sm_M[kHeads];
     __shared__ __attribute__((aligned(16))) double sm_a[kWaves * 64 * 4];
@@ -658,7 +664,7 @@ void launch_decode_f32_dim(const AttnArgs& a, hipStream_t stream)
     auto kern = G == 1 ? paged_decode_f32_kernel<D, 1, 1> : paged_decode_f32_kernel<D, R, kF32MaxGroup>;
     hipLaunchKernelGGL(kern, dim3((uint32_t)(a.batch * a.short_nsplit), (uint32_t)a.cache.num_kv_heads), dim3(kWaves * 64), 0,
                        stream, a.cache, (const float*)a.q, (float*)a.out, a.lse, a.block_table, a.seq_lens, a.num_q_heads,
-                       a.max_blocks, a.scale, log2_groups, a.short_nsplit, a.short_part, a.short_arrive,
+                       a.max_blocks, a.scale, log2_groups, a.short_nsplit, a.short_fill, a.short_chunk, a.short_part, a.short_arrive,
                        a.short_step, (const float*)a.k_new,
                        (const float*)a.v_new);
 }

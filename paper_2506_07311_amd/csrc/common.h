@@ -164,6 +164,8 @@ struct AttnArgs {
     // one-launch decode with several workgroups per (sequence, KV head, slice): their number, their partials and the
     // arrival counters (both parts of the workspace), and the step they count in (see kArrivalStride)
     int32_t short_nsplit;
+    int32_t short_fill;      // fp32 kernel: workgroups every sequence is cut into (while each has a round of tiles), and
+    int32_t short_chunk;     // the most tiles one of them takes: longer contexts take more, up to short_nsplit
     float* short_part;
     uint64_t* short_arrive;
     uint64_t short_step;

@@ -118,3 +118,52 @@ def test_values_that_are_not_finite_stay_with_the_rows_that_see_them(pa, d, dtyp
     other = [c for c in range(d) if c != 3]
     assert (got[at:, :, other] - good[at:, :, other]).abs().max() <= eps
     assert not got[at:, :, 3].isfinite().any()
+
+
+F32_DECODES = [  # lens, Hq, Hkv, d, P
+    ([1, 15, 16, 17, 0, 129, 2049, 33], 8, 8, 64, 16),           # no groups: one row a wave
+    ([300, 0, 2049, 128, 129], 8, 4, 64, 32),                    # two heads a group
+    ([300, 2049, 257, 1], 12, 4, 64, 16),                        # three heads on four rows
+    ([2049, 64, 1000], 16, 4, 64, 128),
+    ([1, 300, 0, 2049, 511], 8, 8, 128, 16),
+    ([300, 2049, 17], 12, 4, 128, 64),
+    ([2049, 64, 1000], 16, 4, 128, 16),
+    ([5000, 1, 63] + [40, 129] * 16, 32, 8, 64, 16),             # more (sequence, KV head) units than compute units: only the
+    ([3000] + [20] * 64, 8, 8, 128, 16),                         # long contexts are cut
+    ([9000], 4, 4, 64, 16),                                      # more workgroups than a round of tiles each
+]
+
+
+@pytest.mark.parametrize("case", F32_DECODES, ids=lambda c: f"n{len(c[0])}-Hq{c[1]}-Hkv{c[2]}-d{c[3]}-P{c[4]}")
+@pytest.mark.parametrize("room", ["workspace", "static array"])
+def test_fp32_decode_on_the_vector_unit(pa, oracle, case, room):
+    """The one-launch fp32 decode kernel, up to four heads a group: its cuts by the real lengths, with the whole workspace and
+    through the entry point whose workspace is the static array; tolerance as above."""
+    from paper_2506_07311_amd import binding
+    lens, Hq, Hkv, d, P = case
+    w = W.make_workload("t", seq_lens=lens, q_lens=[1] * len(lens), append_lens=[min(n, 1) for n in lens], num_q_heads=Hq,
+                        num_kv_heads=Hkv, head_dim=d, page_size=P, dtype=torch.float32, seed=205, device=DEV)
+    k, v, o_ref, lse_ref = parity.oracle_step(oracle, w)
+    pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
+    lse = torch.full((w.batch, Hq), float("nan"), device=DEV)
+    out = torch.full_like(w.q, float("nan"))
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        if room == "workspace":
+            ws = torch.full((pa.paged_attention_workspace_bytes(w.batch, Hq, d, w.batch, w.max_seq_len),), 0xFF,
+                            dtype=torch.uint8, device=DEV)
+            pa.paged_attention_decode(w.k_cache, w.v_cache, w.q, w.block_table, w.seq_lens, w.max_seq_len, w.scale, out=out,
+                                      lse=lse, workspace=ws)
+        else:
+            pa.paged_attention_decode_static(w.k_cache, w.v_cache, w.q, w.block_table, w.seq_lens, w.max_seq_len, w.scale,
+                                             out=out, lse=lse)
+        torch.cuda.synchronize()
+        assert binding.pa_profile_read("paged_decode_f32_kernel")[0] == 1
+        assert binding.pa_profile_read("paged_attention")[0] == 0
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
+    parity.assert_close(parity.to_f64(out), o_ref, torch.float32, "out", tol=(2e-6, 1e-5))
+    got, empty = parity.to_f64(lse), ~torch.tensor(lse_ref).isfinite().numpy()
+    assert (got[empty] == float("-inf")).all() and abs(got[~empty] - lse_ref[~empty]).max() <= 1e-5
