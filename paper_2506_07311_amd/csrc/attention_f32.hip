@@ -377,7 +377,7 @@ __global__ __launch_bounds__(NW * 64) void paged_attention_f32_kernel(
 // Portable kernel / this one, us: 1 x 16 tokens 8 / 8 heads, head_dim 64 6.0 / 4.7; 1 x 128 7.9 / 5.7; 1 x 2048 16.6 / 11.6;
 // 8 x 2048 at head_dim 128 50 / 27 (134 MB), with 32 / 8 heads 99 / 47; 8 x 100 with 32 / 8 heads, head_dim 64 7.7 / 7.7.  With
 // more than 4 heads a group the matrix kernel above is the better one (8 x 2048, 64 / 8 heads: 91 here, 44 there).
-//     part: per workgroup 4 rows of D accumulators, then 4 x (reference, sum) as doubles (G = 1: one row).
+//     part: per workgroup 4 rows of D normalised accumulators, then 4 x (reference, sum) as doubles (G = 1: one row).
 template <int D, int R, int HEADS>
 __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
     CacheView cache, const float* __restrict__ q, float* __restrict__ out, float* __restrict__ lse,
@@ -543,13 +543,16 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
 #pragma unroll
     for (int g = 0; g < R; ++g) {
         l[g] = row_sum(l[g]);
+        // divided by the sum of the weights (up to 2^16 each, see above): a mean of V's values fits fp32, their sum may not
+        const double inv_l = l[g] > 0.0 ? 1.0 / l[g] : 1.0;
 #pragma unroll
         for (int c = 0; c < D / 64; ++c) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[g][c][e] = quad_sum(o[g][c][e]);
             if (quad == 0)
                 *reinterpret_cast<float4*>(sm_o + (wave * R + g) * D + 64 * c + 4 * r16) =
-                    float4{(float)o[g][c][0], (float)o[g][c][1], (float)o[g][c][2], (float)o[g][c][3]};
+                    float4{(float)(o[g][c][0] * inv_l), (float)(o[g][c][1] * inv_l), (float)(o[g][c][2] * inv_l),
+                           (float)(o[g][c][3] * inv_l)};
         }
         if (lane == 0) {
             sm_m[wave * R + g] = m[g];
@@ -567,9 +570,9 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
         for (int p = 0; p < slots; ++p) M = __builtin_fmax(M, sm_m[first + p * step]);
         for (int p = 0; p < slots; ++p) {
             const double mp = sm_m[first + p * step], lp = sm_l[first + p * step];
-            const double w = mp == -INFINITY ? 0.0 : (double)exp2_of(mp - M);
+            const double w = mp == -INFINITY ? lp : (double)exp2_of(mp - M) * lp;    // (no key seen: lp is 0, or NaN)
             const float4 v = *reinterpret_cast<const float4*>(sm_o + (first + p * step) * D + 4 * c4);
-            sum += mp == -INFINITY ? lp : w * lp;
+            sum += w;
             acc[0] += w * v.x;
             acc[1] += w * v.y;
             acc[2] += w * v.z;
@@ -578,9 +581,10 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
         if (nsplit > 1) {
             // component-major, device-scope stores: see the arrival below
             float* po = part + (unit * max_split + split) * kParts;
+            const double inv = sum > 0.0 ? 1.0 / sum : 1.0;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                __hip_atomic_store(po + e * (kHeads * D / 4) + it, (float)acc[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(po + e * (kHeads * D / 4) + it, (float)(acc[e] * inv), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (c4 == 0) {
                 double* ps = reinterpret_cast<double*>(po + kHeads * D) + 2 * g;
                 __hip_atomic_store(ps, M, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -620,8 +624,8 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_f32_kernel(
         for (int p = 0; p < nsplit; ++p) {
             const int i = p * G + threadIdx.x;
             const double lp = sm_a[i];
-            const double w = sm_w[i] == -INFINITY ? 0.0 : (double)exp2_of(sm_w[i] - M);
-            sum += sm_w[i] == -INFINITY ? lp : w * lp;
+            const double w = sm_w[i] == -INFINITY ? lp : (double)exp2_of(sm_w[i] - M) * lp;
+            sum += w;
             sm_w[i] = w;
         }
         sm_M[threadIdx.x] = M;

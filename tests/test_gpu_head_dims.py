@@ -167,3 +167,23 @@ def test_fp32_decode_on_the_vector_unit(pa, oracle, case, room):
     parity.assert_close(parity.to_f64(out), o_ref, torch.float32, "out", tol=(2e-6, 1e-5))
     got, empty = parity.to_f64(lse), ~torch.tensor(lse_ref).isfinite().numpy()
     assert (got[empty] == float("-inf")).all() and abs(got[~empty] - lse_ref[~empty]).max() <= 1e-5
+
+
+@pytest.mark.parametrize("Hq,Hkv,d", [(4, 4, 64), (8, 2, 64), (4, 4, 128), (8, 2, 128)])
+@pytest.mark.parametrize("n", [40, 2049])
+def test_fp32_decode_of_large_values(pa, Hq, Hkv, d, n):
+    """Values whose mean fits fp32 and whose weighted sum relative to an early key's score would not: every first key of a tile
+    scores 0 and the others e^10, which is as far as the kernel's softmax reference may trail (2^16).  Every value is the
+    same, so the output is that value up to the rounding of the partials (a few ulp)."""
+    w = W.make_workload("t", seq_lens=[n], num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=16, dtype=torch.float32,
+                        identity_pages=True, poison=False, seed=206, device=DEV)
+    w.q.fill_(1.0)
+    w.k_cache.fill_(10.0 / d)
+    w.k_cache[:, 0] = 0.0
+    w.v_cache.fill_(1e35)
+    lse = torch.empty((1, Hq), device=DEV)
+    out = pa.paged_attention_decode(w.k_cache, w.v_cache, w.q, w.block_table, w.seq_lens, n, 1.0, lse=lse)
+    assert ((out.double() / 1e35 - 1.0).abs() <= 4e-7).all()
+    firsts = (n + 15) // 16
+    ref = torch.log(torch.tensor(firsts + (n - firsts) * float(torch.exp(torch.tensor(10.0, dtype=torch.float64)))))
+    assert (lse.cpu() - ref).abs().max() <= 1e-5
