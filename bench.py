@@ -63,6 +63,28 @@ WORKLOADS = {
 }
 
 
+# the names under which the library times its kernels (one of them per attention call, and what goes with it)
+ATTENTION_KERNELS = ("paged_decode_mfma_kernel", "paged_decode_short_kernel", "paged_decode_f32_kernel",
+                     "paged_prefill_mfma_kernel", "paged_attention_f32_kernel", "paged_attention_generic_kernel")
+KERNELS = ATTENTION_KERNELS + ("paged_kv_append_kernel", "paged_kv_append_last_kernel", "paged_attention_merge_kernel",
+                               "paged_attention_merge_list_kernel")
+
+
+def read_kernels(binding, names):
+    """Launches and average time of each of these kernels that ran since the last pa_profile_reset."""
+    res = {}
+    for name in names:
+        n, ms = binding.pa_profile_read(name)
+        if n:
+            res[name] = {"launches": n, "avg_us": ms * 1e3 / n}
+    return res
+
+
+def dominant(kernels):
+    """(name, average us) of the longest of these kernels, None if none ran."""
+    return max(((k, v["avg_us"]) for k, v in kernels.items()), key=lambda kv: kv[1], default=None)
+
+
 def measured_traffic(args):
     """The committed counter figures belong to a workload as it is defined; a run that overrides its shape, element
     type or hooks has no measured traffic."""
@@ -225,12 +247,7 @@ def run_other_configs(torch, pa, binding, W, dev):
         time_steps(torch, step, 30, 0)
         binding.pa_profile_enable(False)
         sec = time_steps(torch, step, 30, 0)
-        dom = None
-        for name in ("paged_decode_mfma_kernel", "paged_decode_short_kernel", "paged_attention_generic_kernel"):
-            n, ms = binding.pa_profile_read(name)
-            if n:
-                dom = (name, ms * 1e3 / n)
-                break
+        dom = dominant(read_kernels(binding, ATTENTION_KERNELS))
         binding.pa_profile_reset()
         nbytes = w.logical_kv_bytes()
         res[wl] = {"us_per_step": round(sec * 1e6, 2), "tokens_per_s": round(w.total_q / sec, 1), "kernel": dom[0],
@@ -446,13 +463,7 @@ def main():
         time_steps(torch, step, args.steps, 0, stats_key="step")    # spread of the single steps (one event between steps)
         kernel_timing = ("per-kernel events in a pass of their own over the same K steps "
                          f"({sec_events * 1e6:.1f} us per step with them); step time from the pass without them")
-    for name in ("paged_kv_append_kernel", "paged_kv_append_last_kernel", "paged_decode_mfma_kernel",
-                 "paged_decode_short_kernel",
-                 "paged_attention_generic_kernel",
-                 "paged_attention_merge_kernel", "paged_prefill_mfma_kernel"):
-        n, ms = binding.pa_profile_read(name)
-        if n:
-            kernels[name] = {"launches": n, "avg_us": ms * 1e3 / n}
+    kernels.update(read_kernels(binding, KERNELS))
     binding.pa_profile_reset()
 
     us = sec * 1e6
@@ -490,8 +501,8 @@ def main():
     # the others by the prefill kernel (bound: their flops)
     small = [ql * G <= 16 for ql in w.q_lens_host]
     t_dec = kernels.get("paged_decode_mfma_kernel", {}).get("avg_us", 0.0)
-    t_pre = max(kernels.get("paged_prefill_mfma_kernel", {}).get("avg_us", 0.0),
-                kernels.get("paged_attention_generic_kernel", {}).get("avg_us", 0.0))
+    pre = dominant({k: v for k, v in kernels.items() if k in ATTENTION_KERNELS and k != "paged_decode_mfma_kernel"})
+    t_pre = pre[1] if pre else 0.0
     if is_prefill and t_dec > t_pre:
         small_bytes = sum(L for L, sm in zip(w.seq_lens_host, small) if sm) * 2 * w.num_kv_heads * w.head_dim * 2
         ach = small_bytes / (t_dec * 1e-6) / 1e9
@@ -513,17 +524,14 @@ def main():
             return n
         flops = sum(4 * w.num_q_heads * w.head_dim * pairs(ql, L)
                     for ql, L, sm in zip(w.q_lens_host, w.seq_lens_host, small) if not (sm and routed))
-        dom = kernels.get("paged_prefill_mfma_kernel") or kernels.get("paged_attention_generic_kernel")
-        ach = flops / (dom["avg_us"] * 1e-6) / 1e12
+        ach = flops / (t_pre * 1e-6) / 1e12
         result["roofline"] = {"bound": "mfma", "achieved": round(ach, 1), "peak": MFMA_BF16_PEAK_TFLOPS,
                               "unit": "TFLOP/s", "frac": round(ach / MFMA_BF16_PEAK_TFLOPS, 4),
                               "traffic": measured_traffic(args),
-                              "kernel": "paged_prefill_mfma_kernel" if "paged_prefill_mfma_kernel" in kernels
-                              else "paged_attention_generic_kernel", "useful_flops": flops}
+                              "kernel": pre[0], "useful_flops": flops}
     else:
-        name = next(n for n in ("paged_decode_mfma_kernel", "paged_decode_short_kernel",
-                                "paged_attention_generic_kernel") if n in kernels)
-        ach = kv_bytes / (kernels[name]["avg_us"] * 1e-6) / 1e9
+        name, t_dec = dominant({k: v for k, v in kernels.items() if k in ATTENTION_KERNELS})
+        ach = kv_bytes / (t_dec * 1e-6) / 1e9
         result["roofline"] = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                               "frac": round(ach / HBM_PEAK_GBPS, 4), "traffic": measured_traffic(args),
                               "kernel": name,
@@ -569,12 +577,7 @@ def main():
             psec = time_steps(torch, pstep, max(30, args.steps), 5)   # ... step time: the same steps without them
             S = wp.max_seq_len
             flops = 4 * wp.batch * wp.num_q_heads * wp.head_dim * S * (S + 1) // 2
-            pk = None
-            for name in ("paged_prefill_mfma_kernel", "paged_attention_generic_kernel"):
-                n, ms = binding.pa_profile_read(name)
-                if n:
-                    pk = (name, ms * 1e3 / n)
-                    break
+            pk = dominant(read_kernels(binding, ATTENTION_KERNELS))
             binding.pa_profile_reset()
             result["prefill"] = {"workload": "prefill_b4_s2048_causal", "us_per_step": round(psec * 1e6, 1),
                                  "tokens_per_s": round(wp.total_q / psec, 1), "kernel": pk[0],

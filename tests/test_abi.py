@@ -168,6 +168,24 @@ def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
         binding.load_library()
 
 
+def test_bench_knows_every_kernel_the_library_times():
+    """bench.py reads the library's kernel times by name: a kernel it does not know leaves its workloads without one."""
+    import glob
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("bench", os.path.join(ROOT, "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    named = set()
+    for path in glob.glob(os.path.join(ROOT, "paper_2506_07311_amd", "csrc", "*.hip")):
+        for scope in re.findall(r"ProfileScope prof\((.*?), \w+\);", open(path).read()):
+            named |= set(re.findall(r'"(\w+)"', scope))
+    assert len(named) > 8
+    # outside an attention step: the read yardstick, the gather utility and the page manager's copy
+    assert named - set(bench.KERNELS) == {"pa_stream_read_kernel", "paged_kv_gather_kernel", "paged_kv_copy_page_kernel"}
+    assert set(bench.KERNELS) <= named
+    assert bench.dominant({"a": {"avg_us": 1.0}, "b": {"avg_us": 3.0}}) == ("b", 3.0) and bench.dominant({}) is None
+
+
 def test_bench_refuses_more_than_one_gpu():
     """Every box of this build has one GPU: bench.py says so instead of starting ranks."""
     import subprocess
