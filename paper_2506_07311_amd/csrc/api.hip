@@ -222,7 +222,15 @@ constexpr int64_t kShortMaxRowBytes = 1024 * 512;   // context tokens x bytes of
 // A single sequence has no lengths to balance, and its split reads at what the memory gives: the tile stream's slower start
 // and second launch are worth it only beyond this many bytes of K and V (32 / 8 heads: 32768 tokens 30.0 us against 37.9,
 // 65536 62.0 against 56.1; 8 / 1 heads, 131072 tokens = 67 MB, 48 against 66; 32 / 32, 16384 = 268 MB, 48.0 against 48.5).
+// Nor beyond what so many workgroups read in that time: a unit has at most 32, so with one or two KV heads most of the machine
+// stands by (8 / 1 heads: 131072 tokens = 2.1 MB a workgroup 48 us against 66, 300000 = 4.8 MB 94 against 77; head_dim 64,
+// 600000 99 against 78); with several slices of 16 heads a unit's rows are read by all of them, from the caches at best
+// (64 / 1, 30000 tokens = 0.5 MB 20.6 against 28.2, 200000 = 3.2 MB 67 against 56; 40 / 2, 100000 = 1.6 MB 40.7 against 41.9).
+// head_dim 256, whose tile stream has half the waves: 8 / 1 heads, 150000 tokens = 4.8 MB 107 against 123.
 constexpr int64_t kShortMaxSingleBytes = (int64_t)160 << 20;
+constexpr int64_t kShortMaxSingleShare = (int64_t)3 << 20;
+constexpr int64_t kShortMaxWideShare = (int64_t)5 << 20;
+constexpr int64_t kShortMaxSlicedShare = (int64_t)3 << 19;
 constexpr int64_t kShortMaxWGsPerCU = 2;
 constexpr int32_t kShortMinSplitElems = 16384;   // keys x head_dim
 // The plan that paged_attention_decode_static's scratch limit is stated for (see run_attention).
@@ -251,12 +259,18 @@ int32_t plan_short_splits(const AttnArgs& a, int32_t min_keys = 0, int32_t max_s
     return n < 1 ? 1 : (int32_t)n;
 }
 
-bool short_decode_pays(const AttnArgs& a, int32_t nsplit)
+// any_share: a single sequence may give a workgroup any share (where the tile stream has no room for its partials).
+bool short_decode_pays(const AttnArgs& a, int32_t nsplit, bool any_share = false)
 {
     if (g_opt.decode_workgroups > 0) return false;     // the caller shapes the tile stream: keep it
     const int64_t row_bytes = 4LL * (a.cache.head_dim > 128 ? a.cache.head_dim : 128);
     const int64_t share = ((int64_t)a.max_seq_len + nsplit - 1) / nsplit;
+    const int64_t share_bytes = share * 4LL * a.cache.head_dim;
+    const int64_t most = a.num_q_heads / a.cache.num_kv_heads > 16 ? kShortMaxSlicedShare
+                         : a.cache.head_dim > 128                  ? kShortMaxWideShare
+                                                                   : kShortMaxSingleShare;
     const bool single = a.batch == 1 && nsplit > 1 &&
+                        (any_share || share_bytes <= most) &&
                         4LL * a.max_seq_len * a.cache.num_kv_heads * a.cache.head_dim <= kShortMaxSingleBytes;
     return (single || share * row_bytes <= kShortMaxRowBytes) && short_units(a) * nsplit <= kShortMaxWGsPerCU * device_cus();
 }
@@ -558,12 +572,11 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
     if (decode) {
         if (!g_opt.force_generic && g_opt.decode_short >= 0 && decode_short_supported(a)) {
             const int32_t nsplit = plan_short_splits(a);
-            if (g_opt.decode_short > 0 || short_decode_pays(a, nsplit)) {
+            const bool cramped = !ws.bound && g_opt.decode_short == 0 && ws.bytes < tile_stream_bytes();
+            if (g_opt.decode_short > 0 || short_decode_pays(a, nsplit, cramped)) {
                 // A call that the static scratch array was too small for stays refused, although this kernel now takes it with
                 // less: the limit is that of the tile stream wherever a split of 16 or of 256 keys would have left it that.
-                if (!ws.bound && g_opt.decode_short == 0 &&
-                    !short_decode_pays(a, plan_short_splits(a, kScratchMinSplitKeys, kScratchMaxSplit)) &&
-                    ws.bytes < tile_stream_bytes())
+                if (cramped && !short_decode_pays(a, plan_short_splits(a, kScratchMinSplitKeys, kScratchMaxSplit), true))
                     return PA_ERR_WORKSPACE_TOO_SMALL;
                 a.short_nsplit = nsplit;
                 if (nsplit > 1) {

@@ -136,3 +136,25 @@ def test_captured_calls_replay_beside_each_other(pa, shape):
         eager = prepare(pa, w, qs[rep], torch.empty_like(w.q), None, wss[rep])()
         torch.cuda.synchronize()
         assert torch.equal(eager, ref[rep][0])
+
+
+@pytest.mark.parametrize("L,Hq,Hkv,d,one_launch", [(30000, 8, 1, 128, True), (300000, 8, 1, 128, False),
+                                                   (600000, 8, 1, 64, False), (30000, 64, 1, 128, True),
+                                                   (150000, 64, 1, 128, False), (20000, 32, 8, 128, True),
+                                                   (150000, 8, 1, 256, True)])
+def test_one_launch_takes_a_single_sequence_while_its_workgroups_shares_are_short(pa, L, Hq, Hkv, d, one_launch):
+    """A (sequence, KV head) has at most 32 workgroups: with one KV head a long context belongs on the tile stream."""
+    from paper_2506_07311_amd import binding
+    w = W.make_workload("t", seq_lens=[L], num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=64,
+                        dtype=torch.bfloat16, seed=304, device=DEV, poison=False, pool_factor=1.0)
+    out = torch.empty_like(w.q)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        prepare(pa, w, w.q, out, None, buffers(pa, w, 1)[3][0])()
+        torch.cuda.synchronize()
+        assert binding.pa_profile_read("paged_decode_short_kernel")[0] == (1 if one_launch else 0)
+        assert binding.pa_profile_read("paged_decode_mfma_kernel")[0] == (0 if one_launch else 1)
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
