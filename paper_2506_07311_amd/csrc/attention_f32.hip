@@ -134,6 +134,25 @@ __device__ __forceinline__ void load_v(TileRegs<D>& t, const Rows& a, int64_t pa
     }
 }
 
+// The compact grid's numbering of row tiles: sequence s has tiles first_tile(s) .. first_tile(s + 1) - 1, at most one more
+// than its rows fill.  Returns the sequence of tile t (64 candidates a step: one round trip up to 64 sequences).
+__device__ __forceinline__ int64_t first_tile(const int32_t* __restrict__ cu_q_lens, int32_t s, int32_t G)
+{
+    return (int64_t)cu_q_lens[s] * G / kRows + s;
+}
+__device__ __forceinline__ int32_t tile_sequence(const int32_t* __restrict__ cu_q_lens, int32_t batch, int32_t G, int64_t t,
+                                                 int lane)
+{
+    int32_t lo = 0, hi = batch;
+    while (hi - lo > 1) {
+        const int32_t step = (hi - lo + 63) / 64, i = lo + lane * step;
+        const uint64_t below = __ballot(i < hi && first_tile(cu_q_lens, min(i, batch - 1), G) <= t);
+        lo += (__popcll((unsigned long long)below) - 1) * step;            // (lane 0 always is)
+        hi = min(lo + step, hi);
+    }
+    return lo;
+}
+
 __device__ __forceinline__ float elem(const float4& v, int e) { return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w; }
 
 template <int D, int NW>
@@ -152,14 +171,23 @@ __global__ __launch_bounds__(NW * 64) void paged_attention_f32_kernel(
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int r16 = lane & 15, quad = lane >> 4;
+    const int32_t G = num_q_heads / cache.num_kv_heads;
     // last row tiles (the heaviest under a causal bound) first
     int32_t b = blockIdx.x;
     const int32_t split = b % nsplit;
     b /= nsplit;
     const int32_t kvh = b % cache.num_kv_heads;
     b /= cache.num_kv_heads;
-    const int32_t s = b % batch;
-    const int32_t m0 = (row_tiles - 1 - b / batch) * kRows;
+    int32_t s, m0;
+    if (row_tiles > 0) {
+        s = b % batch;
+        m0 = (row_tiles - 1 - b / batch) * kRows;
+    } else {                                                 // compact grid (see launch_attention_f32)
+        s = tile_sequence(cu_q_lens, batch, G, b, lane);
+        const int32_t rows = (cu_q_lens[s + 1] - cu_q_lens[s]) * G;
+        m0 = ((rows + kRows - 1) / kRows - 1 - (int32_t)(b - first_tile(cu_q_lens, s, G))) * kRows;
+        if (m0 < 0) return;
+    }
     const int32_t c0 = split * chunk;
 
     Rows a;
@@ -176,7 +204,6 @@ __global__ __launch_bounds__(NW * 64) void paged_attention_f32_kernel(
         q_begin = cu_q_lens[s];
         q_len = cu_q_lens[s + 1] - q_begin;
     }
-    const int32_t G = num_q_heads / cache.num_kv_heads;
     const int32_t n_rows = q_len * G;
     if (m0 >= n_rows) return;
     const int32_t row = m0 + r16;
@@ -715,10 +742,21 @@ pa_status launch_decode_f32(const AttnArgs& a, hipStream_t stream)
 pa_status launch_attention_f32(const AttnArgs& a, hipStream_t stream)
 {
     const int64_t G = a.num_q_heads / a.cache.num_kv_heads;
-    const int64_t tiles = (a.max_q_len * G + kRows - 1) / kRows;
-    const int64_t blocks = tiles * a.batch * a.cache.num_kv_heads * a.plan.nsplit;
-    if (blocks <= 0) return PA_OK;
-    if (blocks > 0x7fffffffLL) return PA_ERR_UNSUPPORTED;
+    // One workgroup per (row tile of the longest possible query range, sequence) where most of those exist, the heaviest
+    // tiles of all sequences first; a compact grid of the row tiles that total_q allows where they do not (one prompt among
+    // single queries, a loose max_q_len), since an empty workgroup costs its slot for a microsecond or two.  256 sequences
+    // of 100 .. 400 tokens, four of them with 300 queries, 32 / 8 heads, head_dim 64: 371 / 113 us (portable kernel 310); 16
+    // prompts of 100 .. 1000, 8 / 8 heads 202 / 145; 64 of 64 .. 2048, four with 300 queries 259 / 107.
+    int64_t tiles = (a.max_q_len * G + kRows - 1) / kRows;
+    if (tiles <= 0) return PA_OK;
+    const int64_t compact = (int64_t)a.total_q * G / kRows + a.batch;
+    int64_t blocks = tiles * a.batch;
+    if (a.cu_q_lens && (blocks > 2 * compact || tiles * kRows > 0x7fffffffLL)) {
+        blocks = compact;
+        tiles = 0;
+    }
+    blocks *= (int64_t)a.cache.num_kv_heads * a.plan.nsplit;
+    if (blocks > 0x7fffffffLL) return launch_attention_generic(a, stream);      // (which has its own limit)
     ProfileScope prof("paged_attention_f32_kernel", stream);
     auto kern = a.cache.head_dim == 64 ? paged_attention_f32_kernel<64, kWaves> : paged_attention_f32_kernel<128, kWaves>;
     hipLaunchKernelGGL(kern, dim3((uint32_t)blocks), dim3(kWaves * 64), 0, stream, a.cache, (const float*)a.q, (float*)a.out,

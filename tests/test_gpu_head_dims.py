@@ -187,3 +187,31 @@ def test_fp32_decode_of_large_values(pa, Hq, Hkv, d, n):
     firsts = (n + 15) // 16
     ref = torch.log(torch.tensor(firsts + (n - firsts) * float(torch.exp(torch.tensor(10.0, dtype=torch.float64)))))
     assert (lse.cpu() - ref).abs().max() <= 1e-5
+
+
+@pytest.mark.parametrize("lens,q_lens", [([300] + [40] * 70, [200] + [1] * 70),           # one prompt among single queries
+                                         ([40, 0, 33, 64, 16, 17, 5], [40, 0, 3, 16, 0, 17, 1]),
+                                         ([16] * 5000 + [100], [0, 1] * 2500 + [90])],    # more than 64 x 64 sequences
+                         ids=lambda v: f"n{len(v)}")
+@pytest.mark.parametrize("max_q_len", [0, 1 << 30])
+def test_fp32_prefill_with_mostly_empty_row_tiles(pa, oracle, lens, q_lens, max_q_len):
+    """max_q_len is an upper bound: however loose, the call runs, and gives what the tight one gives."""
+    from paper_2506_07311_amd import binding
+    for Hq, Hkv, d in ((3, 1, 64), (2, 2, 128)):
+        w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=16,
+                            dtype=torch.float32, causal=True, seed=207, device=DEV)
+        _, _, o_ref, lse_ref = parity.oracle_step(oracle, w)
+        pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
+        lse = torch.full((w.total_q, Hq), float("nan"), device=DEV)
+        binding.pa_profile_reset()
+        binding.pa_profile_enable(True)
+        try:
+            out = pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, w.cu_q_lens, max_q_len or w.max_q_len, w.block_table,
+                                             w.seq_lens, w.max_seq_len, w.scale, True, lse=lse)
+            torch.cuda.synchronize()
+            assert binding.pa_profile_read("paged_attention_f32_kernel")[0] == 1
+        finally:
+            binding.pa_profile_enable(False)
+            binding.pa_profile_reset()
+        parity.assert_close(parity.to_f64(out), o_ref, torch.float32, "out", tol=(2e-6, 1e-5))
+        assert abs(parity.to_f64(lse) - lse_ref).max() <= 1e-5
