@@ -648,7 +648,22 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
             ws.bytes >= required_workspace_bytes(batch, num_q_heads, d, total_q, max_seq_len) + list_bytes(d))
             list_items = prefill_list_items(a);
         if (list_items * (num_q_heads >> lg) > 0x7fffffffLL) list_items = 0;
-        if (list_items > 0) {
+        const bool list_cuts = list_items > 0;
+        if (prefill_padded_dim(d) && !list_cuts && prefill_grid_mostly_empty(a)) {
+            // These head_dims came from the portable kernel, whose grid has no empty workgroups.  The list without cuts has none
+            // either; it pays beyond one round of the machine's slots while one wave sees all sequences at once, and where
+            // empty workgroups cost more than its scans (plain grid / list, D = 96: 64 sequences of up to 2048 tokens, four
+            // with 300 queries 100 / 74 us, 8 prompts of 33 .. 900 with 8 / 2 heads, 464 workgroups 30.4 / 31.0; 256 sequences,
+            // four with 300 queries, 20480 workgroups 68 / 89, one with 2048, 131072 155 / 181).  A few rows on a long
+            // context, which the plain grid cuts, go back to the portable kernel where the empty ones cost as much as it does.
+            const double wgs = prefill_grid_workgroups(a, pp.nsplit);
+            if (pp.nsplit == 1 && max_seq_len < (1 << 28) && prefill_list_supported(a) && wgs > 512.0 &&
+                (batch <= 64 || wgs > 262144.0) && prefill_list_items(a) * (num_q_heads >> lg) <= 0x7fffffffLL)
+                list_items = prefill_list_items(a);
+            else if (wgs > 262144.0 || (pp.nsplit > 1 && wgs > 65536.0))
+                return launch_attention_generic(a, s);
+        }
+        if (list_cuts) {
             pp.chunk = max_seq_len;
             pp.nsplit = 1;
             split_bytes = list_bytes(d);
@@ -672,8 +687,9 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
             b.plan = pp;
             b.part_o = reinterpret_cast<float*>(base);
             b.part_lse = reinterpret_cast<float*>(base + part_o_bytes(total_q, num_q_heads, d, pp.nsplit));
-            if (list_items > 0) {
-                a.list_items = b.list_items = (int32_t)list_items;
+            b.list_items = (int32_t)list_items;
+            if (list_cuts) {
+                a.list_items = b.list_items;
                 a.list_o = b.list_o = reinterpret_cast<float*>(base);
                 a.list_lse = b.list_lse = reinterpret_cast<float*>(
                     base + align256(prefill_list_slots() * prefill_list_slot_floats(d) * sizeof(float)));
@@ -681,7 +697,7 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
             }
             st = launch_prefill_mfma(b, s);
             if (st != PA_OK) return st;
-            if (list_items > 0 && !may_have_small) return launch_merge(a, s);
+            if (list_cuts && !may_have_small) return launch_merge(a, s);
         }
         if (may_have_small) {
             AttnArgs b = a;

@@ -756,7 +756,7 @@ pa_status launch_attention_f32(const AttnArgs& a, hipStream_t stream)
         tiles = 0;
     }
     blocks *= (int64_t)a.cache.num_kv_heads * a.plan.nsplit;
-    if (blocks > 0x7fffffffLL) return launch_attention_generic(a, stream);      // (which has its own limit)
+    if (blocks * kWaves * 64 > 0xffffffffLL) return launch_attention_generic(a, stream);   // (a launch has 2^32 threads)
     ProfileScope prof("paged_attention_f32_kernel", stream);
     auto kern = a.cache.head_dim == 64 ? paged_attention_f32_kernel<64, kWaves> : paged_attention_f32_kernel<128, kWaves>;
     hipLaunchKernelGGL(kern, dim3((uint32_t)blocks), dim3(kWaves * 64), 0, stream, a.cache, (const float*)a.q, (float*)a.out,

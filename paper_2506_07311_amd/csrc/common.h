@@ -152,7 +152,7 @@ struct AttnArgs {
     int32_t* seg_last;
     int32_t list_items;      // prefill kernel: > 0 = work-list mode with at most this many (tile, chunk) items per head
                              // group (see prefill_tiles.h); partials by slot in list_o / list_lse
-    float* list_o;
+    float* list_o;           // (null: no context is cut, there are no partials)
     float* list_lse;
     int32_t skip_small;      // prefill kernel: leave sequences with q_len * G <= 16 to the decode kernel
     ModArgs mods;
@@ -214,6 +214,11 @@ pa_status launch_prefill_mfma(const AttnArgs& a, hipStream_t stream);
 // Its work-list mode (prefill_tiles.h): partial slots and floats per slot (plus 128 LSEs), the shortest context it may
 // cut, and the (tile, chunk) items per head group of a call.
 bool prefill_list_supported(const AttnArgs& a);
+// Row tiles of the plain grid are mostly empty (one prompt among single queries, a loose max_q_len); its workgroups.
+bool prefill_grid_mostly_empty(const AttnArgs& a);
+double prefill_grid_workgroups(const AttnArgs& a, int32_t nsplit);
+// The head_dims that the portable kernel served before the padded tiles did: what it took, they take or leave to it.
+inline bool prefill_padded_dim(int32_t d) { return d == 80 || d == 96 || d == 112; }
 int32_t prefill_list_slots();
 size_t prefill_list_slot_floats(int32_t head_dim);
 int32_t prefill_list_min_context();

@@ -27,7 +27,7 @@ bool prefill_mfma_supported(const AttnArgs& a)
     // (append + prefill, portable / this kernel): 1 x 8 tokens 8.6 / 7.2 us, 1 x 100 with 32 heads 20.1 / 9.7, 2 x 300
     // 138 / 13.0, 2 prompts of 700 and 950 tokens with 32 / 32 heads at D = 96 1075 / 36; 2 rows behind 4000 cached
     // tokens 83.5 / 33.3.  Hooks and smaller pages stay on the portable kernel: instantiations for them do not exist.
-    const bool odd = (d == 80 || d == 96 || d == 112) && !a.has_mods && a.cache.page_size >= 16;
+    const bool odd = prefill_padded_dim(d) && !a.has_mods && a.cache.page_size >= 16;
     if (d != 128 && d != 64 && !(d == 256 && a.cache.page_size >= 16) && !odd) return false;
     if (!(a.scale > 0.f)) return false;   // the kernel takes the max before scaling
     // the tile fetch keeps a row's byte offset inside its page (slot, KV head, piece) in 32 bits
@@ -61,13 +61,28 @@ int64_t prefill_list_items(const AttnArgs& a)
            (a.batch < a.total_q ? a.batch : a.total_q) + 1;
 }
 
+static int64_t plain_row_tiles(const AttnArgs& a)
+{
+    return (((int64_t)a.max_q_len << prefill_mfma_log2_pack(a.num_q_heads, a.cache.num_kv_heads)) + kBM - 1) / kBM;
+}
+bool prefill_grid_mostly_empty(const AttnArgs& a)
+{
+    const int32_t lg = prefill_mfma_log2_pack(a.num_q_heads, a.cache.num_kv_heads);
+    return plain_row_tiles(a) * a.batch > 2 * ((((int64_t)a.total_q << lg) / kBM) + a.batch);
+}
+double prefill_grid_workgroups(const AttnArgs& a, int32_t nsplit)
+{
+    const int32_t lg = prefill_mfma_log2_pack(a.num_q_heads, a.cache.num_kv_heads);
+    return (double)plain_row_tiles(a) * nsplit * (a.num_q_heads >> lg) * a.batch;
+}
+
 pa_status launch_prefill_mfma(const AttnArgs& a, hipStream_t stream)
 {
     PrefillPlan plan;
     plan.list_items = a.list_items;
     plan.list_o = a.list_o;
     plan.list_lse = a.list_lse;
-    plan.list_unit = a.cache.page_size > kBN ? a.cache.page_size : kBN;
+    plan.list_unit = !a.list_o ? kListUncut : a.cache.page_size > kBN ? a.cache.page_size : kBN;
     plan.log2_pack = prefill_mfma_log2_pack(a.num_q_heads, a.cache.num_kv_heads);
     plan.chunk = a.plan.chunk;
     plan.nsplit = a.plan.nsplit;

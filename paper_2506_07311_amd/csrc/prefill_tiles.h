@@ -111,6 +111,8 @@ constexpr int32_t kListSlots = 512;
 // for every possible item and quarter, 129 like this, 131 on the plain grid).
 constexpr int32_t kListGrid = 2048;
 constexpr int32_t kListMergeGrid = 2048;
+// The chunk unit that leaves every context whole: the list as a grid of the row tiles that exist.
+constexpr int32_t kListUncut = 1 << 28;
 
 // small_group = query heads per KV head when sequences with q_len * G <= 16 are left to the decode kernel, kNoSmallGroup
 // when none is.

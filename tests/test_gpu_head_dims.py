@@ -215,3 +215,22 @@ def test_fp32_prefill_with_mostly_empty_row_tiles(pa, oracle, lens, q_lens, max_
             binding.pa_profile_reset()
         parity.assert_close(parity.to_f64(out), o_ref, torch.float32, "out", tol=(2e-6, 1e-5))
         assert abs(parity.to_f64(lse) - lse_ref).max() <= 1e-5
+
+
+@pytest.mark.parametrize("lens,q_lens", [([300] + [40] * 70, [200] + [1] * 70),
+                                         ([400, 0, 33, 64, 16, 17, 5], [140, 0, 3, 16, 0, 17, 1]),
+                                         ([2500], [3])],                                   # cut along the context
+                         ids=lambda v: f"n{len(v)}")
+@pytest.mark.parametrize("d", [80, 96, 112])
+def test_padded_head_dims_with_mostly_empty_row_tiles(pa, oracle, d, lens, q_lens):
+    """As above: the bound on the query lengths may be loose, up to where the plain grid has more workgroups than a launch."""
+    for max_q_len in (max(q_lens), 1 << 20, 1 << 30):
+        w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=8, num_kv_heads=2, head_dim=d, page_size=16,
+                            dtype=torch.bfloat16, causal=True, seed=208, device=DEV)
+        _, _, o_ref, lse_ref = parity.oracle_step(oracle, w)
+        pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
+        lse = torch.full((w.total_q, 8), float("nan"), device=DEV)
+        out = pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, w.cu_q_lens, max_q_len, w.block_table, w.seq_lens,
+                                         w.max_seq_len, w.scale, True, lse=lse)
+        parity.assert_close(parity.to_f64(out), o_ref, torch.bfloat16, f"out {max_q_len}")
+        assert abs(parity.to_f64(lse) - lse_ref).max() <= 1e-3
