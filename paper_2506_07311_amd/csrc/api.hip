@@ -710,7 +710,12 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
         }
         return st;
     }
-    return f32 ? launch_attention_f32(a, s) : launch_attention_generic(a, s);
+    // (A few query rows on a short context: the portable kernel has a workgroup for each and was never slower than one matrix
+    // tile for all, at head_dim 128 by up to 8 %: us portable / matrix, 8 / 8 heads, 16 queries on 250 keys 18.6 / 20.2, on
+    // 500 30.1 / 31.4, on 1000 53.2 / 53.0; 32 on 250 19.3 / 20.3, on 500 31.1 / 31.5; 64 on 250 22.7 / 20.4.  At head_dim
+    // 64 2 % and less: 16 on 250 13.3 / 13.5, on 500 19.0 / 19.3, on 1000 31.1 / 31.6; 32 on 250 13.7 / 13.6.)
+    const bool few = batch == 1 && (int64_t)total_q * num_q_heads <= (d > 64 ? 256 : 128) && max_seq_len >= 128 && max_seq_len <= 768;
+    return f32 && !few ? launch_attention_f32(a, s) : launch_attention_generic(a, s);
 }
 
 // Device address of this GPU's copy of `scratch`, looked up once per device with that device current.

@@ -75,7 +75,7 @@ F32_CASES = [  # lens, q_lens (None: decode), Hq, Hkv, d, P, causal
     ([1, 15, 16, 17, 0, 129, 777, 33], [1, 15, 16, 17, 0, 100, 200, 33], 4, 4, 64, 16, True),
     ([1, 15, 16, 300], [1, 15, 16, 50], 6, 2, 128, 32, True),
     ([40, 200], [7, 33], 40, 2, 64, 64, False),                  # 20 heads a group: row tiles that straddle queries
-    ([1, 16, 0, 129, 2049, 255], None, 8, 8, 64, 16, False),     # 2049 keys: chunks of 256 and the merge kernel
+    ([1, 16, 0, 129, 2049, 255], None, 16, 2, 64, 16, False),    # 2049 keys: chunks of 256 and the merge kernel
     ([700, 3, 128], None, 40, 2, 128, 128, False),
 ]
 
@@ -86,13 +86,15 @@ def test_fp32_on_the_matrix_cores(pa, oracle, case):
     of a weight), the fp32 partials (6e-8) and the output's rounding (6e-8) of values below 4."""
     from paper_2506_07311_amd import binding
     lens, q_lens, Hq, Hkv, d, P, causal = case
-    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=P,
-                        dtype=torch.float32, causal=causal, seed=203, device=DEV)
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens or [1] * len(lens), append_lens=q_lens or [min(n, 1) for n in lens],
+                        num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=P, dtype=torch.float32, causal=causal,
+                        seed=203, device=DEV)
     binding.pa_profile_reset()
     binding.pa_profile_enable(True)
     try:
         parity.check_step(pa, oracle, w, f"fp32 {case[2:]}", tol=(2e-6, 1e-5), step_call=q_lens is None)
-        assert binding.pa_profile_read("paged_attention_f32")[0] == 1
+        assert binding.pa_profile_read("paged_attention_f32_kernel")[0] == 1
+        assert binding.pa_profile_read("paged_attention_merge_kernel")[0] == (0 if q_lens else 1)
     finally:
         binding.pa_profile_enable(False)
         binding.pa_profile_reset()
@@ -234,3 +236,21 @@ def test_padded_head_dims_with_mostly_empty_row_tiles(pa, oracle, d, lens, q_len
                                          w.max_seq_len, w.scale, True, lse=lse)
         parity.assert_close(parity.to_f64(out), o_ref, torch.bfloat16, f"out {max_q_len}")
         assert abs(parity.to_f64(lse) - lse_ref).max() <= 1e-3
+
+
+@pytest.mark.parametrize("n,new,Hq,Hkv,d,portable", [(250, 16, 8, 8, 128, True), (500, 32, 8, 8, 128, True), (250, 33, 8, 8, 128, False),
+                                                     (1000, 16, 8, 8, 128, False), (250, 16, 8, 8, 64, True), (250, 17, 8, 8, 64, False),
+                                                     (100, 4, 32, 8, 64, False), (500, 4, 32, 8, 64, True)])
+def test_fp32_prefill_of_few_rows_on_a_short_context(pa, oracle, n, new, Hq, Hkv, d, portable):
+    from paper_2506_07311_amd import binding
+    w = W.make_workload("t", seq_lens=[n], q_lens=[new], num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=16,
+                        dtype=torch.float32, causal=True, seed=209, device=DEV)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        parity.check_step(pa, oracle, w, "few rows")
+        assert binding.pa_profile_read("paged_attention_generic_kernel")[0] == (1 if portable else 0)
+        assert binding.pa_profile_read("paged_attention_f32_kernel")[0] == (0 if portable else 1)
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
