@@ -179,7 +179,17 @@ struct RowMods {
 // M: compile-time policy of the hooks.  With score hooks the scores are first rewritten in place as
 // log2(e) * (cap(scale * s) + slope * (key - pos)) and the rest runs with a unit scale (a call with neither cap nor slopes
 // keeps its scale).
-template <bool MASK, bool FIRST, typename M, int KS, int T>
+// head_dims 80, 96, 112 (KS not a multiple of 4) keep what the portable kernel's fp32 weights gave them.  fp16: the reference
+// stands 2^9 below the largest score, so that weights are lost from 2^-33 of the largest on and not from 2^-24 (8000 keys of
+// which one leads by e^15: error 3.4e-3 with the reference at the maximum, 2.5e-4 like this and on the portable kernel).
+// bf16: 2^14 above it and sums up to 1, so that no weight exceeds 1 and a weighted sum of finite values stays finite.
+template <typename E, int KS>
+struct Reference {
+    static constexpr bool kPadded = KS % 4 != 0, kBf16 = E::kDtype == PA_DTYPE_BF16;
+    static constexpr float kBelow = !kPadded ? 0.f : kBf16 ? -14.f : 9.f;
+    static constexpr float kSumMax = kPadded && kBf16 ? 1.f : kWeightSumMax;
+};
+template <bool MASK, bool FIRST, typename E, typename M, int KS, int T>
 __device__ __forceinline__ void half_softmax(f32x16& p, f32x16& s, f32x16 (&o)[T], float& m_ref, float& l, float sc,
                                              int32_t key0, int32_t nk, const RowMods& rm, const int32_t* docs)
 {
@@ -259,12 +269,13 @@ __device__ __forceinline__ void half_softmax(f32x16& p, f32x16& s, f32x16 (&o)[T
             __builtin_amdgcn_sched_group_barrier(0x002, 72 / KS, 0);
         }
     }
-    const bool jump = !(psum <= kWeightSumMax);               // also true for the NaN / inf of a fresh reference
+    typedef Reference<E, KS> R;
+    const bool jump = !(psum <= R::kSumMax);                  // also true for the NaN / inf of a fresh reference
     if (__any(jump)) {
         float tmax = -INFINITY;
 #pragma unroll
         for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, s[r]);
-        const float top = pair_max(tmax) * sc;                // sc > 0: scaling commutes with the max
+        const float top = pair_max(tmax) * sc - R::kBelow;    // sc > 0: scaling commutes with the max
         const float m_new = fmaxf(m_ref, top);
         const float m_use = m_new == -INFINITY ? 0.f : m_new; // a query with no allowed key so far
         const float alpha = __builtin_amdgcn_exp2f(m_ref - m_use);
@@ -444,21 +455,21 @@ __device__ __forceinline__ void attend_tile(const char* buf, const uint32_t (&kx
         half_scores<E, KS>(s0, buf, 0, kx, qf);
         half_scores<E, KS>(s1, buf, 1, kx, qf);
         load_v_frags<T>(va, vb, buf + TB, 0, vx);
-        half_softmax<MASK, true, M, KS, T>(p, s0, o, m, l, sc, key0, nk, rm, docs);
+        half_softmax<MASK, true, E, M, KS, T>(p, s0, o, m, l, sc, key0, nk, rm, docs);
         // (head_dims 80, 96, 112: what the portable kernel, which never touches a key a row does not see, gave them)
         constexpr bool kGuard = MASK && KS % 4 != 0;
         if (kGuard && __any(not_finite<E, T>(va, vb))) half_pv_by_key<E, T>(o, p, va, vb, key0 - 4 * hh, nk, hh);
         else half_pv_frags<PRECISE, E, T>(o, p, va, vb);
         load_v_frags<T>(va, vb, buf + TB, 1, vx);
-        half_softmax<MASK, false, M, KS, T>(p, s1, o, m, l, sc, key0 + 32, nk, rm, docs + 32);
+        half_softmax<MASK, false, E, M, KS, T>(p, s1, o, m, l, sc, key0 + 32, nk, rm, docs + 32);
         if (kGuard && __any(not_finite<E, T>(va, vb))) half_pv_by_key<E, T>(o, p, va, vb, key0 + 32 - 4 * hh, nk, hh);
         else half_pv_frags<PRECISE, E, T>(o, p, va, vb);
     } else {
         half_scores<E, KS>(s0, buf, 0, kx, qf);
         half_scores<E, KS>(s1, buf, 1, kx, qf);
-        half_softmax<MASK, true, M, KS, T>(p, s0, o, m, l, sc, key0, nk, rm, docs);
+        half_softmax<MASK, true, E, M, KS, T>(p, s0, o, m, l, sc, key0, nk, rm, docs);
         half_pv<PRECISE, E, T>(o, p, buf + TB, 0, vx);
-        half_softmax<MASK, false, M, KS, T>(p, s1, o, m, l, sc, key0 + 32, nk, rm, docs + 32);
+        half_softmax<MASK, false, E, M, KS, T>(p, s1, o, m, l, sc, key0 + 32, nk, rm, docs + 32);
         half_pv<PRECISE, E, T>(o, p, buf + TB, 1, vx);
     }
 }

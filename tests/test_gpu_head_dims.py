@@ -254,3 +254,37 @@ def test_fp32_prefill_of_few_rows_on_a_short_context(pa, oracle, n, new, Hq, Hkv
     finally:
         binding.pa_profile_enable(False)
         binding.pa_profile_reset()
+
+
+@pytest.mark.parametrize("d", [80, 96, 112])
+def test_fp16_weights_far_below_the_largest_are_not_lost(pa, d):
+    """One key leads 8000 others by e^15: each of those weighs less than 2^-21 of it, all of them together 2e-3.  The output is
+    their values' share to the rounding of fp16 (2^-11 of values up to 4e-3, subnormal below 6e-5 only)."""
+    n, at = 8000, 100
+    w = W.make_workload("t", seq_lens=[n], q_lens=[64], num_q_heads=2, num_kv_heads=2, head_dim=d, page_size=16,
+                        dtype=torch.float16, causal=True, identity_pages=True, poison=False, seed=220, device=DEV)
+    w.q.fill_(1.0)
+    w.k_cache.zero_()
+    w.k_cache[at // 16, at % 16] = 15.0 / d
+    w.v_cache.fill_(1.0)
+    w.v_cache[at // 16, at % 16] = 0.0
+    out = pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, w.cu_q_lens, w.max_q_len, w.block_table, w.seq_lens, n, 1.0, True)
+    score = float(w.k_cache[at // 16, at % 16].double().sum(-1)[0])
+    keys = torch.arange(n - 64, n, dtype=torch.float64, device=DEV)              # of the row at that position, but for `at`
+    ref = keys / (keys + torch.exp(torch.tensor(score, dtype=torch.float64)))
+    assert (out.double() / ref[:, None, None] - 1.0).abs().max() <= 2.0 ** -10
+
+
+@pytest.mark.parametrize("d", [80, 96, 112])
+def test_bf16_sums_of_large_values_stay_finite(pa, d):
+    """Later keys outweigh the ones the softmax reference was taken from by 2^9: sums of finite values must not overflow."""
+    n = 300
+    w = W.make_workload("t", seq_lens=[n], q_lens=[n], num_q_heads=2, num_kv_heads=2, head_dim=d, page_size=16,
+                        dtype=torch.bfloat16, causal=True, identity_pages=True, poison=False, seed=221, device=DEV)
+    w.q.fill_(1.0)
+    w.k_cache.fill_(6.25 / d)
+    w.k_cache[:4] = 0.0                                                           # the first 64 keys
+    w.v_cache.fill_(1e35)
+    out = pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, w.cu_q_lens, w.max_q_len, w.block_table, w.seq_lens, n, 1.0, True)
+    v = float(w.v_cache[0, 0, 0, 0].double())
+    assert (out.double() / v - 1.0).abs().max() <= 2.0 ** -8
