@@ -57,7 +57,8 @@ struct RowGeo {
 };
 // head_dims 80, 96 and 112: rows hold 10, 12 or 14 pieces and the last column block of O is padded where D is not a
 // multiple of 32.  Every tile carries two-term weights: the portable kernel, which served these head_dims, keeps its
-// weights in fp32, and the second term (2^-17 of a weight) keeps the error at what the output's rounding leaves.
+// weights in fp32, and the second term (2^-17 of a weight) keeps the error at what the output's rounding leaves (see also
+// Reference, which keeps their range, and half_pv_by_key).
 // 2 prompts of 700 and 950 tokens, 32 / 32 heads, D = 96: 25 us for 9 GFLOP, bound by the start of a workgroup and its
 // heaviest row tile like every short prompt here; 1065 us on the portable kernel, which reads K and V again per row.
 template <int D>
@@ -345,32 +346,24 @@ __device__ __forceinline__ void half_pv_frags(f32x16 (&o)[T], const f32x16& s, c
     }
 }
 
-// Does a lane's share of the half tile's V hold a value that is not finite (exponent all ones)?
-template <typename E, int T>
-__device__ __forceinline__ bool not_finite(const uint4 (&va)[T], const uint4 (&vb)[T])
-{
-    constexpr uint32_t kExp = E::kDtype == PA_DTYPE_BF16 ? 0x7f80u : 0x7c00u;
-    bool odd = false;
-    auto test = [&](uint32_t w) { odd |= (w & kExp) == kExp || (w & (kExp << 16)) == kExp << 16; };
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        test(va[t].x), test(va[t].y), test(va[t].z), test(va[t].w);
-        test(vb[t].x), test(vb[t].y), test(vb[t].z), test(vb[t].w);
-    }
-    return odd;
-}
-
-// The same product for a half tile at a causal edge whose V holds such values: weights of masked keys are exact zeros, but
-// zero times infinity is not.  One key at a time (the other contraction slots zeroed on both sides), added only to the
-// rows that see it.  base = first key of the half tile; weight r of lane half hh is key base + 8 (r / 4) + 4 hh + r % 4.
+// The same product where V may hold values that are not finite: a masked key's weight is an exact zero, but zero times
+// infinity is not, and an infinity times a weight's second term may undo the one times its first.  One key at a time (the
+// other contraction slots zeroed on both sides), added only to the rows that see it, the second term only on finite values.
+// base = first key of the half tile; weight r of lane half hh is key base + 8 (r / 4) + 4 hh + r % 4.
 template <typename E, int T>
 __device__ __forceinline__ void half_pv_by_key(f32x16 (&o)[T], const f32x16& s, const uint4 (&va)[T], const uint4 (&vb)[T],
                                                int32_t base, int32_t nk, int hh)
 {
+    constexpr uint32_t kExp = E::kDtype == PA_DTYPE_BF16 ? 0x7f80u : 0x7c00u;
+    f32x16 p = s;
+    if (E::kDtype == PA_DTYPE_F16) {                         // a weight that fp16 would drop still weighs an infinity
+#pragma unroll
+        for (int r = 0; r < 16; ++r) p[r] = p[r] > 0.f && p[r] < 0x1p-24f ? 0x1p-24f : p[r];
+    }
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
         uint4 w, wl;
-        pack_weights<true, E>(w, wl, s, 8 * st);
+        pack_weights<true, E>(w, wl, p, 8 * st);
 #pragma unroll 1
         for (int i = 0; i < 16; ++i) {
             const int e = i >> 1, h = i & 1;
@@ -378,12 +371,17 @@ __device__ __forceinline__ void half_pv_by_key(f32x16 (&o)[T], const f32x16& s, 
             const uint32_t half = hh != h ? 0u : (e & 1) ? 0xffff0000u : 0xffffu;
             const uint4 keep = {e >> 1 == 0 ? half : 0u, e >> 1 == 1 ? half : 0u, e >> 1 == 2 ? half : 0u, e >> 1 == 3 ? half : 0u};
             auto cut = [&](const uint4& v) { return uint4{v.x & keep.x, v.y & keep.y, v.z & keep.z, v.w & keep.w}; };
+            auto finite = [&](uint32_t v) {
+                if ((v & kExp) == kExp) v &= 0xffff0000u;
+                if ((v & (kExp << 16)) == kExp << 16) v &= 0xffffu;
+                return v;
+            };
 #pragma unroll
             for (int t = 0; t < T; ++t) {
                 const uint4 v = cut(st ? vb[t] : va[t]);
                 f32x16 one = (f32x16)(0.f);
                 one = E::mfma32(v, cut(w), one);
-                one = E::mfma32(v, cut(wl), one);
+                one = E::mfma32(uint4{finite(v.x), finite(v.y), finite(v.z), finite(v.w)}, cut(wl), one);
 #pragma unroll
                 for (int r = 0; r < 16; ++r) o[t][r] = seen ? o[t][r] + one[r] : o[t][r];
                 __builtin_amdgcn_sched_barrier(0);           // (one block's accumulators at a time)
@@ -442,7 +440,8 @@ __device__ __forceinline__ void half_scores(f32x16& s, const char* kbuf, int hal
 //     vector ALU:            softmax(h0)    softmax(h1)
 // buf = tile buffer (K rows, then V rows); key0 = first key of the tile + 4 * (lane/32); nk = keys this lane's
 // query may see (MASK only); sc = scale * log2(e) > 0.
-template <bool PRECISE, bool MASK, typename E, typename M, int T, int KS>
+// CAREFUL: values of V that are not finite stay with the rows that see them (see prefill_body).
+template <bool PRECISE, bool MASK, bool CAREFUL, typename E, typename M, int T, int KS>
 __device__ __forceinline__ void attend_tile(const char* buf, const uint32_t (&kx)[KS], const uint32_t (&vx)[2 * T],
                                             const uint4 (&qf)[KS], f32x16 (&o)[T], float& m, float& l, float sc,
                                             int32_t key0, int32_t nk, const RowMods& rm, const int32_t* docs)
@@ -456,13 +455,11 @@ __device__ __forceinline__ void attend_tile(const char* buf, const uint32_t (&kx
         half_scores<E, KS>(s1, buf, 1, kx, qf);
         load_v_frags<T>(va, vb, buf + TB, 0, vx);
         half_softmax<MASK, true, E, M, KS, T>(p, s0, o, m, l, sc, key0, nk, rm, docs);
-        // (head_dims 80, 96, 112: what the portable kernel, which never touches a key a row does not see, gave them)
-        constexpr bool kGuard = MASK && KS % 4 != 0;
-        if (kGuard && __any(not_finite<E, T>(va, vb))) half_pv_by_key<E, T>(o, p, va, vb, key0 - 4 * hh, nk, hh);
+        if (CAREFUL) half_pv_by_key<E, T>(o, p, va, vb, key0 - 4 * hh, nk, hh);
         else half_pv_frags<PRECISE, E, T>(o, p, va, vb);
         load_v_frags<T>(va, vb, buf + TB, 1, vx);
         half_softmax<MASK, false, E, M, KS, T>(p, s1, o, m, l, sc, key0 + 32, nk, rm, docs + 32);
-        if (kGuard && __any(not_finite<E, T>(va, vb))) half_pv_by_key<E, T>(o, p, va, vb, key0 + 32 - 4 * hh, nk, hh);
+        if (CAREFUL) half_pv_by_key<E, T>(o, p, va, vb, key0 + 32 - 4 * hh, nk, hh);
         else half_pv_frags<PRECISE, E, T>(o, p, va, vb);
     } else {
         half_scores<E, KS>(s0, buf, 0, kx, qf);
@@ -483,8 +480,13 @@ struct WorkItem {
     int32_t slot;            // work-list mode: where a partial goes (-1: the plain layout)
 };
 
-template <bool PRECISE, bool UNIFORM, bool LIST, typename E, typename M, int D>
-__device__ __forceinline__ void prefill_body(
+// Returns whether the item has to be done again with CAREFUL (the same on every thread of the workgroup): at head_dims 80, 96
+// and 112, which keep what the portable kernel, that never touches a key a row does not see, gave them.  An infinity or a NaN
+// in V always leaves its mark on some accumulator of the row tile, so the tile loop need not look for it: the accumulators
+// are looked at once, at the end (append + prefill of 2 prompts of 700 and 950 tokens, 32 / 32 heads, D = 96: 36.1 us, 38.0 with
+// a test of V's fragments on every masked tile; 8 prompts of 33 .. 900, 8 / 2 heads, D = 112: 25.7, 30.5).
+template <bool PRECISE, bool UNIFORM, bool LIST, bool CAREFUL, typename E, typename M, int D>
+__device__ __forceinline__ bool prefill_body(
     char* buf0, char* buf1, int32_t* docs0, int32_t* docs1, const CacheView& cache, const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float* __restrict__ lse,
     const int32_t* __restrict__ block_table, int32_t num_q_heads, int32_t max_blocks, float scale, int32_t causal, const PrefillPlan& plan, int32_t precise_keys,
     const WorkItem& own, const int tid)
@@ -501,8 +503,8 @@ __device__ __forceinline__ void prefill_body(
     const int32_t q_len = own.q_end - own.q_begin;           //  everything else, see there)
     const int32_t n_rows = q_len << lg;
     const int32_t m0 = own.tile * kBM;
-    if (m0 >= n_rows) return;
-    if (plan.skip_small && q_len * (num_q_heads / cache.num_kv_heads) <= 16) return;
+    if (m0 >= n_rows) return false;
+    if (plan.skip_small && q_len * (num_q_heads / cache.num_kv_heads) <= 16) return false;
     const int32_t len = own.len;
     // workgroup-wide key range; it also selects which instantiation handles this tile
     const int32_t q_last = (min(m0 + kBM, n_rows) - 1) >> lg;
@@ -528,12 +530,12 @@ __device__ __forceinline__ void prefill_body(
     const bool few_keys = kTwoTermOnly<D> || n_first <= precise_keys || q_len * (num_q_heads / cache.num_kv_heads) <= 16 ||
                           (M::kScore && plan.mods.alibi_slopes != nullptr) || (M::kDoc && plan.mods.doc_ids != nullptr) ||
                           M::kUser;
-    if (few_keys != PRECISE) return;                        // the other instantiation handles this tile
+    if (few_keys != PRECISE) return false;                        // the other instantiation handles this tile
     // this workgroup's chunk of the context; with a split, chunks without keys leave nothing behind (the merge
     // reads only the chunks that hold keys of a row)
     // (without a causal bound a window also cuts the END of a row's range, which the merge does not know: those
     // chunks must leave explicit empty partials, so the workgroup goes on with zero tiles)
-    if (own.chunks > 1 && split * own.chunk >= nk_wg && !(window > 0 && !causal)) return;
+    if (own.chunks > 1 && split * own.chunk >= nk_wg && !(window > 0 && !causal)) return false;
     const int32_t k_begin = max(split * own.chunk, k_lo);
     const int32_t k_end = min(nk_wg, split * own.chunk + own.chunk);
 
@@ -705,9 +707,9 @@ __device__ __forceinline__ void prefill_body(
         }
         if (t0 < nk_wave && t0 + kBN > lo_wave && docs_overlap(docs0)) {   // wave-uniform: else nothing for this wave here
             if (t0 + kBN > nk_wave_min)                      // wave-uniform: some score of this tile is masked
-                attend_tile<PRECISE, true, E, M, T>(buf0, kx, vx, qf, o, m, l, sc, t0 + 4 * hh, nk, rm, docs0 + 4 * hh);
+                attend_tile<PRECISE, true, CAREFUL, E, M, T>(buf0, kx, vx, qf, o, m, l, sc, t0 + 4 * hh, nk, rm, docs0 + 4 * hh);
             else
-                attend_tile<PRECISE, false, E, M, T>(buf0, kx, vx, qf, o, m, l, sc, t0 + 4 * hh, nk, rm, docs0 + 4 * hh);
+                attend_tile<PRECISE, false, CAREFUL, E, M, T>(buf0, kx, vx, qf, o, m, l, sc, t0 + 4 * hh, nk, rm, docs0 + 4 * hh);
         }
         if (doc_lane && t + 1 < n_tiles) put_docs(docs1, doc_next);
         wait_tile_loads();
@@ -721,18 +723,32 @@ __device__ __forceinline__ void prefill_body(
         }
         if (t1 < nk_wave && t1 + kBN > lo_wave && docs_overlap(docs1)) {
             if (t1 + kBN > nk_wave_min)
-                attend_tile<PRECISE, true, E, M, T>(buf1, kx, vx, qf, o, m, l, sc, t1 + 4 * hh, nk, rm, docs1 + 4 * hh);
+                attend_tile<PRECISE, true, CAREFUL, E, M, T>(buf1, kx, vx, qf, o, m, l, sc, t1 + 4 * hh, nk, rm, docs1 + 4 * hh);
             else
-                attend_tile<PRECISE, false, E, M, T>(buf1, kx, vx, qf, o, m, l, sc, t1 + 4 * hh, nk, rm, docs1 + 4 * hh);
+                attend_tile<PRECISE, false, CAREFUL, E, M, T>(buf1, kx, vx, qf, o, m, l, sc, t1 + 4 * hh, nk, rm, docs1 + 4 * hh);
         }
         if (doc_lane && t + 2 < n_tiles) put_docs(docs0, doc_next);
         wait_tile_loads();
         __syncthreads();
     }
 
+    if constexpr (kTwoTermOnly<D> && !CAREFUL) {
+        bool odd = false;
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) odd |= !(__builtin_fabsf(o[t][r]) <= 3.402823466e38f);
+        const bool any = __any(odd);
+        if (lane == 0) docs0[wave] = any ? 1 : 0;            // (no document masks here: the array is free)
+        __syncthreads();
+        if (docs0[0] | docs0[1] | docs0[2] | docs0[3]) return true;
+    }
     l += __shfl_xor(l, 32, 64);
-    if (!q_valid) return;
+    if (!q_valid) return false;
     const float inv = l > 0.f ? 1.f / l : 0.f;
+    // (a NaN among the scores: head_dims 80, 96 and 112 say so, in a partial by +inf, which the merge turns into NaN)
+    const bool bad = kTwoTermOnly<D> && l != l;
+    const float row_lse = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
     // o[t][r]: column 32*t + 8*(r/4) + 4*hh + r%4 of this lane's query
     if (LIST && own.slot >= 0) {
         // work-list mode: normalised accumulators lane by lane (whole cache lines per store), LSE per row
@@ -745,9 +761,8 @@ __device__ __forceinline__ void prefill_body(
                 po[(4 * t + a) * 64] = float4{o[t][4 * a + 0] * inv, o[t][4 * a + 1] * inv, o[t][4 * a + 2] * inv,
                                               o[t][4 * a + 3] * inv};
         if (hh == 0)
-            plan.list_lse[(int64_t)own.slot * kBM + 32 * wave + ql] =
-                l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
-        return;
+            plan.list_lse[(int64_t)own.slot * kBM + 32 * wave + ql] = bad ? INFINITY : row_lse;
+        return false;
     }
     if (!LIST && own.chunks > 1) {
         // partial of this chunk: normalised output in fp32 and the natural-log LSE over the chunk's keys
@@ -765,8 +780,8 @@ __device__ __forceinline__ void prefill_body(
                 w.w = o[t][4 * a + 3] * inv;
                 *reinterpret_cast<float4*>(prow + 32 * t + 8 * a + 4 * hh) = w;
             }
-        if (hh == 0) plan.part_lse[pidx] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
-        return;
+        if (hh == 0) plan.part_lse[pidx] = bad ? INFINITY : row_lse;
+        return false;
     }
     uint16_t* orow = out + row * D;
 #pragma unroll
@@ -779,7 +794,8 @@ __device__ __forceinline__ void prefill_body(
             w.y = E::pack(o[t][4 * a + 2] * inv, o[t][4 * a + 3] * inv);
             *reinterpret_cast<uint2*>(orow + 32 * t + 8 * a + 4 * hh) = w;
         }
-    if (lse && hh == 0) lse[row] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
+    if (lse && hh == 0) lse[row] = bad ? l : row_lse;
+    return false;
 }
 
 // Both instantiations live in one kernel as two separate code paths (each with its own tile loop); a
@@ -827,11 +843,18 @@ __global__ __launch_bounds__(kThreads, D > 128 ? 1 : 2) void paged_prefill_mfma_
             own.q_end = cu_q_lens[it.s + 1];
             own.len = seq_lens[it.s];
             if constexpr (!kTwoTermOnly<D>)
-                prefill_body<false, UNIFORM, LIST, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
+                prefill_body<false, UNIFORM, LIST, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
                                                             num_q_heads, max_blocks, scale, causal, plan, precise_keys, own,
                                                             tid);
-            prefill_body<true, UNIFORM, LIST, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table, num_q_heads,
-                                                       max_blocks, scale, causal, plan, precise_keys, own, tid);
+            const bool again =
+                prefill_body<true, UNIFORM, LIST, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
+                                                                  num_q_heads, max_blocks, scale, causal, plan, precise_keys,
+                                                                  own, tid);
+            if constexpr (kTwoTermOnly<D>)
+                if (again)
+                    prefill_body<true, UNIFORM, LIST, true, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
+                                                                     num_q_heads, max_blocks, scale, causal, plan,
+                                                                     precise_keys, own, tid);
         }
     } else {
         // Workgroups are dispatched in blockIdx.x order: the row-tile index is the slowest-varying part and runs
@@ -855,11 +878,18 @@ __global__ __launch_bounds__(kThreads, D > 128 ? 1 : 2) void paged_prefill_mfma_
             precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal,
                                              (M::kWindow && plan.mods.window > 0) ? plan.mods.window : 0,
                                              (int)(threadIdx.x & 63));
-            prefill_body<false, UNIFORM, LIST, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table, num_q_heads,
+            prefill_body<false, UNIFORM, LIST, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table, num_q_heads,
                                                         max_blocks, scale, causal, plan, precise_keys, own, (int)threadIdx.x);
         }
-        prefill_body<true, UNIFORM, LIST, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table, num_q_heads,
-                                                   max_blocks, scale, causal, plan, precise_keys, own, (int)threadIdx.x);
+        const bool again =
+            prefill_body<true, UNIFORM, LIST, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
+                                                              num_q_heads, max_blocks, scale, causal, plan, precise_keys, own,
+                                                              (int)threadIdx.x);
+        if constexpr (kTwoTermOnly<D>)
+            if (again)
+                prefill_body<true, UNIFORM, LIST, true, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
+                                                                 num_q_heads, max_blocks, scale, causal, plan, precise_keys,
+                                                                 own, (int)threadIdx.x);
     }
 }
 

@@ -101,25 +101,68 @@ def test_fp32_on_the_matrix_cores(pa, oracle, case):
 
 
 @pytest.mark.parametrize("d,dtype", [(64, torch.float32), (128, torch.float32), (80, torch.bfloat16), (96, torch.float16),
-                                     (112, torch.bfloat16)])
-@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
-def test_values_that_are_not_finite_stay_with_the_rows_that_see_them(pa, d, dtype, bad):
-    """A later token of a prompt with a NaN or an infinity in V (or K) must not reach the queries in front of it."""
-    n, at, P = 150, 70, 16
-    eps = 1e-6 if dtype == torch.float32 else 4e-3 if dtype == torch.float16 else 3e-2     # one rounding step of values below 4
-    w = W.make_workload("t", seq_lens=[n], q_lens=[n], num_q_heads=2, num_kv_heads=2, head_dim=d, page_size=P, dtype=dtype,
-                        causal=True, seed=204, device=DEV)
-    outs = []
-    for value in (0.5, bad):
-        w.v_new[at, :, 3] = value
-        pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
-        outs.append(pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, w.cu_q_lens, w.max_q_len, w.block_table,
-                                               w.seq_lens, w.max_seq_len, w.scale, True))
-    good, got = outs
-    assert (got[:at] - good[:at]).abs().max() <= eps
-    other = [c for c in range(d) if c != 3]
-    assert (got[at:, :, other] - good[at:, :, other]).abs().max() <= eps
-    assert not got[at:, :, 3].isfinite().any()
+                                     (112, torch.bfloat16), (80, torch.float16)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("where", ["v", "k"])
+@pytest.mark.parametrize("n,new,chunk", [(150, 150, 0), (700, 700, 0), (700, 60, 256)], ids=["edge", "inside", "cut"])
+def test_values_that_are_not_finite_do_what_they_did_on_the_portable_kernel(pa, d, dtype, bad, where, n, new, chunk):
+    """A NaN or an infinity in V or K reaches the queries that see it as what it was on the portable kernel, which takes every
+    product in one term, and no other query: on the tile at a row's causal edge, on full tiles, and through a merge."""
+    from paper_2506_07311_amd import binding
+    at = 70
+    eps = 2e-6 if dtype == torch.float32 else 4e-3 if dtype == torch.float16 else 3e-2     # one rounding step of values below 4
+    w = W.make_workload("t", seq_lens=[n], q_lens=[new], append_lens=[n], num_q_heads=4, num_kv_heads=2, head_dim=d, page_size=16,
+                        dtype=dtype, causal=True, seed=204, device=DEV)
+    (w.v_new if where == "v" else w.k_new)[at, :, 3] = bad
+    pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
+    res = []
+    for generic in (1, 0):
+        binding.pa_set_option("force_generic", generic)
+        binding.pa_set_option("prefill_chunk_tokens", chunk)
+        lse = torch.empty((new, 4), device=DEV)
+        try:
+            out = pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, w.cu_q_lens, w.max_q_len, w.block_table, w.seq_lens, n,
+                                             w.scale, True, lse=lse)
+            torch.cuda.synchronize()
+        finally:
+            binding.pa_set_option("force_generic", 0)
+            binding.pa_set_option("prefill_chunk_tokens", 0)
+        res.append((out.float(), lse))
+    for ref, got, tol in ((res[0][0], res[1][0], eps), (res[0][1], res[1][1], 1e-4)):
+        assert torch.equal(got.isnan(), ref.isnan())
+        assert torch.equal(got.isinf(), ref.isinf()) and torch.equal(got[got.isinf()] > 0, ref[ref.isinf()] > 0)
+        assert ((got - ref)[ref.isfinite()].abs() <= tol).all()
+    first = max(at - (n - new), 0)                                # the first query that sees the value
+    assert first == 0 or res[1][0][:first].isfinite().all()
+    assert not res[1][0][first:].isfinite().all()
+
+
+@pytest.mark.parametrize("d,Hq", [(64, 2), (64, 8), (128, 8)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("where", ["v", "k"])
+def test_fp32_decode_of_values_that_are_not_finite(pa, d, Hq, bad, where):
+    """As above for the decode kernel: one sequence that holds the value, at its last key, one that does not."""
+    from paper_2506_07311_amd import binding
+    w = W.make_workload("t", seq_lens=[2049, 300, 77], num_q_heads=Hq, num_kv_heads=2, head_dim=d, page_size=16,
+                        dtype=torch.float32, seed=210, device=DEV)
+    (w.v_new if where == "v" else w.k_new)[0::2, :, 3] = bad
+    pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
+    res = []
+    for generic in (1, 0):
+        binding.pa_set_option("force_generic", generic)
+        binding.pa_set_option("decode_chunk_tokens", generic << 20)   # (its merge takes a chunk that is all NaN for an empty one)
+        lse = torch.empty((3, Hq), device=DEV)
+        try:
+            res.append((pa.paged_attention_decode(w.k_cache, w.v_cache, w.q, w.block_table, w.seq_lens, 2049, w.scale, lse=lse), lse))
+            torch.cuda.synchronize()
+        finally:
+            binding.pa_set_option("force_generic", 0)
+            binding.pa_set_option("decode_chunk_tokens", 0)
+    assert res[1][0][1].isfinite().all()
+    for ref, got, tol in ((res[0][0], res[1][0], 2e-6), (res[0][1], res[1][1], 1e-5)):
+        assert torch.equal(got.isnan(), ref.isnan())
+        assert torch.equal(got.isinf(), ref.isinf()) and torch.equal(got[got.isinf()] > 0, ref[ref.isinf()] > 0)
+        assert ((got - ref)[ref.isfinite()].abs() <= tol).all()
 
 
 F32_DECODES = [  # lens, Hq, Hkv, d, P
