@@ -84,6 +84,7 @@ pa_status launch_prefill_mfma(const AttnArgs& a, hipStream_t stream)
     plan.list_lse = a.list_lse;
     plan.list_unit = !a.list_o ? kListUncut : a.cache.page_size > kBN ? a.cache.page_size : kBN;
     plan.log2_pack = prefill_mfma_log2_pack(a.num_q_heads, a.cache.num_kv_heads);
+    plan.group = a.num_q_heads / a.cache.num_kv_heads;
     plan.chunk = a.plan.chunk;
     plan.nsplit = a.plan.nsplit;
     plan.skip_small = a.skip_small;

@@ -504,7 +504,7 @@ __device__ __forceinline__ bool prefill_body(
     const int32_t n_rows = q_len << lg;
     const int32_t m0 = own.tile * kBM;
     if (m0 >= n_rows) return false;
-    if (plan.skip_small && q_len * (num_q_heads / cache.num_kv_heads) <= 16) return false;
+    if (plan.skip_small && q_len * plan.group <= 16) return false;
     const int32_t len = own.len;
     // workgroup-wide key range; it also selects which instantiation handles this tile
     const int32_t q_last = (min(m0 + kBM, n_rows) - 1) >> lg;
@@ -527,7 +527,7 @@ __device__ __forceinline__ bool prefill_body(
     if (causal) n_first = min(len, len - q_len + (m0 >> lg) + 1);
     if (window > 0) n_first = min(n_first, causal ? window : 2 * window - 1);
     // (sequences with few queries carry two terms as they do on the decode kernel)
-    const bool few_keys = kTwoTermOnly<D> || n_first <= precise_keys || q_len * (num_q_heads / cache.num_kv_heads) <= 16 ||
+    const bool few_keys = kTwoTermOnly<D> || n_first <= precise_keys || q_len * plan.group <= 16 ||
                           (M::kScore && plan.mods.alibi_slopes != nullptr) || (M::kDoc && plan.mods.doc_ids != nullptr) ||
                           M::kUser;
     if (few_keys != PRECISE) return false;                        // the other instantiation handles this tile
@@ -539,7 +539,7 @@ __device__ __forceinline__ bool prefill_body(
     const int32_t k_begin = max(split * own.chunk, k_lo);
     const int32_t k_end = min(nk_wg, split * own.chunk + own.chunk);
 
-    const int32_t G = num_q_heads / cache.num_kv_heads;
+    const int32_t G = plan.group;
     const int32_t* table = block_table + (int64_t)s * max_blocks;
 
     // this lane's row: query, head, and key bound
@@ -822,7 +822,7 @@ __global__ __launch_bounds__(kThreads, D > 128 ? 1 : 2) void paged_prefill_mfma_
         // tile loop ends with the barrier behind its last read of LDS.  The thread index is made opaque for each item:
         // what the body derives from it would otherwise be kept in registers across the loop, which spills.
         const WorkList list = make_list(cu_q_lens, seq_lens, batch, plan.log2_pack,
-                                        plan.skip_small ? num_q_heads / cache.num_kv_heads : kNoSmallGroup, heads,
+                                        plan.skip_small ? plan.group : kNoSmallGroup, heads,
                                         plan.list_unit, (int)(threadIdx.x & 63));
         int32_t precise_keys = 0;
         if constexpr (!kTwoTermOnly<D>)
