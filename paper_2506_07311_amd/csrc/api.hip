@@ -424,13 +424,20 @@ bool list_possible(int32_t batch, int32_t total_q, int32_t max_seq_len)
 // least twice as long as the longest query range (chunks of long prompts, not whole prompts, whose heaviest-first grid
 // balances itself: 4 x 2048 loses 2-3 % in sequence order), and too few row tiles to average the lengths out --
 // estimated as if the queries sat in as few sequences as max_q_len allows, since the host knows no lengths.
+// Every workgroup scans all sequences 64 at a time, several times over: with many of them it pays only while the sequences
+// with queries are few, whose grid cannot balance itself (us plain / list, sequences of 64 .. 4300 tokens: 1000 of which 32
+// bring 100 tokens, 32 / 8 heads 1198 / 960, 16 / 2 481 / 413; 900 of which 100 bring 20 767 / 783, 16 / 2 326 / 353, 8 / 1
+// 247 / 273; 700 of which 100 bring 40 755 / 755, 8 / 1 217 / 222; 500 of 64 .. 5000 of which 167 bring 60, 8 / 1 215 / 217).
 constexpr int64_t kListMaxWGs = 2048;
+constexpr int32_t kListScanBatch = 512;
+constexpr int64_t kListScanLive = 64;
 
 bool list_pays(const AttnArgs& a, int32_t log2_pack)
 {
     if (!list_possible(a.batch, a.total_q, a.max_seq_len) || !prefill_list_supported(a)) return false;
     if ((int64_t)a.batch * a.max_q_len == a.total_q || a.max_seq_len / 2 < a.max_q_len) return false;
     const int64_t live = (a.total_q + a.max_q_len - 1) / (a.max_q_len > 0 ? a.max_q_len : 1);
+    if (a.batch > kListScanBatch && live > kListScanLive) return false;
     return ((((int64_t)a.total_q << log2_pack) / 128) + live) * (a.num_q_heads >> log2_pack) < kListMaxWGs;
 }
 

@@ -74,6 +74,23 @@ def test_a_workspace_of_the_smaller_size_is_accepted_and_keeps_the_plain_grid(pa
     assert ((outs[0] - outs[1]).abs() <= 2.0 ** -7 * outs[1].abs() + 2e-3).all()
 
 
+@pytest.mark.parametrize("batch,live,listed", [(600, 70, 0), (600, 60, 1), (512, 70, 1)])
+def test_many_sequences_with_queries_keep_the_plain_grid(pa, oracle, batch, live, listed):
+    from paper_2506_07311_amd import binding
+    lens = [4096] + [70] * (batch - 1)
+    q_lens = [20 if s < live else 0 for s in range(batch)]
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=4, num_kv_heads=2, head_dim=64, page_size=16,
+                        dtype=torch.bfloat16, causal=True, seed=214, device=DEV)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        parity.check_step(pa, oracle, w, f"{batch} {live}")
+        assert binding.pa_profile_read("paged_attention_merge_list")[0] == listed
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
+
+
 @pytest.mark.parametrize("q_lens,launches", [([200, 1, 150, 190], 0),     # whole prompts in the main: one launch, all sequences
                                              ([200, 5, 1, 3], 1),         # mostly few queries: they take the decode kernel
                                              ([200, 20], 0)])             # no sequence can have few queries
