@@ -828,7 +828,8 @@ size_t paged_attention_workspace_bytes(int32_t batch, int32_t num_q_heads, int32
                                        int32_t max_seq_len)
 {
     const size_t need = required_workspace_bytes(batch, num_q_heads, head_dim, total_q, max_seq_len);
-    const bool sized = batch > 0 && num_q_heads > 0 && head_dim > 0 && head_dim <= 256 && total_q > 0;
+    // (dtype, hooks, page size and the query lengths' spread, which also decide, are not known here)
+    const bool sized = batch > 0 && num_q_heads > 0 && prefill_list_dim(head_dim) && total_q > 0;
     return need + (sized && list_possible(batch, total_q, max_seq_len) ? list_bytes(head_dim) : 0);
 }
 

@@ -219,6 +219,7 @@ bool prefill_grid_mostly_empty(const AttnArgs& a);
 double prefill_grid_workgroups(const AttnArgs& a, int32_t nsplit);
 // The head_dims that the portable kernel served before the padded tiles did: what it took, they take or leave to it.
 inline bool prefill_padded_dim(int32_t d) { return d == 80 || d == 96 || d == 112; }
+inline bool prefill_list_dim(int32_t d) { return d == 64 || d == 128 || d == 256 || prefill_padded_dim(d); }
 int32_t prefill_list_slots();
 size_t prefill_list_slot_floats(int32_t head_dim);
 int32_t prefill_list_min_context();

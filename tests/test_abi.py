@@ -134,6 +134,17 @@ def test_host_validation_rejects_before_launch(lib):
     assert lib.pa_set_option(b"decode_chunk_tokens", ctypes.c_int64(0)) == 0
 
 
+def test_workspace_has_room_for_the_work_list_only_where_it_exists(lib):
+    """Jagged calls with contexts of 4096 tokens and more: the list's partials on top, at the head_dims it has kernels for
+    (9000 query rows: enough that no context is split for their sake)."""
+    size = binding.paged_attention_workspace_bytes
+    for d in (64, 80, 128, 256):
+        assert size(8, 8, d, 9000, 4096) - size(8, 8, d, 9000, 4095) >= 2048 * 128 * d * 4
+    for d in (72, 32, 192):
+        assert size(8, 8, d, 9000, 4096) - size(8, 8, d, 9000, 4095) < 1 << 20
+    assert size(1, 8, 128, 9000, 4096) - size(1, 8, 128, 9000, 4095) < 1 << 20
+
+
 def test_options_are_kept_per_host_thread(lib):
     """A knob set on one thread shapes that thread's calls only: the workspace bound of another thread (and of the
     main thread) does not move when a worker forces a context split."""
