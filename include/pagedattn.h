@@ -38,7 +38,7 @@ typedef enum {
     PA_OK = 0,
     PA_ERR_INVALID_ARG = 1,          /* NULL pointer, negative size, Hq % Hkv != 0, page size not a power of two */
     PA_ERR_UNSUPPORTED = 2,          /* dtype / head_dim / stride combination no kernel is written for            */
-    PA_ERR_WORKSPACE_TOO_SMALL = 3,  /* workspace_bytes < paged_attention_workspace_bytes(...)                    */
+    PA_ERR_WORKSPACE_TOO_SMALL = 3,  /* less than the call requires (paged_attention_workspace_bytes(...) suffices) */
     PA_ERR_HIP = 4,                  /* a HIP call reported an error                                              */
     PA_ERR_OUT_OF_PAGES = 5,         /* the page pool cannot satisfy a reservation (nothing was changed)          */
     PA_ERR_SCRATCH_LIMIT = 6         /* paged_attention_decode_static: the call needs more scratch than the array holds */
@@ -104,8 +104,10 @@ pa_status paged_kv_gather(const pa_kv_cache_desc* cache, void* out_k, void* out_
  * on the prefill kernel when the workspace has no room for their partials).
  * For calls of several sequences with contexts of 4096 tokens and more it
  * includes the room in which a jagged call cuts its long contexts evenly over
- * the GPU (about 135 MB at head_dim 128); a workspace without that room is
- * accepted and such calls run on the plain grid.
+ * the GPU (about 135 MB at head_dim 128, 268 MB at 256).  Only calls on 16-bit
+ * pools without hooks, pages of 16 tokens and more and query lengths that
+ * differ use it; a workspace without that room is accepted by every call and
+ * keeps such calls on the plain grid.
  * Always a multiple of 256; never 0.  Depends on the calling thread's
  * pa_set_option knobs and on the current device's compute-unit count.
  */
@@ -130,6 +132,10 @@ size_t paged_attention_workspace_bytes(int32_t batch, int32_t num_q_heads, int32
  * library keeps no device state of its own between or beside calls (a plan that
  * splits a sequence over several workgroups of one launch counts their arrivals
  * in the workspace too), and a captured HIP graph may be replayed like the call.
+ * Results repeat bit for bit with the same arguments and workspace size.  How a
+ * context is cut, and with it the last bits, can depend on what stands beside a
+ * sequence: on batch and max_seq_len, for fp32 pools on workspace_bytes, and in
+ * jagged prefill calls on the other sequences' lengths.
  */
 pa_status paged_attention_decode(const pa_kv_cache_desc* cache, const void* q, void* out, float* lse,
                                  const int32_t* block_table, const int32_t* seq_lens, int32_t batch,
@@ -141,10 +147,12 @@ pa_status paged_attention_decode(const pa_kv_cache_desc* cache, const void* q, v
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and results as
  * paged_attention_decode (bit-identical: the same kernels and the same plan), without the workspace: the split-KV
  * partials go to a 16 MiB array that lives in the library's device image (one copy per GPU, held until the process
- * ends).  The call allocates and frees nothing.  A call whose plan needs more than the array holds (partials are
- * (workgroups + batch) * Hq * (head_dim + 1) floats; about one workgroup per compute unit) is rejected with
- * PA_ERR_SCRATCH_LIMIT before anything is launched.  Every call on a GPU shares that GPU's array: calls that
- * overlap on one GPU (different streams, different host threads) race and must be serialised by the caller.
+ * ends).  The call allocates and frees nothing.  A call whose plan needs more than the array holds is rejected with
+ * PA_ERR_SCRATCH_LIMIT before anything is launched.  The plan that counts is that of the tile stream (partials are
+ * (workgroups + batch) * Hq * (head_dim + 1) floats; about one workgroup per compute unit), also for some calls that a
+ * one-launch kernel takes with less: the range of accepted calls does not follow the routes.  Every call on a GPU
+ * shares that GPU's array: calls that overlap on one GPU (different streams, different host threads) race and must be
+ * serialised by the caller.
  * Nothing in the array needs to start at zero: the kernels write every partial they later read.
  */
 pa_status paged_attention_decode_static(const pa_kv_cache_desc* cache, const void* q, void* out, float* lse,
@@ -253,7 +261,7 @@ const char* pa_status_string(pa_status status);
 /*
  * Tuning knobs, kept per host thread: they shape the calls (and the workspace
  * bound) of the thread that set them and nothing else.  name is one of
- *   "decode_chunk_tokens"  context tokens per split-KV workgroup of the portable kernel (0 = heuristic)
+ *   "decode_chunk_tokens"  context tokens per split-KV workgroup of the portable and the fp32 kernels (0 = heuristic)
  *   "decode_workgroups"    workgroups the MFMA decode kernel spreads the batch's key tiles over
  *                          (0 = one per compute unit)
  *   "prefill_chunk_tokens" context tokens per workgroup of the MFMA prefill kernel (0 = heuristic: no split
@@ -263,7 +271,7 @@ const char* pa_status_string(pa_status status);
  *                          no workspace, no merge launch): 0 = taken while the step is small enough for it to
  *                          pay (the default), 1 = whenever it supports the call, -1 = never
  *   "decode_short_splits"  workgroups per (sequence, KV head) of the one-launch decode kernel, 1 .. 16 (0 = as many
- *                          as fill the machine, at least 16384 / head_dim keys each); size the workspace AFTER setting it
+ *                          as fill the machine, at most 32, at least 16384 / head_dim keys each); size the workspace AFTER setting it
  *   "step_append_kernel"   1 = paged_decode_step on the tile-stream kernel appends with a kernel launch of its own
  *                          instead of inside the decode kernel (for comparison)
  *   "no_small_q_route"     1 = the prefill entry point keeps sequences with few queries (q_len * G <= 16) on

@@ -401,8 +401,8 @@ __global__ __launch_bounds__(NW * 64) void paged_attention_f32_kernel(
 // in split order (the scheme of the one-launch decode kernel of the
 // 16-bit pools).  One launch, whatever the context; bound by launch and memory
 // round trips while a wave has a tile or two, by the stream of K and V beyond.
-// Portable kernel / this one, us: 1 x 16 tokens 8 / 8 heads, head_dim 64 6.0 / 4.7; 1 x 128 7.9 / 5.7; 1 x 2048 16.6 / 11.6;
-// 8 x 2048 at head_dim 128 50 / 27 (134 MB), with 32 / 8 heads 99 / 47; 8 x 100 with 32 / 8 heads, head_dim 64 7.7 / 7.7.  With
+// Portable kernel / this one, us: 1 x 16 tokens 8 / 8 heads, head_dim 64 6.0 / 4.7; 1 x 128 7.9 / 5.5; 1 x 2048 16.6 / 10.5;
+// 8 x 2048 at head_dim 128 50 / 26 (134 MB), with 32 / 8 heads 99 / 45; 8 x 100 with 32 / 8 heads, head_dim 64 7.7 / 7.7.  With
 // more than 4 heads a group the matrix kernel above is the better one (8 x 2048, 64 / 8 heads: 91 here, 44 there).
 //     part: per workgroup 4 rows of D normalised accumulators, then 4 x (reference, sum) as doubles (G = 1: one row).
 template <int D, int R, int HEADS>

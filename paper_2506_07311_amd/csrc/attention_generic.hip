@@ -1,5 +1,5 @@
 // Portable paged attention kernel (VALU, fp32 accumulation) for every shape the MFMA kernels do not cover: fp32 pools
-// with hooks, with head_dims other than 64 / 128 or with pages of fewer than 16 tokens; 16-bit pools with head_dims other
+// with hooks, with head_dims other than 64 / 128, with pages of fewer than 16 tokens or in prefill with a few query rows; 16-bit pools with head_dims other
 // than 64 / 128 / 256 (in prefill also 80 / 96 / 112 without hooks), with non-positive scales in prefill, or in prefill at
 // head_dim 256 and 80 / 96 / 112 with pages of fewer than 16 tokens.  It also serves as an independent GPU cross-check.  One workgroup
 // computes one (query row, query head, context chunk) by flash-style tiles of 1024 keys:

@@ -258,8 +258,8 @@ STEP_SHAPES = [
     ([300, 77, 1, 513, 16], 24, 8, 256, 64, torch.bfloat16),
     ([300, 77, 1, 513, 17], 40, 2, 128, 4, torch.bfloat16),      # 20 heads per KV head: two grid slices; P < 16
     ([5000, 77, 2049], 32, 8, 128, 16, torch.bfloat16),           # left to itself this takes the tile stream
-    ([300, 77, 31], 8, 8, 64, 16, torch.float32),                 # portable kernel: append inside it, one launch
-    ([5000, 77, 1], 8, 2, 64, 16, torch.float32),                 # portable kernel with a context split and a merge
+    ([300, 77, 31], 8, 8, 64, 16, torch.float32),                 # fp32 decode kernel: append inside it, one launch (hooks: portable)
+    ([5000, 77, 1], 8, 2, 64, 16, torch.float32),                 # the same with a context split merged inside it (hooks: and a merge)
     ([300, 77, 1025, 2], 12, 4, 96, 8, torch.bfloat16),           # head_dim 96: portable kernel, 16-bit rows
 ]
 
