@@ -232,6 +232,8 @@ constexpr int64_t kShortMaxSingleShare = (int64_t)3 << 20;
 constexpr int64_t kShortMaxWideShare = (int64_t)5 << 20;
 constexpr int64_t kShortMaxSlicedShare = (int64_t)3 << 19;
 constexpr int64_t kShortMaxWGsPerCU = 2;
+// Nor while every wave has at most one tile of the whole context: 1 x 256 7.3 with 2, 6.2 with one (300 tokens, two tiles a
+// wave, 7.5 and 7.8); 2 x 512 at head_dim 64 8.0 and 6.7 (700: 8.2 and 8.4); 8 x 256 7.4 and 6.35.
 constexpr int32_t kShortMinSplitElems = 16384;   // keys x head_dim
 // The plan that paged_attention_decode_static's scratch limit is stated for (see run_attention).
 constexpr int32_t kScratchMaxSplit = 16;
@@ -253,6 +255,7 @@ int32_t plan_short_splits(const AttnArgs& a, int32_t min_keys = 0, int32_t max_s
         if (max_split <= 0) max_split = units < 8 ? kShortMaxSplit : kScratchMaxSplit;
         const int64_t by_keys = a.max_seq_len / min_keys;
         if (n > by_keys) n = by_keys;
+        if (a.max_seq_len <= decode_short_one_round(a.cache.head_dim)) n = 1;
     }
     if (max_split > 0 && n > max_split) n = max_split;
     if (n > kShortMaxSplit) n = kShortMaxSplit;

@@ -197,6 +197,8 @@ pa_status launch_decode_short(const AttnArgs& a, hipStream_t stream);
 // workgroups one call may split into.
 inline size_t decode_short_part_floats(int64_t wgs, int32_t head_dim) { return (size_t)wgs * (16 * (size_t)head_dim + 32); }
 constexpr int32_t kShortMaxSplit = 32;
+// Keys of one tile for each wave of a workgroup: 8 waves with tiles of 4096 elements a row, at head_dim 256 4 with as many.
+constexpr int32_t decode_short_one_round(int32_t head_dim) { return (head_dim > 128 ? 16384 : 32768) / head_dim; }
 // Arrival counters of a split call, one 64-bit word per (sequence, KV head, slice) unit, in the workspace behind its
 // partials.  An arrival adds `step`, an odd number of the call's own with random bits: a counter of n workgroups only ever
 // holds 0, step, .. (n-1) * step.  The workspace holds anything when a call starts, so every workgroup of a unit looks at

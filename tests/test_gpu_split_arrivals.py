@@ -158,3 +158,15 @@ def test_one_launch_takes_a_single_sequence_while_its_workgroups_shares_are_shor
     finally:
         binding.pa_profile_enable(False)
         binding.pa_profile_reset()
+
+
+@pytest.mark.parametrize("L,d,split", [(256, 128, False), (257, 128, True), (512, 64, False), (513, 64, True), (64, 256, False),
+                                       (128, 256, True)])
+def test_a_context_of_one_tile_a_wave_is_not_split(pa, L, d, split):
+    """Two workgroups and their merge cost more than the one round of tiles they share: the workspace stays untouched."""
+    w = W.make_workload("t", seq_lens=[L], num_q_heads=8, num_kv_heads=8, head_dim=d, page_size=16, dtype=torch.bfloat16,
+                        seed=305, device=DEV)
+    ws = buffers(pa, w, 1)[3][0]
+    before = ws.clone()
+    prepare(pa, w, w.q, torch.empty_like(w.q), None, ws)()
+    assert torch.equal(ws, before) != split
