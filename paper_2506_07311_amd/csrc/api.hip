@@ -625,7 +625,13 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
         }
         a.part_o = reinterpret_cast<float*>(base);
         a.part_lse = reinterpret_cast<float*>(base + po);
-        st = f32 ? launch_attention_f32(a, s) : launch_attention_generic(a, s);
+        // (With one or two KV heads and room on the machine for every (row, head, chunk) the portable kernel was never slower
+        // than one matrix tile for a group's heads, at head_dim 128 by up to 8 %: us portable / matrix, 16 / 1 heads, 1 x 256
+        // 16.2 / 17.2, 1 x 1000 20.1 / 21.8, 8 x 300 20.3 / 20.9; 32 / 2, 1 x 1000 20.3 / 22.0, 1 x 4000, 512 workgroups, 36.7 /
+        // 27.6; 16 / 1 at head_dim 64, 1 x 1000 14.6 / 15.0; one tile a wave, 1 x 128, 7.9 / 7.6; 40 / 8 heads, 1 x 600 22.6 / 20.2.)
+        const bool few = cache->num_kv_heads <= 2 && max_seq_len > 192 &&
+                         (int64_t)batch * num_q_heads * a.plan.nsplit <= device_cus();
+        st = f32 && !few ? launch_attention_f32(a, s) : launch_attention_generic(a, s);
         if (st != PA_OK) return st;
         if (a.plan.nsplit > 1) st = launch_merge(a, s);
         return st;

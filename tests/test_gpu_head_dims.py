@@ -75,7 +75,7 @@ F32_CASES = [  # lens, q_lens (None: decode), Hq, Hkv, d, P, causal
     ([1, 15, 16, 17, 0, 129, 777, 33], [1, 15, 16, 17, 0, 100, 200, 33], 4, 4, 64, 16, True),
     ([1, 15, 16, 300], [1, 15, 16, 50], 6, 2, 128, 32, True),
     ([40, 200], [7, 33], 40, 2, 64, 64, False),                  # 20 heads a group: row tiles that straddle queries
-    ([1, 16, 0, 129, 2049, 255], None, 16, 2, 64, 16, False),    # 2049 keys: chunks of 256 and the merge kernel
+    ([1, 16, 0, 129, 2049, 255], None, 32, 4, 64, 16, False),    # 2049 keys: chunks of 256 and the merge kernel
     ([700, 3, 128], None, 40, 2, 128, 128, False),
 ]
 
@@ -331,3 +331,21 @@ def test_bf16_sums_of_large_values_stay_finite(pa, d):
     out = pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, w.cu_q_lens, w.max_q_len, w.block_table, w.seq_lens, n, 1.0, True)
     v = float(w.v_cache[0, 0, 0, 0].double())
     assert (out.double() / v - 1.0).abs().max() <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,portable", [([257, 1, 30], 16, 2, True), ([192, 100], 16, 2, False), ([2049], 32, 2, False),
+                                                  ([257, 30], 15, 3, False), ([1000], 16, 1, True)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_decode_of_large_groups_with_few_kv_heads(pa, oracle, lens, Hq, Hkv, portable, d):
+    from paper_2506_07311_amd import binding
+    w = W.make_workload("t", seq_lens=lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=16, dtype=torch.float32,
+                        seed=211, device=DEV)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        parity.check_step(pa, oracle, w, f"{lens}", step_call=True)
+        assert binding.pa_profile_read("paged_attention_generic_kernel")[0] == (1 if portable else 0)
+        assert binding.pa_profile_read("paged_attention_f32_kernel")[0] == (0 if portable else 1)
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
