@@ -2,9 +2,13 @@
 // gfx950 (and D = 256, 80, 96, 112 for page sizes of 16 and more).  Internal header: the kernel templates; one translation unit
 // per head_dim instantiates them.  The text below describes D = 128.  D = 64 is the same kernel with half the steps: LDS rows keep their 256-byte stride and
 // swizzle, only the positions of the 8 existing 16-byte pieces are read (the fetch fills the other 8 positions
-// with repeats), the score product takes 4 steps instead of 8 and the value product covers 2 column blocks, not 4.  D = 256 doubles the
-// steps and the column blocks: LDS rows are 512 bytes (two swizzled 256-byte halves), the two tile buffers fill 128 KiB
-// and the 128 accumulator registers of O leave room for one workgroup per compute unit only.
+// with repeats), the score product takes 4 steps instead of 8 and the value product covers 2 column blocks, not 4.  D = 256 has
+// 512-byte LDS rows (two swizzled 256-byte halves) and fills 128 KiB with its two tile buffers, so one workgroup per compute
+// unit; it runs on eight waves of 16 rows (RowGeo), two a SIMD, because 32 rows of O and Q leave room for one wave a SIMD
+// whose operand reads nothing hides: 1 x 8192 with 32 / 8 heads 1417 us with four waves of 32 rows, 1187 with eight of 16
+// (32768 keys behind 1024 queries 1497 / 1200, 4 x 2048 429 / 365, prompts of 2059 and 3146 tokens with 16 / 8 heads, window
+// 1024 and a soft cap 192 / 166, with slopes 433 / 336).  At D = 128, where 32 rows already fit twice, 16 rows lose: every
+// operand read feeds half the matrix work (1 x 8192 505 / 568, 4 x 2048 154 / 173).
 //
 // Prefill is a dense contraction (about 590 flop per byte at 2048 tokens), so it runs on the matrix cores
 // with v_mfma_f32_32x32x16_bf16 in the flash-attention arrangement: one workgroup of 4 waves owns 128
@@ -39,6 +43,8 @@
 // weights as two bf16 terms (p = hi + lo); over long contexts the rounding averages out.
 #pragma once
 
+#include <type_traits>
+
 #include "prefill_tiles.h"
 
 namespace pa {
@@ -54,6 +60,13 @@ struct RowGeo {
     static constexpr int kRowB = D > 128 ? 512 : 256;
     static constexpr int kTileB = kBN * kRowB;        // K part of a tile buffer; the V part follows
     static constexpr int kBufB = 2 * kTileB;
+    // Rows of a wave, and what follows from them: the lane groups that share a row (each takes four of every kStep
+    // consecutive keys of S and columns of O), the waves of a workgroup.
+    static constexpr int kRows = D > 128 ? 16 : 32;
+    static constexpr int kGroups = 64 / kRows;
+    static constexpr int kStep = 4 * kGroups;
+    static constexpr int kWaves = kBM / kRows;
+    static constexpr int kThreads = 64 * kWaves;
 };
 // head_dims 80, 96 and 112: rows hold 10, 12 or 14 pieces and the last column block of O is padded where D is not a
 // multiple of 32.  Every tile carries two-term weights: the portable kernel, which served these head_dims, keeps its
@@ -63,31 +76,36 @@ struct RowGeo {
 // heaviest row tile like every short prompt here; 1065 us on the portable kernel, which reads K and V again per row.
 template <int D>
 constexpr bool kTwoTermOnly = D % 64 != 0;
+// Swizzle of LDS row r.  16 rows a wave: a transpose load reads 32 bytes of 16 rows, 8 of them at a time, and an operand
+// read one piece of 16 rows: both are free of conflicts if 8 consecutive rows differ in the upper three bits.
+template <int D>
+__device__ __forceinline__ int row_swz(int r)
+{
+    return RowGeo<D>::kRows == 32 ? swz(r) : ((r & 7) << 1) | ((r >> 3) & 1);
+}
 // byte offset inside its row of logical 16-byte piece L of LDS row r
-__device__ __forceinline__ int piece_pos(int L, int r) { return 16 * ((L & 16) | ((L & 15) ^ swz(r))); }
+template <int D>
+__device__ __forceinline__ int piece_pos(int L, int r) { return 16 * ((L & 16) | ((L & 15) ^ row_swz<D>(r))); }
 
 // Tile fetch for 512-byte rows: one load-to-LDS instruction of a wave fills 2 consecutive rows (lane l: position
-// l%32 of row l/32); wave w issues, for i < 8, the K and V instructions of rows 8*i + 2*w, +1.  dst = buffer +
-// 2*w*512; row = 2*w + lane/32; lane_off[i & 1] = kv-head offset + this lane's logical piece, which depends on the
-// parity of i through the swizzle of row 8*i + row.
+// l%32 of row l/32); wave w of eight issues, for i < 4, the K and V instructions of rows 16*i + 2*w, +1: one page each.
+// lds = buffer + 2*w*512; row = 2*w + lane/32; lane_off = kv-head offset + this lane's logical piece (the swizzle repeats
+// every 16 rows).
 template <bool UNIFORM>
 __device__ __forceinline__ void fetch_tile512(uint32_t lds, const PageIds& p, const CacheView& cache, int32_t t0, int32_t row,
-                                              int32_t last_key, const uint32_t (&lane_off)[2])
+                                              int32_t last_key, uint32_t lane_off)
 {
+    static_assert(UNIFORM, "two rows of a load share a page");
     constexpr int TB = RowGeo<256>::kTileB;
     const int32_t pg[4] = {p.p0, p.p1, p.p2, p.p3};
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int32_t key = t0 + 8 * i + row;
-        const int32_t slot = min(key, last_key) & (cache.page_size - 1);
-        int64_t off;
-        if (UNIFORM)
-            off = (int64_t)pg[i >> 1] * cache.page_stride * 2 +
-                  ((uint32_t)slot * (uint32_t)(cache.token_stride * 2) + lane_off[i & 1]);
-        else
-            off = ((int64_t)pg[i >> 1] * cache.page_stride + (int64_t)slot * cache.token_stride) * 2 + lane_off[i & 1];
-        load_to_lds16(lds, i * (8 * 512), reinterpret_cast<const char*>(cache.k) + off);
-        load_to_lds16(lds, i * (8 * 512) + TB, reinterpret_cast<const char*>(cache.v) + off);
+    for (int i = 0; i < 4; ++i) {
+        const int32_t slot = min(t0 + 16 * i + row, last_key) & (cache.page_size - 1);
+        int64_t page_off = (int64_t)pg[i] * cache.page_stride * 2;
+        asm volatile("" : "+s"(page_off));                 // stays in scalar registers
+        const uint32_t off32 = (uint32_t)slot * (uint32_t)(cache.token_stride * 2) + lane_off;
+        load_to_lds16(lds, i * (16 * 512), reinterpret_cast<const char*>(cache.k) + page_off, off32);
+        load_to_lds16(lds, i * (16 * 512) + TB, reinterpret_cast<const char*>(cache.v) + page_off, off32);
     }
 }
 
@@ -155,6 +173,11 @@ __device__ __forceinline__ int32_t precise_key_bound(const int32_t* __restrict__
     return max(kPreciseKeys, (int32_t)fminf(kPreciseShare * h, 1.0e9f));
 }
 
+// Operand reads of the 16-row products ahead of their use (a matrix instruction takes 16 cycles there).
+// The order of the instructions around these reads is fixed by scheduling groups: left to itself the compiler clusters the
+// reads of one base address and waits for nearly all of them at every step (1 x 8192 at head_dim 256 1312 -> 1199 us).
+constexpr int kAheadK = 8, kAheadV = 6;
+
 // Online-softmax update with the 32 keys of one half tile.  s holds raw scores on entry; the weights are
 // returned in p.  The running statistic is a REFERENCE exponent m_ref (log2 domain) that may trail the true
 // running max: weights are exp2(score - m_ref), and as long as a lane's 16 weights sum to at most kWeightSumMax
@@ -177,36 +200,56 @@ struct RowMods {
     pa_mod_ctx uc;      // user modification: what its hooks are told about the row
 };
 
+// A call with a soft cap and no slopes has a kernel of its own (beside the one with every score hook, whose wave-uniform
+// tests cut the tile into pieces that the matrix and the vector work cannot be interleaved across), as has a window alone.
+struct WindowCap : Mods<true, true, false> {
+    static constexpr bool kCapOnly = true;
+};
+template <typename M, typename = void>
+struct CapOnly : std::false_type {};
+template <typename M>
+struct CapOnly<M, std::enable_if_t<M::kCapOnly>> : std::true_type {};
+
 // M: compile-time policy of the hooks.  With score hooks the scores are first rewritten in place as
 // log2(e) * (cap(scale * s) + slope * (key - pos)) and the rest runs with a unit scale (a call with neither cap nor slopes
 // keeps its scale).
-// head_dims 80, 96, 112 (KS not a multiple of 4) keep what the portable kernel's fp32 weights gave them.  fp16: the reference
+// head_dims 80, 96, 112 keep what the portable kernel's fp32 weights gave them.  fp16: the reference
 // stands 2^9 below the largest score, so that weights are lost from 2^-33 of the largest on and not from 2^-24 (8000 keys of
 // which one leads by e^15: error 3.4e-3 with the reference at the maximum, 2.5e-4 like this and on the portable kernel).
 // bf16: 2^14 above it and sums up to 1, so that no weight exceeds 1 and a weighted sum of finite values stays finite.
-template <typename E, int KS>
+template <typename E, int D>
 struct Reference {
-    static constexpr bool kPadded = KS % 4 != 0, kBf16 = E::kDtype == PA_DTYPE_BF16;
+    static constexpr bool kPadded = kTwoTermOnly<D>, kBf16 = E::kDtype == PA_DTYPE_BF16;
     static constexpr float kBelow = !kPadded ? 0.f : kBf16 ? -14.f : 9.f;
     static constexpr float kSumMax = kPadded && kBf16 ? 1.f : kWeightSumMax;
 };
-template <bool MASK, bool FIRST, typename E, typename M, int KS, int T>
-__device__ __forceinline__ void half_softmax(f32x16& p, f32x16& s, f32x16 (&o)[T], float& m_ref, float& l, float sc,
+template <bool MASK, bool FIRST, typename E, typename M, int D, typename S, typename A, int T>
+__device__ __forceinline__ void half_softmax(S& p, S& s, A (&o)[T], float& m_ref, float& l, float sc,
                                              int32_t key0, int32_t nk, const RowMods& rm, const int32_t* docs)
 {
-    // document mask: ids of this lane's 16 keys (4 groups of 4 consecutive keys, 8 apart) from the tile's ids in LDS
-    int4 ids[4];
+    constexpr int KS = D / 16;
+    constexpr int kValu = ((CapOnly<M>::value ? 8 : 4) * kBN / 2 / RowGeo<D>::kGroups + 8) / KS;   // vector instructions a matrix instruction
+    constexpr int kStep = RowGeo<D>::kStep, N = kBN / 2 / RowGeo<D>::kGroups;   // this lane's scores: four of every kStep keys
+    // document mask: ids of this lane's keys (groups of 4 consecutive ones) from the tile's ids in LDS
+    int4 ids[N / 4];
     if (M::kDoc) {
 #pragma unroll
-        for (int a = 0; a < 4; ++a) ids[a] = *reinterpret_cast<const int4*>(docs + 8 * a);
+        for (int a = 0; a < N / 4; ++a) ids[a] = *reinterpret_cast<const int4*>(docs + kStep * a);
     }
-    if (M::kScore) {
+    float shift = 0.f;               // score in the log2 domain = s * sc + shift
+    if constexpr (CapOnly<M>::value) {
+        // c * tanh(y / c) with tanh(z) = 1 - 2 / (1 + e^(2z)): s becomes -1 / (1 + e^(2z)), the rest goes into scale and shift
+#pragma unroll
+        for (int r = 0; r < N; ++r) s[r] = __builtin_amdgcn_rcpf(-1.f - __builtin_amdgcn_exp2f(s[r] * rm.cap_in));
+        sc = 2.f * rm.cap_out;
+        shift = rm.cap_out;
+    } else if (M::kScore) {
         // Each hook's instructions are spent only on calls that have it (wave-uniform tests), and the cap takes five per score:
         // 2 x 1200 tokens, 32 / 8 heads, with a cap 68.3 -> 49.4 us, with a window alone 44.6 -> 38.4, 4 prompts of 1000 ..
-        // 2000 with both 199 -> 148; head_dim 256, 16 / 8 heads, both, prompts of 2000 .. 4000 259 -> 210.
+        // 2000 with both 199 -> 148.
         if (rm.cap) {                // c * tanh(y / c) with tanh(z) = 1 - 2 / (1 + e^(2z)); cap_in carries 2 log2(e) / c
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
+            for (int r = 0; r < N; ++r) {
                 const float t = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(s[r] * rm.cap_in));
                 s[r] = __builtin_fmaf(-2.f * rm.cap_out, t, rm.cap_out);
             }
@@ -215,43 +258,50 @@ __device__ __forceinline__ void half_softmax(f32x16& p, f32x16& s, f32x16 (&o)[T
         if (rm.bias) {
             const float b0 = rm.slope2 * (float)(key0 - rm.pos);
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                s[r] = s[r] * sc + __builtin_fmaf(rm.slope2, (float)(8 * (r / 4) + (r % 4)), b0);
+            for (int r = 0; r < N; ++r)
+                s[r] = s[r] * sc + __builtin_fmaf(rm.slope2, (float)(kStep * (r / 4) + (r % 4)), b0);
             sc = 1.f;
         }
     }
     if (M::kUser) {
         if (sc != 1.f) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) s[r] *= sc;
+            for (int r = 0; r < N; ++r) s[r] *= sc;
             sc = 1.f;
         }   // (a user modification is compiled with the score hooks: the scores are in the log2 domain here)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-            s[r] = user_score<M>(rm.uc, key0 + 8 * (r / 4) + (r % 4), s[r] * kLn2) * kLog2e;
+        for (int r = 0; r < N; ++r)
+            s[r] = user_score<M>(rm.uc, key0 + kStep * (r / 4) + (r % 4), s[r] * kLn2) * kLog2e;
     }
-    const bool below = M::kWindow && key0 < rm.lo_until;      // wave-uniform up to the lane's 4-key offset
+    // (16 rows a wave: a tile that a window cuts is a masked tile, so that no test stands between products and softmax)
+    const bool below = RowGeo<D>::kRows == 32 && M::kWindow && key0 < rm.lo_until;      // wave-uniform up to the lane's 4-key offset
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        if (MASK && key0 + 8 * (r / 4) + (r % 4) >= nk) s[r] = -INFINITY;   // mask by selection
-        if (below && key0 + 8 * (r / 4) + (r % 4) < rm.lo) s[r] = -INFINITY;
+    for (int r = 0; r < N; ++r) {
+        if (MASK && key0 + kStep * (r / 4) + (r % 4) >= nk) s[r] = -INFINITY;   // mask by selection
+        if ((RowGeo<D>::kRows == 16 ? MASK && M::kWindow : below) && key0 + kStep * (r / 4) + (r % 4) < rm.lo) s[r] = -INFINITY;
         if (M::kDoc) {
             const int4 g = ids[r / 4];
             const int32_t id = (r % 4) == 0 ? g.x : (r % 4) == 1 ? g.y : (r % 4) == 2 ? g.z : g.w;
             if (id != rm.doc) s[r] = -INFINITY;
         }
     }
+    // (an addition of no shift would not be free: it is an instruction beside the sign that the multiply-add has for nothing)
+    auto less = [&](float ref) { return CapOnly<M>::value ? shift - ref : -ref; };
     float psum = 0.f;
+    const float off = less(m_ref);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], sc, -m_ref));
+    for (int r = 0; r < N; ++r) {
+        p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], sc, off));
         psum += p[r];
     }
     // keep the speculative weights ahead of the branch below (they are dead on its slow path, and the
     // optimiser would otherwise sink them behind the test, back onto the critical path)
-    asm volatile("" ::"v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(p[4]), "v"(p[5]), "v"(p[6]), "v"(p[7]), "v"(p[8]),
-                 "v"(p[9]), "v"(p[10]), "v"(p[11]), "v"(p[12]), "v"(p[13]), "v"(p[14]), "v"(p[15]));
-    if (FIRST) {
+    if constexpr (N == 8)
+        asm volatile("" ::"v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(p[4]), "v"(p[5]), "v"(p[6]), "v"(p[7]));
+    else
+        asm volatile("" ::"v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(p[4]), "v"(p[5]), "v"(p[6]), "v"(p[7]), "v"(p[8]),
+                     "v"(p[9]), "v"(p[10]), "v"(p[11]), "v"(p[12]), "v"(p[13]), "v"(p[14]), "v"(p[15]));
+    if (FIRST && RowGeo<D>::kRows == 32) {
         // instruction order for the region that holds both score products and this half's softmax: the second
         // half's 8 matrix instructions are issued with the vector work of the first half's softmax in between
         // (KS = matrix instructions per score product)
@@ -261,22 +311,46 @@ __device__ __forceinline__ void half_softmax(f32x16& p, f32x16& s, f32x16 (&o)[T
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
-        // (up to head_dim 128 the region also holds the 4 * T transpose loads of the half's V fragments)
+        // (the region also holds the 4 * T transpose loads of the half's V fragments)
 #pragma unroll
         for (int i = 0; i < KS; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             if (i < KS / 2) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            if (T <= 4) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 72 / KS, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);
         }
     }
-    typedef Reference<E, KS> R;
+    if (RowGeo<D>::kRows == 16) {
+        if (FIRST) {
+            __builtin_amdgcn_sched_group_barrier(0x100, kAheadK, 0);
+#pragma unroll
+            for (int i = 0; i < KS; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < KS; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                if (i >= KS - kAheadK) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < KS; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);
+            }
+        }
+    }
+    typedef Reference<E, D> R;
     const bool jump = !(psum <= R::kSumMax);                  // also true for the NaN / inf of a fresh reference
     if (__any(jump)) {
         float tmax = -INFINITY;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, s[r]);
-        const float top = pair_max(tmax) * sc - R::kBelow;    // sc > 0: scaling commutes with the max
+        for (int r = 0; r < N; ++r) tmax = fmaxf(tmax, s[r]);
+        const float top = row_max<RowGeo<D>::kGroups>(tmax) * sc - (R::kBelow - shift);    // sc > 0: scaling commutes with the max
         const float m_new = fmaxf(m_ref, top);
         const float m_use = m_new == -INFINITY ? 0.f : m_new; // a query with no allowed key so far
         const float alpha = __builtin_amdgcn_exp2f(m_ref - m_use);
@@ -285,9 +359,10 @@ __device__ __forceinline__ void half_softmax(f32x16& p, f32x16& s, f32x16 (&o)[T
         l *= alpha;
         m_ref = m_new;
         psum = 0.f;
+        const float off_use = less(m_use);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], sc, -m_use));
+        for (int r = 0; r < N; ++r) {
+            p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], sc, off_use));
             psum += p[r];
         }
     }
@@ -311,8 +386,8 @@ __device__ __forceinline__ void load_v_frags(uint4 (&va)[T], uint4 (&vb)[T], con
 }
 
 // The weights of 8 keys as a B operand (and their second 16-bit term: p = hi + lo, lo = round(p - hi)).
-template <bool PRECISE, typename E>
-__device__ __forceinline__ void pack_weights(uint4& w, uint4& wl, const f32x16& s, int r0)
+template <bool PRECISE, typename E, typename S>
+__device__ __forceinline__ void pack_weights(uint4& w, uint4& wl, const S& s, int r0)
 {
     w.x = E::pack(s[r0 + 0], s[r0 + 1]);
     w.y = E::pack(s[r0 + 2], s[r0 + 3]);
@@ -390,38 +465,13 @@ __device__ __forceinline__ void half_pv_by_key(f32x16 (&o)[T], const f32x16& s, 
     }
 }
 
-// O^T += V^T P^T for the 32 keys of half tile `half` (two 16-key steps), head_dim 256: the second step's fragments
-// take the place of the first step's as those are consumed (the 8 column blocks leave no room to hold both).
-// vbuf = V part of the tile buffer.
-template <bool PRECISE, typename E, int T>
-__device__ __forceinline__ void half_pv(f32x16 (&o)[T], const f32x16& s, const char* vbuf, int half,
-                                        const uint32_t (&vx)[2 * T])
-{
-    constexpr int RB = 512;
-    uint4 va[T];
-    const char* v0 = vbuf + (32 * half) * RB;
-#pragma unroll
-    for (int t = 0; t < T; ++t) va[t] = lds_frag_tr(v0 + vx[2 * t], v0 + vx[2 * t + 1]);
-#pragma unroll
-    for (int st = 0; st < 2; ++st) {
-        uint4 w, wl;
-        pack_weights<PRECISE, E>(w, wl, s, 8 * st);
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            o[t] = E::mfma32(va[t], w, o[t]);
-            if (PRECISE) o[t] = E::mfma32(va[t], wl, o[t]);
-            if (st == 0) va[t] = lds_frag_tr(v0 + 16 * RB + vx[2 * t], v0 + 16 * RB + vx[2 * t + 1]);
-        }
-    }
-}
-
 // S^T of half tile `half` (32 keys) against the wave's 32 queries: 8 chained matrix instructions, the K operand
 // reads kept four ahead.  kx[ks] = this lane's swizzled operand offset for head_dim step ks.
 template <typename E, int KS>
 __device__ __forceinline__ void half_scores(f32x16& s, const char* kbuf, int half, const uint32_t (&kx)[KS],
                                             const uint4 (&qf)[KS])
 {
-    constexpr int RB = KS > 8 ? 512 : 256;
+    constexpr int RB = 256;
     s = (f32x16)(0.f);   // folded into the first matrix instruction's accumulator operand
     const char* kh = kbuf + (32 * half) * RB;
     uint4 ka[4];
@@ -434,6 +484,62 @@ __device__ __forceinline__ void half_scores(f32x16& s, const char* kbuf, int hal
     }
 }
 
+// ---- 16 rows a wave (head_dim 256) ---------------------------------------------------------------------------------
+// The same two products on 16 x 16 x 32 matrix instructions: lane%16 = query, lane/16 = group g of four.  S^T of a
+// 16-key block leaves keys 4 g + r in lane group g; two blocks are the 8 contraction slots of a lane in the value product.
+// kx / vx are LDS ADDRESSES in the tile's buffer (the other buffer is one bit away), swizzled, of the first 16 pieces of a
+// row; everything else -- the second half row, key blocks, the V part -- is a constant that fits the instruction's offset.
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
+typedef __attribute__((address_space(3))) s16x4 lds_tr;
+
+// S^T of half tile `half`: two blocks of 16 keys, D / 32 steps each, operand reads kept kAheadK ahead.
+template <typename E, int D, int NK>
+__device__ __forceinline__ void half_scores16(f32x8& s, int half, const uint32_t (&kx)[NK], const uint4 (&qf)[D / 32])
+{
+    constexpr int RB = RowGeo<D>::kRowB, N = 2 * (D / 32);
+    auto frag = [&](int i) {
+        return __builtin_bit_cast(uint4, *(lds_u32x4*)(uintptr_t)(kx[(i / 2) % NK] + (32 * half + 16 * (i & 1)) * RB + (i / 2 / NK) * 256));
+    };
+    mfma_f32x4 acc[2] = {(mfma_f32x4)(0.f), (mfma_f32x4)(0.f)};
+    uint4 ka[kAheadK];
+#pragma unroll
+    for (int i = 0; i < kAheadK; ++i) ka[i] = frag(i);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        acc[i & 1] = E::mfma16(ka[i % kAheadK], qf[i / 2], acc[i & 1]);
+        if (i + kAheadK < N) ka[i % kAheadK] = frag(i + kAheadK);
+    }
+    s = __builtin_shufflevector(acc[0], acc[1], 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// V^T operand of column block i % (D / 16) of half tile i / (D / 16).
+template <int D, int NV>
+__device__ __forceinline__ uint4 v_frag16(int i, const uint32_t (&vx)[NV])
+{
+    constexpr int RB = RowGeo<D>::kRowB, T = D / 16;
+    const uint32_t p = vx[i % T % NV] + RowGeo<D>::kTileB + (i / T) * 32 * RB + (i % T / NV) * 256;
+    tr_pair r;
+    r.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr*)(uintptr_t)p);
+    r.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr*)(uintptr_t)(p + 16 * RB));
+    return __builtin_bit_cast(uint4, r);
+}
+// O^T += V^T P^T for the 32 keys of half tile HALF; va holds its first fragments on entry and, HALF == 0, those of the
+// second half on return (kAheadV ahead of their use).
+template <int HALF, bool PRECISE, typename E, int D, int T, int NV>
+__device__ __forceinline__ void half_pv16(mfma_f32x4 (&o)[T], const f32x8& p, uint4 (&va)[kAheadV], const uint32_t (&vx)[NV])
+{
+    uint4 w, wl;
+    pack_weights<PRECISE, E>(w, wl, p, 0);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int i = HALF * T + t;
+        o[t] = E::mfma16(va[i % kAheadV], w, o[t]);
+        if (PRECISE) o[t] = E::mfma16(va[i % kAheadV], wl, o[t]);
+        if (i + kAheadV < 2 * T) va[i % kAheadV] = v_frag16<D>(i + kAheadV, vx);
+    }
+}
+
 // One 64-key tile for one wave, processed as two half tiles of 32 keys so that, within the wave, the softmax of
 // one half (vector ALU) runs under the matrix instructions of the other half:
 //     matrix cores:  S(h0)   S(h1)          PV(h0)          PV(h1)
@@ -441,33 +547,42 @@ __device__ __forceinline__ void half_scores(f32x16& s, const char* kbuf, int hal
 // buf = tile buffer (K rows, then V rows); key0 = first key of the tile + 4 * (lane/32); nk = keys this lane's
 // query may see (MASK only); sc = scale * log2(e) > 0.
 // CAREFUL: values of V that are not finite stay with the rows that see them (see prefill_body).
-template <bool PRECISE, bool MASK, bool CAREFUL, typename E, typename M, int T, int KS>
-__device__ __forceinline__ void attend_tile(const char* buf, const uint32_t (&kx)[KS], const uint32_t (&vx)[2 * T],
-                                            const uint4 (&qf)[KS], f32x16 (&o)[T], float& m, float& l, float sc,
+template <bool PRECISE, bool MASK, bool CAREFUL, typename E, typename M, int D, typename A, int T, int KS, int NK, int NV>
+__device__ __forceinline__ void attend_tile(const char* buf, const uint32_t (&kx)[NK], const uint32_t (&vx)[NV],
+                                            const uint4 (&qf)[KS], A (&o)[T], float& m, float& l, float sc,
                                             int32_t key0, int32_t nk, const RowMods& rm, const int32_t* docs)
 {
-    f32x16 s0, s1, p;
-    const int hh = (int)(threadIdx.x >> 5) & 1;
-    constexpr int TB = kBN * (T > 4 ? 512 : 256);
-    if constexpr (T <= 4) {
+    const char* vbuf = buf + RowGeo<D>::kTileB;
+    if constexpr (RowGeo<D>::kRows == 32) {
+        f32x16 s0, s1, p;
+        const int hh = (int)(threadIdx.x >> 5) & 1;
         uint4 va[T], vb[T];
         half_scores<E, KS>(s0, buf, 0, kx, qf);
         half_scores<E, KS>(s1, buf, 1, kx, qf);
-        load_v_frags<T>(va, vb, buf + TB, 0, vx);
-        half_softmax<MASK, true, E, M, KS, T>(p, s0, o, m, l, sc, key0, nk, rm, docs);
+        load_v_frags<T>(va, vb, vbuf, 0, vx);
+        half_softmax<MASK, true, E, M, D>(p, s0, o, m, l, sc, key0, nk, rm, docs);
         if (CAREFUL) half_pv_by_key<E, T>(o, p, va, vb, key0 - 4 * hh, nk, hh);
         else half_pv_frags<PRECISE, E, T>(o, p, va, vb);
-        load_v_frags<T>(va, vb, buf + TB, 1, vx);
-        half_softmax<MASK, false, E, M, KS, T>(p, s1, o, m, l, sc, key0 + 32, nk, rm, docs + 32);
+        load_v_frags<T>(va, vb, vbuf, 1, vx);
+        half_softmax<MASK, false, E, M, D>(p, s1, o, m, l, sc, key0 + 32, nk, rm, docs + 32);
         if (CAREFUL) half_pv_by_key<E, T>(o, p, va, vb, key0 + 32 - 4 * hh, nk, hh);
         else half_pv_frags<PRECISE, E, T>(o, p, va, vb);
     } else {
-        half_scores<E, KS>(s0, buf, 0, kx, qf);
-        half_scores<E, KS>(s1, buf, 1, kx, qf);
-        half_softmax<MASK, true, E, M, KS, T>(p, s0, o, m, l, sc, key0, nk, rm, docs);
-        half_pv<PRECISE, E, T>(o, p, buf + TB, 0, vx);
-        half_softmax<MASK, false, E, M, KS, T>(p, s1, o, m, l, sc, key0 + 32, nk, rm, docs + 32);
-        half_pv<PRECISE, E, T>(o, p, buf + TB, 1, vx);
+        f32x8 s0, s1, p;
+        uint4 va[kAheadV];
+        half_scores16<E, D>(s0, 0, kx, qf);
+        half_scores16<E, D>(s1, 1, kx, qf);
+#pragma unroll
+        for (int i = 0; i < kAheadV; ++i) va[i] = v_frag16<D>(i, vx);
+        half_softmax<MASK, true, E, M, D>(p, s0, o, m, l, sc, key0, nk, rm, docs);
+        half_pv16<0, PRECISE, E, D>(o, p, va, vx);
+        half_softmax<MASK, false, E, M, D>(p, s1, o, m, l, sc, key0 + 32, nk, rm, docs + 32);
+        half_pv16<1, PRECISE, E, D>(o, p, va, vx);
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);
+        }
     }
 }
 
@@ -491,10 +606,12 @@ __device__ __forceinline__ bool prefill_body(
     const int32_t* __restrict__ block_table, int32_t num_q_heads, int32_t max_blocks, float scale, int32_t causal, const PrefillPlan& plan, int32_t precise_keys,
     const WorkItem& own, const int tid)
 {
-    constexpr int KS = D / 16, T = (D + 31) / 32;        // steps of a score product, 32-column blocks of O
-    constexpr int RB = RowGeo<D>::kRowB;
+    typedef RowGeo<D> Geo;
+    constexpr int R = Geo::kRows, RB = Geo::kRowB, STEP = Geo::kStep;
+    constexpr int KS = D / (8 * Geo::kGroups);               // steps of a score product
+    constexpr int T = (D + R - 1) / R;                       // R-column blocks of O
     const int lane = tid & 63, wave = tid >> 6;
-    const int ql = lane & 31, hh = lane >> 5;
+    const int ql = lane & (R - 1), hh = lane / R;            // the lane's row in the wave, its group
     // Rows of a workgroup's 128-row tile are (query, head) pairs: the 2^log2_pack query heads packed into a tile
     // share one KV head, row r of a sequence is query r >> log2_pack, packed head r & (pack - 1).
     const int32_t lg = plan.log2_pack;
@@ -543,7 +660,7 @@ __device__ __forceinline__ bool prefill_body(
     const int32_t* table = block_table + (int64_t)s * max_blocks;
 
     // this lane's row: query, head, and key bound
-    const int32_t r_lane = m0 + 32 * wave + ql;
+    const int32_t r_lane = m0 + R * wave + ql;
     const bool q_valid = r_lane < n_rows;
     const int32_t r_c = min(r_lane, n_rows - 1);
     const int32_t qi_c = r_c >> lg;
@@ -554,10 +671,10 @@ __device__ __forceinline__ bool prefill_body(
     if (causal) nk = min(len, pos + 1);
     else if (window > 0) nk = min(len, pos + window);
     nk = max(nk, 0);
-    // per wave: the largest bound of its 32 rows decides which tiles it can skip, the smallest which
+    // per wave: the largest bound of its rows decides which tiles it can skip, the smallest which
     // tiles need no mask
-    const int32_t pos_first = len - q_len + (min(m0 + 32 * wave, n_rows - 1) >> lg);
-    const int32_t pos_last = len - q_len + (min(m0 + 32 * wave + 31, n_rows - 1) >> lg);
+    const int32_t pos_first = len - q_len + (min(m0 + R * wave, n_rows - 1) >> lg);
+    const int32_t pos_last = len - q_len + (min(m0 + R * wave + R - 1, n_rows - 1) >> lg);
     int32_t nk_wave = len, nk_wave_min = len;
     if (causal) {
         nk_wave = min(len, pos_last + 1);
@@ -600,52 +717,58 @@ __device__ __forceinline__ bool prefill_body(
     }
 
     const int64_t row = (int64_t)(q_begin + qi_c) * num_q_heads + h;
-    // Q as B operand: lane%32 = query, step ks covers head_dim elements 16*ks + 8*hh .. +7
+    // Q as B operand: lane % R = query, step ks covers 8 head_dim elements of each lane group
     uint4 qf[KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const uint4*>(q + row * D + 16 * ks + 8 * hh);
+    for (int ks = 0; ks < KS; ++ks)
+        qf[ks] = *reinterpret_cast<const uint4*>(q + row * D + 8 * Geo::kGroups * ks + 8 * hh);
 
-    f32x16 o[T];
+    typename std::conditional<R == 32, f32x16, mfma_f32x4>::type o[T];
 #pragma unroll
-    for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[t][r] = 0.f;
+    for (int t = 0; t < T; ++t) o[t] = 0.f;
     float m = -INFINITY, l = 0.f;
     const float sc = scale * kLog2e;
 
     // swizzled LDS offsets of this lane's operands (see the header): K piece (2*ks + hh) of row ql,
     // V pieces of the 32 columns t for the lane's transpose-load row
-    uint32_t kx[KS], vx[2 * T];
+    // (16 rows a wave: piece 4*ks + hh, V pieces of the 16 columns t; those of the second half row are not kept)
+    constexpr int NK = R == 32 ? KS : 4, NV = R == 32 ? 2 * T : 8;
+    uint32_t kx[NK], vx[NV];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kx[ks] = ql * RB + piece_pos(2 * ks + hh, ql);
+    for (int ks = 0; ks < NK; ++ks) kx[ks] = ql * RB + piece_pos<D>(Geo::kGroups * ks + hh, ql);
     {
         // transpose-load rows of this lane: key 4*hh + j (+8 for slots 4-7) of a 16-key step, columns 4*qq..+3 of
         // the 16-column block dblk of the 32 columns t
         const int j = (lane & 15) >> 2, qq = lane & 3, dblk = (lane >> 4) & 1;
+        if constexpr (R == 32) {
 #pragma unroll
-        for (int t = 0; t < T; ++t) {
-            const int piece = 4 * t + 2 * dblk + (qq >> 1);
-            vx[2 * t] = (4 * hh + j) * RB + piece_pos(piece, 4 * hh + j) + 8 * (qq & 1);
-            vx[2 * t + 1] = (4 * hh + j + 8) * RB + piece_pos(piece, 4 * hh + j + 8) + 8 * (qq & 1);
+            for (int t = 0; t < T; ++t) {
+                const int piece = 4 * t + 2 * dblk + (qq >> 1);
+                vx[2 * t] = (4 * hh + j) * RB + piece_pos<D>(piece, 4 * hh + j) + 8 * (qq & 1);
+                vx[2 * t + 1] = (4 * hh + j + 8) * RB + piece_pos<D>(piece, 4 * hh + j + 8) + 8 * (qq & 1);
+            }
+        } else {
+            // key 4*hh + j of a 16-key block, columns 4*qq..+3 of the 16 columns t
+#pragma unroll
+            for (int t = 0; t < NV; ++t)
+                vx[t] = lds_address(buf0) + (4 * hh + j) * RB + piece_pos<D>(2 * t + (qq >> 1), 4 * hh + j) + 8 * (qq & 1);
+#pragma unroll
+            for (int ks = 0; ks < NK; ++ks) kx[ks] += lds_address(buf0);
         }
     }
     // fetch role of this lane.  256-byte rows: position lane%16 of rows 16*i + frow holds logical piece
     // (lane%16) ^ swz(frow) (a row of head_dim 64 has 8 pieces: the other 8 positions receive repeats that nobody
     // reads; head_dims 80, 96 and 112 repeat their first pieces likewise, and the columns of O beyond D that are computed
-    // from repeats are not stored).  512-byte rows: position lane%32 of rows 8*i + frow; the swizzle of that row depends on the parity of i.
+    // from repeats are not stored).  512-byte rows: position lane%32 of rows 16*i + frow.
     const int frow = D > 128 ? 2 * wave + (lane >> 5) : 4 * wave + (lane >> 4);
     const uint32_t head_off = (uint32_t)(kvh * cache.head_stride * 2);
-    const int piece = (lane & 15) ^ swz(frow);
+    const int piece = (D > 128 ? lane & 16 : 0) | ((lane & 15) ^ row_swz<D>(frow));
     const uint32_t lane_off = head_off + 16 * (D <= 128 && piece >= D / 8 ? piece - D / 8 : piece);
-    uint32_t lane_off2[2];
-#pragma unroll
-    for (int par = 0; par < 2; ++par)
-        lane_off2[par] = head_off + 16 * ((lane & 16) | ((lane & 15) ^ swz(8 * par + frow)));
     const int32_t wrow = __builtin_amdgcn_readfirstlane(D > 128 ? 2 * wave * 512 : 4 * wave * 256);
     const int32_t last_key = len - 1;
     const uint32_t lds0 = lds_address(buf0 + wrow), lds1 = lds_address(buf1 + wrow);
     auto fetch = [&](uint32_t lds, const PageIds& pg, int32_t t0) {
-        if constexpr (D > 128) fetch_tile512<UNIFORM>(lds, pg, cache, t0, frow, last_key, lane_off2);
+        if constexpr (D > 128) fetch_tile512<UNIFORM>(lds, pg, cache, t0, frow, last_key, lane_off);
         else fetch_tile<UNIFORM>(lds, pg, cache, t0, frow, last_key, lane_off);
     };
 
@@ -695,6 +818,31 @@ __device__ __forceinline__ bool prefill_body(
     }
     wait_tile_loads();                                       // (outside the test: the loop below must start from a
     __syncthreads();                                         //  state without pending loads on every path)
+    if constexpr (R == 16) {
+        // (one copy of the tile's code: the two buffers are one bit apart, and so are the addresses of their operands)
+        for (int32_t t = 0; t < n_tiles; ++t) {
+            const int32_t t0 = k_begin + t * kBN;
+            if (t + 1 < n_tiles) {
+                fetch(t & 1 ? lds0 : lds1, ids, t0 + kBN);
+                if (doc_lane) doc_next = tile_ids(t0 + kBN);
+                if (t + 2 < n_tiles) load_ids<UNIFORM>(ids, cache, table, t0 + 2 * kBN, frow, last_key);
+            }
+            int32_t* const docs = t & 1 ? docs1 : docs0;
+            if (t0 < nk_wave && t0 + kBN > lo_wave && docs_overlap(docs)) {
+                if (t0 + kBN > nk_wave_min || (M::kWindow && t0 < rm.lo_until))
+                    attend_tile<PRECISE, true, CAREFUL, E, M, D>(nullptr, kx, vx, qf, o, m, l, sc, t0 + 4 * hh, nk, rm, docs + 4 * hh);
+                else
+                    attend_tile<PRECISE, false, CAREFUL, E, M, D>(nullptr, kx, vx, qf, o, m, l, sc, t0 + 4 * hh, nk, rm, docs + 4 * hh);
+            }
+            if (doc_lane && t + 1 < n_tiles) put_docs(t & 1 ? docs0 : docs1, doc_next);
+            wait_tile_loads();
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < NK; ++i) kx[i] ^= Geo::kBufB;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) vx[i] ^= Geo::kBufB;
+        }
+    } else {
     // Two tiles per trip so that each buffer is a distinct LDS object for the compiler: while the matrix cores
     // read one, the load unit fills the other with the next tile; the page ids of the tile after that are requested
     // at the same time.  The barrier at the end of a tile waits for this wave's loads first.
@@ -707,9 +855,9 @@ __device__ __forceinline__ bool prefill_body(
         }
         if (t0 < nk_wave && t0 + kBN > lo_wave && docs_overlap(docs0)) {   // wave-uniform: else nothing for this wave here
             if (t0 + kBN > nk_wave_min)                      // wave-uniform: some score of this tile is masked
-                attend_tile<PRECISE, true, CAREFUL, E, M, T>(buf0, kx, vx, qf, o, m, l, sc, t0 + 4 * hh, nk, rm, docs0 + 4 * hh);
+                attend_tile<PRECISE, true, CAREFUL, E, M, D>(buf0, kx, vx, qf, o, m, l, sc, t0 + 4 * hh, nk, rm, docs0 + 4 * hh);
             else
-                attend_tile<PRECISE, false, CAREFUL, E, M, T>(buf0, kx, vx, qf, o, m, l, sc, t0 + 4 * hh, nk, rm, docs0 + 4 * hh);
+                attend_tile<PRECISE, false, CAREFUL, E, M, D>(buf0, kx, vx, qf, o, m, l, sc, t0 + 4 * hh, nk, rm, docs0 + 4 * hh);
         }
         if (doc_lane && t + 1 < n_tiles) put_docs(docs1, doc_next);
         wait_tile_loads();
@@ -723,13 +871,14 @@ __device__ __forceinline__ bool prefill_body(
         }
         if (t1 < nk_wave && t1 + kBN > lo_wave && docs_overlap(docs1)) {
             if (t1 + kBN > nk_wave_min)
-                attend_tile<PRECISE, true, CAREFUL, E, M, T>(buf1, kx, vx, qf, o, m, l, sc, t1 + 4 * hh, nk, rm, docs1 + 4 * hh);
+                attend_tile<PRECISE, true, CAREFUL, E, M, D>(buf1, kx, vx, qf, o, m, l, sc, t1 + 4 * hh, nk, rm, docs1 + 4 * hh);
             else
-                attend_tile<PRECISE, false, CAREFUL, E, M, T>(buf1, kx, vx, qf, o, m, l, sc, t1 + 4 * hh, nk, rm, docs1 + 4 * hh);
+                attend_tile<PRECISE, false, CAREFUL, E, M, D>(buf1, kx, vx, qf, o, m, l, sc, t1 + 4 * hh, nk, rm, docs1 + 4 * hh);
         }
         if (doc_lane && t + 2 < n_tiles) put_docs(docs0, doc_next);
         wait_tile_loads();
         __syncthreads();
+    }
     }
 
     if constexpr (kTwoTermOnly<D> && !CAREFUL) {
@@ -743,25 +892,33 @@ __device__ __forceinline__ bool prefill_body(
         __syncthreads();
         if (docs0[0] | docs0[1] | docs0[2] | docs0[3]) return true;
     }
+    if (R == 16) l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
     if (!q_valid) return false;
     const float inv = l > 0.f ? 1.f / l : 0.f;
     // (a NaN among the scores: head_dims 80, 96 and 112 say so, in a partial by +inf, which the merge turns into NaN)
     const bool bad = kTwoTermOnly<D> && l != l;
     const float row_lse = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
-    // o[t][r]: column 32*t + 8*(r/4) + 4*hh + r%4 of this lane's query
+    // four columns STEP*i + 4*hh .. +3 of this lane's query: o[t][r] is column 32*t + 8*(r/4) + 4*hh + r%4, or with 16
+    // rows a wave column 16*t + 4*hh + r
+    constexpr int NC = T * (R / STEP);
+    auto cols = [&](int i) {
+        if constexpr (R == 32)
+            return float4{o[i / 4][4 * (i % 4) + 0] * inv, o[i / 4][4 * (i % 4) + 1] * inv, o[i / 4][4 * (i % 4) + 2] * inv,
+                          o[i / 4][4 * (i % 4) + 3] * inv};
+        else return float4{o[i][0] * inv, o[i][1] * inv, o[i][2] * inv, o[i][3] * inv};
+    };
     if (LIST && own.slot >= 0) {
-        // work-list mode: normalised accumulators lane by lane (whole cache lines per store), LSE per row
+        // work-list mode: normalised accumulators lane by lane (whole cache lines per store), LSE per row.  The layout is
+        // that of 32 rows a wave: 16-byte piece i of lane (row, group of two), piece = 8 columns.
         float4* po = reinterpret_cast<float4*>(plan.list_o) + (int64_t)own.slot * (list_slot_floats(D) / 4) +
-                     wave * (T * 4 * 64) + lane;
+                     (R * wave / 32) * (list_slot_floats(D) / 16);
+        if constexpr (R == 32) po += lane;
+        else po += (hh >> 1) * 64 + (hh & 1) * 32 + (16 * wave + ql) % 32;
 #pragma unroll
-        for (int t = 0; t < T; ++t)
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-                po[(4 * t + a) * 64] = float4{o[t][4 * a + 0] * inv, o[t][4 * a + 1] * inv, o[t][4 * a + 2] * inv,
-                                              o[t][4 * a + 3] * inv};
+        for (int i = 0; i < NC; ++i) po[i * (R == 32 ? 64 : 128)] = cols(i);
         if (hh == 0)
-            plan.list_lse[(int64_t)own.slot * kBM + 32 * wave + ql] = bad ? INFINITY : row_lse;
+            plan.list_lse[(int64_t)own.slot * kBM + R * wave + ql] = bad ? INFINITY : row_lse;
         return false;
     }
     if (!LIST && own.chunks > 1) {
@@ -769,31 +926,20 @@ __device__ __forceinline__ bool prefill_body(
         const int64_t pidx = row * plan.nsplit + split;
         float* prow = plan.part_o + pidx * D;
 #pragma unroll
-        for (int t = 0; t < T; ++t)
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                if (32 * t + 8 * a >= D) continue;           // columns that pad the last block
-                float4 w;
-                w.x = o[t][4 * a + 0] * inv;
-                w.y = o[t][4 * a + 1] * inv;
-                w.z = o[t][4 * a + 2] * inv;
-                w.w = o[t][4 * a + 3] * inv;
-                *reinterpret_cast<float4*>(prow + 32 * t + 8 * a + 4 * hh) = w;
-            }
+        for (int i = 0; i < NC; ++i) {
+            if (STEP * i >= D) continue;                     // columns that pad the last block
+            *reinterpret_cast<float4*>(prow + STEP * i + 4 * hh) = cols(i);
+        }
         if (hh == 0) plan.part_lse[pidx] = bad ? INFINITY : row_lse;
         return false;
     }
     uint16_t* orow = out + row * D;
 #pragma unroll
-    for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            if (32 * t + 8 * a >= D) continue;
-            uint2 w;
-            w.x = E::pack(o[t][4 * a + 0] * inv, o[t][4 * a + 1] * inv);
-            w.y = E::pack(o[t][4 * a + 2] * inv, o[t][4 * a + 3] * inv);
-            *reinterpret_cast<uint2*>(orow + 32 * t + 8 * a + 4 * hh) = w;
-        }
+    for (int i = 0; i < NC; ++i) {
+        if (STEP * i >= D) continue;
+        const float4 c = cols(i);
+        *reinterpret_cast<uint2*>(orow + STEP * i + 4 * hh) = uint2{E::pack(c.x, c.y), E::pack(c.z, c.w)};
+    }
     if (lse && hh == 0) lse[row] = bad ? l : row_lse;
     return false;
 }
@@ -802,14 +948,17 @@ __device__ __forceinline__ bool prefill_body(
 // workgroup runs exactly one of them, decided by its context length.
 // LIST: the work-list mode of prefill_tiles.h.
 template <bool UNIFORM, typename E, typename M, int D, bool LIST = false>
-__global__ __launch_bounds__(kThreads, D > 128 ? 1 : 2) void paged_prefill_mfma_kernel(
+__global__ __launch_bounds__(RowGeo<D>::kThreads, 2) void paged_prefill_mfma_kernel(
     CacheView cache, const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float* __restrict__ lse,
     const int32_t* __restrict__ cu_q_lens, const int32_t* __restrict__ block_table,
     const int32_t* __restrict__ seq_lens, int32_t batch, int32_t num_tiles, int32_t num_q_heads, int32_t max_blocks,
     float scale, int32_t causal, PrefillPlan plan)
 {
-    __shared__ __attribute__((aligned(1024))) char buf0[RowGeo<D>::kBufB];
-    __shared__ __attribute__((aligned(1024))) char buf1[RowGeo<D>::kBufB];
+    // two tile buffers; with 16 rows a wave they are one object, aligned so that one address bit tells them apart
+    constexpr int kOne = RowGeo<D>::kRows == 16 ? 2 * RowGeo<D>::kBufB : RowGeo<D>::kBufB;
+    __shared__ __attribute__((aligned(kOne > (1 << 16) ? (1 << 17) : 1024))) char buf0[kOne];
+    __shared__ __attribute__((aligned(1024))) char other[RowGeo<D>::kRows == 16 ? 16 : RowGeo<D>::kBufB];
+    char* const buf1 = RowGeo<D>::kRows == 16 ? buf0 + RowGeo<D>::kBufB : other;
     __shared__ __attribute__((aligned(16))) int32_t docs0[kBN + 4];
     __shared__ __attribute__((aligned(16))) int32_t docs1[kBN + 4];
     // The workgroup's own lengths are requested first (scalar loads), the scan of every sequence's lengths for the
@@ -908,7 +1057,7 @@ pa_status launch_prefill_mfma_dim(const AttnArgs& a, const PrefillPlan& plan, in
                                                : paged_prefill_mfma_kernel<true, ElemBf16, NoMods, D>)
                         : (plan.list_items > 0 ? paged_prefill_mfma_kernel<true, ElemF16, NoMods, D, true>
                                                : paged_prefill_mfma_kernel<true, ElemF16, NoMods, D>);
-        hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, stream, a.cache, (const uint16_t*)a.q, (uint16_t*)a.out, a.lse,
+        hipLaunchKernelGGL(kern, grid, dim3(RowGeo<D>::kThreads), 0, stream, a.cache, (const uint16_t*)a.q, (uint16_t*)a.out, a.lse,
                            a.cu_q_lens, a.block_table, a.seq_lens, a.batch, (int32_t)tiles, a.num_q_heads, a.max_blocks,
                            a.scale, a.causal, plan);
         return launch_status();
@@ -916,7 +1065,15 @@ pa_status launch_prefill_mfma_dim(const AttnArgs& a, const PrefillPlan& plan, in
     // page sizes of 16 and more make the page of a 16-key group wave-uniform (scalar page translation)
     const bool uniform = a.cache.page_size >= 16;
     if (D > 128 && !uniform) return PA_ERR_UNSUPPORTED;   // 512-byte rows: two rows per load must share a page
+    constexpr bool kLargePagesOnly = D > 128;             // (no kernels for smaller pages then)
     typedef Mods<true, true, false> WindowScore;
+    // (a window alone and a soft cap have kernels of their own at head_dim 256 only: prompts of 2059 and 3146 tokens, 16 / 8
+    // heads, window 1024 with the shared kernel / the own one 178 / 157 us, with a cap 193 / 166; 32 / 8 heads at head_dim
+    // 128 104.4 / 103.9 and 128.1 / 127.1, at 64 74.5 / 77.1 and 103.9 / 103.8)
+    typedef std::conditional_t<(D > 128), Mods<true, false, false>, WindowScore> Window;
+    typedef std::conditional_t<(D > 128), WindowCap, WindowScore> Cap;
+    const bool windowed = D > 128 && a.has_mods && !a.mods.alibi_slopes && !(a.mods.softcap > 0.f);
+    const bool capped = D > 128 && a.mods.softcap > 0.f && !a.mods.alibi_slopes;
     auto kern = paged_prefill_mfma_kernel<true, ElemBf16, NoMods, D>;
     if (plan.list_items > 0) {                            // (prefill_list_supported)
         if (a.has_mods || !uniform) return PA_ERR_UNSUPPORTED;
@@ -930,10 +1087,10 @@ pa_status launch_prefill_mfma_dim(const AttnArgs& a, const PrefillPlan& plan, in
             found = true;                                                                                   \
             if (a.dtype == PA_DTYPE_BF16)                                                                   \
                 kern = uniform ? paged_prefill_mfma_kernel<true, ElemBf16, UM, D>                           \
-                               : paged_prefill_mfma_kernel<false, ElemBf16, UM, D>;                         \
+                               : paged_prefill_mfma_kernel<kLargePagesOnly, ElemBf16, UM, D>;                         \
             else                                                                                            \
                 kern = uniform ? paged_prefill_mfma_kernel<true, ElemF16, UM, D>                            \
-                               : paged_prefill_mfma_kernel<false, ElemF16, UM, D>;                          \
+                               : paged_prefill_mfma_kernel<kLargePagesOnly, ElemF16, UM, D>;                          \
         }
         PA_USER_MODS(PA_USER_CASE)
 #undef PA_USER_CASE
@@ -941,21 +1098,25 @@ pa_status launch_prefill_mfma_dim(const AttnArgs& a, const PrefillPlan& plan, in
     } else if (a.has_mods && a.mods.doc_ids) {
         if (a.dtype == PA_DTYPE_BF16)
             kern = uniform ? paged_prefill_mfma_kernel<true, ElemBf16, AllMods, D>
-                           : paged_prefill_mfma_kernel<false, ElemBf16, AllMods, D>;
+                           : paged_prefill_mfma_kernel<kLargePagesOnly, ElemBf16, AllMods, D>;
         else
             kern = uniform ? paged_prefill_mfma_kernel<true, ElemF16, AllMods, D>
-                           : paged_prefill_mfma_kernel<false, ElemF16, AllMods, D>;
+                           : paged_prefill_mfma_kernel<kLargePagesOnly, ElemF16, AllMods, D>;
     } else if (a.dtype == PA_DTYPE_BF16) {
-        if (a.has_mods) kern = uniform ? paged_prefill_mfma_kernel<true, ElemBf16, WindowScore, D>
-                                       : paged_prefill_mfma_kernel<false, ElemBf16, WindowScore, D>;
-        else if (!uniform) kern = paged_prefill_mfma_kernel<false, ElemBf16, NoMods, D>;
+        if (windowed) kern = paged_prefill_mfma_kernel<true, ElemBf16, Window, D>;
+        else if (capped) kern = paged_prefill_mfma_kernel<true, ElemBf16, Cap, D>;
+        else if (a.has_mods) kern = uniform ? paged_prefill_mfma_kernel<true, ElemBf16, WindowScore, D>
+                                       : paged_prefill_mfma_kernel<kLargePagesOnly, ElemBf16, WindowScore, D>;
+        else if (!uniform) kern = paged_prefill_mfma_kernel<kLargePagesOnly, ElemBf16, NoMods, D>;
     } else {
-        if (a.has_mods) kern = uniform ? paged_prefill_mfma_kernel<true, ElemF16, WindowScore, D>
-                                       : paged_prefill_mfma_kernel<false, ElemF16, WindowScore, D>;
+        if (windowed) kern = paged_prefill_mfma_kernel<true, ElemF16, Window, D>;
+        else if (capped) kern = paged_prefill_mfma_kernel<true, ElemF16, Cap, D>;
+        else if (a.has_mods) kern = uniform ? paged_prefill_mfma_kernel<true, ElemF16, WindowScore, D>
+                                       : paged_prefill_mfma_kernel<kLargePagesOnly, ElemF16, WindowScore, D>;
         else kern = uniform ? paged_prefill_mfma_kernel<true, ElemF16, NoMods, D>
-                            : paged_prefill_mfma_kernel<false, ElemF16, NoMods, D>;
+                            : paged_prefill_mfma_kernel<kLargePagesOnly, ElemF16, NoMods, D>;
     }
-    hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, stream, a.cache, (const uint16_t*)a.q, (uint16_t*)a.out, a.lse,
+    hipLaunchKernelGGL(kern, grid, dim3(RowGeo<D>::kThreads), 0, stream, a.cache, (const uint16_t*)a.q, (uint16_t*)a.out, a.lse,
                        a.cu_q_lens, a.block_table, a.seq_lens, a.batch, (int32_t)tiles, a.num_q_heads, a.max_blocks,
                        a.scale, a.causal, plan);
     return launch_status();

@@ -9,6 +9,7 @@ namespace prefill {
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef mfma_f32x16 f32x16;
+typedef __attribute__((ext_vector_type(8))) float f32x8;
 
 constexpr int kBM = 128;              // rows per workgroup of the 32-rows-per-wave kernel
 constexpr int kBN = 64;               // keys per tile
@@ -294,11 +295,17 @@ __device__ __forceinline__ void fetch_tile(uint32_t lds, const PageIds& p, const
 }
 
 
-// max over the two lanes that share a row (lane and lane ^ 32) without an LDS round trip
-__device__ __forceinline__ float pair_max(float x)
+// max over the GROUPS lanes that share a row (lane, lane ^ 32 and, of four, lane ^ 16) without an LDS round trip
+template <int GROUPS>
+__device__ __forceinline__ float row_max(float x)
 {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    if (GROUPS == 4) {
+        const auto u = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        x = fmaxf(__uint_as_float(u[0]), __uint_as_float(u[1]));
+    }
+    return x;
 }
 
 // Online softmax keeps a REFERENCE exponent (log2 domain) that may trail the true running max; the reference is

@@ -1,5 +1,5 @@
 """GPU parity of the matrix-core kernels at head_dims whose rows do not fill their tiles (80, 96, 112): padded column
-blocks, padded score steps, repeated row pieces."""
+blocks, padded score steps, repeated row pieces; and at head_dim 256, whose waves hold 16 rows."""
 import pytest
 import torch
 
@@ -68,6 +68,36 @@ def test_prefill_at_padded_head_dims_equals_the_portable_kernel(pa, d):
     for out, lse in outs[1:]:
         assert ((out - ref).abs() <= 2.0 ** -7 * ref.abs() + 1e-4).all()
         assert (lse - ref_lse).abs().max() <= 2e-5
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("causal,chunk", [(True, 0), (False, 0), (True, 128)])
+@pytest.mark.parametrize("case", [None, dict(window=1), dict(window=70), dict(softcap=2.0), dict(window=33, softcap=5.0),
+                                  dict(window=70, softcap=5.0, alibi=True)],
+                         ids=["plain", "window1", "window70", "cap", "window_cap", "window_cap_alibi"])
+def test_prefill_at_head_dim_256(pa, oracle, dtype, causal, chunk, case):
+    """Row counts around the 16 rows of a wave and the 128 of a workgroup (two heads a row tile), contexts around the
+    64-key tile, windows that cut a tile's first keys, and each of the kernels a call's hooks choose between."""
+    from paper_2506_07311_amd import binding
+    lens = [1, 15, 16, 17, 0, 64, 65, 129, 300, 191]
+    q_lens = [1, 7, 8, 9, 0, 63, 64, 65, 128, 33]
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=4, num_kv_heads=2, head_dim=256, page_size=32,
+                        dtype=dtype, causal=causal, seed=211, device=DEV)
+    mods = None
+    if case:
+        mods = {k: v for k, v in case.items() if k != "alibi"}
+        if case.get("alibi"):
+            mods["alibi_slopes"] = [2.0 ** -(i + 1) for i in range(4)]
+    binding.pa_set_option("prefill_chunk_tokens", chunk)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        parity.check_step(pa, oracle, w, f"prefill d=256 {dtype} {case}", mods=mods)
+        assert binding.pa_profile_read("paged_prefill_mfma")[0] == 1
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
+        binding.pa_set_option("prefill_chunk_tokens", 0)
 
 
 # ----------------------------------------------------------------------------- fp32 pools on the fp64 matrix cores
