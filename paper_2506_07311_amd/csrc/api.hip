@@ -711,6 +711,15 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
                     base + align256(prefill_list_slots() * prefill_list_slot_floats(d) * sizeof(float)));
                 a.skip_small = b.skip_small;
             }
+            const int32_t beside = list_cuts && may_have_small ? jagged_mfma_stream_wgs(b, device_cus()) : 0;
+            if (beside > 0) {                              // both in one launch, their pieces merged by one
+                AttnArgs c = a;
+                c.stream_split = 1;
+                c.num_wgs = beside < small_wgs ? beside : small_wgs;
+                place_stream(c, base + split_bytes, ((size_t)c.num_wgs + batch) * cache->num_kv_heads * 16);
+                st = launch_jagged_mfma(b, c, s);
+                return st != PA_OK ? st : launch_merge(c, s);
+            }
             st = launch_prefill_mfma(b, s);
             if (st != PA_OK) return st;
             if (list_cuts && !may_have_small) return launch_merge(a, s);

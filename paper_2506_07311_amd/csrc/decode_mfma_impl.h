@@ -32,6 +32,7 @@
 
 namespace pa {
 
+namespace decode {
 namespace {
 
 typedef mfma_f32x4 f32x4;
@@ -407,21 +408,22 @@ __device__ __forceinline__ void locate_tile(const int32_t* __restrict__ seq_lens
 // E: element traits (bf16 / fp16).  M: compile-time policy of the mask / score hooks.
 // FUSED (plain decode only): the step's append is folded in as in the one-launch kernel below -- the wave whose
 // segment holds a sequence's last tile stores the new token's rows of its KV head and reads them from k_new / v_new.
+// w of num_wgs workgroups, head_group: which NW KV heads, slice: which 16 heads of a group.
 template <int NW, bool UNIFORM, bool RAGGED, typename E, typename M, typename GE, bool FUSED = false>
-__global__ __launch_bounds__(NW * 64) void paged_decode_mfma_kernel(
-    CacheView cache, const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float* __restrict__ lse,
+__device__ __forceinline__ void stream_body(
+    const CacheView& cache, const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float* __restrict__ lse,
     const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_lens, int32_t batch,
     int32_t num_q_heads, int32_t max_blocks, float scale, float* __restrict__ part_o, float* __restrict__ part_lse,
     int32_t* __restrict__ seg_first, int32_t* __restrict__ seg_last, const int32_t* __restrict__ cu_q_lens,
-    int32_t causal, ModArgs mods, const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new)
+    int32_t causal, const ModArgs& mods, const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new,
+    const int32_t w, const int32_t num_wgs, const int32_t head_group, const int32_t slice)
 {
     constexpr int kD = GE::kD;
     constexpr int kTileKeys = GE::kTileKeys;
     const int32_t window = M::kWindow ? mods.window : 0;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // wave-uniform: a scalar
-    const int32_t w = blockIdx.x;
-    const int32_t kvh = blockIdx.y * NW + wave;
+    const int32_t kvh = head_group * NW + wave;
     const int32_t G = num_q_heads / cache.num_kv_heads;
     const int32_t r16 = lane & 15, quad = lane >> 4;
     const float sc = scale * kLog2e;
@@ -439,7 +441,7 @@ __global__ __launch_bounds__(NW * 64) void paged_decode_mfma_kernel(
             if (lane >= o) inc += t;
         }
         total = __shfl(inc, 63, 64);
-        const int32_t nwg = min((int32_t)gridDim.x, total);
+        const int32_t nwg = min(num_wgs, total);
         if (w >= nwg) return;
         g = (int32_t)(((int64_t)w * total) / nwg);
         g_end = (int32_t)(((int64_t)(w + 1) * total) / nwg);
@@ -448,7 +450,7 @@ __global__ __launch_bounds__(NW * 64) void paged_decode_mfma_kernel(
         before = __shfl(inc, s, 64) - __shfl(n, s, 64);
     } else {
         total = total_tiles<RAGGED, kTileKeys>(seq_lens, cu_q_lens, G, batch, lane, window);
-        const int32_t nwg = min((int32_t)gridDim.x, total);
+        const int32_t nwg = min(num_wgs, total);
         if (w >= nwg) return;
         g = (int32_t)(((int64_t)w * total) / nwg);
         g_end = (int32_t)(((int64_t)(w + 1) * total) / nwg);
@@ -484,8 +486,8 @@ __global__ __launch_bounds__(NW * 64) void paged_decode_mfma_kernel(
         const int32_t t_begin = g - before;
         const int32_t t_end = min(nt, g_end - before);
         // this lane's column: query qi of the sequence's q_len, head h (valid if r16 < rows)
-        // (group sizes above 16: blockIdx.z picks 16 of the group's heads; these workgroups stream the same K/V)
-        const int32_t h0 = RAGGED ? 0 : 16 * (int32_t)blockIdx.z;
+        // (group sizes above 16: slice picks 16 of the group's heads; these workgroups stream the same K/V)
+        const int32_t h0 = RAGGED ? 0 : 16 * slice;
         int32_t rows = min(G - h0, 16), qi = 0, q_row = s, q_len = 1;
         if (RAGGED) {
             const int32_t q_begin = cu_q_lens[s];
@@ -539,7 +541,7 @@ __global__ __launch_bounds__(NW * 64) void paged_decode_mfma_kernel(
                 a.vnew = reinterpret_cast<const char*>(v_new) + new_row;
                 a.new_pos = len - 1;
                 constexpr int kPieces = kD / 8;
-                if (blockIdx.z == 0 && lane < 2 * kPieces) {
+                if (slice == 0 && lane < 2 * kPieces) {
                     const bool is_v = lane >= kPieces;
                     const int piece = lane - (is_v ? kPieces : 0);
                     const int64_t page = a.table[a.new_pos >> a.log2_page];
@@ -623,7 +625,7 @@ __global__ __launch_bounds__(NW * 64) void paged_decode_mfma_kernel(
                 if (quad == 0) part_lse[p_idx] = lse_nat;
             }
         }
-        if (wave == 0 && lane == 0 && blockIdx.y == 0 && blockIdx.z == 0) {
+        if (wave == 0 && lane == 0 && head_group == 0 && slice == 0) {
             if (t_begin == 0) seg_first[s] = whole ? -1 : w;
             if (t_end == nt) seg_last[s] = w;
         }
@@ -631,6 +633,19 @@ __global__ __launch_bounds__(NW * 64) void paged_decode_mfma_kernel(
         before += nt;
         ++s;
     }
+}
+
+template <int NW, bool UNIFORM, bool RAGGED, typename E, typename M, typename GE, bool FUSED = false>
+__global__ __launch_bounds__(NW * 64) void paged_decode_mfma_kernel(
+    CacheView cache, const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float* __restrict__ lse,
+    const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_lens, int32_t batch,
+    int32_t num_q_heads, int32_t max_blocks, float scale, float* __restrict__ part_o, float* __restrict__ part_lse,
+    int32_t* __restrict__ seg_first, int32_t* __restrict__ seg_last, const int32_t* __restrict__ cu_q_lens,
+    int32_t causal, ModArgs mods, const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new)
+{
+    stream_body<NW, UNIFORM, RAGGED, E, M, GE, FUSED>(cache, q, out, lse, block_table, seq_lens, batch, num_q_heads, max_blocks,
+                                                      scale, part_o, part_lse, seg_first, seg_last, cu_q_lens, causal, mods,
+                                                      k_new, v_new, blockIdx.x, gridDim.x, blockIdx.y, blockIdx.z);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -985,11 +1000,13 @@ void launch_em(const AttnArgs& a, hipStream_t stream)
 }
 
 }  // namespace
+}  // namespace decode
 
 // Every kernel instantiation of one head_dim; defined in that head_dim's translation unit.
 template <int D>
 void launch_decode_short_dim(const AttnArgs& a, hipStream_t stream)
 {
+    using namespace decode;
     typedef Mods<true, true, false> WindowScore;
     typedef Geo<D> GE;
     constexpr int NW = D > 128 ? 4 : 8;                 // head_dim 256: two tiles take about 250 registers
@@ -1019,6 +1036,7 @@ void launch_decode_short_dim(const AttnArgs& a, hipStream_t stream)
 template <int D>
 void launch_decode_mfma_dim(const AttnArgs& a, hipStream_t stream)
 {
+    using namespace decode;
     typedef Mods<true, true, false> WindowScore;
     typedef Geo<D> GE;
     const bool docs = a.has_mods && a.mods.doc_ids;

@@ -76,7 +76,7 @@ double prefill_grid_workgroups(const AttnArgs& a, int32_t nsplit)
     return (double)plain_row_tiles(a) * nsplit * (a.num_q_heads >> lg) * a.batch;
 }
 
-pa_status launch_prefill_mfma(const AttnArgs& a, hipStream_t stream)
+PrefillPlan prefill::make_plan(const AttnArgs& a)
 {
     PrefillPlan plan;
     plan.list_items = a.list_items;
@@ -91,6 +91,12 @@ pa_status launch_prefill_mfma(const AttnArgs& a, hipStream_t stream)
     plan.part_o = a.part_o;
     plan.part_lse = a.part_lse;
     plan.mods = a.mods;
+    return plan;
+}
+
+pa_status launch_prefill_mfma(const AttnArgs& a, hipStream_t stream)
+{
+    const PrefillPlan plan = make_plan(a);
     if (plan.nsplit > 1 && (plan.chunk % kBN != 0 || plan.chunk % a.cache.page_size != 0)) return PA_ERR_INVALID_ARG;
     const int64_t tiles = (((int64_t)a.max_q_len << plan.log2_pack) + kBM - 1) / kBM;
     if (tiles <= 0) return PA_OK;

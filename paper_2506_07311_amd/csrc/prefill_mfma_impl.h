@@ -944,6 +944,56 @@ __device__ __forceinline__ bool prefill_body(
     return false;
 }
 
+// The work-list mode of prefill_tiles.h: items first, first + step, ... of the call's list.
+template <bool UNIFORM, typename E, typename M, int D>
+__device__ __forceinline__ void list_body(
+    char* buf0, char* buf1, int32_t* docs0, int32_t* docs1, const CacheView& cache, const uint16_t* __restrict__ q,
+    uint16_t* __restrict__ out, float* __restrict__ lse, const int32_t* __restrict__ cu_q_lens,
+    const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_lens, int32_t batch, int32_t num_q_heads,
+    int32_t max_blocks, float scale, int32_t causal, const PrefillPlan& plan, uint32_t first, uint32_t step)
+{
+    WorkItem own;
+    const int32_t heads = num_q_heads >> plan.log2_pack;
+    // A workgroup steps over the list by `step`.  Between two items nothing has to be waited for: a
+    // tile loop ends with the barrier behind its last read of LDS.  The thread index is made opaque for each item:
+    // what the body derives from it would otherwise be kept in registers across the loop, which spills.
+    const WorkList list = make_list(cu_q_lens, seq_lens, batch, plan.log2_pack,
+                                    plan.skip_small ? plan.group : kNoSmallGroup, heads,
+                                    plan.list_unit, (int)(threadIdx.x & 63));
+    int32_t precise_keys = 0;
+    if constexpr (!kTwoTermOnly<D>)
+        precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal, 0, (int)(threadIdx.x & 63));
+    for (uint32_t index = first;; index += step) {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        ListItem it;
+        if (!list_locate<false>(it, list, cu_q_lens, seq_lens, (int32_t)(index / (uint32_t)heads), tid & 63)) return;
+        own.s = it.s;
+        own.hg = (int32_t)(index % (uint32_t)heads);
+        own.tile = it.tile;
+        own.split = it.split;
+        own.chunks = it.chunks;
+        own.chunk = list.chunk;
+        own.slot = it.chunks > 1 ? list_slot(it, it.split, heads, own.hg) : -1;
+        own.q_begin = cu_q_lens[it.s];
+        own.q_end = cu_q_lens[it.s + 1];
+        own.len = seq_lens[it.s];
+        if constexpr (!kTwoTermOnly<D>)
+            prefill_body<false, UNIFORM, true, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
+                                                        num_q_heads, max_blocks, scale, causal, plan, precise_keys, own,
+                                                        tid);
+        const bool again =
+            prefill_body<true, UNIFORM, true, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
+                                                              num_q_heads, max_blocks, scale, causal, plan, precise_keys,
+                                                              own, tid);
+        if constexpr (kTwoTermOnly<D>)
+            if (again)
+                prefill_body<true, UNIFORM, true, true, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
+                                                                 num_q_heads, max_blocks, scale, causal, plan,
+                                                                 precise_keys, own, tid);
+    }
+}
+
 // Both instantiations live in one kernel as two separate code paths (each with its own tile loop); a
 // workgroup runs exactly one of them, decided by its context length.
 // LIST: the work-list mode of prefill_tiles.h.
@@ -964,51 +1014,15 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, 2) void paged_prefill_mfma_ker
     // The workgroup's own lengths are requested first (scalar loads), the scan of every sequence's lengths for the
     // two-term rule right behind them (vector loads): one round trip to memory instead of three in a row in front
     // of the query and block-table loads that depend on them.
-    WorkItem own;
-    const int32_t heads = num_q_heads >> plan.log2_pack;
     if constexpr (LIST) {
-        // A workgroup steps over the list by the size of the grid.  Between two items nothing has to be waited for: a
-        // tile loop ends with the barrier behind its last read of LDS.  The thread index is made opaque for each item:
-        // what the body derives from it would otherwise be kept in registers across the loop, which spills.
-        const WorkList list = make_list(cu_q_lens, seq_lens, batch, plan.log2_pack,
-                                        plan.skip_small ? plan.group : kNoSmallGroup, heads,
-                                        plan.list_unit, (int)(threadIdx.x & 63));
-        int32_t precise_keys = 0;
-        if constexpr (!kTwoTermOnly<D>)
-            precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal, 0, (int)(threadIdx.x & 63));
-        for (uint32_t index = blockIdx.x;; index += gridDim.x) {
-            int tid = threadIdx.x;
-            asm volatile("" : "+v"(tid));
-            ListItem it;
-            if (!list_locate<false>(it, list, cu_q_lens, seq_lens, (int32_t)(index / (uint32_t)heads), tid & 63)) return;
-            own.s = it.s;
-            own.hg = (int32_t)(index % (uint32_t)heads);
-            own.tile = it.tile;
-            own.split = it.split;
-            own.chunks = it.chunks;
-            own.chunk = list.chunk;
-            own.slot = it.chunks > 1 ? list_slot(it, it.split, heads, own.hg) : -1;
-            own.q_begin = cu_q_lens[it.s];
-            own.q_end = cu_q_lens[it.s + 1];
-            own.len = seq_lens[it.s];
-            if constexpr (!kTwoTermOnly<D>)
-                prefill_body<false, UNIFORM, LIST, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
-                                                            num_q_heads, max_blocks, scale, causal, plan, precise_keys, own,
-                                                            tid);
-            const bool again =
-                prefill_body<true, UNIFORM, LIST, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
-                                                                  num_q_heads, max_blocks, scale, causal, plan, precise_keys,
-                                                                  own, tid);
-            if constexpr (kTwoTermOnly<D>)
-                if (again)
-                    prefill_body<true, UNIFORM, LIST, true, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
-                                                                     num_q_heads, max_blocks, scale, causal, plan,
-                                                                     precise_keys, own, tid);
-        }
+        list_body<UNIFORM, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, cu_q_lens, block_table, seq_lens, batch,
+                                    num_q_heads, max_blocks, scale, causal, plan, blockIdx.x, gridDim.x);
     } else {
         // Workgroups are dispatched in blockIdx.x order: the row-tile index is the slowest-varying part and runs
         // backwards, so the whole grid is handed out heaviest (latest causal tiles) first; the context chunks of a
         // tile follow each other.
+        WorkItem own;
+        const int32_t heads = num_q_heads >> plan.log2_pack;
         const int32_t hb = heads * batch;
         const int32_t slow = (int32_t)(blockIdx.x / (uint32_t)hb);
         const int32_t rest = (int32_t)(blockIdx.x % (uint32_t)hb);

@@ -88,6 +88,8 @@ struct PrefillPlan {
     ModArgs mods;         // mask / score hooks (used by the instantiations that have them)
 };
 
+PrefillPlan make_plan(const AttnArgs& a);
+
 // ---------------------------------------------------------------------------------------------------
 // Work-list mode.  A jagged call (a few chunks of long prompts among decode rows) has neither of the shapes the plain
 // grid serves: most of its (tile, sequence) pairs are empty, and the host, which knows no lengths, cannot see that a

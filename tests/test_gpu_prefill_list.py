@@ -49,6 +49,36 @@ def test_jagged_calls_with_long_contexts(pa, oracle, case):
         binding.pa_profile_reset()
 
 
+@pytest.mark.parametrize("Hq,Hkv,P,dtype,causal,extra", [
+    (16, 4, 16, torch.bfloat16, True, []),                    # one group of four KV heads
+    (32, 8, 128, torch.float16, True, []),                    # two
+    (12, 12, 16, torch.bfloat16, False, []),                  # three; no grouping, no causal bound
+    (64, 4, 32, torch.bfloat16, True, []),                    # 16 heads a group: single queries alone are few
+    (8, 4, 16, torch.float16, True, [40] * 70 + [2000, 1])])  # more sequences than lanes, most of a tile or two
+def test_chunks_and_single_queries_in_one_launch(pa, oracle, Hq, Hkv, P, dtype, causal, extra):
+    """The list's workgroups and the stream's in one launch: sequences that either side takes, of one tile, of none, cut by
+    workgroup boundaries and by chunks; a second call on the same workspace gives the same bits."""
+    from paper_2506_07311_amd import binding
+    lens, q_lens = extra + LENS, [1] * len(extra) + Q_LENS
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=128, page_size=P,
+                        dtype=dtype, causal=causal, seed=215, device=DEV)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        parity.check_step(pa, oracle, w, f"{Hq} {Hkv} {dtype} {causal}")
+        counts = [binding.pa_profile_read(k)[0] for k in ("paged_jagged_mfma", "paged_decode_mfma", "paged_prefill_mfma",
+                                                          "paged_attention_merge_list")]
+        assert counts == [1, 0, 0, 1]
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
+    ws = torch.full((pa.paged_attention_workspace_bytes(w.batch, Hq, 128, w.total_q, w.max_seq_len),), 0xFF,
+                    dtype=torch.uint8, device=DEV)
+    outs = [pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, w.cu_q_lens, w.max_q_len, w.block_table, w.seq_lens,
+                                       w.max_seq_len, w.scale, causal, workspace=ws) for _ in range(2)]
+    assert torch.equal(outs[0], outs[1])
+
+
 def test_a_workspace_of_the_smaller_size_is_accepted_and_keeps_the_plain_grid(pa):
     """The list's partials are room on top of what a call requires: without it the plain grid runs, with the same results
     up to the merge's rounding (bf16 outputs one step apart at most)."""
