@@ -171,6 +171,35 @@ SplitPlan plan_prefill(int32_t batch, int32_t num_q_heads, int32_t log2_pack, in
     return p;
 }
 
+// The number of chunks for a call whose contexts are much longer than its query ranges, where every workgroup walks a whole
+// chunk: at most plan_prefill's (which workspaces are sized for), the one for which the fullest compute unit is done first.
+// A compute unit works through the tiles of two workgroups hardly faster than through those of one after the other
+// (64 keys at head_dim 128: 1.93 us two at a time, 1.05 alone; one at a time only at head_dim 256), so what counts is
+// how evenly the workgroups divide among the compute units; a chunk more costs its partials' way to memory and back (3.3 GB a
+// ms in the merge).  Append + prefill, with about 1024 workgroups as before / like this, 32 / 8 heads: 1024 tokens of a
+// 32768-token context 532 / 524 us, 512 of it 292 / 274, 128 of it 117 / 89, 500 of 12000 127 / 114, 1000 of 20000 with 32 / 32
+// heads 392 / 349, 500 of 20000 with 8 / 1 heads 82 / 67, at head_dim 64 135 / 121, at 256 418 / 373.
+SplitPlan even_prefill_split(const SplitPlan& most, int64_t wgs, int64_t rows, int32_t max_seq_len, int32_t page_size, int32_t d)
+{
+    const double one = d > 128 ? 2.4 : d > 64 ? 1.05 : 0.75, two = d > 128 ? 4.8 : d > 64 ? 1.93 : 1.4;
+    const int64_t unit = page_size > 64 ? page_size : 64;
+    SplitPlan best = most;
+    double best_us = 1e30;
+    for (int32_t n = 1; n <= most.nsplit; ++n) {
+        const int64_t chunk = (((int64_t)max_seq_len + n - 1) / n + unit - 1) / unit * unit;
+        if (((int64_t)max_seq_len + chunk - 1) / chunk != n) continue;
+        const int64_t per_cu = (wgs * n + device_cus() - 1) / device_cus();
+        const double us = (double)(chunk / 64) * ((per_cu / 2) * two + (per_cu % 2) * one) +
+                          (n > 1 ? 4.0 + (double)rows * n * d * 4.0 / 3.3e6 : 0.0);
+        if (us < best_us) {
+            best_us = us;
+            best.nsplit = n;
+            best.chunk = n > 1 ? (int32_t)chunk : max_seq_len;
+        }
+    }
+    return best;
+}
+
 // Largest number of chunks plan_prefill can choose for these sizes, whatever the packing and page size.
 int32_t prefill_nsplit_bound(int32_t batch, int32_t num_q_heads, int32_t total_q, int32_t max_seq_len)
 {
@@ -655,9 +684,6 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
                               !whole_prompts;
         const int32_t lg = prefill_mfma_log2_pack(num_q_heads, cache->num_kv_heads);
         SplitPlan pp = plan_prefill(batch, num_q_heads, lg, total_q, max_seq_len, cache->page_size);
-        size_t split_bytes =
-            pp.nsplit > 1 ? part_o_bytes(total_q, num_q_heads, d, pp.nsplit) + part_lse_bytes(total_q, num_q_heads, pp.nsplit)
-                          : 0;
         // (a workspace that holds what is required and not the list's partials as well keeps the plain grid)
         int64_t list_items = 0;
         if (list_pays(a, lg) &&
@@ -679,6 +705,15 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
             else if (wgs > 262144.0 || (pp.nsplit > 1 && wgs > 65536.0))
                 return launch_attention_generic(a, s);
         }
+        if (pp.nsplit > 1 && g_opt.prefill_chunk_tokens == 0 && m.window == 0 && max_seq_len / 2 >= max_q_len) {
+            const int64_t q_rows = (int64_t)total_q << lg, longest = (int64_t)max_q_len << lg;
+            const int64_t tiles = (int64_t)batch * max_q_len == total_q ? (longest + 127) / 128 * batch : q_rows / 128 + batch;
+            pp = even_prefill_split(pp, tiles * (num_q_heads >> lg), (int64_t)total_q * num_q_heads, max_seq_len,
+                                    cache->page_size, d);
+        }
+        size_t split_bytes =
+            pp.nsplit > 1 ? part_o_bytes(total_q, num_q_heads, d, pp.nsplit) + part_lse_bytes(total_q, num_q_heads, pp.nsplit)
+                          : 0;
         if (list_cuts) {
             pp.chunk = max_seq_len;
             pp.nsplit = 1;

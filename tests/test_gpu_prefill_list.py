@@ -79,6 +79,20 @@ def test_chunks_and_single_queries_in_one_launch(pa, oracle, Hq, Hkv, P, dtype, 
     assert torch.equal(outs[0], outs[1])
 
 
+@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,d,P,dtype,causal", [
+    ([4096], [128], 8, 8, 128, 16, torch.bfloat16, True),     # chunks of 1024 keys, the last one ends the diagonal
+    ([2049], [129], 4, 2, 64, 128, torch.float16, True),      # one key in the last page, one row in the last tile
+    ([3000, 3000], [64, 64], 16, 4, 128, 64, torch.bfloat16, False),
+    ([2500], [130], 4, 4, 96, 16, torch.bfloat16, True),
+    ([5000], [33], 2, 1, 256, 32, torch.float16, True),
+    ([3000, 2000], [70, 64], 4, 4, 256, 16, torch.bfloat16, True)])
+def test_chunks_of_prompts_on_long_contexts(pa, oracle, lens, q_lens, Hq, Hkv, d, P, dtype, causal):
+    """Contexts cut as evenly as the compute units take them, whatever the number of chunks that is."""
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=P,
+                        dtype=dtype, causal=causal, seed=216, device=DEV)
+    parity.check_step(pa, oracle, w, f"{lens} {q_lens} {Hq} {Hkv} {d}")
+
+
 def test_a_workspace_of_the_smaller_size_is_accepted_and_keeps_the_plain_grid(pa):
     """The list's partials are room on top of what a call requires: without it the plain grid runs, with the same results
     up to the merge's rounding (bf16 outputs one step apart at most)."""
