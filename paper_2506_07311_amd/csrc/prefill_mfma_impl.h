@@ -1,8 +1,12 @@
 // Paged prefill (ragged packed queries, optional causal bound) for bf16 / fp16 pools with head_dim D = 128 or 64 on
 // gfx950 (and D = 256, 80, 96, 112 for page sizes of 16 and more).  Internal header: the kernel templates; one translation unit
-// per head_dim instantiates them.  The text below describes D = 128.  D = 64 is the same kernel with half the steps: LDS rows keep their 256-byte stride and
-// swizzle, only the positions of the 8 existing 16-byte pieces are read (the fetch fills the other 8 positions
-// with repeats), the score product takes 4 steps instead of 8 and the value product covers 2 column blocks, not 4.  D = 256 has
+// per head_dim instantiates them.  The text below describes D = 128.  D = 64 is the same kernel with half the steps:
+// LDS rows are 128 bytes (a load instruction brings 8 of them), the score product takes 4 steps instead of 8 and the value
+// product covers 2 column blocks, not 4.  What a tile costs besides its matrix work then hides behind a third workgroup of a
+// compute unit, for which there are registers (148) and, with rows of their own size, LDS (32 KiB): 4 x 2048 with 32 / 8 heads
+// 119 us with half-empty 256-byte rows and two workgroups, 102 like this, 1 x 8192 341 / 303, prompts of 2059 and 3146 tokens
+// with a window 81 / 67, 1024 tokens of a 32768-token context 348 / 324; a fourth workgroup spills (158, 465, 102, -).
+// D = 256 has
 // 512-byte LDS rows (two swizzled 256-byte halves) and fills 128 KiB with its two tile buffers, so one workgroup per compute
 // unit; it runs on eight waves of 16 rows (RowGeo), two a SIMD, because 32 rows of O and Q leave room for one wave a SIMD
 // whose operand reads nothing hides: 1 x 8192 with 32 / 8 heads 1417 us with four waves of 32 rows, 1187 with eight of 16
@@ -57,7 +61,7 @@ using namespace prefill;
 // permutes the 16 pieces of a 256-byte half row among themselves (every row starts at bank 0 either way).
 template <int D>
 struct RowGeo {
-    static constexpr int kRowB = D > 128 ? 512 : 256;
+    static constexpr int kRowB = D > 128 ? 512 : D > 64 ? 256 : 128;
     static constexpr int kTileB = kBN * kRowB;        // K part of a tile buffer; the V part follows
     static constexpr int kBufB = 2 * kTileB;
     // Rows of a wave, and what follows from them: the lane groups that share a row (each takes four of every kStep
@@ -78,10 +82,12 @@ template <int D>
 constexpr bool kTwoTermOnly = D % 64 != 0;
 // Swizzle of LDS row r.  16 rows a wave: a transpose load reads 32 bytes of 16 rows, 8 of them at a time, and an operand
 // read one piece of 16 rows: both are free of conflicts if 8 consecutive rows differ in the upper three bits.
+// head_dim 64: two rows share 256 bytes, so it is pairs of rows that differ; the two pairs of a transpose load's 4 rows in the
+// upper bit, as it reads 4 of a row's 8 pieces.
 template <int D>
 __device__ __forceinline__ int row_swz(int r)
 {
-    return RowGeo<D>::kRows == 32 ? swz(r) : ((r & 7) << 1) | ((r >> 3) & 1);
+    return D == 64 ? ((r & 2) << 1) | ((r >> 2) & 3) : RowGeo<D>::kRows == 32 ? swz(r) : ((r & 7) << 1) | ((r >> 3) & 1);
 }
 // byte offset inside its row of logical 16-byte piece L of LDS row r
 template <int D>
@@ -377,7 +383,7 @@ template <int T>
 __device__ __forceinline__ void load_v_frags(uint4 (&va)[T], uint4 (&vb)[T], const char* vbuf, int half,
                                              const uint32_t (&vx)[2 * T])
 {
-    constexpr int RB = 256;
+    constexpr int RB = T > 2 ? 256 : 128;
     const char* v0 = vbuf + (32 * half) * RB;
 #pragma unroll
     for (int t = 0; t < T; ++t) va[t] = lds_frag_tr(v0 + vx[2 * t], v0 + vx[2 * t + 1]);
@@ -471,7 +477,7 @@ template <typename E, int KS>
 __device__ __forceinline__ void half_scores(f32x16& s, const char* kbuf, int half, const uint32_t (&kx)[KS],
                                             const uint4 (&qf)[KS])
 {
-    constexpr int RB = 256;
+    constexpr int RB = KS > 4 ? 256 : 128;
     s = (f32x16)(0.f);   // folded into the first matrix instruction's accumulator operand
     const char* kh = kbuf + (32 * half) * RB;
     uint4 ka[4];
@@ -757,19 +763,24 @@ __device__ __forceinline__ bool prefill_body(
         }
     }
     // fetch role of this lane.  256-byte rows: position lane%16 of rows 16*i + frow holds logical piece
-    // (lane%16) ^ swz(frow) (a row of head_dim 64 has 8 pieces: the other 8 positions receive repeats that nobody
-    // reads; head_dims 80, 96 and 112 repeat their first pieces likewise, and the columns of O beyond D that are computed
-    // from repeats are not stored).  512-byte rows: position lane%32 of rows 16*i + frow.
-    const int frow = D > 128 ? 2 * wave + (lane >> 5) : 4 * wave + (lane >> 4);
+    // (lane%16) ^ swz(frow) (head_dims 80, 96 and 112 repeat their first pieces in the positions that they do not have, and the
+    // columns of O beyond D that are computed from repeats are not stored).  512-byte rows: position lane%32 of rows
+    // 16*i + frow.  128-byte rows: position lane%8 of rows 32*i + frow, one page each.
+    const int frow = D > 128 ? 2 * wave + (lane >> 5) : D > 64 ? 4 * wave + (lane >> 4) : 8 * wave + (lane >> 3);
     const uint32_t head_off = (uint32_t)(kvh * cache.head_stride * 2);
-    const int piece = (D > 128 ? lane & 16 : 0) | ((lane & 15) ^ row_swz<D>(frow));
+    const int piece = (D > 128 ? lane & 16 : 0) | ((lane & (D > 64 ? 15 : 7)) ^ row_swz<D>(frow));
     const uint32_t lane_off = head_off + 16 * (D <= 128 && piece >= D / 8 ? piece - D / 8 : piece);
-    const int32_t wrow = __builtin_amdgcn_readfirstlane(D > 128 ? 2 * wave * 512 : 4 * wave * 256);
+    const int32_t wrow = __builtin_amdgcn_readfirstlane(1024 * wave);    // (a load instruction fills 1 KiB)
+    const int32_t second16 = D == 64 ? __builtin_amdgcn_readfirstlane(wave >> 1) : 0;
     const int32_t last_key = len - 1;
     const uint32_t lds0 = lds_address(buf0 + wrow), lds1 = lds_address(buf1 + wrow);
     auto fetch = [&](uint32_t lds, const PageIds& pg, int32_t t0) {
         if constexpr (D > 128) fetch_tile512<UNIFORM>(lds, pg, cache, t0, frow, last_key, lane_off);
-        else fetch_tile<UNIFORM>(lds, pg, cache, t0, frow, last_key, lane_off);
+        else if constexpr (D == 64) {
+            constexpr int TB = Geo::kTileB;
+            fetch_rows<UNIFORM, 0, TB>(lds, cache, UNIFORM && second16 ? pg.p1 : pg.p0, t0 + frow, last_key, lane_off);
+            fetch_rows<UNIFORM, 32 * RB, TB>(lds, cache, UNIFORM && second16 ? pg.p3 : pg.p2, t0 + frow + 32, last_key, lane_off);
+        } else fetch_tile<UNIFORM>(lds, pg, cache, t0, frow, last_key, lane_off);
     };
 
     // Document masks: wave 0 brings the 64 ids of the next tile (one per lane) and stores them next to the tile
@@ -998,7 +1009,7 @@ __device__ __forceinline__ void list_body(
 // workgroup runs exactly one of them, decided by its context length.
 // LIST: the work-list mode of prefill_tiles.h.
 template <bool UNIFORM, typename E, typename M, int D, bool LIST = false>
-__global__ __launch_bounds__(RowGeo<D>::kThreads, 2) void paged_prefill_mfma_kernel(
+__global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_prefill_mfma_kernel(
     CacheView cache, const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float* __restrict__ lse,
     const int32_t* __restrict__ cu_q_lens, const int32_t* __restrict__ block_table,
     const int32_t* __restrict__ seq_lens, int32_t batch, int32_t num_tiles, int32_t num_q_heads, int32_t max_blocks,

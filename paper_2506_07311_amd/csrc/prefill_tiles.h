@@ -261,8 +261,8 @@ __device__ __forceinline__ void load_ids(PageIds& p, const CacheView& cache, con
     }
 }
 
-// K row and V row of `key` (clamped to a live slot) in page `page` -> LDS rows at lds + IMM (K) and kTileBytes further (V).
-template <bool UNIFORM, int IMM>
+// K row and V row of `key` (clamped to a live slot) in page `page` -> LDS rows at lds + IMM (K) and TB further (V).
+template <bool UNIFORM, int IMM, int TB = kTileBytes>
 __device__ __forceinline__ void fetch_rows(uint32_t lds, const CacheView& cache, int32_t page, int32_t key,
                                            int32_t last_key, uint32_t lane_off)
 {
@@ -276,12 +276,12 @@ __device__ __forceinline__ void fetch_rows(uint32_t lds, const CacheView& cache,
         const char* kp = reinterpret_cast<const char*>(cache.k) + page_off;
         const char* vp = reinterpret_cast<const char*>(cache.v) + page_off;
         load_to_lds16(lds, IMM, kp, off32);
-        load_to_lds16(lds, IMM + kTileBytes, vp, off32);
+        load_to_lds16(lds, IMM + TB, vp, off32);
         return;
     }
     const int64_t off = ((int64_t)page * cache.page_stride + (int64_t)slot * cache.token_stride) * 2 + lane_off;
     load_to_lds16(lds, IMM, reinterpret_cast<const char*>(cache.k) + off);
-    load_to_lds16(lds, IMM + kTileBytes, reinterpret_cast<const char*>(cache.v) + off);
+    load_to_lds16(lds, IMM + TB, reinterpret_cast<const char*>(cache.v) + off);
 }
 
 // lds = LDS address of buffer + 4*w*kRow (this wave's first row); row = 4*w + lane/16 (this lane's row within a
