@@ -473,6 +473,20 @@ bool list_pays(const AttnArgs& a, int32_t log2_pack)
     return ((((int64_t)a.total_q << log2_pack) / 128) + live) * (a.num_q_heads >> log2_pack) < kListMaxWGs;
 }
 
+// Jagged calls whose contexts are too short for the list to cut take it uncut where one launch then holds it and the
+// few-query stream: the plain grid is row tiles of every sequence, most of them of decode rows and empty, and the stream waits
+// behind it (us plain / like this, 32 / 8 heads: 33 sequences of up to 2232 tokens, four with 200 queries 85 / 59; 56 of up to 3500,
+// four with 512 117 / 63; 27 of up to 4090, four with 512, 128 / 116; 39 of up to 1500, five with 200 74 / 54; 17 of which one
+// brings 512 32 / 24).
+bool jagged_whole_pays(const AttnArgs& a, int32_t log2_pack)
+{
+    const int64_t live = (a.total_q + a.max_q_len - 1) / (a.max_q_len > 0 ? a.max_q_len : 1);
+    return jagged_mfma_stream_wgs(a, device_cus()) > 0 && a.batch > 1 && a.batch <= kListScanBatch &&
+           (int64_t)a.batch * a.max_q_len != a.total_q && a.max_seq_len / 2 >= a.max_q_len &&
+           a.max_seq_len < prefill_list_min_context() && g_opt.prefill_chunk_tokens == 0 &&
+           ((((int64_t)a.total_q << log2_pack) / 128) + live) * (a.num_q_heads >> log2_pack) < kListMaxWGs;
+}
+
 // What a call's workspace has to hold.  (paged_attention_workspace_bytes adds the room of the prefill kernel's
 // work-list mode, an optimisation that a smaller workspace does without.)
 size_t required_workspace_bytes(int32_t batch, int32_t num_q_heads, int32_t head_dim, int32_t total_q,
@@ -705,19 +719,25 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
             else if (wgs > 262144.0 || (pp.nsplit > 1 && wgs > 65536.0))
                 return launch_attention_generic(a, s);
         }
-        if (pp.nsplit > 1 && g_opt.prefill_chunk_tokens == 0 && m.window == 0 && max_seq_len / 2 >= max_q_len) {
-            const int64_t q_rows = (int64_t)total_q << lg, longest = (int64_t)max_q_len << lg;
-            const int64_t tiles = (int64_t)batch * max_q_len == total_q ? (longest + 127) / 128 * batch : q_rows / 128 + batch;
+        // (a ragged call's row tiles are few and unequal, its bound on them loose: 33 sequences of up to 2232 tokens, four with 200
+        // queries, 85 us with the two chunks of plan_prefill, 89 with the one that this would choose)
+        if (pp.nsplit > 1 && g_opt.prefill_chunk_tokens == 0 && m.window == 0 && max_seq_len / 2 >= max_q_len &&
+            (int64_t)batch * max_q_len == total_q) {
+            const int64_t tiles = (((int64_t)max_q_len << lg) + 127) / 128 * batch;
             pp = even_prefill_split(pp, tiles * (num_q_heads >> lg), (int64_t)total_q * num_q_heads, max_seq_len,
                                     cache->page_size, d);
         }
+        // Jagged calls on shorter contexts than the list cuts: the list without cuts, for the sake of the launch that it shares
+        // with the few-query stream.
+        const bool list_whole = list_items == 0 && may_have_small && jagged_whole_pays(a, lg);
+        if (list_whole) list_items = prefill_list_items(a);
         size_t split_bytes =
             pp.nsplit > 1 ? part_o_bytes(total_q, num_q_heads, d, pp.nsplit) + part_lse_bytes(total_q, num_q_heads, pp.nsplit)
                           : 0;
-        if (list_cuts) {
+        if (list_cuts || list_whole) {
             pp.chunk = max_seq_len;
             pp.nsplit = 1;
-            split_bytes = list_bytes(d);
+            split_bytes = list_cuts ? list_bytes(d) : 0;
         }
         int32_t small_wgs = 0;
         if (may_have_small) {
@@ -746,7 +766,7 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
                     base + align256(prefill_list_slots() * prefill_list_slot_floats(d) * sizeof(float)));
                 a.skip_small = b.skip_small;
             }
-            const int32_t beside = list_cuts && may_have_small ? jagged_mfma_stream_wgs(b, device_cus()) : 0;
+            const int32_t beside = (list_cuts || list_whole) && may_have_small ? jagged_mfma_stream_wgs(b, device_cus()) : 0;
             if (beside > 0) {                              // both in one launch, their pieces merged by one
                 AttnArgs c = a;
                 c.stream_split = 1;

@@ -79,6 +79,29 @@ def test_chunks_and_single_queries_in_one_launch(pa, oracle, Hq, Hkv, P, dtype, 
     assert torch.equal(outs[0], outs[1])
 
 
+@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,P,dtype,causal", [
+    ([2100, 0, 700, 1, 1500, 64, 65], [130, 0, 1, 1, 129, 2, 17], 16, 4, 16, torch.bfloat16, True),
+    ([4095, 300, 33], [33, 1, 1], 8, 8, 64, torch.float16, False),            # one key short of the list that is cut
+    ([40] * 70 + [600, 500], [1] * 70 + [250, 3], 4, 4, 32, torch.float16, True),
+    ([500, 700, 900], [100, 101, 102], 8, 4, 16, torch.bfloat16, True)])      # nothing for the stream, and may be
+def test_uncut_chunks_and_single_queries_in_one_launch(pa, oracle, lens, q_lens, Hq, Hkv, P, dtype, causal):
+    """Contexts below the length that the list cuts: whole row tiles beside the stream, no partials of the list's."""
+    from paper_2506_07311_amd import binding
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=128, page_size=P,
+                        dtype=dtype, causal=causal, seed=217, device=DEV)
+    may_be_small = (w.total_q - (w.batch - 1) * w.max_q_len) * (Hq // Hkv) <= 16
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        parity.check_step(pa, oracle, w, f"{lens} {q_lens}")
+        counts = [binding.pa_profile_read(k)[0] for k in ("paged_jagged_mfma", "paged_decode_mfma", "paged_prefill_mfma",
+                                                          "paged_attention_merge_list")]
+        assert counts == ([1, 0, 0, 0] if may_be_small else [0, 0, 1, 0])
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
+
+
 @pytest.mark.parametrize("lens,q_lens,Hq,Hkv,d,P,dtype,causal", [
     ([4096], [128], 8, 8, 128, 16, torch.bfloat16, True),     # chunks of 1024 keys, the last one ends the diagonal
     ([2049], [129], 4, 2, 64, 128, torch.float16, True),      # one key in the last page, one row in the last tile
