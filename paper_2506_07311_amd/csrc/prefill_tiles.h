@@ -100,7 +100,8 @@ PrefillPlan make_plan(const AttnArgs& a);
 // (two per workgroup slot; none shorter than kListMinTiles, where a workgroup's start and its partial begin to show).
 // Item order: sequence, chunk, row tile from last to first, head group -- the workgroups that run together on a
 // chiplet walk the same keys, so a chunk's K/V comes from HBM once per head.  Same call: prefill kernel
-// 1510 -> 460 us (410 GFLOP: 0.9 PFLOP/s) + 10 us of merging; the whole call 1690 -> 655 us.
+// 1510 -> 460 us (410 GFLOP: 0.9 PFLOP/s) + 10 us of merging; the whole call 1690 -> 655 us (600 with the few-query sequences
+// beside it in the same launch).
 // ---------------------------------------------------------------------------------------------------
 constexpr int32_t kListTarget = 1024;
 constexpr int32_t kListMinTiles = 32;
