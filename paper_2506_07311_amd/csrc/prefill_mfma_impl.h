@@ -147,6 +147,19 @@ __device__ __forceinline__ uint4 lds_frag_tr(const char* lo, const char* hi)
 // sees fewer than kPreciseShare * H keys take the two-term path.  Wave-uniform result.
 constexpr float kPreciseShare = 0.9f;
 
+// Sum over the wave with data-parallel-primitive moves (shifts by 1, 2, 4, 8 inside each row of 16 lanes, then lane 15 of a
+// row into the next row, lane 31 into the upper half) instead of six round trips through LDS in front of a workgroup's
+// first tile (append + prefill of one prompt, 32 / 8 heads: 128 tokens 11.9 -> 11.6 us, 200 13.2 -> 13.0, 500 and more the same).
+__device__ __forceinline__ float wave_sum(float v)
+{
+#define PA_SUM_STEP(CTRL, ROWS) \
+    v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, ROWS, 0xF, true));
+    PA_SUM_STEP(0x111, 0xF) PA_SUM_STEP(0x112, 0xF) PA_SUM_STEP(0x114, 0xF) PA_SUM_STEP(0x118, 0xF)
+    PA_SUM_STEP(0x142, 0xA) PA_SUM_STEP(0x143, 0xC)
+#undef PA_SUM_STEP
+    return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), 63));
+}
+
 __device__ __forceinline__ int32_t precise_key_bound(const int32_t* __restrict__ cu_q_lens,
                                                      const int32_t* __restrict__ seq_lens, int32_t batch,
                                                      int32_t causal, int32_t window, int lane)
@@ -170,11 +183,8 @@ __device__ __forceinline__ int32_t precise_key_bound(const int32_t* __restrict__
         const int32_t above = hi - max(lo, cap + 1) + 1;              // rows that see the whole window
         if (above > 0) inv += (float)above / (float)cap;
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        rows += __shfl_xor(rows, o, 64);
-        inv += __shfl_xor(inv, o, 64);
-    }
+    rows = wave_sum(rows);
+    inv = wave_sum(inv);
     const float h = inv > 0.f ? rows / inv : 0.f;
     return max(kPreciseKeys, (int32_t)fminf(kPreciseShare * h, 1.0e9f));
 }
