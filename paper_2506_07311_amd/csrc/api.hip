@@ -136,7 +136,6 @@ size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 // mixed batch that is mostly decode rows) is cut along the context into chunks of at least kPrefillMinChunk
 // tokens until about kPrefillTargetWGs work items exist.  A pure function of its arguments: the workspace size is
 // computed from the same rule with the largest packing.
-constexpr int32_t kPrefillMinChunk = 1024;
 constexpr int64_t kPrefillTargetWGs = 1024;
 constexpr int64_t kPrefillFullWGs = 512;
 
@@ -176,18 +175,29 @@ SplitPlan plan_prefill(int32_t batch, int32_t num_q_heads, int32_t log2_pack, in
 // A compute unit works through the tiles of two workgroups hardly faster than through those of one after the other
 // (64 keys at head_dim 128: 1.93 us two at a time, 1.05 alone; one at a time only at head_dim 256), so what counts is
 // how evenly the workgroups divide among the compute units; a chunk more costs its partials' way to memory and back (3.3 GB a
-// ms in the merge).  Append + prefill, with about 1024 workgroups as before / like this, 32 / 8 heads: 1024 tokens of a
-// 32768-token context 532 / 524 us, 512 of it 292 / 274, 128 of it 117 / 89, 500 of 12000 127 / 114, 1000 of 20000 with 32 / 32
-// heads 392 / 349, 500 of 20000 with 8 / 1 heads 82 / 67, at head_dim 64 135 / 121, at 256 418 / 373.
-SplitPlan even_prefill_split(const SplitPlan& most, int64_t wgs, int64_t rows, int32_t max_seq_len, int32_t page_size, int32_t d)
+// ms in the merge).  us a call with about 1024 workgroups / like this, 32 / 8 heads: 1024 tokens of a 32768-token context
+// 514 / 511, 512 of it 273 / 265, 128 of it 109 / 87, 500 of 12000 125 / 109, two sequences with 128 tokens of 32768 each
+// 184 / 154, four 374 / 290, 500 of 20000 at head_dim 256 488 / 363.
+// max_seq_len is a bound and query counts say nothing of contexts: each sequence's own length is cut on the device
+// (sequence_chunk), which divides as evenly for any length (1024 workgroups and chunks of the bound / this many chunks of the
+// bound / like this: 128 tokens of 8192 in a call for up to 131072 97 / 200 / 40, 1000 of 20000 for up to 32768 403 / 413 / 320).
+// A batch need not be as even as its query counts: one long context among short ones has its own workgroups alone, so they
+// have to fill the machine by themselves, or there are nearly as many chunks as there can be (all chunks of the bound / what is
+// even for equal contexts / like this: 64 tokens of 32768 and of 1500 seven times 145 / 204 / 114, 128 of 12284 and of
+// 1500 with 32 / 32 heads 58 / 67 / 56; equal contexts pay at most for chunks that only they could spare: 200 tokens of 18000
+// three times 239 / 204 / 220, 256 of 20496 four times with 8 / 1 heads 120 / 103 / 113, 128 of 32768 twice 193 / 157 / 157).
+SplitPlan even_prefill_split(const SplitPlan& most, int32_t batch, int64_t wgs, int64_t rows, int32_t max_seq_len,
+                             int32_t page_size, int32_t d)
 {
     const double one = d > 128 ? 2.4 : d > 64 ? 1.05 : 0.75, two = d > 128 ? 4.8 : d > 64 ? 1.93 : 1.4;
     const int64_t unit = page_size > 64 ? page_size : 64;
     SplitPlan best = most;
+    best.unit = (int32_t)unit;
     double best_us = 1e30;
     for (int32_t n = 1; n <= most.nsplit; ++n) {
         const int64_t chunk = (((int64_t)max_seq_len + n - 1) / n + unit - 1) / unit * unit;
         if (((int64_t)max_seq_len + chunk - 1) / chunk != n) continue;
+        if (batch > 1 && wgs / batch * n < device_cus() && 4 * n < 3 * most.nsplit) continue;
         const int64_t per_cu = (wgs * n + device_cus() - 1) / device_cus();
         const double us = (double)(chunk / 64) * ((per_cu / 2) * two + (per_cu % 2) * one) +
                           (n > 1 ? 4.0 + (double)rows * n * d * 4.0 / 3.3e6 : 0.0);
@@ -724,7 +734,7 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
         if (pp.nsplit > 1 && g_opt.prefill_chunk_tokens == 0 && m.window == 0 && max_seq_len / 2 >= max_q_len &&
             (int64_t)batch * max_q_len == total_q) {
             const int64_t tiles = (((int64_t)max_q_len << lg) + 127) / 128 * batch;
-            pp = even_prefill_split(pp, tiles * (num_q_heads >> lg), (int64_t)total_q * num_q_heads, max_seq_len,
+            pp = even_prefill_split(pp, batch, tiles * (num_q_heads >> lg), (int64_t)total_q * num_q_heads, max_seq_len,
                                     cache->page_size, d);
         }
         // Jagged calls on shorter contexts than the list cuts: the list without cuts, for the sake of the launch that it shares

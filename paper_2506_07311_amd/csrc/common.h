@@ -48,6 +48,7 @@ inline CacheView make_view(const pa_kv_cache_desc* c)
 struct SplitPlan {
     int32_t chunk;   // tokens per chunk; a multiple of max(P, 32)
     int32_t nsplit;  // grid extent = ceil(max_seq_len / chunk)
+    int32_t unit = 0;  // > 0 (prefill kernel): not by `chunk`, see sequence_chunk
 };
 
 constexpr int32_t kMinChunk = 256;     // smallest chunk the planner will pick
@@ -364,6 +365,17 @@ __device__ __forceinline__ F user_score(const pa_mod_ctx& c, int32_t j, F x)
 // prefix-sum vector of Sec. III-B (null for decode, where row == sequence).  Query i of a sequence with
 // q_len queries sits at position len - q_len + i; keys 0 .. n_keys-1 are allowed: n_keys = len under the
 // length mask alone, min(len, position + 1) with the causal bound.
+// Tokens per chunk of a sequence of `len` tokens.  With a unit the sequence's own length is cut into nsplit even chunks
+// (multiples of the unit, none shorter than kPrefillMinChunk): the longest context that the host knows of is a bound, for a
+// captured call what the cache holds at most, and chunks of the bound would leave a short sequence in one piece.
+constexpr int32_t kPrefillMinChunk = 1024;
+__device__ __forceinline__ int32_t sequence_chunk(int32_t len, int32_t chunk, int32_t nsplit, int32_t unit)
+{
+    if (unit == 0) return chunk;
+    const int32_t even = len > 0 ? (len - 1) / nsplit + 1 : 0;
+    return (max(even, kPrefillMinChunk) + unit - 1) & -unit;   // (a power of two)
+}
+
 struct RowInfo {
     int32_t seq;
     int32_t n_keys;

@@ -49,14 +49,15 @@ template <int OUT>
 __global__ __launch_bounds__(256) void paged_attention_merge_kernel(
     const float* __restrict__ part_o, const float* __restrict__ part_lse, void* __restrict__ out,
     float* __restrict__ lse, const int32_t* __restrict__ cu_q_lens, const int32_t* __restrict__ seq_lens,
-    int32_t batch, int32_t num_q_heads, int32_t d, int32_t causal, int32_t chunk, int32_t nsplit, int64_t pairs)
+    int32_t batch, int32_t num_q_heads, int32_t d, int32_t causal, int32_t chunk, int32_t nsplit, int32_t unit, int64_t pairs)
 {
     const int64_t o_idx = (int64_t)blockIdx.x * kMergePairs + (threadIdx.x >> 5);
     if (o_idx >= pairs) return;
     const int lane = threadIdx.x & 31;
     const int32_t row = (int32_t)(o_idx / num_q_heads);
     const RowInfo ri = locate_row(cu_q_lens, seq_lens, batch, row, causal);
-    const int32_t n = (ri.n_keys + chunk - 1) / chunk;   // chunks that hold keys
+    const int32_t own = sequence_chunk(ri.len, chunk, nsplit, unit);
+    const int32_t n = (ri.n_keys + own - 1) / own;       // chunks that hold keys
     const float* pl = part_lse + o_idx * nsplit;
     const float* po = part_o + o_idx * nsplit * d;
 
@@ -276,7 +277,7 @@ pa_status launch_merge(const AttnArgs& a, hipStream_t stream)
     if (a.cache.head_dim % 4 != 0) return PA_ERR_UNSUPPORTED;   // (16-byte rows: every supported element type has it)
     hipLaunchKernelGGL(kern, dim3((uint32_t)((blocks + kMergePairs - 1) / kMergePairs)), dim3(256), 0, stream, a.part_o,
                        a.part_lse, a.out, a.lse, a.cu_q_lens, a.seq_lens, a.batch, a.num_q_heads, a.cache.head_dim,
-                       a.causal, a.plan.chunk, a.plan.nsplit, blocks);
+                       a.causal, a.plan.chunk, a.plan.nsplit, a.plan.unit, blocks);
     return launch_status();
 }
 

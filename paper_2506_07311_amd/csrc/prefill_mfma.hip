@@ -86,6 +86,7 @@ PrefillPlan prefill::make_plan(const AttnArgs& a)
     plan.log2_pack = prefill_mfma_log2_pack(a.num_q_heads, a.cache.num_kv_heads);
     plan.group = a.num_q_heads / a.cache.num_kv_heads;
     plan.chunk = a.plan.chunk;
+    plan.chunk_unit = a.plan.unit;
     plan.nsplit = a.plan.nsplit;
     plan.skip_small = a.skip_small;
     plan.part_o = a.part_o;

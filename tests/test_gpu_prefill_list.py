@@ -110,10 +110,68 @@ def test_uncut_chunks_and_single_queries_in_one_launch(pa, oracle, lens, q_lens,
     ([5000], [33], 2, 1, 256, 32, torch.float16, True),
     ([3000, 2000], [70, 64], 4, 4, 256, 16, torch.bfloat16, True)])
 def test_chunks_of_prompts_on_long_contexts(pa, oracle, lens, q_lens, Hq, Hkv, d, P, dtype, causal):
-    """Contexts cut as evenly as the compute units take them, whatever the number of chunks that is."""
+    """Contexts cut into as many chunks as the workspace holds partials for, at each kernel's head_dims."""
     w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=P,
                         dtype=dtype, causal=causal, seed=216, device=DEV)
     parity.check_step(pa, oracle, w, f"{lens} {q_lens} {Hq} {Hkv} {d}")
+
+
+def _reference(w):
+    """Attention of every row over the gathered pages in fp32, one KV head at a time."""
+    out = torch.zeros(w.q.shape, device=DEV)
+    G = w.num_q_heads // w.num_kv_heads
+    row = 0
+    for s, (n, nq) in enumerate(zip(w.seq_lens_host, w.q_lens_host)):
+        pages = w.block_table[s, :-(-n // w.page_size)].long()
+        hidden = torch.arange(n, device=DEV)[None, :] > torch.arange(n - nq, n, device=DEV)[:, None]
+        for g in range(w.num_kv_heads):
+            k, v = (c[pages, :, g].reshape(-1, w.head_dim)[:n].float() for c in (w.k_cache, w.v_cache))
+            for h in range(g * G, g * G + G):
+                x = w.q[row:row + nq, h].float() @ k.t() * w.scale
+                if w.causal:
+                    x.masked_fill_(hidden, float("-inf"))
+                out[row:row + nq, h] = torch.softmax(x, dim=1) @ v
+        row += nq
+    return out
+
+
+@pytest.mark.parametrize("lens,q,bound,Hq,Hkv,d,P,dtype,causal,chunks", [
+    ([32768], 1024, 32768, 32, 8, 128, 16, torch.bfloat16, True, [2]),               # of four possible ones
+    ([32768, 32768], 128, 32768, 32, 8, 128, 16, torch.bfloat16, True, [8, 8]),      # of 13
+    ([2048], 1024, 2048, 32, 8, 128, 16, torch.bfloat16, True, [1]),                 # of two
+    ([8192], 128, 131072, 32, 8, 128, 16, torch.bfloat16, True, [8]),                # a bound far from the length
+    ([700], 128, 131072, 32, 8, 128, 64, torch.float16, True, [1]),
+    ([32768, 16000, 900], 128, 32768, 32, 8, 128, 16, torch.bfloat16, False, [8, 8, 1]),
+    ([2000] * 3 + [32768] + [2000] * 4, 64, 32768, 32, 8, 128, 32, torch.float16, True, [2] * 3 + [6] + [2] * 4),
+    ([9000, 1100, 64], 64, 10000, 8, 8, 64, 128, torch.bfloat16, True, [9, 2, 1]),
+    ([5000, 4999], 33, 9000, 8, 2, 256, 32, torch.bfloat16, True, [5, 5])])
+def test_chunks_follow_the_compute_units_and_each_context(pa, lens, q, bound, Hq, Hkv, d, P, dtype, causal, chunks):
+    """The number of chunks that the rule picks on 256 compute units, and that a sequence is cut by its own length whatever the
+    bound and the other sequences: counted by the partials that the call leaves in its workspace."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the expected chunks are those of 256 compute units")
+    w = W.make_workload("t", seq_lens=lens, q_lens=[q] * len(lens), num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=P,
+                        dtype=dtype, causal=causal, seed=218, device=DEV)
+    pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
+    table = torch.nn.functional.pad(w.block_table, (0, max(0, -(-bound // P) - w.block_table.shape[1])), value=-1)
+    nbytes = pa.paged_attention_workspace_bytes(w.batch, Hq, d, w.total_q, bound)
+    ws = torch.full((-(-nbytes // 4),), -1, dtype=torch.int32, device=DEV)       # (a NaN as a float)
+    out = pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, w.cu_q_lens, q, table, w.seq_lens, bound, w.scale, causal,
+                                     workspace=ws)
+    parity.assert_close(parity.to_f64(out), parity.to_f64(_reference(w)), dtype, f"{lens} {q}")
+    written = int((ws != -1).sum())
+    if len(lens) == 1 and chunks == [1] and bound == lens[0]:
+        assert written == 0                                   # uncut: no partials at all
+    else:
+        assert written == q * Hq * (d + 1) * sum(chunks)
+
+
+def test_chunks_of_each_context_with_score_hooks(pa, oracle):
+    from tests.test_gpu_parity import build_mods
+    lens, q_lens = [5000, 2100, 70], [40, 40, 40]
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=4, num_kv_heads=2, head_dim=128, page_size=16,
+                        dtype=torch.bfloat16, causal=True, seed=219, device=DEV)
+    parity.check_step(pa, oracle, w, "hooks", mods=build_mods(dict(alibi=True, softcap=30.0), 4, lens))
 
 
 def test_a_workspace_of_the_smaller_size_is_accepted_and_keeps_the_plain_grid(pa):
