@@ -737,9 +737,18 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
             pp = even_prefill_split(pp, batch, tiles * (num_q_heads >> lg), (int64_t)total_q * num_q_heads, max_seq_len,
                                     cache->page_size, d);
         }
+        int32_t small_wgs = 0;
+        if (may_have_small) {
+            const int32_t head_groups = cache->num_kv_heads / decode_mfma_heads_per_wg(cache->num_kv_heads, d);
+            small_wgs = plan_stream_wgs(batch, max_seq_len, head_groups, cache->num_kv_heads, 1);
+            const int32_t cap = small_route_wgs_cap(cache->num_kv_heads);
+            if (small_wgs > cap) small_wgs = cap;
+        }
+        const size_t small_bytes = may_have_small ? small_route_bytes(small_wgs, batch, cache->num_kv_heads, d) : 0;
         // Jagged calls on shorter contexts than the list cuts: the list without cuts, for the sake of the launch that it shares
-        // with the few-query stream.
-        const bool list_whole = list_items == 0 && may_have_small && jagged_whole_pays(a, lg);
+        // with the few-query stream (if the workspace holds the stream's partials: the list alone would only lose the plain
+        // plan's chunks).
+        const bool list_whole = list_items == 0 && may_have_small && ws.bytes >= small_bytes && jagged_whole_pays(a, lg);
         if (list_whole) list_items = prefill_list_items(a);
         size_t split_bytes =
             pp.nsplit > 1 ? part_o_bytes(total_q, num_q_heads, d, pp.nsplit) + part_lse_bytes(total_q, num_q_heads, pp.nsplit)
@@ -749,17 +758,9 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
             pp.nsplit = 1;
             split_bytes = list_cuts ? list_bytes(d) : 0;
         }
-        int32_t small_wgs = 0;
-        if (may_have_small) {
-            const int32_t head_groups = cache->num_kv_heads / decode_mfma_heads_per_wg(cache->num_kv_heads, d);
-            small_wgs = plan_stream_wgs(batch, max_seq_len, head_groups, cache->num_kv_heads, 1);
-            const int32_t cap = small_route_wgs_cap(cache->num_kv_heads);
-            if (small_wgs > cap) small_wgs = cap;
-            // The route is an optimisation: a workspace without room for its partials (a call with total_q == batch
-            // is promised the decode bound only) keeps those sequences on the prefill kernel.
-            if (ws.bytes < split_bytes + small_route_bytes(small_wgs, batch, cache->num_kv_heads, d))
-                may_have_small = false;
-        }
+        // The route is an optimisation: a workspace without room for its partials (a call with total_q == batch is promised the
+        // decode bound only) keeps those sequences on the prefill kernel.
+        if (ws.bytes < split_bytes + small_bytes) may_have_small = false;
         const bool may_have_large = (int64_t)max_q_len * G > 16 || !may_have_small;
         if (ws.bytes < split_bytes) return PA_ERR_WORKSPACE_TOO_SMALL;
         if (may_have_large) {

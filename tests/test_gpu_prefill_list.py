@@ -174,6 +174,24 @@ def test_chunks_of_each_context_with_score_hooks(pa, oracle):
     parity.check_step(pa, oracle, w, "hooks", mods=build_mods(dict(alibi=True, softcap=30.0), 4, lens))
 
 
+def test_a_short_jagged_call_without_room_for_the_stream_keeps_its_chunks(pa, oracle):
+    """A call with no more queries than sequences is promised the decode bound, which does not hold the stream's partials:
+    without the stream there is no reason for the list either."""
+    from paper_2506_07311_amd import binding
+    w = W.make_workload("t", seq_lens=[4000] + [50] * 39, q_lens=[36, 1, 1, 1] + [0] * 36, num_q_heads=32, num_kv_heads=8,
+                        head_dim=128, page_size=16, dtype=torch.bfloat16, causal=True, seed=221, device=DEV)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        parity.check_step(pa, oracle, w, "no room")
+        counts = [binding.pa_profile_read(k)[0] for k in ("paged_jagged_mfma", "paged_decode_mfma", "paged_prefill_mfma",
+                                                          "paged_attention_merge_kernel")]
+        assert counts == [0, 0, 1, 1]
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
+
+
 def test_a_workspace_of_the_smaller_size_is_accepted_and_keeps_the_plain_grid(pa):
     """The list's partials are room on top of what a call requires: without it the plain grid runs, with the same results
     up to the merge's rounding (bf16 outputs one step apart at most)."""
