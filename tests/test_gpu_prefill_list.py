@@ -79,13 +79,16 @@ def test_chunks_and_single_queries_in_one_launch(pa, oracle, Hq, Hkv, P, dtype, 
     assert torch.equal(outs[0], outs[1])
 
 
-@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,P,dtype,causal", [
-    ([2100, 0, 700, 1, 1500, 64, 65], [130, 0, 1, 1, 129, 2, 17], 16, 4, 16, torch.bfloat16, True),
-    ([4095, 300, 33], [33, 1, 1], 8, 8, 64, torch.float16, False),            # one key short of the list that is cut
-    ([40] * 70 + [600, 500], [1] * 70 + [250, 3], 4, 4, 32, torch.float16, True),
-    ([500, 700, 900], [100, 101, 102], 8, 4, 16, torch.bfloat16, True)])      # nothing for the stream, and may be
-def test_uncut_chunks_and_single_queries_in_one_launch(pa, oracle, lens, q_lens, Hq, Hkv, P, dtype, causal):
-    """Contexts below the length that the list cuts: whole row tiles beside the stream, no partials of the list's."""
+@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,P,dtype,causal,whole", [
+    ([2100, 0, 700, 1, 1500, 64, 65], [530, 0, 1, 1, 129, 2, 17], 32, 8, 16, torch.bfloat16, True, 1),
+    ([2047, 300, 33], [33, 1, 1], 8, 8, 64, torch.float16, False, 1),         # one key short of the grid that is cut
+    ([2100, 0, 700, 1, 1500, 64, 65], [130, 0, 1, 1, 129, 2, 17], 16, 4, 16, torch.bfloat16, True, 0),    # few row tiles
+    ([4095, 300, 33], [33, 1, 1], 8, 8, 64, torch.float16, False, 0),         # one key short of the list that is cut
+    ([40] * 70 + [600, 500], [1] * 70 + [250, 3], 4, 4, 32, torch.float16, True, 1),
+    ([500, 700, 900], [100, 101, 102], 8, 4, 16, torch.bfloat16, True, 0)])   # nothing for the stream, and may be
+def test_uncut_chunks_and_single_queries_in_one_launch(pa, oracle, lens, q_lens, Hq, Hkv, P, dtype, causal, whole):
+    """Contexts below the length that the list cuts: whole row tiles beside the stream, no partials of the list's, or, with
+    fewer row tiles than would fill the machine, the grid that is cut and the stream behind it."""
     from paper_2506_07311_amd import binding
     w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=128, page_size=P,
                         dtype=dtype, causal=causal, seed=217, device=DEV)
@@ -96,7 +99,7 @@ def test_uncut_chunks_and_single_queries_in_one_launch(pa, oracle, lens, q_lens,
         parity.check_step(pa, oracle, w, f"{lens} {q_lens}")
         counts = [binding.pa_profile_read(k)[0] for k in ("paged_jagged_mfma", "paged_decode_mfma", "paged_prefill_mfma",
                                                           "paged_attention_merge_list")]
-        assert counts == ([1, 0, 0, 0] if may_be_small else [0, 0, 1, 0])
+        assert counts == ([1, 0, 0, 0] if whole else [0, 1, 1, 0] if may_be_small else [0, 0, 1, 0])
     finally:
         binding.pa_profile_enable(False)
         binding.pa_profile_reset()
@@ -172,6 +175,29 @@ def test_chunks_of_each_context_with_score_hooks(pa, oracle):
     w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=4, num_kv_heads=2, head_dim=128, page_size=16,
                         dtype=torch.bfloat16, causal=True, seed=219, device=DEV)
     parity.check_step(pa, oracle, w, "hooks", mods=build_mods(dict(alibi=True, softcap=30.0), 4, lens))
+
+
+@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,whole", [
+    ([4095, 4095, 4000, 300, 33], [520, 520, 520, 1, 1], 32, 8, 1),           # three chunks, row tiles for them all
+    ([4095, 4095, 4000, 300, 33], [500, 500, 500, 1, 1], 32, 8, 0),           # not quite
+    ([4000, 4000], [200, 1], 32, 8, 0),
+    ([2100, 300, 200], [520, 1, 1], 32, 8, 1),                                # two chunks
+    ([2100, 300, 200], [500, 1, 1], 32, 8, 0)])
+def test_short_jagged_calls_walk_whole_contexts_only_with_a_full_machine(pa, lens, q_lens, Hq, Hkv, whole):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are those of 256 compute units")
+    from paper_2506_07311_amd import binding
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=128, page_size=16,
+                        dtype=torch.bfloat16, causal=True, seed=220, device=DEV)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        out, _ = parity.gpu_step(pa, w)
+        assert binding.pa_profile_read("paged_jagged_mfma")[0] == whole
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
+    parity.assert_close(parity.to_f64(out), parity.to_f64(_reference(w)), torch.bfloat16, f"{lens} {q_lens}")
 
 
 def test_a_short_jagged_call_without_room_for_the_stream_keeps_its_chunks(pa, oracle):
