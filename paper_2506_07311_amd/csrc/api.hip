@@ -173,11 +173,14 @@ SplitPlan plan_prefill(int32_t batch, int32_t num_q_heads, int32_t log2_pack, in
 // The number of chunks for a call whose contexts are much longer than its query ranges, where every workgroup walks a whole
 // chunk: at most plan_prefill's (which workspaces are sized for), the one for which the fullest compute unit is done first.
 // A compute unit works through the tiles of two workgroups hardly faster than through those of one after the other
-// (64 keys at head_dim 128: 1.93 us two at a time, 1.05 alone; one at a time only at head_dim 256), so what counts is
-// how evenly the workgroups divide among the compute units; a chunk more costs its partials' way to memory and back (3.3 GB a
-// ms in the merge).  us a call with about 1024 workgroups / like this, 32 / 8 heads: 1024 tokens of a 32768-token context
-// 514 / 511, 512 of it 273 / 265, 128 of it 109 / 87, 500 of 12000 125 / 109, two sequences with 128 tokens of 32768 each
-// 184 / 154, four 374 / 290, 500 of 20000 at head_dim 256 488 / 363.
+// (64 keys at head_dim 128: 1.93 us two at a time, 1.05 alone; one at a time only at head_dim 256; three at head_dim 64), so
+// what counts is how evenly the workgroups divide among the compute units; a chunk more costs its partials' way to memory and
+// back (3.3 GB a ms in the merge, and 10 us for its launch and the workgroups' other end).  With every number of chunks measured
+// for 56 calls with equal contexts this one is at most 2 % behind the best (two sequences at head_dim 256 4 and 12 %); at
+// head_dim 64, two, four and eight chunks, as for two workgroups a compute unit, are behind three, six and 16 by 1 to 9 %.
+// us a call with about 1024 workgroups / like this, 32 / 8 heads: 1024 tokens of a 32768-token context 514 / 511, 512 of it
+// 273 / 265, 128 of it 109 / 87, 500 of 12000 125 / 109, two sequences with 128 tokens of 32768 each 184 / 154, four
+// 374 / 290, 500 of 20000 at head_dim 256 488 / 363, 1024 of 32768 at 64 343 / 314.
 // max_seq_len is a bound and query counts say nothing of contexts: each sequence's own length is cut on the device
 // (sequence_chunk), which divides as evenly for any length (1024 workgroups and chunks of the bound / this many chunks of the
 // bound / like this: 128 tokens of 8192 in a call for up to 131072 97 / 200 / 40, 1000 of 20000 for up to 32768 403 / 413 / 320).
@@ -189,7 +192,11 @@ SplitPlan plan_prefill(int32_t batch, int32_t num_q_heads, int32_t log2_pack, in
 SplitPlan even_prefill_split(const SplitPlan& most, int32_t batch, int64_t wgs, int64_t rows, int32_t max_seq_len,
                              int32_t page_size, int32_t d)
 {
-    const double one = d > 128 ? 2.4 : d > 64 ? 1.05 : 0.75, two = d > 128 ? 4.8 : d > 64 ? 1.93 : 1.4;
+    // us that a compute unit takes for 64 keys of its first, second and third workgroup together (as many as fit it at once;
+    // 32 heads' rows on 8192 and 16384 keys with one to three workgroups a compute unit)
+    const double tile[3] = {d > 128 ? 2.4 : d > 112 ? 1.05 : d > 96 ? 1.6 : d > 64 ? 1.35 : 0.84,
+                            d > 128 ? 4.8 : d > 112 ? 1.93 : d > 96 ? 2.75 : d > 64 ? 2.25 : 1.25, 1.75};
+    const int64_t slots = d > 64 ? 2 : 3;
     const int64_t unit = page_size > 64 ? page_size : 64;
     SplitPlan best = most;
     best.unit = (int32_t)unit;
@@ -199,8 +206,9 @@ SplitPlan even_prefill_split(const SplitPlan& most, int32_t batch, int64_t wgs, 
         if (((int64_t)max_seq_len + chunk - 1) / chunk != n) continue;
         if (batch > 1 && wgs / batch * n < device_cus() && 4 * n < 3 * most.nsplit) continue;
         const int64_t per_cu = (wgs * n + device_cus() - 1) / device_cus();
-        const double us = (double)(chunk / 64) * ((per_cu / 2) * two + (per_cu % 2) * one) +
-                          (n > 1 ? 4.0 + (double)rows * n * d * 4.0 / 3.3e6 : 0.0);
+        const double us = (double)(chunk / 64) * ((per_cu / slots) * tile[slots - 1] +
+                                                  (per_cu % slots ? tile[per_cu % slots - 1] : 0.0)) +
+                          (n > 1 ? 10.0 + (double)rows * n * d * 4.0 / 3.3e6 : 0.0);
         if (us < best_us) {
             best_us = us;
             best.nsplit = n;

@@ -141,6 +141,8 @@ def _reference(w):
 @pytest.mark.parametrize("lens,q,bound,Hq,Hkv,d,P,dtype,causal,chunks", [
     ([32768], 1024, 32768, 32, 8, 128, 16, torch.bfloat16, True, [2]),               # of four possible ones
     ([32768, 32768], 128, 32768, 32, 8, 128, 16, torch.bfloat16, True, [8, 8]),      # of 13
+    ([32768], 1024, 32768, 32, 8, 64, 16, torch.bfloat16, True, [3]),                # three workgroups a compute unit
+    ([8192], 256, 8192, 32, 8, 96, 16, torch.float16, True, [8]),
     ([2048], 1024, 2048, 32, 8, 128, 16, torch.bfloat16, True, [1]),                 # of two
     ([8192], 128, 131072, 32, 8, 128, 16, torch.bfloat16, True, [8]),                # a bound far from the length
     ([700], 128, 131072, 32, 8, 128, 64, torch.float16, True, [1]),
