@@ -110,7 +110,7 @@ __device__ void merge_list(const ListMerge& p, int32_t block, void* __restrict__
     const int lane = threadIdx.x & 63;
     const int32_t quarter = block & 3, piece = (block >> 1 & 2) + (int32_t)(threadIdx.x >> 6);
     const int32_t lg = p.log2_pack, T = (d + 31) / 32;
-    const WorkList list = make_list(cu_q_lens, seq_lens, p.batch, lg, p.small_group, p.heads, p.unit, lane);
+    const WorkList list = make_list(cu_q_lens, seq_lens, p.batch, lg, p.small_group, p.heads, p.unit, d, lane);
     for (int32_t index = block >> 3;; index += p.blocks >> 3) {
         const int32_t hg = index % p.heads;
         ListItem it;

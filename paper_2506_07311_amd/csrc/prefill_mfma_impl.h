@@ -980,7 +980,7 @@ __device__ __forceinline__ void list_body(
     // what the body derives from it would otherwise be kept in registers across the loop, which spills.
     const WorkList list = make_list(cu_q_lens, seq_lens, batch, plan.log2_pack,
                                     plan.skip_small ? plan.group : kNoSmallGroup, heads,
-                                    plan.list_unit, (int)(threadIdx.x & 63));
+                                    plan.list_unit, D, (int)(threadIdx.x & 63));
     int32_t precise_keys = 0;
     if constexpr (!kTwoTermOnly<D>)
         precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal, 0, (int)(threadIdx.x & 63));

@@ -107,10 +107,13 @@ PrefillPlan make_plan(const AttnArgs& a);
 constexpr int32_t kListTarget = 1024;
 constexpr int32_t kListMinTiles = 32;
 // ... except that chunks may be as short as kListShortTiles while all items fit the workgroup slots of the machine (two
-// per compute unit): one chunk of 512 tokens on 2787 among 16 sequences 73 us against 86 with 32 tiles, but six chunks of
+// per compute unit up to head_dim 128): one chunk of 512 tokens on 2787 among 16 sequences 73 us against 86 with 32 tiles, but six chunks of
 // 200 tokens on up to 3508, whose 728 items of 16 tiles need a second round, 134 against 123.
 constexpr int32_t kListShortTiles = 16;
-constexpr int32_t kListSlots = 512;
+// At head_dim 256 one workgroup fits a compute unit (200 queries among 17 sequences of up to 8000 tokens, 32 / 8 heads, 186 -> 158
+// us, two of 200 among 30 to 6000 180 -> 161, calls with more work 340 - 369 the same).  At head_dim 64 three do, but slots for
+// 768 items gain nothing in the mean (60 sequences to 4500, six with 200, 95 -> 88, 40 to 12000, three with 200, 93 -> 97).
+__host__ __device__ constexpr int32_t list_wg_slots(int32_t d) { return d > 128 ? 256 : 512; }
 // Workgroups of the launch and of its merge (an eighth of a row tile each).  Items beyond the grid are taken by
 // stepping over the list: the host can only bound the number of items, and a workgroup that finds none still costs its
 // slot for the 3 us that finding out takes (60 sequences with three short chunks of 200 tokens: 147 us with a workgroup
@@ -149,7 +152,7 @@ struct WorkList {
 };
 __device__ __forceinline__ WorkList make_list(const int32_t* __restrict__ cu_q_lens,
                                               const int32_t* __restrict__ seq_lens, int32_t batch, int32_t log2_pack,
-                                              int32_t small_group, int32_t heads, int32_t unit, int lane)
+                                              int32_t small_group, int32_t heads, int32_t unit, int32_t d, int lane)
 {
     WorkList w;
     w.small_group = small_group;
@@ -172,12 +175,12 @@ __device__ __forceinline__ WorkList make_list(const int32_t* __restrict__ cu_q_l
             int32_t n = 0;
             for (int32_t i = lane; i < batch; i += 64) {
                 const ListSeq q = i < 64 ? w.own : list_seq(cu_q_lens, seq_lens, batch, i, log2_pack, small_group);
-                n += min(q.tiles * ((max(q.len, 1) + c * kBN - 1) / (c * kBN)), 2 * kListSlots);
+                n += min(q.tiles * ((max(q.len, 1) + c * kBN - 1) / (c * kBN)), 2 * list_wg_slots(d));
             }
             n = min(n, 1 << 20);
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
-            if ((int64_t)n * heads <= kListSlots) {
+            if ((int64_t)n * heads <= list_wg_slots(d)) {
                 tiles = c;
                 break;
             }

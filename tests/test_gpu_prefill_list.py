@@ -179,6 +179,21 @@ def test_chunks_of_each_context_with_score_hooks(pa, oracle):
     parity.check_step(pa, oracle, w, "hooks", mods=build_mods(dict(alibi=True, softcap=30.0), 4, lens))
 
 
+@pytest.mark.parametrize("d,chunks", [(256, 4), (128, 8)])
+def test_chunks_of_the_list_fill_the_workgroups_that_fit_at_once(pa, d, chunks):
+    """58 row tiles and heads' items of 1024 keys are one round of two workgroups a compute unit, and more than one of the single
+    one at head_dim 256, which takes chunks of 2048 keys instead; counted by the partials that are left."""
+    w = W.make_workload("t", seq_lens=[8192, 300, 300], q_lens=[200, 20, 20], num_q_heads=32, num_kv_heads=8, head_dim=d,
+                        page_size=16, dtype=torch.bfloat16, causal=True, seed=222, device=DEV)
+    pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
+    nbytes = pa.paged_attention_workspace_bytes(w.batch, 32, d, w.total_q, w.max_seq_len)
+    ws = torch.full((-(-nbytes // 4),), -1, dtype=torch.int32, device=DEV)
+    out = pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, w.cu_q_lens, w.max_q_len, w.block_table, w.seq_lens,
+                                     w.max_seq_len, w.scale, True, workspace=ws)
+    parity.assert_close(parity.to_f64(out), parity.to_f64(_reference(w)), torch.bfloat16, f"{d}")
+    assert int((ws != -1).sum()) == 200 * 32 * (d + 1) * chunks
+
+
 @pytest.mark.parametrize("lens,q_lens,Hq,Hkv,whole", [
     ([4095, 4095, 4000, 300, 33], [520, 520, 520, 1, 1], 32, 8, 1),           # three chunks, row tiles for them all
     ([4095, 4095, 4000, 300, 33], [500, 500, 500, 1, 1], 32, 8, 0),           # not quite
