@@ -3,7 +3,8 @@
 // per head_dim instantiates them.  The text below describes D = 128.  D = 64 is the same kernel with half the steps:
 // LDS rows are 128 bytes (a load instruction brings 8 of them), the score product takes 4 steps instead of 8 and the value
 // product covers 2 column blocks, not 4.  What a tile costs besides its matrix work then hides behind a third workgroup of a
-// compute unit, for which there are registers (148) and, with rows of their own size, LDS (32 KiB): 4 x 2048 with 32 / 8 heads
+// compute unit, for which there are registers (148; document masks and user modifications spill 4 to 6, see the kernel) and,
+// with rows of their own size, LDS (32 KiB): 4 x 2048 with 32 / 8 heads
 // 119 us with half-empty 256-byte rows and two workgroups, 102 like this, 1 x 8192 341 / 303, prompts of 2059 and 3146 tokens
 // with a window 81 / 67, 1024 tokens of a 32768-token context 348 / 324; a fourth workgroup spills (158, 465, 102, -).
 // D = 256 has
@@ -57,8 +58,9 @@ namespace {
 
 using namespace prefill;
 
-// LDS row stride of a K or V row: 256 bytes up to head_dim 128, 512 bytes at head_dim 256.  The swizzle always
-// permutes the 16 pieces of a 256-byte half row among themselves (every row starts at bank 0 either way).
+// LDS row stride of a K or V row: 256 bytes (head_dims 80 to 128), 512 at head_dim 256, 128 at 64.  The swizzle permutes the 16
+// pieces of a 256-byte half row among themselves (such a row starts at bank 0), or the 8 of a 128-byte row, of which every
+// second one starts half way through the banks (row_swz).
 template <int D>
 struct RowGeo {
     static constexpr int kRowB = D > 128 ? 512 : D > 64 ? 256 : 128;
@@ -147,15 +149,18 @@ __device__ __forceinline__ uint4 lds_frag_tr(const char* lo, const char* hi)
 // sees fewer than kPreciseShare * H keys take the two-term path.  Wave-uniform result.
 constexpr float kPreciseShare = 0.9f;
 
-// Sum over the wave with data-parallel-primitive moves (shifts by 1, 2, 4, 8 inside each row of 16 lanes, then lane 15 of a
-// row into the next row, lane 31 into the upper half) instead of six round trips through LDS in front of a workgroup's
-// first tile (append + prefill of one prompt, 32 / 8 heads: 128 tokens 11.9 -> 11.6 us, 200 13.2 -> 13.0, 500 and more the same).
-__device__ __forceinline__ float wave_sum(float v)
+// A fold over the wave in data-parallel-primitive moves, STEP(control, rows that receive): shifts by 1, 2, 4, 8 inside each row
+// of 16 lanes, then lane 15 of a row into the next row, lane 31 into the upper half; lane 63 holds the result.
+#define PA_WAVE_FOLD(STEP) \
+    STEP(0x111, 0xF) STEP(0x112, 0xF) STEP(0x114, 0xF) STEP(0x118, 0xF) STEP(0x142, 0xA) STEP(0x143, 0xC)
+
+// Sum over the wave without six round trips through LDS in front of a workgroup's first tile (append + prefill of one prompt,
+// 32 / 8 heads: 128 tokens 11.9 -> 11.6 us, 200 13.2 -> 13.0, 500 and more the same).
+__device__ __forceinline__ float wave_sum_moves(float v)
 {
 #define PA_SUM_STEP(CTRL, ROWS) \
     v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, ROWS, 0xF, true));
-    PA_SUM_STEP(0x111, 0xF) PA_SUM_STEP(0x112, 0xF) PA_SUM_STEP(0x114, 0xF) PA_SUM_STEP(0x118, 0xF)
-    PA_SUM_STEP(0x142, 0xA) PA_SUM_STEP(0x143, 0xC)
+    PA_WAVE_FOLD(PA_SUM_STEP)
 #undef PA_SUM_STEP
     return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), 63));
 }
@@ -183,8 +188,8 @@ __device__ __forceinline__ int32_t precise_key_bound(const int32_t* __restrict__
         const int32_t above = hi - max(lo, cap + 1) + 1;              // rows that see the whole window
         if (above > 0) inv += (float)above / (float)cap;
     }
-    rows = wave_sum(rows);
-    inv = wave_sum(inv);
+    rows = wave_sum_moves(rows);
+    inv = wave_sum_moves(inv);
     const float h = inv > 0.f ? rows / inv : 0.f;
     return max(kPreciseKeys, (int32_t)fminf(kPreciseShare * h, 1.0e9f));
 }
@@ -196,7 +201,8 @@ constexpr int kAheadK = 8, kAheadV = 6;
 
 // Online-softmax update with the 32 keys of one half tile.  s holds raw scores on entry; the weights are
 // returned in p.  The running statistic is a REFERENCE exponent m_ref (log2 domain) that may trail the true
-// running max: weights are exp2(score - m_ref), and as long as a lane's 16 weights sum to at most kWeightSumMax
+// running max: weights are exp2(score - m_ref), and as long as a lane's weights (16, or 8 with
+// 16 rows a wave) sum to at most kWeightSumMax
 // every one of them is a number that fp32 sums and 16-bit operands carry without loss, and out = O / l does not
 // depend on the reference.  So the common path takes no maximum at all: the weights are computed with the
 // reference as it stands, and only when some lane's sum exceeds the bound (or is not a number: a fresh reference
@@ -801,16 +807,14 @@ __device__ __forceinline__ bool prefill_body(
     const bool doc_lane = M::kDoc && wave == 0;
     int32_t doc_next = 0;
     int32_t row_doc_min = rm.doc, row_doc_max = rm.doc;
-    // minimum and maximum over the wave with data-parallel-primitive moves: shifts by 1, 2, 4, 8 inside each row
-    // of 16 lanes, then lane 15 of a row into the next row, lane 31 into the upper half; lane 63 holds the result
+    // minimum and maximum over the wave
     auto wave_range = [&](int32_t v, int32_t& mn, int32_t& mx) {
         mn = v;
         mx = v;
 #define PA_RANGE_STEP(CTRL, ROWS)                                                                   \
         mn = min(mn, __builtin_amdgcn_update_dpp(mn, mn, CTRL, ROWS, 0xF, false));                  \
         mx = max(mx, __builtin_amdgcn_update_dpp(mx, mx, CTRL, ROWS, 0xF, false));
-        PA_RANGE_STEP(0x111, 0xF) PA_RANGE_STEP(0x112, 0xF) PA_RANGE_STEP(0x114, 0xF) PA_RANGE_STEP(0x118, 0xF)
-        PA_RANGE_STEP(0x142, 0xA) PA_RANGE_STEP(0x143, 0xC)
+        PA_WAVE_FOLD(PA_RANGE_STEP)
 #undef PA_RANGE_STEP
         mn = __builtin_amdgcn_readlane(mn, 63);
         mx = __builtin_amdgcn_readlane(mx, 63);
@@ -864,42 +868,42 @@ __device__ __forceinline__ bool prefill_body(
             for (int i = 0; i < NV; ++i) vx[i] ^= Geo::kBufB;
         }
     } else {
-    // Two tiles per trip so that each buffer is a distinct LDS object for the compiler: while the matrix cores
-    // read one, the load unit fills the other with the next tile; the page ids of the tile after that are requested
-    // at the same time.  The barrier at the end of a tile waits for this wave's loads first.
-    for (int32_t t = 0; t < n_tiles; t += 2) {
-        const int32_t t0 = k_begin + t * kBN;
-        if (t + 1 < n_tiles) {
-            fetch(lds1, ids, t0 + kBN);
-            if (doc_lane) doc_next = tile_ids(t0 + kBN);
-            if (t + 2 < n_tiles) load_ids<UNIFORM>(ids, cache, table, t0 + 2 * kBN, frow, last_key);
+        // Two tiles per trip so that each buffer is a distinct LDS object for the compiler: while the matrix cores
+        // read one, the load unit fills the other with the next tile; the page ids of the tile after that are requested
+        // at the same time.  The barrier at the end of a tile waits for this wave's loads first.
+        for (int32_t t = 0; t < n_tiles; t += 2) {
+            const int32_t t0 = k_begin + t * kBN;
+            if (t + 1 < n_tiles) {
+                fetch(lds1, ids, t0 + kBN);
+                if (doc_lane) doc_next = tile_ids(t0 + kBN);
+                if (t + 2 < n_tiles) load_ids<UNIFORM>(ids, cache, table, t0 + 2 * kBN, frow, last_key);
+            }
+            if (t0 < nk_wave && t0 + kBN > lo_wave && docs_overlap(docs0)) {   // wave-uniform: else nothing for this wave here
+                if (t0 + kBN > nk_wave_min)                      // wave-uniform: some score of this tile is masked
+                    attend_tile<PRECISE, true, CAREFUL, E, M, D>(buf0, kx, vx, qf, o, m, l, sc, t0 + 4 * hh, nk, rm, docs0 + 4 * hh);
+                else
+                    attend_tile<PRECISE, false, CAREFUL, E, M, D>(buf0, kx, vx, qf, o, m, l, sc, t0 + 4 * hh, nk, rm, docs0 + 4 * hh);
+            }
+            if (doc_lane && t + 1 < n_tiles) put_docs(docs1, doc_next);
+            wait_tile_loads();
+            __syncthreads();
+            if (t + 1 >= n_tiles) break;
+            const int32_t t1 = t0 + kBN;
+            if (t + 2 < n_tiles) {
+                fetch(lds0, ids, t1 + kBN);
+                if (doc_lane) doc_next = tile_ids(t1 + kBN);
+                if (t + 3 < n_tiles) load_ids<UNIFORM>(ids, cache, table, t1 + 2 * kBN, frow, last_key);
+            }
+            if (t1 < nk_wave && t1 + kBN > lo_wave && docs_overlap(docs1)) {
+                if (t1 + kBN > nk_wave_min)
+                    attend_tile<PRECISE, true, CAREFUL, E, M, D>(buf1, kx, vx, qf, o, m, l, sc, t1 + 4 * hh, nk, rm, docs1 + 4 * hh);
+                else
+                    attend_tile<PRECISE, false, CAREFUL, E, M, D>(buf1, kx, vx, qf, o, m, l, sc, t1 + 4 * hh, nk, rm, docs1 + 4 * hh);
+            }
+            if (doc_lane && t + 2 < n_tiles) put_docs(docs0, doc_next);
+            wait_tile_loads();
+            __syncthreads();
         }
-        if (t0 < nk_wave && t0 + kBN > lo_wave && docs_overlap(docs0)) {   // wave-uniform: else nothing for this wave here
-            if (t0 + kBN > nk_wave_min)                      // wave-uniform: some score of this tile is masked
-                attend_tile<PRECISE, true, CAREFUL, E, M, D>(buf0, kx, vx, qf, o, m, l, sc, t0 + 4 * hh, nk, rm, docs0 + 4 * hh);
-            else
-                attend_tile<PRECISE, false, CAREFUL, E, M, D>(buf0, kx, vx, qf, o, m, l, sc, t0 + 4 * hh, nk, rm, docs0 + 4 * hh);
-        }
-        if (doc_lane && t + 1 < n_tiles) put_docs(docs1, doc_next);
-        wait_tile_loads();
-        __syncthreads();
-        if (t + 1 >= n_tiles) break;
-        const int32_t t1 = t0 + kBN;
-        if (t + 2 < n_tiles) {
-            fetch(lds0, ids, t1 + kBN);
-            if (doc_lane) doc_next = tile_ids(t1 + kBN);
-            if (t + 3 < n_tiles) load_ids<UNIFORM>(ids, cache, table, t1 + 2 * kBN, frow, last_key);
-        }
-        if (t1 < nk_wave && t1 + kBN > lo_wave && docs_overlap(docs1)) {
-            if (t1 + kBN > nk_wave_min)
-                attend_tile<PRECISE, true, CAREFUL, E, M, D>(buf1, kx, vx, qf, o, m, l, sc, t1 + 4 * hh, nk, rm, docs1 + 4 * hh);
-            else
-                attend_tile<PRECISE, false, CAREFUL, E, M, D>(buf1, kx, vx, qf, o, m, l, sc, t1 + 4 * hh, nk, rm, docs1 + 4 * hh);
-        }
-        if (doc_lane && t + 2 < n_tiles) put_docs(docs0, doc_next);
-        wait_tile_loads();
-        __syncthreads();
-    }
     }
 
     if constexpr (kTwoTermOnly<D> && !CAREFUL) {
@@ -1018,6 +1022,11 @@ __device__ __forceinline__ void list_body(
 // Both instantiations live in one kernel as two separate code paths (each with its own tile loop); a
 // workgroup runs exactly one of them, decided by its context length.
 // LIST: the work-list mode of prefill_tiles.h.
+// Waves a SIMD: two, three at head_dim 64.  Hooks that keep more state spill under that bound: document masks and user
+// modifications 4 - 6 registers at head_dim 64, 12 and 24 at 256, slopes 7 at 256, and nothing at 128.  us for 4 x 2048, 2 x 1200 and
+// 1 x 500 tokens (32 / 8 heads, 16 / 8 at 256), one wave less and no spill / like this: at head_dim 64 documents 105 / 89,
+// 34.0 / 34.8, 19.0 / 18.7, prefix-LM 504 / 399, 142 / 96, 35 / 35; at 256, where that is four waves of 32 rows, documents
+// 191 / 173, 72 / 53, 35 / 32, prefix-LM 725 / 638, 226 / 198, 56 / 47, slopes 350 / 270, 100 / 77, 46 / 37.
 template <bool UNIFORM, typename E, typename M, int D, bool LIST = false>
 __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_prefill_mfma_kernel(
     CacheView cache, const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float* __restrict__ lse,
@@ -1025,11 +1034,13 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
     const int32_t* __restrict__ seq_lens, int32_t batch, int32_t num_tiles, int32_t num_q_heads, int32_t max_blocks,
     float scale, int32_t causal, PrefillPlan plan)
 {
-    // two tile buffers; with 16 rows a wave they are one object, aligned so that one address bit tells them apart
-    constexpr int kOne = RowGeo<D>::kRows == 16 ? 2 * RowGeo<D>::kBufB : RowGeo<D>::kBufB;
-    __shared__ __attribute__((aligned(kOne > (1 << 16) ? (1 << 17) : 1024))) char buf0[kOne];
-    __shared__ __attribute__((aligned(1024))) char other[RowGeo<D>::kRows == 16 ? 16 : RowGeo<D>::kBufB];
-    char* const buf1 = RowGeo<D>::kRows == 16 ? buf0 + RowGeo<D>::kBufB : other;
+    // two tile buffers; with 16 rows a wave they are one object, aligned to its size, so that one address bit tells them apart
+    constexpr bool kPair = RowGeo<D>::kRows == 16;
+    constexpr int kOne = kPair ? 2 * RowGeo<D>::kBufB : RowGeo<D>::kBufB;
+    static_assert(!kPair || (RowGeo<D>::kBufB & (RowGeo<D>::kBufB - 1)) == 0, "the buffers of a pair are one bit apart");
+    __shared__ __attribute__((aligned(kPair ? kOne : 1024))) char buf0[kOne];
+    __shared__ __attribute__((aligned(1024))) char other[kPair ? 16 : RowGeo<D>::kBufB];
+    char* const buf1 = kPair ? buf0 + RowGeo<D>::kBufB : other;
     __shared__ __attribute__((aligned(16))) int32_t docs0[kBN + 4];
     __shared__ __attribute__((aligned(16))) int32_t docs1[kBN + 4];
     // The workgroup's own lengths are requested first (scalar loads), the scan of every sequence's lengths for the

@@ -316,7 +316,8 @@ __device__ __forceinline__ float row_max(float x)
 }
 
 // Online softmax keeps a REFERENCE exponent (log2 domain) that may trail the true running max; the reference is
-// raised when the 16 weights a lane computes for a half tile sum to more than this (fp16 operands end at 65504).
+// raised when the weights a lane computes for a half tile (16, or 8 with 16 rows a wave) sum to more than this (fp16
+// operands end at 65504).
 constexpr float kWeightSumMax = 16384.f;
 
 }  // namespace prefill
