@@ -491,33 +491,21 @@ bool list_pays(const AttnArgs& a, int32_t log2_pack)
     return ((((int64_t)a.total_q << log2_pack) / 128) + live) * (a.num_q_heads >> log2_pack) < kListMaxWGs;
 }
 
-// Jagged calls whose contexts are too short for the list to cut may take it uncut where one launch then holds it and the
+// Jagged calls whose contexts are too short for the list with slots take it all the same where one launch then holds it and the
 // few-query stream: the plain grid is row tiles of every sequence, most of them of decode rows and empty, and the stream waits
-// behind it.
-bool jagged_whole_possible(const AttnArgs& a, int32_t log2_pack)
+// behind it.  What the plain grid would cut (from 2048 keys on, while row tiles do not fill the machine) the list cuts as well,
+// by each context's own length: the longest one may be a decode row's.  us plain / uncut / like this, 32 / 8 heads: 2 sequences of
+// 4000 keys with 200 queries and one 64 / 90 / 47 (8 / 4 heads 49 / 87 / 42), 40 to 3900, two with 128, 85 / 93 / 50, 32 to 3212,
+// two with 200 on 81 and 3076 104 / 80 / 50, 33 to 2232, four with 200, 86 / 63 / 59; where nothing needs a cut: 21 to 2917, three
+// with up to 512 on 136 .. 525 62 / 32 / 35, 56 to 3500, four with 512 214 / 100 / 101 and 39 to 1500, five with 200
+// 69 / 51 / 52.  Of 114 such calls none is slower than 0.89 of the plain grid's time, nor than 1.1 of the uncut list's.
+bool jagged_short_list_pays(const AttnArgs& a, int32_t log2_pack)
 {
     const int64_t live = (a.total_q + a.max_q_len - 1) / (a.max_q_len > 0 ? a.max_q_len : 1);
     return jagged_mfma_stream_wgs(a, device_cus()) > 0 && a.batch > 1 && a.batch <= kListScanBatch &&
            (int64_t)a.batch * a.max_q_len != a.total_q && a.max_seq_len / 2 >= a.max_q_len &&
            a.max_seq_len < prefill_list_min_context() && g_opt.prefill_chunk_tokens == 0 &&
            ((((int64_t)a.total_q << log2_pack) / 128) + live) * (a.num_q_heads >> log2_pack) < kListMaxWGs;
-}
-
-// Against a plain grid that is not cut either (`nsplit` chunks) it always pays.  A whole walk of up to 4095 keys is long (64
-// tiles of 1.25 us beside the stream, a third of it 21 and the call a launch more), so against chunks it pays only where row
-// tiles fill the machine without a cut: workgroups for more than half of the compute units with two chunks, for each one and a
-// half with three.  us cut / like this, n chunks and w workgroups: n = 2, 3 of 200 queries among 6 sequences to 2102, w = 150
-// 60 / 52, 2 of 300 among 24 to 2500 65 / 64, 1 of 512, 64 / 8 heads, to 2202, w = 256 92 / 60; but 1 of 300 among 5 to 2745,
-// w = 75 52 / 64, 2 of 512, 16 / 4 heads, to 2507, w = 128 55 / 63; n = 3, 4 of 800, 16 / 4, to 3945, w = 400 95 / 90; but 6 of
-// 200 among 8 to 3866, w = 300 67 / 87, 1 of 200 among 2 to 4000 55 / 90, 8 / 4 heads 49 / 87.  n = 1, 33 sequences to 2232,
-// four with 200 86 / 63; 56 to 3500, four with 512 214 / 100; 39 to 1500, five with 200 70 / 51.
-bool jagged_whole_pays(const AttnArgs& a, int32_t log2_pack, int32_t nsplit)
-{
-    const int64_t live = (a.total_q + a.max_q_len - 1) / (a.max_q_len > 0 ? a.max_q_len : 1);
-    int64_t rows = a.total_q - (a.batch - live);          // of the sequences with more than one query, at a guess
-    if (rows < a.max_q_len) rows = a.max_q_len;
-    const int64_t wgs = (rows << log2_pack) * (a.num_q_heads >> log2_pack) / 128;
-    return nsplit == 1 || 2 * wgs > (nsplit == 2 ? 1 : 3) * (int64_t)device_cus();
 }
 
 // What a call's workspace has to hold.  (paged_attention_workspace_bytes adds the room of the prefill kernel's
@@ -614,6 +602,7 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
     a.stream_split = 0;
     a.num_wgs = 0;
     a.seg_first = a.seg_last = nullptr;
+    a.rows_o = a.rows_lse = nullptr;
     a.list_items = 0;
     a.list_o = a.list_lse = nullptr;
     a.skip_small = 0;
@@ -768,24 +757,20 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
             if (small_wgs > cap) small_wgs = cap;
         }
         const size_t small_bytes = may_have_small ? small_route_bytes(small_wgs, batch, cache->num_kv_heads, d) : 0;
-        // Jagged calls on shorter contexts than the list cuts: the list without cuts, for the sake of the launch that it shares
-        // with the few-query stream (if the workspace holds the stream's partials: the list alone would only lose the plain
-        // plan's chunks).  Those it does not pay for are cut by their own lengths: few row tiles among empty ones, which the
-        // plain order piles on a few compute units (40 sequences to 3900 keys, two with 128 queries 84 -> 66 us, 24 to 2500, two
-        // with 300, 105 -> 65).
-        bool list_whole = list_items == 0 && may_have_small && ws.bytes >= small_bytes && jagged_whole_possible(a, lg);
-        if (list_whole && !jagged_whole_pays(a, lg, pp.nsplit)) {
-            list_whole = false;
-            pp.unit = cache->page_size > 64 ? cache->page_size : 64;
-        }
-        if (list_whole) list_items = prefill_list_items(a);
+        // Jagged calls on shorter contexts than the list has slots for: the list for the sake of the launch that it shares with
+        // the few-query stream, uncut where the plain grid is, else cut by each context's own length into the plain grid's
+        // partials (if the workspace holds the stream's as well: the list alone would only lose the plain order).
         size_t split_bytes =
             pp.nsplit > 1 ? part_o_bytes(total_q, num_q_heads, d, pp.nsplit) + part_lse_bytes(total_q, num_q_heads, pp.nsplit)
                           : 0;
-        if (list_cuts || list_whole) {
+        const bool list_short = list_items == 0 && may_have_small && ws.bytes >= split_bytes + small_bytes &&
+                                jagged_short_list_pays(a, lg);
+        if (list_short) list_items = prefill_list_items(a);
+        if (list_short && pp.nsplit > 1) pp.unit = cache->page_size > 64 ? cache->page_size : 64;
+        if (list_cuts) {
             pp.chunk = max_seq_len;
             pp.nsplit = 1;
-            split_bytes = list_cuts ? list_bytes(d) : 0;
+            split_bytes = list_bytes(d);
         }
         // The route is an optimisation: a workspace without room for its partials (a call with total_q == batch is promised the
         // decode bound only) keeps those sequences on the prefill kernel.
@@ -806,12 +791,17 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
                     base + align256(prefill_list_slots() * prefill_list_slot_floats(d) * sizeof(float)));
                 a.skip_small = b.skip_small;
             }
-            const int32_t beside = (list_cuts || list_whole) && may_have_small ? jagged_mfma_stream_wgs(b, device_cus()) : 0;
+            const int32_t beside = (list_cuts || list_short) && may_have_small ? jagged_mfma_stream_wgs(b, device_cus()) : 0;
             if (beside > 0) {                              // both in one launch, their pieces merged by one
                 AttnArgs c = a;
                 c.stream_split = 1;
                 c.num_wgs = beside < small_wgs ? beside : small_wgs;
                 place_stream(c, base + split_bytes, ((size_t)c.num_wgs + batch) * cache->num_kv_heads * 16);
+                if (pp.nsplit > 1) {
+                    c.plan = pp;
+                    c.rows_o = b.part_o;
+                    c.rows_lse = b.part_lse;
+                }
                 st = launch_jagged_mfma(b, c, s);
                 return st != PA_OK ? st : launch_merge(c, s);
             }

@@ -151,6 +151,8 @@ struct AttnArgs {
     int32_t num_wgs;
     int32_t* seg_first;
     int32_t* seg_last;
+    const float* rows_o;     // partials by (row, head) that are merged beside the stream's (with `plan`); null = none
+    const float* rows_lse;
     int32_t list_items;      // prefill kernel: > 0 = work-list mode with at most this many (tile, chunk) items per head
                              // group (see prefill_tiles.h); partials by slot in list_o / list_lse
     float* list_o;           // (null: no context is cut, there are no partials)
@@ -381,6 +383,7 @@ struct RowInfo {
     int32_t n_keys;
     int32_t pos;      // the query's absolute position
     int32_t len;
+    int32_t q_len;
 };
 
 __device__ __forceinline__ RowInfo locate_row(const int32_t* __restrict__ cu_q_lens,
@@ -407,6 +410,7 @@ __device__ __forceinline__ RowInfo locate_row(const int32_t* __restrict__ cu_q_l
     r.n_keys = max(n, 0);
     r.pos = len - q_len + qi;
     r.len = len;
+    r.q_len = q_len;
     return r;
 }
 

@@ -25,7 +25,7 @@ struct StreamPart {
 // waves (one a KV head: half of what the decode kernel has in flight, which costs it little beside a neighbour that wants
 // nothing from HBM), all others step over the list, and a compute unit has one of each until the stream ends.  The whole call
 // 655 -> 600 us; 56 with eight chunks of 200 495 -> 445, 18 with two of 512 on up to 8192 keys 51 -> 38, 63 on 16384 with
-// one chunk of 64 774 -> 762.  Stream workgroups on every second compute unit 587, 479, -, 1199 us, on three of four 603, 429,
+// one chunk of 64 774 -> 762 (40 with 32 / 32 heads 1746 -> 1757, the only one of twenty-one that lost).  Stream workgroups on every second compute unit 587, 479, -, 1199 us, on three of four 603, 429,
 // -, 878, two a compute unit (a second round of them behind the first 512 workgroups) 616, 450, 42, 772.
 template <typename E>
 __global__ __launch_bounds__(kThreads, 2) void paged_jagged_mfma_kernel(
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kThreads, 2) void paged_jagged_mfma_kernel(
             stream.wgs, b % stream.head_groups, 0);
         return;
     }
-    list_body<true, E, NoMods, 128>(buf0, buf1, nullptr, nullptr, cache, q, out, lse, cu_q_lens, block_table, seq_lens,
+    list_body<true, kEitherList, E, NoMods, 128>(buf0, buf1, nullptr, nullptr, cache, q, out, lse, cu_q_lens, block_table, seq_lens,
                                     batch, num_q_heads, max_blocks, scale, causal, plan, blockIdx.x - streaming,
                                     gridDim.x - streaming);
 }

@@ -45,21 +45,31 @@ __device__ __forceinline__ void store_out4(void* out, int64_t i, float4 r)
 // dispatched: 65536 of them for a 2048-token prompt with 32 heads.)
 constexpr int kMergePairs = 8;
 
+// Partials by (query row, head): `nsplit` slots each, filled as sequence_chunk cuts the row's context.
+struct RowMerge {
+    const float* part_o;
+    const float* part_lse;
+    int64_t pairs;
+    int32_t blocks;          // of the launch, where it merges other partials too; 0 = none
+    int32_t batch, causal, chunk, nsplit, unit;
+    int32_t final_group;     // > 0: what a list beside the few-query stream wrote itself is left alone: rows of sequences with
+                             // q_len * final_group <= 16 (the stream's) and of contexts in one piece
+};
+
 template <int OUT>
-__global__ __launch_bounds__(256) void paged_attention_merge_kernel(
-    const float* __restrict__ part_o, const float* __restrict__ part_lse, void* __restrict__ out,
-    float* __restrict__ lse, const int32_t* __restrict__ cu_q_lens, const int32_t* __restrict__ seq_lens,
-    int32_t batch, int32_t num_q_heads, int32_t d, int32_t causal, int32_t chunk, int32_t nsplit, int32_t unit, int64_t pairs)
+__device__ __forceinline__ void merge_rows(const RowMerge& p, int64_t o_idx, void* __restrict__ out, float* __restrict__ lse,
+                                           const int32_t* __restrict__ cu_q_lens, const int32_t* __restrict__ seq_lens,
+                                           int32_t num_q_heads, int32_t d)
 {
-    const int64_t o_idx = (int64_t)blockIdx.x * kMergePairs + (threadIdx.x >> 5);
-    if (o_idx >= pairs) return;
+    if (o_idx >= p.pairs) return;
     const int lane = threadIdx.x & 31;
     const int32_t row = (int32_t)(o_idx / num_q_heads);
-    const RowInfo ri = locate_row(cu_q_lens, seq_lens, batch, row, causal);
-    const int32_t own = sequence_chunk(ri.len, chunk, nsplit, unit);
+    const RowInfo ri = locate_row(cu_q_lens, seq_lens, p.batch, row, p.causal);
+    const int32_t own = sequence_chunk(ri.len, p.chunk, p.nsplit, p.unit);
+    if (p.final_group > 0 && (ri.q_len * p.final_group <= 16 || own >= ri.len)) return;
     const int32_t n = (ri.n_keys + own - 1) / own;       // chunks that hold keys
-    const float* pl = part_lse + o_idx * nsplit;
-    const float* po = part_o + o_idx * nsplit * d;
+    const float* pl = p.part_lse + o_idx * p.nsplit;
+    const float* po = p.part_o + o_idx * p.nsplit * d;
 
     float M = -INFINITY;
     for (int32_t c = 0; c < n; ++c) M = fmaxf(M, pl[c]);
@@ -81,6 +91,14 @@ __global__ __launch_bounds__(256) void paged_attention_merge_kernel(
         store_out4<OUT>(out, o_idx * d + e, r);
     }
     if (lse && lane == 0) lse[o_idx] = !none ? M + logf(wsum) : -INFINITY;
+}
+
+template <int OUT>
+__global__ __launch_bounds__(256) void paged_attention_merge_kernel(
+    RowMerge rows, void* __restrict__ out, float* __restrict__ lse, const int32_t* __restrict__ cu_q_lens,
+    const int32_t* __restrict__ seq_lens, int32_t num_q_heads, int32_t d)
+{
+    merge_rows<OUT>(rows, (int64_t)blockIdx.x * kMergePairs + (threadIdx.x >> 5), out, lse, cu_q_lens, seq_lens, num_q_heads, d);
 }
 
 // Tile-stream layout: sequence s was cut by the workgroups seg_first[s] .. seg_last[s]; workgroup w left its
@@ -160,13 +178,19 @@ __global__ __launch_bounds__(kMergeThreads) void paged_attention_merge_stream_ke
     const float* __restrict__ part_o, const float* __restrict__ part_lse, void* __restrict__ out,
     float* __restrict__ lse, const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ seg_first,
     const int32_t* __restrict__ seg_last, int32_t num_q_heads, int32_t d, const int32_t* __restrict__ cu_q_lens,
-    int32_t num_kv_heads, ListMerge list)
+    int32_t num_kv_heads, ListMerge list, RowMerge by_row)
 {
     if (RAGGED && (int32_t)blockIdx.x < list.blocks) {
         merge_list<OUT>(list, blockIdx.x, out, lse, cu_q_lens, seq_lens, num_q_heads, d);
         return;
     }
-    const int32_t block = RAGGED ? (int32_t)blockIdx.x - list.blocks : (int32_t)blockIdx.x;
+    int32_t block = RAGGED ? (int32_t)blockIdx.x - list.blocks : (int32_t)blockIdx.x;
+    if (RAGGED && block < by_row.blocks) {
+        merge_rows<OUT>(by_row, (int64_t)block * (kMergeThreads / 32) + (threadIdx.x >> 5), out, lse, cu_q_lens, seq_lens,
+                        num_q_heads, d);
+        return;
+    }
+    if (RAGGED) block -= by_row.blocks;
     __shared__ float w_s[kMaxDecodeWGs + 1];
     __shared__ float red[4];
     const int32_t rows = RAGGED ? num_kv_heads * 16 : num_q_heads;   // partial rows per (workgroup, sequence)
@@ -231,6 +255,11 @@ __global__ __launch_bounds__(kMergeThreads) void paged_attention_merge_stream_ke
     if (lse && tid == 0) lse[o_idx] = (n > 0 && !no_keys) ? M + logf(wsum) : -INFINITY;
 }
 
+RowMerge row_merge(const AttnArgs& a, const float* part_o, const float* part_lse, int64_t pairs)
+{
+    return {part_o, part_lse, pairs, 0, a.batch, a.causal, a.plan.chunk, a.plan.nsplit, a.plan.unit, 0};
+}
+
 }  // namespace
 
 pa_status launch_merge(const AttnArgs& a, hipStream_t stream)
@@ -259,7 +288,13 @@ pa_status launch_merge(const AttnArgs& a, hipStream_t stream)
             const int64_t eighths = 8 * list.heads * (most < a.list_items ? most : a.list_items);
             list.blocks = (int32_t)(eighths < prefill::kListMergeGrid ? eighths : prefill::kListMergeGrid);
         }
-        const int64_t sblocks = list.blocks + (!a.stream_split ? 0 : ragged ? (int64_t)a.batch * a.cache.num_kv_heads * 16 : blocks);
+        RowMerge by_row = {};
+        if (a.rows_o) {
+            by_row = row_merge(a, a.rows_o, a.rows_lse, blocks);
+            by_row.blocks = (int32_t)((blocks + kMergeThreads / 32 - 1) / (kMergeThreads / 32));
+            by_row.final_group = a.num_q_heads / a.cache.num_kv_heads;
+        }
+        const int64_t sblocks = (int64_t)list.blocks + by_row.blocks + (!a.stream_split ? 0 : ragged ? (int64_t)a.batch * a.cache.num_kv_heads * 16 : blocks);
         if (sblocks > 0x7fffffffLL || a.dtype == PA_DTYPE_F32) return PA_ERR_UNSUPPORTED;
         auto kern = a.dtype == PA_DTYPE_BF16
                         ? (ragged ? paged_attention_merge_stream_kernel<PA_DTYPE_BF16, true>
@@ -268,16 +303,16 @@ pa_status launch_merge(const AttnArgs& a, hipStream_t stream)
                                   : paged_attention_merge_stream_kernel<PA_DTYPE_F16, false>);
         hipLaunchKernelGGL(kern, dim3((uint32_t)sblocks), dim3(kMergeThreads), 0, stream, a.part_o, a.part_lse, a.out,
                            a.lse, a.seq_lens, a.seg_first, a.seg_last, a.num_q_heads, a.cache.head_dim, a.cu_q_lens,
-                           a.cache.num_kv_heads, list);
+                           a.cache.num_kv_heads, list, by_row);
         return launch_status();
     }
     auto kern = a.dtype == PA_DTYPE_BF16  ? paged_attention_merge_kernel<PA_DTYPE_BF16>
                 : a.dtype == PA_DTYPE_F16 ? paged_attention_merge_kernel<PA_DTYPE_F16>
                                           : paged_attention_merge_kernel<PA_DTYPE_F32>;
     if (a.cache.head_dim % 4 != 0) return PA_ERR_UNSUPPORTED;   // (16-byte rows: every supported element type has it)
-    hipLaunchKernelGGL(kern, dim3((uint32_t)((blocks + kMergePairs - 1) / kMergePairs)), dim3(256), 0, stream, a.part_o,
-                       a.part_lse, a.out, a.lse, a.cu_q_lens, a.seq_lens, a.batch, a.num_q_heads, a.cache.head_dim,
-                       a.causal, a.plan.chunk, a.plan.nsplit, a.plan.unit, blocks);
+    hipLaunchKernelGGL(kern, dim3((uint32_t)((blocks + kMergePairs - 1) / kMergePairs)), dim3(256), 0, stream,
+                       row_merge(a, a.part_o, a.part_lse, blocks), a.out, a.lse, a.cu_q_lens, a.seq_lens, a.num_q_heads,
+                       a.cache.head_dim);
     return launch_status();
 }
 

@@ -608,6 +608,9 @@ __device__ __forceinline__ void attend_tile(const char* buf, const uint32_t (&kx
     }
 }
 
+// Where an item and its partial go.
+constexpr int kPlainGrid = 0, kSlotList = 1, kEitherList = 2;
+
 // What a workgroup works on: sequence, its query range and context length, row tile, head group, and its chunk of the
 // context (chunks == 1: all of it).
 struct WorkItem {
@@ -622,7 +625,8 @@ struct WorkItem {
 // in V always leaves its mark on some accumulator of the row tile, so the tile loop need not look for it: the accumulators
 // are looked at once, at the end (append + prefill of 2 prompts of 700 and 950 tokens, 32 / 32 heads, D = 96: 36.1 us, 38.0 with
 // a test of V's fragments on every masked tile; 8 prompts of 33 .. 900, 8 / 2 heads, D = 112: 25.7, 30.5).
-template <bool PRECISE, bool UNIFORM, bool LIST, bool CAREFUL, typename E, typename M, int D>
+// LIST: the kind of list the item comes from (0: a plain grid).
+template <bool PRECISE, bool UNIFORM, int LIST, bool CAREFUL, typename E, typename M, int D>
 __device__ __forceinline__ bool prefill_body(
     char* buf0, char* buf1, int32_t* docs0, int32_t* docs1, const CacheView& cache, const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float* __restrict__ lse,
     const int32_t* __restrict__ block_table, int32_t num_q_heads, int32_t max_blocks, float scale, int32_t causal, const PrefillPlan& plan, int32_t precise_keys,
@@ -933,7 +937,7 @@ __device__ __forceinline__ bool prefill_body(
                           o[i / 4][4 * (i % 4) + 3] * inv};
         else return float4{o[i][0] * inv, o[i][1] * inv, o[i][2] * inv, o[i][3] * inv};
     };
-    if (LIST && own.slot >= 0) {
+    if (LIST != kPlainGrid && own.slot >= 0) {
         // work-list mode: normalised accumulators lane by lane (whole cache lines per store), LSE per row.  The layout is
         // that of 32 rows a wave: 16-byte piece i of lane (row, group of two), piece = 8 columns.
         float4* po = reinterpret_cast<float4*>(plan.list_o) + (int64_t)own.slot * (list_slot_floats(D) / 4) +
@@ -946,7 +950,7 @@ __device__ __forceinline__ bool prefill_body(
             plan.list_lse[(int64_t)own.slot * kBM + R * wave + ql] = bad ? INFINITY : row_lse;
         return false;
     }
-    if (!LIST && own.chunks > 1) {
+    if (LIST != kSlotList && own.chunks > 1) {
         // partial of this chunk: normalised output in fp32 and the natural-log LSE over the chunk's keys
         const int64_t pidx = row * plan.nsplit + split;
         float* prow = plan.part_o + pidx * D;
@@ -969,8 +973,9 @@ __device__ __forceinline__ bool prefill_body(
     return false;
 }
 
-// The work-list mode of prefill_tiles.h: items first, first + step, ... of the call's list.
-template <bool UNIFORM, typename E, typename M, int D>
+// The work-list mode of prefill_tiles.h: items first, first + step, ... of the call's list.  LIST: kSlotList (partials by slot) or
+// kEitherList (also, with chunk_unit, contexts cut by their own lengths and partials by row, as a plain grid leaves them).
+template <bool UNIFORM, int LIST, typename E, typename M, int D>
 __device__ __forceinline__ void list_body(
     char* buf0, char* buf1, int32_t* docs0, int32_t* docs1, const CacheView& cache, const uint16_t* __restrict__ q,
     uint16_t* __restrict__ out, float* __restrict__ lse, const int32_t* __restrict__ cu_q_lens,
@@ -982,9 +987,11 @@ __device__ __forceinline__ void list_body(
     // A workgroup steps over the list by `step`.  Between two items nothing has to be waited for: a
     // tile loop ends with the barrier behind its last read of LDS.  The thread index is made opaque for each item:
     // what the body derives from it would otherwise be kept in registers across the loop, which spills.
-    const WorkList list = make_list(cu_q_lens, seq_lens, batch, plan.log2_pack,
-                                    plan.skip_small ? plan.group : kNoSmallGroup, heads,
-                                    plan.list_unit, D, (int)(threadIdx.x & 63));
+    constexpr bool kByLength = LIST == kEitherList;
+    WorkList list = make_list(cu_q_lens, seq_lens, batch, plan.log2_pack, plan.skip_small ? plan.group : kNoSmallGroup, heads,
+                              plan.list_unit, D, (int)(threadIdx.x & 63));
+    list.nsplit = plan.nsplit;
+    list.unit = plan.chunk_unit;
     int32_t precise_keys = 0;
     if constexpr (!kTwoTermOnly<D>)
         precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal, 0, (int)(threadIdx.x & 63));
@@ -992,28 +999,28 @@ __device__ __forceinline__ void list_body(
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
         ListItem it;
-        if (!list_locate<false>(it, list, cu_q_lens, seq_lens, (int32_t)(index / (uint32_t)heads), tid & 63)) return;
+        if (!list_locate<false, kByLength>(it, list, cu_q_lens, seq_lens, (int32_t)(index / (uint32_t)heads), tid & 63)) return;
         own.s = it.s;
         own.hg = (int32_t)(index % (uint32_t)heads);
         own.tile = it.tile;
         own.split = it.split;
         own.chunks = it.chunks;
-        own.chunk = list.chunk;
-        own.slot = it.chunks > 1 ? list_slot(it, it.split, heads, own.hg) : -1;
+        own.slot = it.chunks > 1 && !(kByLength && list.unit > 0) ? list_slot(it, it.split, heads, own.hg) : -1;
         own.q_begin = cu_q_lens[it.s];
         own.q_end = cu_q_lens[it.s + 1];
         own.len = seq_lens[it.s];
+        own.chunk = list_chunk<kByLength>(list, own.len);
         if constexpr (!kTwoTermOnly<D>)
-            prefill_body<false, UNIFORM, true, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
+            prefill_body<false, UNIFORM, LIST, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
                                                         num_q_heads, max_blocks, scale, causal, plan, precise_keys, own,
                                                         tid);
         const bool again =
-            prefill_body<true, UNIFORM, true, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
+            prefill_body<true, UNIFORM, LIST, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
                                                               num_q_heads, max_blocks, scale, causal, plan, precise_keys,
                                                               own, tid);
         if constexpr (kTwoTermOnly<D>)
             if (again)
-                prefill_body<true, UNIFORM, true, true, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
+                prefill_body<true, UNIFORM, LIST, true, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
                                                                  num_q_heads, max_blocks, scale, causal, plan,
                                                                  precise_keys, own, tid);
     }
@@ -1047,7 +1054,7 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
     // two-term rule right behind them (vector loads): one round trip to memory instead of three in a row in front
     // of the query and block-table loads that depend on them.
     if constexpr (LIST) {
-        list_body<UNIFORM, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, cu_q_lens, block_table, seq_lens, batch,
+        list_body<UNIFORM, kSlotList, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, cu_q_lens, block_table, seq_lens, batch,
                                     num_q_heads, max_blocks, scale, causal, plan, blockIdx.x, gridDim.x);
     } else {
         // Workgroups are dispatched in blockIdx.x order: the row-tile index is the slowest-varying part and runs
@@ -1082,16 +1089,16 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
             precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal,
                                              (M::kWindow && plan.mods.window > 0) ? plan.mods.window : 0,
                                              (int)(threadIdx.x & 63));
-            prefill_body<false, UNIFORM, LIST, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table, num_q_heads,
+            prefill_body<false, UNIFORM, kPlainGrid, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table, num_q_heads,
                                                         max_blocks, scale, causal, plan, precise_keys, own, (int)threadIdx.x);
         }
         const bool again =
-            prefill_body<true, UNIFORM, LIST, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
+            prefill_body<true, UNIFORM, kPlainGrid, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
                                                               num_q_heads, max_blocks, scale, causal, plan, precise_keys, own,
                                                               (int)threadIdx.x);
         if constexpr (kTwoTermOnly<D>)
             if (again)
-                prefill_body<true, UNIFORM, LIST, true, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
+                prefill_body<true, UNIFORM, kPlainGrid, true, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table,
                                                                  num_q_heads, max_blocks, scale, causal, plan, precise_keys,
                                                                  own, (int)threadIdx.x);
     }

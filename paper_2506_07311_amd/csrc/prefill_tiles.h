@@ -147,6 +147,7 @@ __device__ __forceinline__ ListSeq list_seq(const int32_t* __restrict__ cu_q_len
 // batches of up to 64 sequences, this lane's sequence, so that finding an item needs no further load.
 struct WorkList {
     int32_t chunk;
+    int32_t nsplit, unit;    // BY_LENGTH with unit > 0: each sequence's chunk from its own length instead (sequence_chunk)
     int32_t small_group, log2_pack, heads, batch;
     ListSeq own;
 };
@@ -200,14 +201,20 @@ struct ListItem {
     int32_t chunks;      // chunks of the sequence; 1 = the item writes its rows, > 1 = a partial
     int32_t slot;        // partial of chunk 0 of the sequence's last row tile, per head group
 };
-template <bool SPLIT_TILES>
+template <bool BY_LENGTH>
+__device__ __forceinline__ int32_t list_chunk(const WorkList& w, int32_t len)
+{
+    return BY_LENGTH && w.unit > 0 ? sequence_chunk(len, 0, w.nsplit, w.unit) : w.chunk;
+}
+template <bool SPLIT_TILES, bool BY_LENGTH = false>
 __device__ __forceinline__ bool list_locate(ListItem& it, const WorkList& w, const int32_t* __restrict__ cu_q_lens,
                                             const int32_t* __restrict__ seq_lens, int32_t idx, int lane)
 {
     int32_t items_before = 0, slots_before = 0;
     for (int32_t blk = 0; blk < w.batch; blk += 64) {
         const ListSeq q = blk == 0 ? w.own : list_seq(cu_q_lens, seq_lens, w.batch, blk + lane, w.log2_pack, w.small_group);
-        const int32_t chunks = max((q.len + w.chunk - 1) / w.chunk, 1);
+        const int32_t chunk = list_chunk<BY_LENGTH>(w, q.len);
+        const int32_t chunks = max((q.len + chunk - 1) / chunk, 1);
         const int32_t slots = chunks > 1 ? q.tiles * chunks : 0;
         const int32_t n = !SPLIT_TILES ? q.tiles * chunks : chunks > 1 ? q.tiles : 0;
         int32_t inc = n, sinc = slots;                        // inclusive scans over the 64 lanes

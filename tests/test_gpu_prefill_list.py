@@ -79,16 +79,13 @@ def test_chunks_and_single_queries_in_one_launch(pa, oracle, Hq, Hkv, P, dtype, 
     assert torch.equal(outs[0], outs[1])
 
 
-@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,P,dtype,causal,whole", [
-    ([2100, 0, 700, 1, 1500, 64, 65], [530, 0, 1, 1, 129, 2, 17], 32, 8, 16, torch.bfloat16, True, 1),
-    ([2047, 300, 33], [33, 1, 1], 8, 8, 64, torch.float16, False, 1),         # one key short of the grid that is cut
-    ([2100, 0, 700, 1, 1500, 64, 65], [130, 0, 1, 1, 129, 2, 17], 16, 4, 16, torch.bfloat16, True, 0),    # few row tiles
-    ([4095, 300, 33], [33, 1, 1], 8, 8, 64, torch.float16, False, 0),         # one key short of the list that is cut
-    ([40] * 70 + [600, 500], [1] * 70 + [250, 3], 4, 4, 32, torch.float16, True, 1),
-    ([500, 700, 900], [100, 101, 102], 8, 4, 16, torch.bfloat16, True, 0)])   # nothing for the stream, and may be
-def test_uncut_chunks_and_single_queries_in_one_launch(pa, oracle, lens, q_lens, Hq, Hkv, P, dtype, causal, whole):
-    """Contexts below the length that the list cuts: whole row tiles beside the stream, no partials of the list's, or, with
-    fewer row tiles than would fill the machine, the grid that is cut and the stream behind it."""
+@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,P,dtype,causal", [
+    ([2100, 0, 700, 1, 1500, 64, 65], [130, 0, 1, 1, 129, 2, 17], 16, 4, 16, torch.bfloat16, True),
+    ([4095, 300, 33], [33, 1, 1], 8, 8, 64, torch.float16, False),            # one key short of the list that is cut
+    ([40] * 70 + [600, 500], [1] * 70 + [250, 3], 4, 4, 32, torch.float16, True),
+    ([500, 700, 900], [100, 101, 102], 8, 4, 16, torch.bfloat16, True)])      # nothing for the stream, and may be
+def test_uncut_chunks_and_single_queries_in_one_launch(pa, oracle, lens, q_lens, Hq, Hkv, P, dtype, causal):
+    """Contexts below the length that the list has slots for: row tiles beside the stream, no partials by slot."""
     from paper_2506_07311_amd import binding
     w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=128, page_size=P,
                         dtype=dtype, causal=causal, seed=217, device=DEV)
@@ -99,7 +96,7 @@ def test_uncut_chunks_and_single_queries_in_one_launch(pa, oracle, lens, q_lens,
         parity.check_step(pa, oracle, w, f"{lens} {q_lens}")
         counts = [binding.pa_profile_read(k)[0] for k in ("paged_jagged_mfma", "paged_decode_mfma", "paged_prefill_mfma",
                                                           "paged_attention_merge_list")]
-        assert counts == ([1, 0, 0, 0] if whole else [0, 1, 1, 0] if may_be_small else [0, 0, 1, 0])
+        assert counts == ([1, 0, 0, 0] if may_be_small else [0, 0, 1, 0])
     finally:
         binding.pa_profile_enable(False)
         binding.pa_profile_reset()
@@ -194,27 +191,41 @@ def test_chunks_of_the_list_fill_the_workgroups_that_fit_at_once(pa, d, chunks):
     assert int((ws != -1).sum()) == 200 * 32 * (d + 1) * chunks
 
 
-@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,whole", [
-    ([4095, 4095, 4000, 300, 33], [520, 520, 520, 1, 1], 32, 8, 1),           # three chunks, row tiles for them all
-    ([4095, 4095, 4000, 300, 33], [500, 500, 500, 1, 1], 32, 8, 0),           # not quite
-    ([4000, 4000], [200, 1], 32, 8, 0),
-    ([2100, 300, 200], [520, 1, 1], 32, 8, 1),                                # two chunks
-    ([2100, 300, 200], [500, 1, 1], 32, 8, 0)])
-def test_short_jagged_calls_walk_whole_contexts_only_with_a_full_machine(pa, lens, q_lens, Hq, Hkv, whole):
-    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
-        pytest.skip("the sizes are those of 256 compute units")
+@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,P,dtype,causal,nsplit,chunks", [
+    ([4000, 4000], [200, 1], 32, 8, 16, torch.bfloat16, True, 3, [3, 0]),
+    ([4095, 1300, 900, 300, 33, 0], [64, 64, 64, 1, 1, 0], 8, 8, 128, torch.float16, True, 3, [3, 2, 0, 0, 0, 0]),
+    ([2100, 1060, 200], [500, 300, 1], 8, 4, 16, torch.bfloat16, False, 2, [2, 2, 0]),
+    ([40] * 70 + [3000], [1] * 70 + [90], 4, 4, 32, torch.bfloat16, True, 2, [0] * 70 + [2]),
+    ([1900, 300], [300, 1], 8, 4, 16, torch.bfloat16, True, 1, [0, 0])])
+def test_short_jagged_calls_cut_each_context_by_its_length(pa, lens, q_lens, Hq, Hkv, P, dtype, causal, nsplit, chunks):
+    """The list beside the stream cuts what the plain grid would: counted by the partials that it leaves, none of them of
+    contexts in one piece or of the stream's sequences.  A second call on the same workspace gives the same bits."""
     from paper_2506_07311_amd import binding
-    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=128, page_size=16,
-                        dtype=torch.bfloat16, causal=True, seed=220, device=DEV)
-    binding.pa_profile_reset()
-    binding.pa_profile_enable(True)
-    try:
-        out, _ = parity.gpu_step(pa, w)
-        assert binding.pa_profile_read("paged_jagged_mfma")[0] == whole
-    finally:
-        binding.pa_profile_enable(False)
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=128, page_size=P,
+                        dtype=dtype, causal=causal, seed=220, device=DEV)
+    pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
+    nbytes = pa.paged_attention_workspace_bytes(w.batch, Hq, 128, w.total_q, w.max_seq_len)
+    ws = torch.full((-(-nbytes // 4),), -1, dtype=torch.int32, device=DEV)
+    lse = torch.full((w.total_q, Hq), float("nan"), device=DEV)
+    outs = []
+    for _ in range(2):
         binding.pa_profile_reset()
-    parity.assert_close(parity.to_f64(out), parity.to_f64(_reference(w)), torch.bfloat16, f"{lens} {q_lens}")
+        binding.pa_profile_enable(True)
+        try:
+            outs.append(pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, w.cu_q_lens, w.max_q_len, w.block_table,
+                                                   w.seq_lens, w.max_seq_len, w.scale, causal, lse=lse, workspace=ws))
+            torch.cuda.synchronize()
+            counts = [binding.pa_profile_read(k)[0] for k in ("paged_jagged_mfma", "paged_attention_merge_kernel")]
+            assert counts == [1, 1]
+        finally:
+            binding.pa_profile_enable(False)
+            binding.pa_profile_reset()
+    assert torch.equal(outs[0], outs[1])
+    parity.assert_close(parity.to_f64(outs[0]), parity.to_f64(_reference(w)), dtype, f"{lens} {q_lens}")
+    assert torch.isfinite(lse).all()
+    if nsplit > 1:
+        rows = ws[:w.total_q * Hq * nsplit * 128]
+        assert int((rows != -1).sum()) == 128 * Hq * sum(n * c for n, c in zip(q_lens, chunks))
 
 
 def test_a_short_jagged_call_without_room_for_the_stream_keeps_its_chunks(pa, oracle):
