@@ -213,6 +213,7 @@ SplitPlan even_prefill_split(const SplitPlan& most, int32_t batch, int64_t wgs, 
             best_us = us;
             best.nsplit = n;
             best.chunk = n > 1 ? (int32_t)chunk : max_seq_len;
+            best.unit = n > 1 ? (int32_t)unit : 0;
         }
     }
     return best;

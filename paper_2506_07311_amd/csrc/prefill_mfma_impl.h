@@ -608,8 +608,8 @@ __device__ __forceinline__ void attend_tile(const char* buf, const uint32_t (&kx
     }
 }
 
-// Where an item and its partial go.
-constexpr int kPlainGrid = 0, kSlotList = 1, kEitherList = 2;
+// Where an item and its partial go.  (kLengthGrid: a plain grid in the order of contexts that are cut by their own lengths.)
+constexpr int kPlainGrid = 0, kSlotList = 1, kEitherList = 2, kLengthGrid = 3;
 
 // What a workgroup works on: sequence, its query range and context length, row tile, head group, and its chunk of the
 // context (chunks == 1: all of it).
@@ -1028,13 +1028,14 @@ __device__ __forceinline__ void list_body(
 
 // Both instantiations live in one kernel as two separate code paths (each with its own tile loop); a
 // workgroup runs exactly one of them, decided by its context length.
-// LIST: the work-list mode of prefill_tiles.h.
+// LIST: kSlotList, the work-list mode of prefill_tiles.h; kPlainGrid; or kLengthGrid (an instantiation of its own: deciding it
+// here by plan.chunk_unit scattered the first loads and cost a prompt of 128 tokens 0.4 us of 9).
 // Waves a SIMD: two, three at head_dim 64.  Hooks that keep more state spill under that bound: document masks and user
 // modifications 4 - 6 registers at head_dim 64, 12 and 24 at 256, slopes 7 at 256, and nothing at 128.  us for 4 x 2048, 2 x 1200 and
 // 1 x 500 tokens (32 / 8 heads, 16 / 8 at 256), one wave less and no spill / like this: at head_dim 64 documents 105 / 89,
 // 34.0 / 34.8, 19.0 / 18.7, prefix-LM 504 / 399, 142 / 96, 35 / 35; at 256, where that is four waves of 32 rows, documents
 // 191 / 173, 72 / 53, 35 / 32, prefix-LM 725 / 638, 226 / 198, 56 / 47, slopes 350 / 270, 100 / 77, 46 / 37.
-template <bool UNIFORM, typename E, typename M, int D, bool LIST = false>
+template <bool UNIFORM, typename E, typename M, int D, int LIST = kPlainGrid>
 __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_prefill_mfma_kernel(
     CacheView cache, const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float* __restrict__ lse,
     const int32_t* __restrict__ cu_q_lens, const int32_t* __restrict__ block_table,
@@ -1053,37 +1054,40 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
     // The workgroup's own lengths are requested first (scalar loads), the scan of every sequence's lengths for the
     // two-term rule right behind them (vector loads): one round trip to memory instead of three in a row in front
     // of the query and block-table loads that depend on them.
-    if constexpr (LIST) {
+    if constexpr (LIST == kSlotList) {
         list_body<UNIFORM, kSlotList, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, cu_q_lens, block_table, seq_lens, batch,
                                     num_q_heads, max_blocks, scale, causal, plan, blockIdx.x, gridDim.x);
     } else {
         // Workgroups are dispatched in blockIdx.x order: the row-tile index is the slowest-varying part and runs
         // backwards, so the whole grid is handed out heaviest (latest causal tiles) first; the context chunks of a
-        // tile follow each other.  Where contexts are cut by their own lengths (chunk_unit) they are much longer than the query
+        // tile follow each other.  Where contexts are cut by their own lengths (kLengthGrid) they are much longer than the query
         // ranges and no tile is heavy: there the sequence is the slowest part and then the chunk, so that the workgroups with
         // keys stand side by side and get a compute unit each, whatever is empty between them (128 queries on 32768 keys and
-        // on 2000 three times 205 -> 160 us, 256 on 32768 and on 16000 256 -> 221, 2048 keys of a call for up to 32768 51 -> 44).
+        // on 2000 three times 206 -> 119 us, 256 on 32768 and on 16000 285 -> 224, 500 on 2048 in a call for up to 32768
+        // 65 -> 42).
         WorkItem own;
         const int32_t heads = num_q_heads >> plan.log2_pack;
-        const int32_t hb = heads * (plan.chunk_unit > 0 ? 1 : batch);
+        constexpr bool kByLength = LIST == kLengthGrid;
+        const int32_t hb = heads * (kByLength ? 1 : batch);
         const int32_t slow = (int32_t)(blockIdx.x / (uint32_t)hb);
         const int32_t rest = (int32_t)(blockIdx.x % (uint32_t)hb);
         own.hg = rest % heads;
-        if (plan.chunk_unit > 0) {
+        if constexpr (kByLength) {
             own.tile = num_tiles - 1 - slow % num_tiles;
             own.split = slow / num_tiles % plan.nsplit;
             own.s = slow / num_tiles / plan.nsplit;
         } else {
+            own.s = rest / heads;
             own.tile = num_tiles - 1 - slow / plan.nsplit;
             own.split = slow % plan.nsplit;
-            own.s = rest / heads;
         }
         own.chunks = plan.nsplit;
+        own.chunk = plan.chunk;
         own.slot = -1;
         own.q_begin = cu_q_lens[own.s];
         own.q_end = cu_q_lens[own.s + 1];
         own.len = seq_lens[own.s];
-        own.chunk = sequence_chunk(own.len, plan.chunk, plan.nsplit, plan.chunk_unit);
+        if constexpr (kByLength) own.chunk = sequence_chunk(own.len, plan.chunk, plan.nsplit, plan.chunk_unit);
         int32_t precise_keys = 0;
         if constexpr (!kTwoTermOnly<D>) {
             precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal,
@@ -1106,6 +1110,10 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
 
 }  // namespace
 
+// The plain grid's kernel in the order that the plan asks for.
+#define PA_GRID_KERNEL(UNIFORM, E, M)                                                                                  \
+    (plan.chunk_unit > 0 ? paged_prefill_mfma_kernel<UNIFORM, E, M, D, kLengthGrid> : paged_prefill_mfma_kernel<UNIFORM, E, M, D>)
+
 // Every kernel instantiation of one head_dim; defined in that head_dim's translation unit.
 template <int D>
 pa_status launch_prefill_mfma_dim(const AttnArgs& a, const PrefillPlan& plan, int64_t blocks, int64_t tiles,
@@ -1115,10 +1123,10 @@ pa_status launch_prefill_mfma_dim(const AttnArgs& a, const PrefillPlan& plan, in
     if constexpr (kTwoTermOnly<D>) {   // (prefill_mfma_supported takes no hooks and no pages below 16 tokens here)
         if (a.has_mods || a.cache.page_size < 16) return PA_ERR_UNSUPPORTED;
         auto kern = a.dtype == PA_DTYPE_BF16
-                        ? (plan.list_items > 0 ? paged_prefill_mfma_kernel<true, ElemBf16, NoMods, D, true>
-                                               : paged_prefill_mfma_kernel<true, ElemBf16, NoMods, D>)
-                        : (plan.list_items > 0 ? paged_prefill_mfma_kernel<true, ElemF16, NoMods, D, true>
-                                               : paged_prefill_mfma_kernel<true, ElemF16, NoMods, D>);
+                        ? (plan.list_items > 0 ? paged_prefill_mfma_kernel<true, ElemBf16, NoMods, D, kSlotList>
+                                               : PA_GRID_KERNEL(true, ElemBf16, NoMods))
+                        : (plan.list_items > 0 ? paged_prefill_mfma_kernel<true, ElemF16, NoMods, D, kSlotList>
+                                               : PA_GRID_KERNEL(true, ElemF16, NoMods));
         hipLaunchKernelGGL(kern, grid, dim3(RowGeo<D>::kThreads), 0, stream, a.cache, (const uint16_t*)a.q, (uint16_t*)a.out, a.lse,
                            a.cu_q_lens, a.block_table, a.seq_lens, a.batch, (int32_t)tiles, a.num_q_heads, a.max_blocks,
                            a.scale, a.causal, plan);
@@ -1136,11 +1144,11 @@ pa_status launch_prefill_mfma_dim(const AttnArgs& a, const PrefillPlan& plan, in
     typedef std::conditional_t<(D > 128), WindowCap, WindowScore> Cap;
     const bool windowed = D > 128 && a.has_mods && !a.mods.alibi_slopes && !(a.mods.softcap > 0.f);
     const bool capped = D > 128 && a.mods.softcap > 0.f && !a.mods.alibi_slopes;
-    auto kern = paged_prefill_mfma_kernel<true, ElemBf16, NoMods, D>;
+    auto kern = PA_GRID_KERNEL(true, ElemBf16, NoMods);
     if (plan.list_items > 0) {                            // (prefill_list_supported)
         if (a.has_mods || !uniform) return PA_ERR_UNSUPPORTED;
-        kern = a.dtype == PA_DTYPE_BF16 ? paged_prefill_mfma_kernel<true, ElemBf16, NoMods, D, true>
-                                        : paged_prefill_mfma_kernel<true, ElemF16, NoMods, D, true>;
+        kern = a.dtype == PA_DTYPE_BF16 ? paged_prefill_mfma_kernel<true, ElemBf16, NoMods, D, kSlotList>
+                                        : paged_prefill_mfma_kernel<true, ElemF16, NoMods, D, kSlotList>;
     } else if (a.mods.user_mod) {                         // a user modification: one instantiation per listed struct
         bool found = false;
 #define PA_USER_CASE(U)                                                                                     \
@@ -1148,35 +1156,35 @@ pa_status launch_prefill_mfma_dim(const AttnArgs& a, const PrefillPlan& plan, in
             typedef Mods<true, true, true, U> UM;                                                           \
             found = true;                                                                                   \
             if (a.dtype == PA_DTYPE_BF16)                                                                   \
-                kern = uniform ? paged_prefill_mfma_kernel<true, ElemBf16, UM, D>                           \
-                               : paged_prefill_mfma_kernel<kLargePagesOnly, ElemBf16, UM, D>;                         \
+                kern = uniform ? PA_GRID_KERNEL(true, ElemBf16, UM)                           \
+                               : PA_GRID_KERNEL(kLargePagesOnly, ElemBf16, UM);                         \
             else                                                                                            \
-                kern = uniform ? paged_prefill_mfma_kernel<true, ElemF16, UM, D>                            \
-                               : paged_prefill_mfma_kernel<kLargePagesOnly, ElemF16, UM, D>;                          \
+                kern = uniform ? PA_GRID_KERNEL(true, ElemF16, UM)                            \
+                               : PA_GRID_KERNEL(kLargePagesOnly, ElemF16, UM);                          \
         }
         PA_USER_MODS(PA_USER_CASE)
 #undef PA_USER_CASE
         if (!found) return PA_ERR_INVALID_ARG;
     } else if (a.has_mods && a.mods.doc_ids) {
         if (a.dtype == PA_DTYPE_BF16)
-            kern = uniform ? paged_prefill_mfma_kernel<true, ElemBf16, AllMods, D>
-                           : paged_prefill_mfma_kernel<kLargePagesOnly, ElemBf16, AllMods, D>;
+            kern = uniform ? PA_GRID_KERNEL(true, ElemBf16, AllMods)
+                           : PA_GRID_KERNEL(kLargePagesOnly, ElemBf16, AllMods);
         else
-            kern = uniform ? paged_prefill_mfma_kernel<true, ElemF16, AllMods, D>
-                           : paged_prefill_mfma_kernel<kLargePagesOnly, ElemF16, AllMods, D>;
+            kern = uniform ? PA_GRID_KERNEL(true, ElemF16, AllMods)
+                           : PA_GRID_KERNEL(kLargePagesOnly, ElemF16, AllMods);
     } else if (a.dtype == PA_DTYPE_BF16) {
         if (windowed) kern = paged_prefill_mfma_kernel<true, ElemBf16, Window, D>;
-        else if (capped) kern = paged_prefill_mfma_kernel<true, ElemBf16, Cap, D>;
-        else if (a.has_mods) kern = uniform ? paged_prefill_mfma_kernel<true, ElemBf16, WindowScore, D>
-                                       : paged_prefill_mfma_kernel<kLargePagesOnly, ElemBf16, WindowScore, D>;
-        else if (!uniform) kern = paged_prefill_mfma_kernel<kLargePagesOnly, ElemBf16, NoMods, D>;
+        else if (capped) kern = PA_GRID_KERNEL(true, ElemBf16, Cap);
+        else if (a.has_mods) kern = uniform ? PA_GRID_KERNEL(true, ElemBf16, WindowScore)
+                                       : PA_GRID_KERNEL(kLargePagesOnly, ElemBf16, WindowScore);
+        else if (!uniform) kern = PA_GRID_KERNEL(kLargePagesOnly, ElemBf16, NoMods);
     } else {
         if (windowed) kern = paged_prefill_mfma_kernel<true, ElemF16, Window, D>;
-        else if (capped) kern = paged_prefill_mfma_kernel<true, ElemF16, Cap, D>;
-        else if (a.has_mods) kern = uniform ? paged_prefill_mfma_kernel<true, ElemF16, WindowScore, D>
-                                       : paged_prefill_mfma_kernel<kLargePagesOnly, ElemF16, WindowScore, D>;
-        else kern = uniform ? paged_prefill_mfma_kernel<true, ElemF16, NoMods, D>
-                            : paged_prefill_mfma_kernel<kLargePagesOnly, ElemF16, NoMods, D>;
+        else if (capped) kern = PA_GRID_KERNEL(true, ElemF16, Cap);
+        else if (a.has_mods) kern = uniform ? PA_GRID_KERNEL(true, ElemF16, WindowScore)
+                                       : PA_GRID_KERNEL(kLargePagesOnly, ElemF16, WindowScore);
+        else kern = uniform ? PA_GRID_KERNEL(true, ElemF16, NoMods)
+                            : PA_GRID_KERNEL(kLargePagesOnly, ElemF16, NoMods);
     }
     hipLaunchKernelGGL(kern, grid, dim3(RowGeo<D>::kThreads), 0, stream, a.cache, (const uint16_t*)a.q, (uint16_t*)a.out, a.lse,
                        a.cu_q_lens, a.block_table, a.seq_lens, a.batch, (int32_t)tiles, a.num_q_heads, a.max_blocks,
@@ -1184,5 +1192,7 @@ pa_status launch_prefill_mfma_dim(const AttnArgs& a, const PrefillPlan& plan, in
     return launch_status();
     }
 }
+
+#undef PA_GRID_KERNEL
 
 }  // namespace pa

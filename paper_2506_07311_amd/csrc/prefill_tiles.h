@@ -77,7 +77,6 @@ struct PrefillPlan {
     int32_t log2_pack;    // query heads of one KV head packed into a row tile (1 << log2_pack divides the group size)
     int32_t group;        // query heads per KV head
     int32_t chunk;        // context tokens per workgroup (multiple of 64 and of the page size when nsplit > 1)
-    int32_t chunk_unit;   // > 0: chunks by each sequence's own length instead (sequence_chunk)
     int32_t nsplit;       // chunks along the grid; > 1: partials go to part_o / part_lse for the merge kernel
     int32_t skip_small;   // 1: sequences with q_len * G <= 16 are computed by the decode kernel, not here
     int32_t list_items;   // > 0: work-list mode (below); at most list_items x head groups items, the grid steps over them
@@ -87,6 +86,7 @@ struct PrefillPlan {
     float* part_o;        // [total_q, Hq, nsplit, head_dim]
     float* part_lse;      // [total_q, Hq, nsplit]
     ModArgs mods;         // mask / score hooks (used by the instantiations that have them)
+    int32_t chunk_unit;   // > 0: chunks by each sequence's own length instead (sequence_chunk; kLengthGrid, kEitherList)
 };
 
 PrefillPlan make_plan(const AttnArgs& a);
