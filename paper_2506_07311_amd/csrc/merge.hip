@@ -294,7 +294,8 @@ pa_status launch_merge(const AttnArgs& a, hipStream_t stream)
             by_row.blocks = (int32_t)((blocks + kMergeThreads / 32 - 1) / (kMergeThreads / 32));
             by_row.final_group = a.num_q_heads / a.cache.num_kv_heads;
         }
-        const int64_t sblocks = (int64_t)list.blocks + by_row.blocks + (!a.stream_split ? 0 : ragged ? (int64_t)a.batch * a.cache.num_kv_heads * 16 : blocks);
+        const int64_t sblocks = (int64_t)list.blocks + by_row.blocks +
+                                (!a.stream_split ? 0 : ragged ? (int64_t)a.batch * a.cache.num_kv_heads * 16 : blocks);
         if (sblocks > 0x7fffffffLL || a.dtype == PA_DTYPE_F32) return PA_ERR_UNSUPPORTED;
         auto kern = a.dtype == PA_DTYPE_BF16
                         ? (ragged ? paged_attention_merge_stream_kernel<PA_DTYPE_BF16, true>

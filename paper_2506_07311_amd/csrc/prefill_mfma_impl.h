@@ -1055,8 +1055,8 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
     // two-term rule right behind them (vector loads): one round trip to memory instead of three in a row in front
     // of the query and block-table loads that depend on them.
     if constexpr (LIST == kSlotList) {
-        list_body<UNIFORM, kSlotList, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, cu_q_lens, block_table, seq_lens, batch,
-                                    num_q_heads, max_blocks, scale, causal, plan, blockIdx.x, gridDim.x);
+        list_body<UNIFORM, kSlotList, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, cu_q_lens, block_table, seq_lens,
+                                               batch, num_q_heads, max_blocks, scale, causal, plan, blockIdx.x, gridDim.x);
     } else {
         // Workgroups are dispatched in blockIdx.x order: the row-tile index is the slowest-varying part and runs
         // backwards, so the whole grid is handed out heaviest (latest causal tiles) first; the context chunks of a

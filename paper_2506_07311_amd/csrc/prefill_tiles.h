@@ -107,8 +107,8 @@ PrefillPlan make_plan(const AttnArgs& a);
 constexpr int32_t kListTarget = 1024;
 constexpr int32_t kListMinTiles = 32;
 // ... except that chunks may be as short as kListShortTiles while all items fit the workgroup slots of the machine (two
-// per compute unit up to head_dim 128): one chunk of 512 tokens on 2787 among 16 sequences 73 us against 86 with 32 tiles, but six chunks of
-// 200 tokens on up to 3508, whose 728 items of 16 tiles need a second round, 134 against 123.
+// per compute unit up to head_dim 128): one chunk of 512 tokens on 2787 among 16 sequences 73 us against 86 with 32 tiles, but
+// six chunks of 200 tokens on up to 3508, whose 728 items of 16 tiles need a second round, 134 against 123.
 constexpr int32_t kListShortTiles = 16;
 // At head_dim 256 one workgroup fits a compute unit (200 queries among 17 sequences of up to 8000 tokens, 32 / 8 heads, 186 -> 158
 // us, two of 200 among 30 to 6000 180 -> 161, calls with more work 340 - 369 the same).  At head_dim 64 three do, but slots for
