@@ -373,8 +373,10 @@ __device__ __forceinline__ F user_score(const pa_mod_ctx& c, int32_t j, F x)
 constexpr int32_t kPrefillMinChunk = 1024;
 __device__ __forceinline__ int32_t sequence_chunk(int32_t len, int32_t chunk, int32_t nsplit, int32_t unit)
 {
-    if (unit == 0) return chunk;
-    const int32_t even = len > 0 ? (len - 1) / nsplit + 1 : 0;
+    if (unit == 0 || nsplit <= 1) return chunk;
+    // (len - 1) / nsplit + 1, or one more: by 2^32 / nsplit rounded up, whose division waits for no load
+    const uint32_t part = 0xffffffffu / (uint32_t)nsplit + 1u;
+    const int32_t even = len > 0 ? (int32_t)__umulhi((uint32_t)(len - 1), part) + 1 : 0;
     return (max(even, kPrefillMinChunk) + unit - 1) & -unit;   // (a power of two)
 }
 

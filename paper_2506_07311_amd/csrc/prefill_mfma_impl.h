@@ -1061,10 +1061,12 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
         // Workgroups are dispatched in blockIdx.x order: the row-tile index is the slowest-varying part and runs
         // backwards, so the whole grid is handed out heaviest (latest causal tiles) first; the context chunks of a
         // tile follow each other.  Where contexts are cut by their own lengths (kLengthGrid) they are much longer than the query
-        // ranges and no tile is heavy: there the sequence is the slowest part and then the chunk, so that the workgroups with
-        // keys stand side by side and get a compute unit each, whatever is empty between them (128 queries on 32768 keys and
-        // on 2000 three times 206 -> 119 us, 256 on 32768 and on 16000 285 -> 224, 500 on 2048 in a call for up to 32768
-        // 65 -> 42).
+        // ranges and no tile is heavy: there the sequence is the slowest part, so that the workgroups with keys stand side by
+        // side and get a compute unit each, whatever is empty between them (128 queries on 32768 keys and on 2000 three times
+        // 206 -> 119 us, 256 on 32768 and on 16000 285 -> 224, 500 on 2048 in a call for up to 32768 65 -> 42).  In a
+        // sequence the chunks of a tile follow each other if it is alone, so that a compute unit's workgroups walk the same
+        // keys (1024 queries on 32768 with the append 506 us, tile after tile in a chunk 510); in batches tile after tile
+        // (four with 128 queries on 32768 300, chunk after chunk 313; 256 on 16000 and on 1500 with 8 / 8 heads 43 and 51).
         WorkItem own;
         const int32_t heads = num_q_heads >> plan.log2_pack;
         constexpr bool kByLength = LIST == kLengthGrid;
@@ -1072,10 +1074,9 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
         const int32_t slow = (int32_t)(blockIdx.x / (uint32_t)hb);
         const int32_t rest = (int32_t)(blockIdx.x % (uint32_t)hb);
         own.hg = rest % heads;
+        const int32_t each = num_tiles * plan.nsplit;        // (kByLength: row tiles and chunks of a sequence)
         if constexpr (kByLength) {
-            own.tile = num_tiles - 1 - slow % num_tiles;
-            own.split = slow / num_tiles % plan.nsplit;
-            own.s = slow / num_tiles / plan.nsplit;
+            own.s = slow / each;
         } else {
             own.s = rest / heads;
             own.tile = num_tiles - 1 - slow / plan.nsplit;
@@ -1087,7 +1088,14 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
         own.q_begin = cu_q_lens[own.s];
         own.q_end = cu_q_lens[own.s + 1];
         own.len = seq_lens[own.s];
-        if constexpr (kByLength) own.chunk = sequence_chunk(own.len, plan.chunk, plan.nsplit, plan.chunk_unit);
+        if constexpr (kByLength) {
+            own.chunk = sequence_chunk(own.len, plan.chunk, plan.nsplit, plan.chunk_unit);
+            const int32_t live = max((own.len + own.chunk - 1) / own.chunk, 1), part = slow - own.s * each;
+            const int32_t per = batch == 1 ? live : num_tiles, quot = part / per, rem = part - quot * per;
+            own.tile = num_tiles - 1 - (batch == 1 ? quot : rem);
+            own.split = batch == 1 ? rem : quot;
+            if (own.tile < 0) return;                        // (beyond a single sequence's chunks)
+        }
         int32_t precise_keys = 0;
         if constexpr (!kTwoTermOnly<D>) {
             precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal,
