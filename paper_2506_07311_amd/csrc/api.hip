@@ -803,7 +803,7 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
                     c.rows_o = b.part_o;
                     c.rows_lse = b.part_lse;
                 }
-                st = launch_jagged_mfma(b, c, s);
+                st = launch_jagged_mfma(b, c, device_cus(), s);
                 return st != PA_OK ? st : launch_merge(c, s);
             }
             st = launch_prefill_mfma(b, s);

@@ -217,7 +217,7 @@ bool prefill_mfma_supported(const AttnArgs& a);
 int32_t prefill_mfma_log2_pack(int32_t num_q_heads, int32_t num_kv_heads);
 pa_status launch_prefill_mfma(const AttnArgs& a, hipStream_t stream);
 int32_t jagged_mfma_stream_wgs(const AttnArgs& a, int32_t cus);
-pa_status launch_jagged_mfma(const AttnArgs& a, const AttnArgs& s, hipStream_t stream);
+pa_status launch_jagged_mfma(const AttnArgs& a, const AttnArgs& s, int32_t cus, hipStream_t stream);
 // Its work-list mode (prefill_tiles.h): partial slots and floats per slot (plus 128 LSEs), the shortest context it may
 // cut, and the (tile, chunk) items per head group of a call.
 bool prefill_list_supported(const AttnArgs& a);

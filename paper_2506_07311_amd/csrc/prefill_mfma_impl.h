@@ -149,22 +149,6 @@ __device__ __forceinline__ uint4 lds_frag_tr(const char* lo, const char* hi)
 // sees fewer than kPreciseShare * H keys take the two-term path.  Wave-uniform result.
 constexpr float kPreciseShare = 0.9f;
 
-// A fold over the wave in data-parallel-primitive moves, STEP(control, rows that receive): shifts by 1, 2, 4, 8 inside each row
-// of 16 lanes, then lane 15 of a row into the next row, lane 31 into the upper half; lane 63 holds the result.
-#define PA_WAVE_FOLD(STEP) \
-    STEP(0x111, 0xF) STEP(0x112, 0xF) STEP(0x114, 0xF) STEP(0x118, 0xF) STEP(0x142, 0xA) STEP(0x143, 0xC)
-
-// Sum over the wave without six round trips through LDS in front of a workgroup's first tile (append + prefill of one prompt,
-// 32 / 8 heads: 128 tokens 11.9 -> 11.6 us, 200 13.2 -> 13.0, 500 and more the same).
-__device__ __forceinline__ float wave_sum_moves(float v)
-{
-#define PA_SUM_STEP(CTRL, ROWS) \
-    v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, ROWS, 0xF, true));
-    PA_WAVE_FOLD(PA_SUM_STEP)
-#undef PA_SUM_STEP
-    return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), 63));
-}
-
 __device__ __forceinline__ int32_t precise_key_bound(const int32_t* __restrict__ cu_q_lens,
                                                      const int32_t* __restrict__ seq_lens, int32_t batch,
                                                      int32_t causal, int32_t window, int lane)
@@ -973,14 +957,21 @@ __device__ __forceinline__ bool prefill_body(
     return false;
 }
 
-// The work-list mode of prefill_tiles.h: items first, first + step, ... of the call's list.  LIST: kSlotList (partials by slot) or
+__device__ __forceinline__ WorkList scan_plan_list(const PrefillPlan& plan, const int32_t* __restrict__ cu_q_lens,
+                                                   const int32_t* __restrict__ seq_lens, int32_t batch, int32_t num_q_heads)
+{
+    return scan_list(cu_q_lens, seq_lens, batch, plan.log2_pack, plan.skip_small ? plan.group : kNoSmallGroup,
+                     num_q_heads >> plan.log2_pack, (int)(threadIdx.x & 63));
+}
+
+// The work-list mode of prefill_tiles.h: items first, first + step, ... of the call's list (as scan_plan_list left it).  LIST: kSlotList (partials by slot) or
 // kEitherList (also, with chunk_unit, contexts cut by their own lengths and partials by row, as a plain grid leaves them).
 template <bool UNIFORM, int LIST, typename E, typename M, int D>
 __device__ __forceinline__ void list_body(
     char* buf0, char* buf1, int32_t* docs0, int32_t* docs1, const CacheView& cache, const uint16_t* __restrict__ q,
     uint16_t* __restrict__ out, float* __restrict__ lse, const int32_t* __restrict__ cu_q_lens,
     const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_lens, int32_t batch, int32_t num_q_heads,
-    int32_t max_blocks, float scale, int32_t causal, const PrefillPlan& plan, uint32_t first, uint32_t step)
+    int32_t max_blocks, float scale, int32_t causal, const PrefillPlan& plan, WorkList& list, uint32_t first, uint32_t step)
 {
     WorkItem own;
     const int32_t heads = num_q_heads >> plan.log2_pack;
@@ -988,8 +979,7 @@ __device__ __forceinline__ void list_body(
     // tile loop ends with the barrier behind its last read of LDS.  The thread index is made opaque for each item:
     // what the body derives from it would otherwise be kept in registers across the loop, which spills.
     constexpr bool kByLength = LIST == kEitherList;
-    WorkList list = make_list(cu_q_lens, seq_lens, batch, plan.log2_pack, plan.skip_small ? plan.group : kNoSmallGroup, heads,
-                              plan.list_unit, D, (int)(threadIdx.x & 63));
+    cut_list(list, cu_q_lens, seq_lens, plan.list_unit, D, (int)(threadIdx.x & 63));
     list.nsplit = plan.nsplit;
     list.unit = plan.chunk_unit;
     int32_t precise_keys = 0;
@@ -1055,8 +1045,9 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
     // two-term rule right behind them (vector loads): one round trip to memory instead of three in a row in front
     // of the query and block-table loads that depend on them.
     if constexpr (LIST == kSlotList) {
+        WorkList list = scan_plan_list(plan, cu_q_lens, seq_lens, batch, num_q_heads);
         list_body<UNIFORM, kSlotList, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, cu_q_lens, block_table, seq_lens,
-                                               batch, num_q_heads, max_blocks, scale, causal, plan, blockIdx.x, gridDim.x);
+                                               batch, num_q_heads, max_blocks, scale, causal, plan, list, blockIdx.x, gridDim.x);
     } else {
         // Workgroups are dispatched in blockIdx.x order: the row-tile index is the slowest-varying part and runs
         // backwards, so the whole grid is handed out heaviest (latest causal tiles) first; the context chunks of a

@@ -72,6 +72,34 @@ __device__ __forceinline__ void wait_tile_loads()
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), the other counters left alone
 }
 
+// A fold over the wave in data-parallel-primitive moves, STEP(control, rows that receive): shifts by 1, 2, 4, 8 inside each row
+// of 16 lanes, then lane 15 of a row into the next row, lane 31 into the upper half; lane 63 holds the
+// result, every other lane the fold over the lanes up to it.
+#define PA_WAVE_FOLD(STEP) \
+    STEP(0x111, 0xF) STEP(0x112, 0xF) STEP(0x114, 0xF) STEP(0x118, 0xF) STEP(0x142, 0xA) STEP(0x143, 0xC)
+
+// Sum over the wave without six round trips through LDS in front of a workgroup's first tile (append + prefill of one prompt,
+// 32 / 8 heads: 128 tokens 11.9 -> 11.6 us, 200 13.2 -> 13.0, 500 and more the same).
+__device__ __forceinline__ float wave_sum_moves(float v)
+{
+#define PA_SUM_STEP(CTRL, ROWS) \
+    v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, ROWS, 0xF, true));
+    PA_WAVE_FOLD(PA_SUM_STEP)
+#undef PA_SUM_STEP
+    return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), 63));
+}
+
+// The same for the inclusive scans and sums that find an item (a workgroup without one 4.4 -> 3.8 us; 23 sequences of up to 5465
+// tokens, three with 200 queries, 62.9 -> 60.7 us a call).
+__device__ __forceinline__ int32_t wave_scan_moves(int32_t v)
+{
+#define PA_SCAN_STEP(CTRL, ROWS) v += __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, true);
+    PA_WAVE_FOLD(PA_SCAN_STEP)
+#undef PA_SCAN_STEP
+    return v;
+}
+__device__ __forceinline__ int32_t wave_total_moves(int32_t v) { return __builtin_amdgcn_readlane(wave_scan_moves(v), 63); }
+
 // How the launch cuts the work: head packing and the context split.
 struct PrefillPlan {
     int32_t log2_pack;    // query heads of one KV head packed into a row tile (1 << log2_pack divides the group size)
@@ -101,8 +129,10 @@ PrefillPlan make_plan(const AttnArgs& a);
 // (two per workgroup slot; none shorter than kListMinTiles, where a workgroup's start and its partial begin to show).
 // Item order: sequence, chunk, row tile from last to first, head group -- the workgroups that run together on a
 // chiplet walk the same keys, so a chunk's K/V comes from HBM once per head.  Same call: prefill kernel
-// 1510 -> 460 us (410 GFLOP: 0.9 PFLOP/s) + 10 us of merging; the whole call 1690 -> 655 us (600 with the few-query sequences
-// beside it in the same launch).
+// 1510 -> 460 us (410 GFLOP: 0.9 PFLOP/s) + 10 us of merging; the whole call 1690 -> 655 us (560 with the few-query sequences
+// beside it in the same launch).  All whole chunks come before the shorter ones that end the sequences (list_locate): an
+// item is a sixth of the launch, so the last ones to start decide when it ends (574 -> 557; 64 sequences of up to
+// 13000 tokens, eight with 200 queries, 276 -> 267, 24 such calls 0.98 in the mean).
 // ---------------------------------------------------------------------------------------------------
 constexpr int32_t kListTarget = 1024;
 constexpr int32_t kListMinTiles = 32;
@@ -130,15 +160,17 @@ constexpr int32_t kNoSmallGroup = 17;
 // One lane's sequence of a block of 64: row tiles (0: no queries, or left to the decode kernel) and key tiles.
 struct ListSeq {
     int32_t tiles, len;
+    bool few;            // left to the decode kernel
 };
 __device__ __forceinline__ ListSeq list_seq(const int32_t* __restrict__ cu_q_lens, const int32_t* __restrict__ seq_lens,
                                             int32_t batch, int32_t i, int32_t log2_pack, int32_t small_group)
 {
-    ListSeq q = {0, 0};
+    ListSeq q = {0, 0, false};
     if (i < batch) {
         const int32_t q_len = cu_q_lens[i + 1] - cu_q_lens[i];
         q.len = seq_lens[i];
-        if (q_len > 0 && q_len * small_group > 16) q.tiles = ((q_len << log2_pack) + kBM - 1) / kBM;
+        q.few = q_len > 0 && q_len * small_group <= 16;
+        if (q_len > 0 && !q.few) q.tiles = ((q_len << log2_pack) + kBM - 1) / kBM;
     }
     return q;
 }
@@ -149,11 +181,14 @@ struct WorkList {
     int32_t chunk;
     int32_t nsplit, unit;    // BY_LENGTH with unit > 0: each sequence's chunk from its own length instead (sequence_chunk)
     int32_t small_group, log2_pack, heads, batch;
+    float work;              // (row tile, key tile) pairs per head group
+    int32_t few_tiles;       // 32-key tiles of the sequences left to the decode kernel
     ListSeq own;
 };
-__device__ __forceinline__ WorkList make_list(const int32_t* __restrict__ cu_q_lens,
+// The sequences and the work of the list; cut_list completes it.
+__device__ __forceinline__ WorkList scan_list(const int32_t* __restrict__ cu_q_lens,
                                               const int32_t* __restrict__ seq_lens, int32_t batch, int32_t log2_pack,
-                                              int32_t small_group, int32_t heads, int32_t unit, int32_t d, int lane)
+                                              int32_t small_group, int32_t heads, int lane)
 {
     WorkList w;
     w.small_group = small_group;
@@ -162,13 +197,21 @@ __device__ __forceinline__ WorkList make_list(const int32_t* __restrict__ cu_q_l
     w.batch = batch;
     w.own = list_seq(cu_q_lens, seq_lens, batch, lane, log2_pack, small_group);
     float work = (float)w.own.tiles * (float)((w.own.len + kBN - 1) / kBN);   // (row tile, key tile) pairs per head group
+    int32_t few = w.own.few ? (w.own.len + 31) / 32 : 0;
     for (int32_t i = lane + 64; i < batch; i += 64) {
         const ListSeq q = list_seq(cu_q_lens, seq_lens, batch, i, log2_pack, small_group);
         work += (float)q.tiles * (float)((q.len + kBN - 1) / kBN);
+        few += q.few ? (q.len + 31) / 32 : 0;
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) work += __shfl_xor(work, o, 64);
-    int32_t tiles = max(kListMinTiles, (int32_t)(work * (float)heads * (1.f / kListTarget)) + 1);
+    w.work = wave_sum_moves(work);
+    w.few_tiles = wave_total_moves(few);
+    return w;
+}
+__device__ __forceinline__ void cut_list(WorkList& w, const int32_t* __restrict__ cu_q_lens,
+                                         const int32_t* __restrict__ seq_lens, int32_t unit, int32_t d, int lane)
+{
+    const int32_t batch = w.batch, log2_pack = w.log2_pack, small_group = w.small_group, heads = w.heads;
+    int32_t tiles = max(kListMinTiles, (int32_t)(w.work * (float)heads * (1.f / kListTarget)) + 1);
     if (tiles == kListMinTiles) {
         // little work: shorter chunks, if all items still run at once
 #pragma unroll 1
@@ -178,9 +221,7 @@ __device__ __forceinline__ WorkList make_list(const int32_t* __restrict__ cu_q_l
                 const ListSeq q = i < 64 ? w.own : list_seq(cu_q_lens, seq_lens, batch, i, log2_pack, small_group);
                 n += min(q.tiles * ((max(q.len, 1) + c * kBN - 1) / (c * kBN)), 2 * list_wg_slots(d));
             }
-            n = min(n, 1 << 20);
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
+            n = wave_total_moves(min(n, 1 << 20));
             if ((int64_t)n * heads <= list_wg_slots(d)) {
                 tiles = c;
                 break;
@@ -189,6 +230,13 @@ __device__ __forceinline__ WorkList make_list(const int32_t* __restrict__ cu_q_l
         tiles = __builtin_amdgcn_readfirstlane(tiles);
     }
     w.chunk = __builtin_amdgcn_readfirstlane((min(tiles, 1 << 22) * kBN + unit - 1) / unit * unit);
+}
+__device__ __forceinline__ WorkList make_list(const int32_t* __restrict__ cu_q_lens,
+                                              const int32_t* __restrict__ seq_lens, int32_t batch, int32_t log2_pack,
+                                              int32_t small_group, int32_t heads, int32_t unit, int32_t d, int lane)
+{
+    WorkList w = scan_list(cu_q_lens, seq_lens, batch, log2_pack, small_group, heads, lane);
+    cut_list(w, cu_q_lens, seq_lens, unit, d, lane);
     return w;
 }
 
@@ -210,37 +258,33 @@ template <bool SPLIT_TILES, bool BY_LENGTH = false>
 __device__ __forceinline__ bool list_locate(ListItem& it, const WorkList& w, const int32_t* __restrict__ cu_q_lens,
                                             const int32_t* __restrict__ seq_lens, int32_t idx, int lane)
 {
-    int32_t items_before = 0, slots_before = 0;
-    for (int32_t blk = 0; blk < w.batch; blk += 64) {
-        const ListSeq q = blk == 0 ? w.own : list_seq(cu_q_lens, seq_lens, w.batch, blk + lane, w.log2_pack, w.small_group);
-        const int32_t chunk = list_chunk<BY_LENGTH>(w, q.len);
-        const int32_t chunks = max((q.len + chunk - 1) / chunk, 1);
-        const int32_t slots = chunks > 1 ? q.tiles * chunks : 0;
-        const int32_t n = !SPLIT_TILES ? q.tiles * chunks : chunks > 1 ? q.tiles : 0;
-        int32_t inc = n, sinc = slots;                        // inclusive scans over the 64 lanes
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int32_t t = __shfl_up(inc, o, 64), u = __shfl_up(sinc, o, 64);
-            if (lane >= o) {
-                inc += t;
-                sinc += u;
+    int32_t items_before = 0;
+    for (int32_t part = 0; part < (SPLIT_TILES ? 1 : 2); ++part) {
+        int32_t slots_before = 0;
+        for (int32_t blk = 0; blk < w.batch; blk += 64) {
+            const ListSeq q = blk == 0 ? w.own : list_seq(cu_q_lens, seq_lens, w.batch, blk + lane, w.log2_pack, w.small_group);
+            const int32_t chunk = list_chunk<BY_LENGTH>(w, q.len);
+            const int32_t chunks = max((q.len + chunk - 1) / chunk, 1);
+            const int32_t slots = chunks > 1 ? q.tiles * chunks : 0;
+            const int32_t whole = BY_LENGTH && w.unit > 0 ? chunks : q.len / chunk;
+            const int32_t n = SPLIT_TILES ? (chunks > 1 ? q.tiles : 0) : q.tiles * (part == 0 ? whole : chunks - whole);
+            const int32_t inc = wave_scan_moves(n), sinc = wave_scan_moves(slots);
+            const uint64_t hit = __ballot(items_before + inc > idx);
+            if (hit) {
+                const int first = __ffsll((unsigned long long)hit) - 1;
+                it.s = blk + first;
+                it.tiles = __builtin_amdgcn_readlane(q.tiles, first);
+                it.chunks = __builtin_amdgcn_readlane(chunks, first);
+                it.slot = slots_before + __builtin_amdgcn_readlane(sinc, first) - __builtin_amdgcn_readlane(slots, first);
+                const int32_t rest = idx - (items_before + __builtin_amdgcn_readlane(inc, first) -
+                                            __builtin_amdgcn_readlane(n, first));
+                it.split = rest / it.tiles + (part == 0 ? 0 : __builtin_amdgcn_readlane(whole, first));
+                it.tile = it.tiles - 1 - rest % it.tiles;
+                return true;
             }
+            items_before += __builtin_amdgcn_readlane(inc, 63);
+            slots_before += __builtin_amdgcn_readlane(sinc, 63);
         }
-        const uint64_t hit = __ballot(items_before + inc > idx);
-        if (hit) {
-            const int first = __ffsll((unsigned long long)hit) - 1;
-            it.s = blk + first;
-            it.tiles = __builtin_amdgcn_readlane(q.tiles, first);
-            it.chunks = __builtin_amdgcn_readlane(chunks, first);
-            it.slot = slots_before + __builtin_amdgcn_readlane(sinc, first) - __builtin_amdgcn_readlane(slots, first);
-            const int32_t rest = idx - (items_before + __builtin_amdgcn_readlane(inc, first) -
-                                        __builtin_amdgcn_readlane(n, first));
-            it.split = rest / it.tiles;
-            it.tile = it.tiles - 1 - rest % it.tiles;
-            return true;
-        }
-        items_before += __builtin_amdgcn_readlane(inc, 63);
-        slots_before += __builtin_amdgcn_readlane(sinc, 63);
     }
     return false;
 }

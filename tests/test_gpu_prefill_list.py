@@ -79,6 +79,19 @@ def test_chunks_and_single_queries_in_one_launch(pa, oracle, Hq, Hkv, P, dtype, 
     assert torch.equal(outs[0], outs[1])
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(8, 4), (32, 8), (12, 12)])
+@pytest.mark.parametrize("lens,q_lens", [
+    ([5000] * 6 + [33], [200] * 6 + [1]),                     # the stream is two tiles of one sequence
+    ([6100] * 12 + [4096], [1] * 12 + [33]),                  # nearly all of the call
+    ([4100, 9000, 6200, 2048], [130, 1, 70, 200])])           # whole chunks and remainders of one key and more
+def test_the_streams_share_of_the_machine(pa, oracle, lens, q_lens, Hq, Hkv):
+    """The stream's workgroups are counted on the device from both sides' work, from one a head group to all there is room for;
+    chunks that are whole come before those that are not."""
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=128, page_size=16,
+                        dtype=torch.bfloat16, causal=True, seed=219, device=DEV)
+    parity.check_step(pa, oracle, w, f"{lens} {q_lens} {Hq} {Hkv}")
+
+
 @pytest.mark.parametrize("lens,q_lens,Hq,Hkv,P,dtype,causal", [
     ([2100, 0, 700, 1, 1500, 64, 65], [130, 0, 1, 1, 129, 2, 17], 16, 4, 16, torch.bfloat16, True),
     ([4095, 300, 33], [33, 1, 1], 8, 8, 64, torch.float16, False),            # one key short of the list that is cut
