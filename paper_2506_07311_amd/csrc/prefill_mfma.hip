@@ -87,6 +87,7 @@ PrefillPlan prefill::make_plan(const AttnArgs& a)
     plan.group = a.num_q_heads / a.cache.num_kv_heads;
     plan.chunk = a.plan.chunk;
     plan.chunk_unit = a.plan.unit;
+    plan.live = 0;
     plan.nsplit = a.plan.nsplit;
     plan.skip_small = a.skip_small;
     plan.part_o = a.part_o;
@@ -97,12 +98,27 @@ PrefillPlan prefill::make_plan(const AttnArgs& a)
 
 pa_status launch_prefill_mfma(const AttnArgs& a, hipStream_t stream)
 {
-    const PrefillPlan plan = make_plan(a);
+    PrefillPlan plan = make_plan(a);
     if (plan.nsplit > 1 && (plan.chunk % kBN != 0 || plan.chunk % a.cache.page_size != 0)) return PA_ERR_INVALID_ARG;
     const int64_t tiles = (((int64_t)a.max_q_len << plan.log2_pack) + kBM - 1) / kBM;
     if (tiles <= 0) return PA_OK;
     const int32_t heads = a.num_q_heads >> plan.log2_pack;
-    int64_t blocks = plan.list_items > 0 ? (int64_t)plan.list_items * heads : tiles * plan.nsplit * heads * a.batch;
+    int64_t row_tiles = tiles * a.batch;
+    // Sequences with fewer queries than the longest leave gaps in a grid of the longest's row tiles.  Gaps that fall on the
+    // same shader engines again and again (four to a chiplet, dealt workgroups in turn: as they do unless a sequence's head
+    // groups go round evenly) leave their compute units idle while the others have a queue (locate_live); without gaps a
+    // workgroup starts 0.5 us later, which shows where the longest walk is a few tiles.  us with gaps / without: prompts of 2059
+    // and 3146 tokens, 16 / 8 heads, head_dim 256, 228 / 181, with a window and a cap 181 / 152 (append included); 32 / 8
+    // heads, 8 of 300 .. 1000 85 / 65, 4 of 947 .. 1894 with slopes 153 / 110, 2 of 3000 .. 4096 with 64 / 8 403 / 381, 2 of 387 ..
+    // 1162 31.2 / 31.8; 16 of 60 .. 170, 3 tiles at most, 23.6 / 25.3; 16 of 100 .. 500 with 32 / 32 72.5 / 75.0.
+    const int64_t walk = a.mods.window > 0 && a.mods.window < a.max_seq_len ? a.mods.window : a.max_seq_len;
+    if (plan.list_items == 0 && plan.chunk_unit == 0 && plan.nsplit == 1 && a.batch > 1 && a.batch <= 64 &&
+        (int64_t)a.batch * a.max_q_len != a.total_q && heads % 32 != 0 && row_tiles * heads > 256 && walk >= 8 * kBN) {
+        plan.live = 1;
+        const int64_t most = (((int64_t)a.total_q << plan.log2_pack) / kBM) + a.batch;
+        if (row_tiles > most) row_tiles = most;
+    }
+    int64_t blocks = plan.list_items > 0 ? (int64_t)plan.list_items * heads : row_tiles * plan.nsplit * heads;
     if (plan.list_items > 0 && blocks > kListGrid) blocks = kListGrid;
     if (blocks > 0x7fffffffLL) return PA_ERR_UNSUPPORTED;
     {

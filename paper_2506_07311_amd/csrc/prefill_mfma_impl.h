@@ -149,33 +149,39 @@ __device__ __forceinline__ uint4 lds_frag_tr(const char* lo, const char* hi)
 // sees fewer than kPreciseShare * H keys take the two-term path.  Wave-uniform result.
 constexpr float kPreciseShare = 0.9f;
 
+struct RowSums {
+    float rows, inv;     // rows, and the sum of 1 / n over them
+};
+__device__ __forceinline__ void add_rows(RowSums& r, int32_t q_len, int32_t len, int32_t causal, int32_t window)
+{
+    if (q_len <= 0 || len <= 0) return;
+    const int32_t hi = len;                                       // keys of the last row
+    const int32_t lo = causal ? max(len - q_len + 1, 1) : len;    // keys of the first row that sees any
+    const int32_t cap = window > 0 ? (causal ? window : 2 * window - 1) : 0x7fffffff;
+    const int32_t n_rows = causal ? hi - lo + 1 : q_len;
+    r.rows += (float)n_rows;
+    if (!causal) {
+        r.inv += (float)q_len / (float)min(len, cap);
+        return;
+    }
+    const int32_t b = min(hi, cap);
+    if (b >= lo) r.inv += __builtin_amdgcn_logf(((float)b + 0.5f) / ((float)lo - 0.5f)) * kLn2;
+    const int32_t above = hi - max(lo, cap + 1) + 1;              // rows that see the whole window
+    if (above > 0) r.inv += (float)above / (float)cap;
+}
+__device__ __forceinline__ int32_t precise_keys_of(const RowSums& r)   // (every lane's rows)
+{
+    const float rows = wave_sum_moves(r.rows), inv = wave_sum_moves(r.inv);
+    const float h = inv > 0.f ? rows / inv : 0.f;
+    return max(kPreciseKeys, (int32_t)fminf(kPreciseShare * h, 1.0e9f));
+}
 __device__ __forceinline__ int32_t precise_key_bound(const int32_t* __restrict__ cu_q_lens,
                                                      const int32_t* __restrict__ seq_lens, int32_t batch,
                                                      int32_t causal, int32_t window, int lane)
 {
-    float rows = 0.f, inv = 0.f;
-    for (int32_t i = lane; i < batch; i += 64) {
-        const int32_t q_len = cu_q_lens[i + 1] - cu_q_lens[i];
-        const int32_t len = seq_lens[i];
-        if (q_len <= 0 || len <= 0) continue;
-        const int32_t hi = len;                                       // keys of the last row
-        const int32_t lo = causal ? max(len - q_len + 1, 1) : len;    // keys of the first row that sees any
-        const int32_t cap = window > 0 ? (causal ? window : 2 * window - 1) : 0x7fffffff;
-        const int32_t n_rows = causal ? hi - lo + 1 : q_len;
-        rows += (float)n_rows;
-        if (!causal) {
-            inv += (float)q_len / (float)min(len, cap);
-            continue;
-        }
-        const int32_t b = min(hi, cap);
-        if (b >= lo) inv += __builtin_amdgcn_logf(((float)b + 0.5f) / ((float)lo - 0.5f)) * kLn2;
-        const int32_t above = hi - max(lo, cap + 1) + 1;              // rows that see the whole window
-        if (above > 0) inv += (float)above / (float)cap;
-    }
-    rows = wave_sum_moves(rows);
-    inv = wave_sum_moves(inv);
-    const float h = inv > 0.f ? rows / inv : 0.f;
-    return max(kPreciseKeys, (int32_t)fminf(kPreciseShare * h, 1.0e9f));
+    RowSums r = {0.f, 0.f};
+    for (int32_t i = lane; i < batch; i += 64) add_rows(r, cu_q_lens[i + 1] - cu_q_lens[i], seq_lens[i], causal, window);
+    return precise_keys_of(r);
 }
 
 // Operand reads of the 16-row products ahead of their use (a matrix instruction takes 16 cycles there).
@@ -592,7 +598,8 @@ __device__ __forceinline__ void attend_tile(const char* buf, const uint32_t (&kx
     }
 }
 
-// Where an item and its partial go.  (kLengthGrid: a plain grid in the order of contexts that are cut by their own lengths.)
+// Where an item and its partial go.  (kLengthGrid: a plain grid in the order of contexts that are cut by their own lengths, or of
+// the row tiles that there are: locate_live.)
 constexpr int kPlainGrid = 0, kSlotList = 1, kEitherList = 2, kLengthGrid = 3;
 
 // What a workgroup works on: sequence, its query range and context length, row tile, head group, and its chunk of the
@@ -1016,10 +1023,56 @@ __device__ __forceinline__ void list_body(
     }
 }
 
+// Row tile number `index` of those that the call has, from the last ones of every sequence to the first (at most 64 sequences).
+// Without it the grid has a workgroup for every tile of the longest query range in every sequence, and the ones that a shorter
+// sequence does not have come first: they end at once, but workgroups go to the shader engines of a chiplet in turn and each
+// waits for room on its own, so the compute units that empty workgroups leave stand by while the others are full.
+// The lengths that every lane brings (one sequence each) serve the two-term rule as well.
+__device__ __forceinline__ bool locate_live(WorkItem& own, int32_t& precise_keys, int32_t index, int32_t num_tiles,
+                                            const int32_t* __restrict__ cu_q_lens, const int32_t* __restrict__ seq_lens,
+                                            int32_t batch, int32_t causal, int32_t window, const PrefillPlan& plan)
+{
+    const int32_t lane = (int32_t)(threadIdx.x & 63), s = min(lane, batch - 1);
+    const int32_t q_begin = cu_q_lens[s], q_end = cu_q_lens[s + 1], len = seq_lens[s], q_len = q_end - q_begin;
+    int32_t n = min(((max(q_len, 0) << plan.log2_pack) + kBM - 1) / kBM, num_tiles);
+    if (lane >= batch || (plan.skip_small && q_len * plan.group <= 16)) n = 0;
+    // lo: the last tile index of which, and of those above, there are more than `index`; above: tiles of the indexes beyond it
+    int32_t lo = -1, above = 0;
+    if (num_tiles <= 64 && batch <= 16) {                    // (a lane for every tile index)
+        int32_t f = 0;
+        for (int32_t i = 0; i < batch; ++i) f += max(__builtin_amdgcn_readlane(n, i) - lane, 0);
+        lo = 63 - __clzll((unsigned long long)__ballot(f > index));
+        if (lo < 63) above = __builtin_amdgcn_readlane(f, lo + 1);
+    } else {
+        for (int32_t hi = num_tiles; hi - lo > 1;) {
+            const int32_t mid = (lo + hi) >> 1, f = wave_total_moves(max(n - mid, 0));
+            if (f > index) {
+                lo = mid;
+            } else {
+                hi = mid;
+                above = f;
+            }
+        }
+    }
+    if (lo < 0) return false;
+    RowSums rows = {0.f, 0.f};
+    if (lane < batch) add_rows(rows, q_len, len, causal, window);
+    precise_keys = precise_keys_of(rows);
+    const uint64_t have = __ballot(n > lo);
+    const int32_t rank = (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(have >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)have, 0));
+    const int at = __ffsll((unsigned long long)__ballot(n > lo && rank == index - above)) - 1;
+    own.s = at;
+    own.tile = lo;
+    own.q_begin = __builtin_amdgcn_readlane(q_begin, at);
+    own.q_end = __builtin_amdgcn_readlane(q_end, at);
+    own.len = __builtin_amdgcn_readlane(len, at);
+    return true;
+}
+
 // Both instantiations live in one kernel as two separate code paths (each with its own tile loop); a
 // workgroup runs exactly one of them, decided by its context length.
-// LIST: kSlotList, the work-list mode of prefill_tiles.h; kPlainGrid; or kLengthGrid (an instantiation of its own: deciding it
-// here by plan.chunk_unit scattered the first loads and cost a prompt of 128 tokens 0.4 us of 9).
+// LIST: kSlotList, the work-list mode of prefill_tiles.h; kPlainGrid; or kLengthGrid (with plan.chunk_unit or plan.live; an instantiation of its own: deciding it
+// here scattered the first loads and cost a prompt of 128 tokens 0.4 us of 9).
 // Waves a SIMD: two, three at head_dim 64.  Hooks that keep more state spill under that bound: document masks and user
 // modifications 4 - 6 registers at head_dim 64, 12 and 24 at 256, slopes 7 at 256, and nothing at 128.  us for 4 x 2048, 2 x 1200 and
 // 1 x 500 tokens (32 / 8 heads, 16 / 8 at 256), one wave less and no spill / like this: at head_dim 64 documents 105 / 89,
@@ -1061,7 +1114,7 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
         WorkItem own;
         const int32_t heads = num_q_heads >> plan.log2_pack;
         constexpr bool kByLength = LIST == kLengthGrid;
-        const int32_t hb = heads * (kByLength ? 1 : batch);
+        const int32_t hb = heads * (kByLength ? 1 : batch);      // (by length and live: the sequence is not beside the heads)
         const int32_t slow = (int32_t)(blockIdx.x / (uint32_t)hb);
         const int32_t rest = (int32_t)(blockIdx.x % (uint32_t)hb);
         own.hg = rest % heads;
@@ -1076,10 +1129,17 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
         own.chunks = plan.nsplit;
         own.chunk = plan.chunk;
         own.slot = -1;
-        own.q_begin = cu_q_lens[own.s];
-        own.q_end = cu_q_lens[own.s + 1];
-        own.len = seq_lens[own.s];
-        if constexpr (kByLength) {
+        if (!kByLength || !plan.live) {
+            own.q_begin = cu_q_lens[own.s];
+            own.q_end = cu_q_lens[own.s + 1];
+            own.len = seq_lens[own.s];
+        }
+        const int32_t window = (M::kWindow && plan.mods.window > 0) ? plan.mods.window : 0;
+        int32_t precise_keys = 0;
+        if (kByLength && plan.live) {
+            own.split = 0;
+            if (!locate_live(own, precise_keys, slow, num_tiles, cu_q_lens, seq_lens, batch, causal, window, plan)) return;
+        } else if constexpr (kByLength) {
             own.chunk = sequence_chunk(own.len, plan.chunk, plan.nsplit, plan.chunk_unit);
             const int32_t live = max((own.len + own.chunk - 1) / own.chunk, 1), part = slow - own.s * each;
             const int32_t per = batch == 1 ? live : num_tiles, quot = part / per, rem = part - quot * per;
@@ -1087,11 +1147,9 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
             own.split = batch == 1 ? rem : quot;
             if (own.tile < 0) return;                        // (beyond a single sequence's chunks)
         }
-        int32_t precise_keys = 0;
         if constexpr (!kTwoTermOnly<D>) {
-            precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal,
-                                             (M::kWindow && plan.mods.window > 0) ? plan.mods.window : 0,
-                                             (int)(threadIdx.x & 63));
+            if (!kByLength || !plan.live)
+                precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal, window, (int)(threadIdx.x & 63));
             prefill_body<false, UNIFORM, kPlainGrid, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table, num_q_heads,
                                                         max_blocks, scale, causal, plan, precise_keys, own, (int)threadIdx.x);
         }
@@ -1111,7 +1169,7 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
 
 // The plain grid's kernel in the order that the plan asks for.
 #define PA_GRID_KERNEL(UNIFORM, E, M)                                                                                  \
-    (plan.chunk_unit > 0 ? paged_prefill_mfma_kernel<UNIFORM, E, M, D, kLengthGrid> : paged_prefill_mfma_kernel<UNIFORM, E, M, D>)
+    (plan.chunk_unit > 0 || plan.live ? paged_prefill_mfma_kernel<UNIFORM, E, M, D, kLengthGrid> : paged_prefill_mfma_kernel<UNIFORM, E, M, D>)
 
 // Every kernel instantiation of one head_dim; defined in that head_dim's translation unit.
 template <int D>
@@ -1172,13 +1230,13 @@ pa_status launch_prefill_mfma_dim(const AttnArgs& a, const PrefillPlan& plan, in
             kern = uniform ? PA_GRID_KERNEL(true, ElemF16, AllMods)
                            : PA_GRID_KERNEL(kLargePagesOnly, ElemF16, AllMods);
     } else if (a.dtype == PA_DTYPE_BF16) {
-        if (windowed) kern = paged_prefill_mfma_kernel<true, ElemBf16, Window, D>;
+        if (windowed) kern = PA_GRID_KERNEL(true, ElemBf16, Window);
         else if (capped) kern = PA_GRID_KERNEL(true, ElemBf16, Cap);
         else if (a.has_mods) kern = uniform ? PA_GRID_KERNEL(true, ElemBf16, WindowScore)
                                        : PA_GRID_KERNEL(kLargePagesOnly, ElemBf16, WindowScore);
         else if (!uniform) kern = PA_GRID_KERNEL(kLargePagesOnly, ElemBf16, NoMods);
     } else {
-        if (windowed) kern = paged_prefill_mfma_kernel<true, ElemF16, Window, D>;
+        if (windowed) kern = PA_GRID_KERNEL(true, ElemF16, Window);
         else if (capped) kern = PA_GRID_KERNEL(true, ElemF16, Cap);
         else if (a.has_mods) kern = uniform ? PA_GRID_KERNEL(true, ElemF16, WindowScore)
                                        : PA_GRID_KERNEL(kLargePagesOnly, ElemF16, WindowScore);

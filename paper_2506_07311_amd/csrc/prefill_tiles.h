@@ -115,6 +115,7 @@ struct PrefillPlan {
     float* part_lse;      // [total_q, Hq, nsplit]
     ModArgs mods;         // mask / score hooks (used by the instantiations that have them)
     int32_t chunk_unit;   // > 0: chunks by each sequence's own length instead (sequence_chunk; kLengthGrid, kEitherList)
+    int32_t live;         // 1: the grid holds the row tiles that there are (kLengthGrid without chunk_unit)
 };
 
 PrefillPlan make_plan(const AttnArgs& a);
