@@ -457,6 +457,61 @@ size_t part_lse_bytes(int64_t rows, int32_t hq, int32_t nsplit)
     return align256((size_t)rows * hq * nsplit * sizeof(float));
 }
 
+// The number of chunks for whole prompts (and chunks of prompts on less than themselves) whose row tiles are few: the launch
+// lasts as long as the longest row tile's walk while most of the machine stands by, which costs more than partials and their merge
+// do.  Estimated from the sizes: t1 us for 64 keys of a workgroup alone on its compute unit, up to 1.67 times that beside another,
+// `start` for its start and end, and of the row tiles of causal prompts half a walk on average; the merge 5.5 us and its partials at
+// 3.3 MB a us.  us a call in one piece / in so many, 8 / 1 heads, head_dim 128: 600 tokens 16.4 / 17.2 (2), 1000 22.9 / 19.6 (4),
+// 2000 39.2 / 31.5 (2: as many as the workspace holds), 4000 73.7 / 58.7 (3), 69.0 (4); with slopes 600 28.4 / 21.5 (6), 1000
+// 41.9 / 24.7 (4); 600 and 1195 with a cap 39.3 / 32.4 (2); head_dim 256 1000 42.9 / 30.0 (4), 32 / 8 heads and 500 26.9 / 30.5 (2), 16
+// / 8 and 3000 111.6 / 145.3 (2); the estimates are within 10 % of these and of 30 others.
+SplitPlan prompt_split(const AttnArgs& a, int32_t log2_pack, const SplitPlan& given, size_t ws_bytes)
+{
+    const int32_t d = a.cache.head_dim, heads = a.num_q_heads >> log2_pack;
+    const int64_t bound = ((((int64_t)a.max_q_len << log2_pack) + 127) / 128) * a.batch;
+    int64_t tiles = (((int64_t)a.total_q << log2_pack) / 128) + a.batch;
+    if (tiles > bound) tiles = bound;
+    const double cus = device_cus(), wgs = (double)tiles * heads;
+    if (given.nsplit == 1 && wgs > cus) return given;
+    const bool windowed = a.mods.window > 0 && a.mods.window < a.max_seq_len;
+    double t1 = d > 128 ? 2.25 : d == 128 ? 1.05 : d > 96 ? 1.5 : d > 80 ? 1.28 : d > 64 ? 1.05 : 0.75;
+    if (a.mods.alibi_slopes || a.mods.user_mod) t1 *= 2.0;
+    else if (a.mods.doc_ids) t1 *= 1.5;
+    if (a.mods.softcap > 0.f) t1 += 0.65;
+    const double start = d > 128 ? 7.0 : 6.0, part = a.causal ? 0.5 : 1.0;
+    const double walk = ((windowed ? a.mods.window : a.max_seq_len) + 63) / 64;      // key tiles of the longest row tile
+    const double slots = d > 128 ? 1.0 : d > 64 ? 2.0 : 3.0;
+    const int64_t unit = a.cache.page_size > 64 ? a.cache.page_size : 64;
+    const double mb = (double)a.total_q * a.num_q_heads * d * 4e-6;
+    SplitPlan best = given;
+    double best_us = 1e30;
+    for (int32_t n = 1; n <= 8; ++n) {
+        const int64_t chunk = (((int64_t)a.max_seq_len + n - 1) / n + unit - 1) / unit * unit;
+        if (n > 1 && (chunk < 256 || ((int64_t)a.max_seq_len + chunk - 1) / chunk != n)) continue;
+        if (n > 1 && part_o_bytes(a.total_q, a.num_q_heads, d, n) + part_lse_bytes(a.total_q, a.num_q_heads, n) > ws_bytes) break;
+        // (a window's row tiles reach into two chunks)
+        const double own = n == 1 || walk < (double)chunk / 64 ? walk : (double)chunk / 64;
+        const double live = n == 1 ? wgs : wgs * (windowed ? 2.0 : 1.0 + (n - 1) * part);
+        const double beside = slots > 1.0 && live > cus ? 0.67 * (live < 2 * cus ? live / cus - 1.0 : 1.0) : 0.0;
+        double us = start + own * t1 * (1.0 + beside);
+        if (n > 1) {
+            if (live > slots * cus) us *= live / (slots * cus);
+            us += 5.5 + n * mb / 3.3;
+        } else {
+            const double all = wgs / cus * (walk * part * t1 * (slots > 1.0 ? 0.84 : 1.0) + start / slots);
+            if (all > us) us = all;
+        }
+        if (n > 1 && best.nsplit == 1) us *= 1.05;           // (not for an estimate's margin)
+        if (us < best_us) {
+            best_us = us;
+            best.nsplit = n;
+            best.chunk = n > 1 ? (int32_t)chunk : a.max_seq_len;
+            best.unit = 0;
+        }
+    }
+    return best;
+}
+
 // Partials of the prefill kernel's work-list mode.
 size_t list_bytes(int32_t d)
 {
@@ -750,6 +805,8 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
             pp = even_prefill_split(pp, batch, tiles * (num_q_heads >> lg), (int64_t)total_q * num_q_heads, max_seq_len,
                                     cache->page_size, d);
         }
+        if (!may_have_small && list_items == 0 && g_opt.prefill_chunk_tokens == 0 && max_seq_len / 2 < max_q_len)
+            pp = prompt_split(a, lg, pp, ws.bytes);
         int32_t small_wgs = 0;
         if (may_have_small) {
             const int32_t head_groups = cache->num_kv_heads / decode_mfma_heads_per_wg(cache->num_kv_heads, d);

@@ -149,39 +149,33 @@ __device__ __forceinline__ uint4 lds_frag_tr(const char* lo, const char* hi)
 // sees fewer than kPreciseShare * H keys take the two-term path.  Wave-uniform result.
 constexpr float kPreciseShare = 0.9f;
 
-struct RowSums {
-    float rows, inv;     // rows, and the sum of 1 / n over them
-};
-__device__ __forceinline__ void add_rows(RowSums& r, int32_t q_len, int32_t len, int32_t causal, int32_t window)
-{
-    if (q_len <= 0 || len <= 0) return;
-    const int32_t hi = len;                                       // keys of the last row
-    const int32_t lo = causal ? max(len - q_len + 1, 1) : len;    // keys of the first row that sees any
-    const int32_t cap = window > 0 ? (causal ? window : 2 * window - 1) : 0x7fffffff;
-    const int32_t n_rows = causal ? hi - lo + 1 : q_len;
-    r.rows += (float)n_rows;
-    if (!causal) {
-        r.inv += (float)q_len / (float)min(len, cap);
-        return;
-    }
-    const int32_t b = min(hi, cap);
-    if (b >= lo) r.inv += __builtin_amdgcn_logf(((float)b + 0.5f) / ((float)lo - 0.5f)) * kLn2;
-    const int32_t above = hi - max(lo, cap + 1) + 1;              // rows that see the whole window
-    if (above > 0) r.inv += (float)above / (float)cap;
-}
-__device__ __forceinline__ int32_t precise_keys_of(const RowSums& r)   // (every lane's rows)
-{
-    const float rows = wave_sum_moves(r.rows), inv = wave_sum_moves(r.inv);
-    const float h = inv > 0.f ? rows / inv : 0.f;
-    return max(kPreciseKeys, (int32_t)fminf(kPreciseShare * h, 1.0e9f));
-}
 __device__ __forceinline__ int32_t precise_key_bound(const int32_t* __restrict__ cu_q_lens,
                                                      const int32_t* __restrict__ seq_lens, int32_t batch,
                                                      int32_t causal, int32_t window, int lane)
 {
-    RowSums r = {0.f, 0.f};
-    for (int32_t i = lane; i < batch; i += 64) add_rows(r, cu_q_lens[i + 1] - cu_q_lens[i], seq_lens[i], causal, window);
-    return precise_keys_of(r);
+    float rows = 0.f, inv = 0.f;
+    for (int32_t i = lane; i < batch; i += 64) {
+        const int32_t q_len = cu_q_lens[i + 1] - cu_q_lens[i];
+        const int32_t len = seq_lens[i];
+        if (q_len <= 0 || len <= 0) continue;
+        const int32_t hi = len;                                       // keys of the last row
+        const int32_t lo = causal ? max(len - q_len + 1, 1) : len;    // keys of the first row that sees any
+        const int32_t cap = window > 0 ? (causal ? window : 2 * window - 1) : 0x7fffffff;
+        const int32_t n_rows = causal ? hi - lo + 1 : q_len;
+        rows += (float)n_rows;
+        if (!causal) {
+            inv += (float)q_len / (float)min(len, cap);
+            continue;
+        }
+        const int32_t b = min(hi, cap);
+        if (b >= lo) inv += __builtin_amdgcn_logf(((float)b + 0.5f) / ((float)lo - 0.5f)) * kLn2;
+        const int32_t above = hi - max(lo, cap + 1) + 1;              // rows that see the whole window
+        if (above > 0) inv += (float)above / (float)cap;
+    }
+    rows = wave_sum_moves(rows);
+    inv = wave_sum_moves(inv);
+    const float h = inv > 0.f ? rows / inv : 0.f;
+    return max(kPreciseKeys, (int32_t)fminf(kPreciseShare * h, 1.0e9f));
 }
 
 // Operand reads of the 16-row products ahead of their use (a matrix instruction takes 16 cycles there).
@@ -1023,6 +1017,35 @@ __device__ __forceinline__ void list_body(
     }
 }
 
+// precise_key_bound from a lane's own sequence.  (A text of its own: sharing one changed the plain kernel's code, whose start and
+// tile loop answer to such changes with up to 10 %.)
+struct RowSums {
+    float rows, inv;     // rows, and the sum of 1 / n over them
+};
+__device__ __forceinline__ void add_rows(RowSums& r, int32_t q_len, int32_t len, int32_t causal, int32_t window)
+{
+    if (q_len <= 0 || len <= 0) return;
+    const int32_t hi = len;                                       // keys of the last row
+    const int32_t lo = causal ? max(len - q_len + 1, 1) : len;    // keys of the first row that sees any
+    const int32_t cap = window > 0 ? (causal ? window : 2 * window - 1) : 0x7fffffff;
+    const int32_t n_rows = causal ? hi - lo + 1 : q_len;
+    r.rows += (float)n_rows;
+    if (!causal) {
+        r.inv += (float)q_len / (float)min(len, cap);
+        return;
+    }
+    const int32_t b = min(hi, cap);
+    if (b >= lo) r.inv += __builtin_amdgcn_logf(((float)b + 0.5f) / ((float)lo - 0.5f)) * kLn2;
+    const int32_t above = hi - max(lo, cap + 1) + 1;              // rows that see the whole window
+    if (above > 0) r.inv += (float)above / (float)cap;
+}
+__device__ __forceinline__ int32_t precise_keys_of(const RowSums& r)   // (every lane's rows)
+{
+    const float rows = wave_sum_moves(r.rows), inv = wave_sum_moves(r.inv);
+    const float h = inv > 0.f ? rows / inv : 0.f;
+    return max(kPreciseKeys, (int32_t)fminf(kPreciseShare * h, 1.0e9f));
+}
+
 // Row tile number `index` of those that the call has, from the last ones of every sequence to the first (at most 64 sequences).
 // Without it the grid has a workgroup for every tile of the longest query range in every sequence, and the ones that a shorter
 // sequence does not have come first: they end at once, but workgroups go to the shader engines of a chiplet in turn and each
@@ -1071,7 +1094,7 @@ __device__ __forceinline__ bool locate_live(WorkItem& own, int32_t& precise_keys
 
 // Both instantiations live in one kernel as two separate code paths (each with its own tile loop); a
 // workgroup runs exactly one of them, decided by its context length.
-// LIST: kSlotList, the work-list mode of prefill_tiles.h; kPlainGrid; or kLengthGrid (with plan.chunk_unit or plan.live; an instantiation of its own: deciding it
+// LIST: kSlotList, the work-list mode of prefill_tiles.h; kPlainGrid; or kLengthGrid (chunks or plan.live; an instantiation of its own: deciding it
 // here scattered the first loads and cost a prompt of 128 tokens 0.4 us of 9).
 // Waves a SIMD: two, three at head_dim 64.  Hooks that keep more state spill under that bound: document masks and user
 // modifications 4 - 6 registers at head_dim 64, 12 and 24 at 256, slopes 7 at 256, and nothing at 128.  us for 4 x 2048, 2 x 1200 and
@@ -1103,8 +1126,10 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
                                                batch, num_q_heads, max_blocks, scale, causal, plan, list, blockIdx.x, gridDim.x);
     } else {
         // Workgroups are dispatched in blockIdx.x order: the row-tile index is the slowest-varying part and runs
-        // backwards, so the whole grid is handed out heaviest (latest causal tiles) first; the context chunks of a
-        // tile follow each other.  Where contexts are cut by their own lengths (kLengthGrid) they are much longer than the query
+        // backwards, so the whole grid is handed out heaviest (latest causal tiles) first.  With chunks (kLengthGrid) all row
+        // tiles of a context chunk precede the next chunk's, whose first ones have no keys there: chunk beside chunk those would
+        // recur at one place in every few workgroups (see locate_live; 3000 tokens in two chunks, 16 / 8 heads, head_dim 256, 169
+        // -> 145 us, 20 sequences of which two have 128 queries with a cap 231 -> 224).  Where contexts are cut by their own lengths (kLengthGrid) they are much longer than the query
         // ranges and no tile is heavy: there the sequence is the slowest part, so that the workgroups with keys stand side by
         // side and get a compute unit each, whatever is empty between them (128 queries on 32768 keys and on 2000 three times
         // 206 -> 119 us, 256 on 32768 and on 16000 285 -> 224, 500 on 2048 in a call for up to 32768 65 -> 42).  In a
@@ -1114,42 +1139,51 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
         WorkItem own;
         const int32_t heads = num_q_heads >> plan.log2_pack;
         constexpr bool kByLength = LIST == kLengthGrid;
-        const int32_t hb = heads * (kByLength ? 1 : batch);      // (by length and live: the sequence is not beside the heads)
+        const int32_t hb = heads * (kByLength ? 1 : batch);
         const int32_t slow = (int32_t)(blockIdx.x / (uint32_t)hb);
         const int32_t rest = (int32_t)(blockIdx.x % (uint32_t)hb);
         own.hg = rest % heads;
-        const int32_t each = num_tiles * plan.nsplit;        // (kByLength: row tiles and chunks of a sequence)
+        own.chunks = plan.nsplit;
+        own.chunk = plan.chunk;
+        own.slot = -1;
+        int32_t precise_keys = 0;
         if constexpr (kByLength) {
-            own.s = slow / each;
+            if (plan.live) {
+                own.split = 0;
+                if (!locate_live(own, precise_keys, slow, num_tiles, cu_q_lens, seq_lens, batch, causal,
+                                 (M::kWindow && plan.mods.window > 0) ? plan.mods.window : 0, plan)) return;
+            } else {
+                const int32_t each = num_tiles * plan.nsplit;    // (by length: row tiles and chunks of a sequence)
+                const int32_t of_all = slow / batch;
+                own.s = plan.chunk_unit > 0 ? slow / each : slow - of_all * batch;
+                own.q_begin = cu_q_lens[own.s];
+                own.q_end = cu_q_lens[own.s + 1];
+                own.len = seq_lens[own.s];
+                if (plan.chunk_unit > 0) {
+                    own.chunk = sequence_chunk(own.len, plan.chunk, plan.nsplit, plan.chunk_unit);
+                    const int32_t live = max((own.len + own.chunk - 1) / own.chunk, 1), part = slow - own.s * each;
+                    const int32_t per = batch == 1 ? live : num_tiles, quot = part / per, rem = part - quot * per;
+                    own.tile = num_tiles - 1 - (batch == 1 ? quot : rem);
+                    own.split = batch == 1 ? rem : quot;
+                    if (own.tile < 0) return;                    // (beyond a single sequence's chunks)
+                } else {
+                    own.split = of_all / num_tiles;
+                    own.tile = num_tiles - 1 - (of_all - own.split * num_tiles);
+                }
+            }
         } else {
             own.s = rest / heads;
             own.tile = num_tiles - 1 - slow / plan.nsplit;
             own.split = slow % plan.nsplit;
-        }
-        own.chunks = plan.nsplit;
-        own.chunk = plan.chunk;
-        own.slot = -1;
-        if (!kByLength || !plan.live) {
             own.q_begin = cu_q_lens[own.s];
             own.q_end = cu_q_lens[own.s + 1];
             own.len = seq_lens[own.s];
         }
-        const int32_t window = (M::kWindow && plan.mods.window > 0) ? plan.mods.window : 0;
-        int32_t precise_keys = 0;
-        if (kByLength && plan.live) {
-            own.split = 0;
-            if (!locate_live(own, precise_keys, slow, num_tiles, cu_q_lens, seq_lens, batch, causal, window, plan)) return;
-        } else if constexpr (kByLength) {
-            own.chunk = sequence_chunk(own.len, plan.chunk, plan.nsplit, plan.chunk_unit);
-            const int32_t live = max((own.len + own.chunk - 1) / own.chunk, 1), part = slow - own.s * each;
-            const int32_t per = batch == 1 ? live : num_tiles, quot = part / per, rem = part - quot * per;
-            own.tile = num_tiles - 1 - (batch == 1 ? quot : rem);
-            own.split = batch == 1 ? rem : quot;
-            if (own.tile < 0) return;                        // (beyond a single sequence's chunks)
-        }
         if constexpr (!kTwoTermOnly<D>) {
             if (!kByLength || !plan.live)
-                precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal, window, (int)(threadIdx.x & 63));
+                precise_keys = precise_key_bound(cu_q_lens, seq_lens, batch, causal,
+                                                 (M::kWindow && plan.mods.window > 0) ? plan.mods.window : 0,
+                                                 (int)(threadIdx.x & 63));
             prefill_body<false, UNIFORM, kPlainGrid, false, E, M, D>(buf0, buf1, docs0, docs1, cache, q, out, lse, block_table, num_q_heads,
                                                         max_blocks, scale, causal, plan, precise_keys, own, (int)threadIdx.x);
         }
@@ -1169,7 +1203,7 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
 
 // The plain grid's kernel in the order that the plan asks for.
 #define PA_GRID_KERNEL(UNIFORM, E, M)                                                                                  \
-    (plan.chunk_unit > 0 || plan.live ? paged_prefill_mfma_kernel<UNIFORM, E, M, D, kLengthGrid> : paged_prefill_mfma_kernel<UNIFORM, E, M, D>)
+    (plan.nsplit > 1 || plan.live ? paged_prefill_mfma_kernel<UNIFORM, E, M, D, kLengthGrid> : paged_prefill_mfma_kernel<UNIFORM, E, M, D>)
 
 // Every kernel instantiation of one head_dim; defined in that head_dim's translation unit.
 template <int D>

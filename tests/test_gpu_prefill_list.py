@@ -332,3 +332,27 @@ def test_a_grid_of_the_row_tiles_that_there_are(pa, oracle, lens, q_lens, Hq, Hk
     w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=P,
                         dtype=dtype, causal=causal, seed=221, device=DEV)
     parity.check_step(pa, oracle, w, f"{lens} {q_lens} {d}", mods=build_mods(hooks, Hq, lens) if hooks else None)
+
+
+@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,d,P,dtype,causal,hooks", [
+    ([1025], [1025], 8, 1, 128, 16, torch.bfloat16, True, None),                # the last chunk holds one key
+    ([1000], [900], 8, 1, 128, 128, torch.float16, False, None),                # every row tile reaches into every chunk
+    ([1100, 640], [1100, 640], 8, 1, 64, 16, torch.bfloat16, True, dict(alibi=True)),
+    ([1000], [1000], 8, 1, 256, 32, torch.float16, True, dict(softcap=30.0)),
+    ([1900], [1900], 8, 1, 128, 16, torch.bfloat16, True, dict(window=1500, softcap=30.0)),     # windows begin in a later chunk
+    ([1300], [1000], 4, 1, 96, 16, torch.bfloat16, True, None),
+    ([1200], [1200], 8, 1, 128, 16, torch.bfloat16, True, dict(docs=True))])
+def test_prompts_of_few_row_tiles_in_chunks(pa, oracle, lens, q_lens, Hq, Hkv, d, P, dtype, causal, hooks):
+    """Whole prompts that leave most of the machine idle are cut along their keys; with the workspace's bound and not more."""
+    from paper_2506_07311_amd import binding
+    from tests.test_gpu_parity import build_mods
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=P,
+                        dtype=dtype, causal=causal, seed=223, device=DEV)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        parity.check_step(pa, oracle, w, f"{lens} {d}", mods=build_mods(hooks, Hq, lens) if hooks else None)
+        assert binding.pa_profile_read("paged_attention_merge_kernel")[0] == 1
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
