@@ -356,3 +356,36 @@ def test_prompts_of_few_row_tiles_in_chunks(pa, oracle, lens, q_lens, Hq, Hkv, d
     finally:
         binding.pa_profile_enable(False)
         binding.pa_profile_reset()
+
+
+@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,d,dtype,kernel", [
+    ([1000], [1000], 8, 1, 128, torch.bfloat16, "paged_attention_merge_kernel"),               # a whole prompt in chunks
+    ([8192], [128], 8, 2, 64, torch.float16, "paged_attention_merge_kernel"),                  # a chunk of a long one
+    ([300, 70, 4000], [1, 1, 200], 32, 8, 128, torch.bfloat16, "paged_jagged_mfma_kernel"),    # by row, beside the stream
+    ([4096, 300], [130, 1], 8, 2, 128, torch.bfloat16, "paged_attention_merge_list_kernel")])
+def test_rows_behind_the_last_sequence_are_left_alone(pa, lens, q_lens, Hq, Hkv, d, dtype, kernel):
+    """A query buffer longer than its sequences' queries (as a captured call has): the merge of a context that is cut writes what
+    the kernels in one piece write."""
+    from paper_2506_07311_amd import binding
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=16,
+                        dtype=dtype, causal=True, seed=224, device=DEV)
+    pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
+    n, pad = w.total_q, 37
+    q = torch.cat([w.q, torch.zeros((pad, Hq, d), dtype=dtype, device=DEV)])
+    out = torch.full_like(q, 7.0)
+    lse = torch.full((n + pad, Hq), 7.0, device=DEV)
+    ws = torch.full((pa.paged_attention_workspace_bytes(w.batch, Hq, d, n + pad, w.max_seq_len),), 0xFF, dtype=torch.uint8,
+                    device=DEV)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        pa.paged_attention_prefill(w.k_cache, w.v_cache, q, w.cu_q_lens, w.max_q_len, w.block_table, w.seq_lens, w.max_seq_len,
+                                   w.scale, True, out=out, lse=lse, workspace=ws)
+        torch.cuda.synchronize()
+        assert binding.pa_profile_read(kernel)[0] == 1
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
+    parity.assert_close(parity.to_f64(out[:n]), parity.to_f64(_reference(w)), dtype, f"{lens}")
+    assert torch.isfinite(lse[:n]).all()
+    assert (out[n:] == 7.0).all() and (lse[n:] == 7.0).all()
