@@ -594,7 +594,7 @@ __device__ __forceinline__ void stream_body(
             // l == 0: a row whose causal bound lies before this segment, or none of whose document's keys lie in it
             constexpr bool kMayBeEmpty = RAGGED || M::kDoc;
             const float inv = (!kMayBeEmpty || l > 0.f) ? 1.f / l : 0.f;
-            const float lse_nat = (!kMayBeEmpty || l > 0.f) ? (st.m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
+            const float lse_nat = kMayBeEmpty && l <= 0.f ? -INFINITY : (st.m + __builtin_amdgcn_logf(l)) * kLn2;
             if (whole) {
 #pragma unroll
                 for (int c = 0; c < GE::kPasses; ++c)
@@ -873,7 +873,7 @@ __global__ __launch_bounds__(NW * 64) void paged_decode_short_kernel(
         wv.x = E::pack(acc.x * inv, acc.y * inv);
         wv.y = E::pack(acc.z * inv, acc.w * inv);
         *reinterpret_cast<uint2*>(out + (out_row0 + row) * kD + 4 * c4) = wv;
-        if (lse && c4 == 0) lse[out_row0 + row] = sum > 0.f ? (mx + __builtin_amdgcn_logf(sum)) * kLn2 : -INFINITY;
+        if (lse && c4 == 0) lse[out_row0 + row] = sum <= 0.f ? -INFINITY : (mx + __builtin_amdgcn_logf(sum)) * kLn2;
     }
     if (nsplit == 1) return;
 
@@ -947,7 +947,7 @@ __global__ __launch_bounds__(NW * 64) void paged_decode_short_kernel(
         wv.x = E::pack(acc.x * inv, acc.y * inv);
         wv.y = E::pack(acc.z * inv, acc.w * inv);
         *reinterpret_cast<uint2*>(out + (out_row0 + row) * kD + 4 * c4) = wv;
-        if (lse && c4 == 0) lse[out_row0 + row] = sum > 0.f ? (mx + __builtin_amdgcn_logf(sum)) * kLn2 : -INFINITY;
+        if (lse && c4 == 0) lse[out_row0 + row] = sum <= 0.f ? -INFINITY : (mx + __builtin_amdgcn_logf(sum)) * kLn2;
     }
 }
 

@@ -2,11 +2,15 @@
 // With partial c holding the normalised output o_c and lse_c = log sum_j exp(score_j) over its keys,
 //   M = max_c lse_c,  w_c = exp(lse_c - M),  out = sum_c w_c o_c / sum_c w_c,  lse = M + log sum_c w_c.
 // Only the ceil(n_keys / chunk) chunks that hold keys are read; a row without keys gets out = 0, lse = -inf.
+// A chunk whose scores held a NaN says so by a NaN for its LSE, and the row becomes NaN: only LSEs of -inf mean no key.
 #include "prefill_tiles.h"
 
 namespace pa {
 
 namespace {
+
+// An LSE as the maximum over the chunks takes it: a NaN, which fmaxf would drop, as +inf (and its weight is exp(NaN - inf)).
+__device__ __forceinline__ float max_term(float lse) { return lse == lse ? lse : INFINITY; }
 
 // OUT: element type of `out` as a pa_dtype value.
 template <int OUT>
@@ -73,7 +77,7 @@ __device__ __forceinline__ void merge_rows(const RowMerge& p, int64_t o_idx, voi
     const float* po = p.part_o + o_idx * p.nsplit * d;
 
     float M = -INFINITY;
-    for (int32_t c = 0; c < n; ++c) M = fmaxf(M, pl[c]);
+    for (int32_t c = 0; c < n; ++c) M = fmaxf(M, max_term(pl[c]));
     const bool none = M == -INFINITY;            // no chunk holds a visible key (masks can empty every chunk)
     float wsum = 0.f;
     for (int32_t c = 0; c < n && !none; ++c) wsum += expf(pl[c] - M);
@@ -144,7 +148,7 @@ __device__ void merge_list(const ListMerge& p, int32_t block, void* __restrict__
         if (row >= n_rows) continue;                          // (nothing below is shared between lanes)
         const float* pl = p.part_lse + 32 * quarter + (lane & 31);
         float M = -INFINITY;
-        for (int32_t c = 0; c < n; ++c) M = fmaxf(M, pl[(int64_t)list_slot(it, c, p.heads, hg) * kBM]);
+        for (int32_t c = 0; c < n; ++c) M = fmaxf(M, max_term(pl[(int64_t)list_slot(it, c, p.heads, hg) * kBM]));
         const bool none = M == -INFINITY;
         float wsum = 0.f;
         for (int32_t c = 0; c < n && !none; ++c) wsum += expf(pl[(int64_t)list_slot(it, c, p.heads, hg) * kBM] - M);
@@ -218,7 +222,7 @@ __global__ __launch_bounds__(kMergeThreads) void paged_attention_merge_stream_ke
     for (int32_t c = tid; c < n; c += kMergeThreads) {
         const float v = part_lse[p0 + (int64_t)c * rows];
         w_s[c] = v;
-        mx = fmaxf(mx, v);
+        mx = fmaxf(mx, max_term(v));
     }
     mx = wave_max(mx);
     if ((tid & 63) == 0) red[tid >> 6] = mx;

@@ -910,9 +910,8 @@ __device__ __forceinline__ bool prefill_body(
     l += __shfl_xor(l, 32, 64);
     if (!q_valid) return false;
     const float inv = l > 0.f ? 1.f / l : 0.f;
-    // (a NaN among the scores: head_dims 80, 96 and 112 say so, in a partial by +inf, which the merge turns into NaN)
-    const bool bad = kTwoTermOnly<D> && l != l;
-    const float row_lse = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
+    // (a NaN among the scores makes l and the LSE NaN, in a partial too: the merge hands it on)
+    const float row_lse = l <= 0.f ? -INFINITY : (m + __builtin_amdgcn_logf(l)) * kLn2;
     // four columns STEP*i + 4*hh .. +3 of this lane's query: o[t][r] is column 32*t + 8*(r/4) + 4*hh + r%4, or with 16
     // rows a wave column 16*t + 4*hh + r
     constexpr int NC = T * (R / STEP);
@@ -931,8 +930,7 @@ __device__ __forceinline__ bool prefill_body(
         else po += (hh >> 1) * 64 + (hh & 1) * 32 + (16 * wave + ql) % 32;
 #pragma unroll
         for (int i = 0; i < NC; ++i) po[i * (R == 32 ? 64 : 128)] = cols(i);
-        if (hh == 0)
-            plan.list_lse[(int64_t)own.slot * kBM + R * wave + ql] = bad ? INFINITY : row_lse;
+        if (hh == 0) plan.list_lse[(int64_t)own.slot * kBM + R * wave + ql] = row_lse;
         return false;
     }
     if (LIST != kSlotList && own.chunks > 1) {
@@ -944,7 +942,7 @@ __device__ __forceinline__ bool prefill_body(
             if (STEP * i >= D) continue;                     // columns that pad the last block
             *reinterpret_cast<float4*>(prow + STEP * i + 4 * hh) = cols(i);
         }
-        if (hh == 0) plan.part_lse[pidx] = bad ? INFINITY : row_lse;
+        if (hh == 0) plan.part_lse[pidx] = row_lse;
         return false;
     }
     uint16_t* orow = out + row * D;
@@ -954,7 +952,7 @@ __device__ __forceinline__ bool prefill_body(
         const float4 c = cols(i);
         *reinterpret_cast<uint2*>(orow + STEP * i + 4 * hh) = uint2{E::pack(c.x, c.y), E::pack(c.z, c.w)};
     }
-    if (lse && hh == 0) lse[row] = bad ? l : row_lse;
+    if (lse && hh == 0) lse[row] = row_lse;
     return false;
 }
 

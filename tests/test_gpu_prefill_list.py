@@ -389,3 +389,57 @@ def test_rows_behind_the_last_sequence_are_left_alone(pa, lens, q_lens, Hq, Hkv,
     parity.assert_close(parity.to_f64(out[:n]), parity.to_f64(_reference(w)), dtype, f"{lens}")
     assert torch.isfinite(lse[:n]).all()
     assert (out[n:] == 7.0).all() and (lse[n:] == 7.0).all()
+
+
+@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,d,dtype,kernel", [
+    ([1000], [1000], 8, 1, 128, torch.bfloat16, "paged_attention_merge_kernel"),               # a whole prompt in chunks
+    ([2000], [2000], 8, 1, 64, torch.float16, "paged_attention_merge_kernel"),
+    ([1000], [1000], 8, 1, 256, torch.bfloat16, "paged_attention_merge_kernel"),
+    ([1300], [1000], 4, 1, 96, torch.bfloat16, "paged_attention_merge_kernel"),
+    ([8192], [128], 8, 2, 128, torch.bfloat16, "paged_attention_merge_kernel"),                # a chunk of a long one
+    ([300, 70, 4000], [1, 1, 200], 32, 8, 128, torch.bfloat16, "paged_jagged_mfma_kernel"),    # by row, beside the stream
+    ([4096, 6000], [130, 1], 8, 2, 64, torch.float16, "paged_attention_merge_list_kernel"),
+    ([4096, 6000], [130, 1], 8, 4, 128, torch.bfloat16, "paged_jagged_mfma_kernel"),
+    ([20000, 9000, 70, 300], [1, 1, 1, 1], 32, 8, 128, torch.bfloat16, "paged_decode_mfma_kernel"),      # the tile stream
+    ([900, 700, 70, 300], [1, 1, 1, 1], 32, 8, 128, torch.bfloat16, "paged_decode_short_kernel"),        # one launch, split
+    ([500, 300], [500, 300], 32, 8, 128, torch.bfloat16, "paged_prefill_mfma_kernel")])                  # in one piece
+@pytest.mark.parametrize("where", ["q", "k"])
+def test_a_nan_reaches_the_rows_that_see_it_through_every_merge(pa, lens, q_lens, Hq, Hkv, d, dtype, kernel, where):
+    """A NaN in a query makes its row NaN, LSE included, and one in K the rows that see the key: chunks whose scores are all NaN
+    are not taken for chunks without a visible key, nor is the NaN of one chunk lost beside the others."""
+    from paper_2506_07311_amd import binding
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, append_lens=lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=16,
+                        dtype=dtype, causal=True, seed=225, device=DEV)
+    s = max(range(len(lens)), key=lambda i: q_lens[i])
+    cu, G = w.cu_q_lens.tolist(), Hq // Hkv
+    bad = torch.zeros((w.total_q, Hq), dtype=torch.bool, device=DEV)
+    if where == "q":
+        rows = {cu[s], cu[s + 1] - 1, cu[0], cu[-1] - 1}      # (among them a sequence's only row)
+        for r in rows:
+            w.q[r, Hq - 1, 5] = float("nan")
+            bad[r, Hq - 1] = True
+    else:
+        at = lens[s] - q_lens[s] // 2 - 1                     # the half of the queries behind it, on one KV head
+        w.k_new[sum(lens[:s]) + at, 0, 5] = float("nan")
+        bad[cu[s] + max(at - (lens[s] - q_lens[s]), 0):cu[s + 1], :G] = True
+    pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
+    out, lse = torch.zeros_like(w.q), torch.zeros((w.total_q, Hq), device=DEV)
+    ws = torch.full((pa.paged_attention_workspace_bytes(w.batch, Hq, d, w.total_q, w.max_seq_len),), 0x3F, dtype=torch.uint8,
+                    device=DEV)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, w.cu_q_lens, w.max_q_len, w.block_table, w.seq_lens, w.max_seq_len,
+                                   w.scale, True, out=out, lse=lse, workspace=ws)
+        torch.cuda.synchronize()
+        assert binding.pa_profile_read(kernel)[0] == 1
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
+    assert torch.equal(lse.isnan(), bad)
+    assert torch.equal(out.isnan(), bad[..., None].expand_as(out))
+    ref = _reference(w)
+    ref[bad] = 0.0
+    out[bad] = 0.0
+    assert torch.isfinite(lse[~bad]).all()
+    parity.assert_close(parity.to_f64(out), parity.to_f64(ref), dtype, f"{lens}")
