@@ -134,8 +134,10 @@ size_t paged_attention_workspace_bytes(int32_t batch, int32_t num_q_heads, int32
  * in the workspace too), and a captured HIP graph may be replayed like the call.
  * Results repeat bit for bit with the same arguments and workspace size.  How a
  * context is cut, and with it the last bits, can depend on what stands beside a
- * sequence: on batch and max_seq_len, for fp32 pools on workspace_bytes, and in
- * jagged prefill calls on the other sequences' lengths.
+ * sequence: on batch and max_seq_len, for prefill also on total_q, max_q_len and
+ * the hooks, for fp32 pools on workspace_bytes, and in jagged prefill calls on
+ * the other sequences' lengths and on whether the workspace holds the whole
+ * bound of paged_attention_workspace_bytes.
  */
 pa_status paged_attention_decode(const pa_kv_cache_desc* cache, const void* q, void* out, float* lse,
                                  const int32_t* block_table, const int32_t* seq_lens, int32_t batch,
@@ -173,8 +175,9 @@ pa_status paged_attention_decode_static(const pa_kv_cache_desc* cache, const voi
  * q_len_s may be anything from 0 to seq_lens[s] and differ per sequence: a
  * chunk of a long prompt on top of cached context, decode rows (q_len 1) and
  * whole prompts can share one call (the jagged batch of Sec. III-B: sequence
- * ids are implied by the prefix sums).  A call with few query rows over a long
- * context is cut along the context and merged through the workspace.
+ * ids are implied by the prefix sums).  A call whose query rows are too few to
+ * fill the GPU (a chunk on top of a long context, a whole prompt on few heads) is
+ * cut along the context and merged through the workspace.
  */
 pa_status paged_attention_prefill(const pa_kv_cache_desc* cache, const void* q, void* out, float* lse,
                                   const int32_t* cu_q_lens, int32_t total_q, int32_t max_q_len,

@@ -465,7 +465,7 @@ size_t part_lse_bytes(int64_t rows, int32_t hq, int32_t nsplit)
 // 2000 39.2 / 31.5 (2: as many as the workspace holds), 4000 73.7 / 58.7 (3), 69.0 (4); with slopes 600 28.4 / 21.5 (6), 1000
 // 41.9 / 24.7 (4); 600 and 1195 with a cap 39.3 / 32.4 (2); head_dim 256 1000 42.9 / 30.0 (4), 32 / 8 heads and 500 26.9 / 30.5 (2), 16
 // / 8 and 3000 111.6 / 145.3 (2); the estimates are within 10 % of these and of 30 others.
-SplitPlan prompt_split(const AttnArgs& a, int32_t log2_pack, const SplitPlan& given, size_t ws_bytes)
+SplitPlan prompt_split(const AttnArgs& a, int32_t log2_pack, const SplitPlan& given, size_t room)
 {
     const int32_t d = a.cache.head_dim, heads = a.num_q_heads >> log2_pack;
     const int64_t bound = ((((int64_t)a.max_q_len << log2_pack) + 127) / 128) * a.batch;
@@ -488,7 +488,7 @@ SplitPlan prompt_split(const AttnArgs& a, int32_t log2_pack, const SplitPlan& gi
     for (int32_t n = 1; n <= 8; ++n) {
         const int64_t chunk = (((int64_t)a.max_seq_len + n - 1) / n + unit - 1) / unit * unit;
         if (n > 1 && (chunk < 256 || ((int64_t)a.max_seq_len + chunk - 1) / chunk != n)) continue;
-        if (n > 1 && part_o_bytes(a.total_q, a.num_q_heads, d, n) + part_lse_bytes(a.total_q, a.num_q_heads, n) > ws_bytes) break;
+        if (n > 1 && part_o_bytes(a.total_q, a.num_q_heads, d, n) + part_lse_bytes(a.total_q, a.num_q_heads, n) > room) break;
         // (a window's row tiles reach into two chunks)
         const double own = n == 1 || walk < (double)chunk / 64 ? walk : (double)chunk / 64;
         const double live = n == 1 ? wgs : wgs * (windowed ? 2.0 : 1.0 + (n - 1) * part);
@@ -806,7 +806,8 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
                                     cache->page_size, d);
         }
         if (!may_have_small && list_items == 0 && g_opt.prefill_chunk_tokens == 0 && max_seq_len / 2 < max_q_len)
-            pp = prompt_split(a, lg, pp, ws.bytes);
+            // (as many as a workspace of the required size holds, also in a larger one: the same call gives the same bits)
+            pp = prompt_split(a, lg, pp, required_workspace_bytes(batch, num_q_heads, d, total_q, max_seq_len));
         int32_t small_wgs = 0;
         if (may_have_small) {
             const int32_t head_groups = cache->num_kv_heads / decode_mfma_heads_per_wg(cache->num_kv_heads, d);

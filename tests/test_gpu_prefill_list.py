@@ -443,3 +443,24 @@ def test_a_nan_reaches_the_rows_that_see_it_through_every_merge(pa, lens, q_lens
     out[bad] = 0.0
     assert torch.isfinite(lse[~bad]).all()
     parity.assert_close(parity.to_f64(out), parity.to_f64(ref), dtype, f"{lens}")
+
+
+@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,d,dtype", [
+    ([2000], [2000], 8, 1, 128, torch.bfloat16),              # the workspace's bound holds two chunks, the GPU has room for four
+    ([1700], [1600], 8, 1, 128, torch.float16),
+    ([3000], [3000], 8, 1, 256, torch.bfloat16)])
+def test_chunks_of_a_prompt_do_not_depend_on_the_workspace(pa, lens, q_lens, Hq, Hkv, d, dtype):
+    """A workspace that was sized for a larger call gives the same bits as one of the call's own size."""
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=16, dtype=dtype,
+                        causal=True, seed=226, device=DEV)
+    pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
+    nbytes = pa.paged_attention_workspace_bytes(w.batch, Hq, d, w.total_q, w.max_seq_len)
+    res = []
+    for room in (0, 256 << 20):
+        ws = torch.full((nbytes + room,), 0xFF, dtype=torch.uint8, device=DEV)
+        lse = torch.empty((w.total_q, Hq), device=DEV)
+        out = pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, w.cu_q_lens, w.max_q_len, w.block_table, w.seq_lens,
+                                         w.max_seq_len, w.scale, True, lse=lse, workspace=ws)
+        res.append((out, lse, int((ws.view(torch.int32) != -1).sum())))
+    assert res[0][2] == res[1][2] > 0                         # as many words of partials
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
