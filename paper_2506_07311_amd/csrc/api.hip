@@ -864,7 +864,7 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
                 st = launch_jagged_mfma(b, c, device_cus(), s);
                 return st != PA_OK ? st : launch_merge(c, s);
             }
-            st = launch_prefill_mfma(b, s);
+            st = launch_prefill_mfma(b, device_cus(), s);
             if (st != PA_OK) return st;
             if (list_cuts && !may_have_small) return launch_merge(a, s);
         }

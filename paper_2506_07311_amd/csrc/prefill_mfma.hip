@@ -96,7 +96,7 @@ PrefillPlan prefill::make_plan(const AttnArgs& a)
     return plan;
 }
 
-pa_status launch_prefill_mfma(const AttnArgs& a, hipStream_t stream)
+pa_status launch_prefill_mfma(const AttnArgs& a, int32_t cus, hipStream_t stream)
 {
     PrefillPlan plan = make_plan(a);
     if (plan.nsplit > 1 && (plan.chunk % kBN != 0 || plan.chunk % a.cache.page_size != 0)) return PA_ERR_INVALID_ARG;
@@ -105,24 +105,29 @@ pa_status launch_prefill_mfma(const AttnArgs& a, hipStream_t stream)
     const int32_t heads = a.num_q_heads >> plan.log2_pack;
     int64_t row_tiles = tiles * a.batch;
     // Sequences with fewer queries than the longest leave gaps in a grid of the longest's row tiles.  Gaps that fall on the
-    // same shader engines again and again (four to a chiplet, dealt workgroups in turn: as they do unless a sequence's head
-    // groups go round evenly) leave their compute units idle while the others have a queue (locate_live); without gaps a
-    // workgroup starts 0.5 us later, which shows where the longest walk is a few tiles.  us with gaps / without: prompts of 2059
-    // and 3146 tokens, 16 / 8 heads, head_dim 256, 228 / 181, with a window and a cap 181 / 152 (append included); 32 / 8
-    // heads, 8 of 300 .. 1000 85 / 65, 4 of 947 .. 1894 with slopes 153 / 110, 2 of 3000 .. 4096 with 64 / 8 403 / 381, 2 of 387 ..
-    // 1162 31.2 / 31.8; 16 of 60 .. 170, 3 tiles at most, 23.6 / 25.3; 16 of 100 .. 500 with 32 / 32 72.5 / 75.0.
-    const int64_t walk = a.mods.window > 0 && a.mods.window < a.max_seq_len ? a.mods.window : a.max_seq_len;
+    // same shader engines again and again (goes_round) leave their compute units idle while the others have a queue
+    // (locate_live); without gaps a workgroup starts 0.5 us later, which shows where the longest walk is a few tiles and is all there
+    // is to see where the gaps go round.  us with gaps / without, attention alone, 32 / 8 heads: 4 prompts of up to 1546 tokens at
+    // head_dim 256 224 / 106, of up to 2436 500 / 420, 8 of up to 727 with a cap 48 / 41, 16 of up to 738 92 / 84, 4 of up to 838 with
+    // 64 / 8 heads 60 / 34; where they go round, 5 of up to 1359 at head_dim 64 29.1 / 30.9, 3 of up to 3519 with 16 / 2 80 / 84, 15
+    // of up to 675 with 40 / 8 56 / 60.  Of 150 ragged calls 30 lost (1 % in the mean) where the gaps go round, and 56 gained 10 %
+    // elsewhere; the rule still loses with 24 / 8 heads, 4 of up to 1261 at head_dim 64 22.9 / 24.3, and gives up 3 of up to 827 with
+    // 40 / 8 19.9 / 17.4.
+    int64_t window = a.mods.window;
+    if (!a.causal && window > 0) window = 2 * window - 1;    // keys that a row sees
+    const int64_t walk = window > 0 && window < a.max_seq_len ? window : a.max_seq_len;
+    const int64_t most = (((int64_t)a.total_q << plan.log2_pack) / kBM) + a.batch;
     if (plan.list_items == 0 && plan.chunk_unit == 0 && plan.nsplit == 1 && a.batch > 1 && a.batch <= 64 &&
-        (int64_t)a.batch * a.max_q_len != a.total_q && heads % 32 != 0 && row_tiles * heads > 256 && walk >= 8 * kBN) {
+        (int64_t)a.batch * a.max_q_len != a.total_q && most < row_tiles && !goes_round((int64_t)a.batch * heads, heads) &&
+        row_tiles * heads > cus && walk >= 8 * kBN) {
         plan.live = 1;
-        const int64_t most = (((int64_t)a.total_q << plan.log2_pack) / kBM) + a.batch;
-        if (row_tiles > most) row_tiles = most;
+        row_tiles = most;
     }
     int64_t blocks = plan.list_items > 0 ? (int64_t)plan.list_items * heads : row_tiles * plan.nsplit * heads;
     if (plan.list_items > 0 && blocks > kListGrid) blocks = kListGrid;
     if (blocks > 0x7fffffffLL) return PA_ERR_UNSUPPORTED;
     {
-        ProfileScope prof("paged_prefill_mfma_kernel", stream);
+        ProfileScope prof(plan.live ? "paged_prefill_mfma_kernel_live" : "paged_prefill_mfma_kernel", stream);
         pa_status st;
         switch (a.cache.head_dim) {
             case 64: st = launch_prefill_mfma_dim<64>(a, plan, blocks, tiles, stream); break;

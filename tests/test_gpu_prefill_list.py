@@ -1,4 +1,5 @@
 """GPU parity of the prefill kernel's work-list mode: jagged calls whose long contexts are cut into chunks on the device."""
+import numpy as np
 import pytest
 import torch
 
@@ -321,17 +322,102 @@ def test_the_few_query_launches_are_left_out_of_ragged_prompts(pa, oracle, q_len
 @pytest.mark.parametrize("lens,q_lens,Hq,Hkv,d,P,dtype,causal,hooks", [
     # prompts of all tiles, of one row, of none, one row beyond a tile; a lane for every tile index
     ([700, 33, 0, 545, 129, 1], [700, 33, 0, 513, 129, 1], 32, 8, 128, 16, torch.bfloat16, True, None),
-    ([700, 600, 520], [641, 64, 65], 16, 8, 256, 32, torch.float16, True, dict(window=520, softcap=30.0)),
-    ([600] * 3 + [90] * 20, [257] * 3 + [70] * 20, 16, 8, 64, 16, torch.bfloat16, False, None),   # more than 16 sequences
-    ([1100, 600, 70], [1100, 33, 64], 16, 2, 64, 16, torch.float16, True, dict(alibi=True)),      # more than 64 tile indexes
-    ([900, 800, 700, 600], [180, 1, 2, 150], 32, 8, 128, 64, torch.bfloat16, True, dict(window=600)),  # some are the stream's
-    ([600, 700, 70, 650], [600, 20, 70, 300], 12, 12, 128, 16, torch.bfloat16, True, dict(docs=True))])
+    ([700, 600, 520, 9], [641, 64, 65, 0], 16, 8, 256, 32, torch.float16, True, dict(window=520, softcap=30.0)),
+    ([600] * 3 + [90] * 21, [257] * 3 + [70] * 21, 16, 8, 64, 16, torch.bfloat16, False, None),   # more than 16 sequences
+    ([1100, 600, 70, 5], [1100, 33, 64, 1], 16, 2, 64, 16, torch.float16, True, dict(alibi=True)),      # more than 64 tile indexes
+    ([900, 800, 700, 600], [300, 1, 2, 250], 32, 8, 128, 64, torch.bfloat16, True, dict(window=600)),  # some are the stream's
+    ([900, 600], [900, 300], 32, 8, 128, 16, torch.float16, False, dict(window=400)),    # a window to both sides: 799 keys
+    ([700, 700, 70, 650], [700, 20, 70, 300], 12, 12, 128, 16, torch.bfloat16, True, dict(docs=True)),
+    ([700, 133, 600, 1], [700, 133, 600, 1], 32, 8, 96, 16, torch.bfloat16, True, None),
+    ([700, 133, 600, 64], [700, 133, 600, 64], 32, 8, 128, 16, torch.bfloat16, True, dict(prefix=True))])
 def test_a_grid_of_the_row_tiles_that_there_are(pa, oracle, lens, q_lens, Hq, Hkv, d, P, dtype, causal, hooks):
     """Ragged batches whose grid leaves out what shorter sequences do not have, in the order of the full grid."""
+    from paper_2506_07311_amd import binding
     from tests.test_gpu_parity import build_mods
     w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=P,
                         dtype=dtype, causal=causal, seed=221, device=DEV)
-    parity.check_step(pa, oracle, w, f"{lens} {q_lens} {d}", mods=build_mods(hooks, Hq, lens) if hooks else None)
+    mods = build_mods(hooks, Hq, lens) if hooks else None
+    if hooks and "prefix" in hooks:                           # a user modification
+        mods = dict(prefix_lens=np.array([n // 2 for n in lens], dtype=np.int32), prefix_bias=0.5)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        parity.check_step(pa, oracle, w, f"{lens} {q_lens} {d}", mods=mods)
+        assert binding.pa_profile_read("paged_prefill_mfma_kernel_live")[0] == 1
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,live", [
+    ([900, 400], 32, 8, 1),                                    # 8 head groups: every second shader engine
+    ([900, 400, 400], 32, 8, 0),                               # 24 a tile index: each sequence meets all four in turn
+    ([900, 400, 400, 300], 32, 8, 1),                          # always the same one
+    ([900, 400, 400, 300, 300], 32, 8, 0),
+    ([900, 400, 400, 300, 300, 300], 32, 8, 1),
+    ([900, 400], 32, 32, 0),                                   # all of them in every sequence
+    ([900, 400, 300], 16, 2, 0),
+    ([900, 400, 300, 300], 16, 2, 1),
+    ([900, 897], 32, 8, 0)])                                   # no gaps
+def test_gaps_that_go_round_stay_in_the_grid(pa, lens, Hq, Hkv, live):
+    """A grid without gaps costs its workgroups a later start: only where the gaps would keep the same shader engines idle.  The
+    same bits in either grid, here against one in which 70 sequences without queries keep the full grid."""
+    from paper_2506_07311_amd import binding
+    w = W.make_workload("t", seq_lens=lens, q_lens=lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=64, page_size=16,
+                        dtype=torch.bfloat16, causal=True, seed=227, device=DEV)
+    pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
+    pad = torch.nn.functional.pad
+    more = (pad(w.cu_q_lens, (0, 70), value=w.total_q), pad(w.block_table, (0, 0, 0, 70)), pad(w.seq_lens, (0, 70)))
+    res = []
+    for cu, table, n in ((w.cu_q_lens, w.block_table, w.seq_lens), more):
+        binding.pa_profile_reset()
+        binding.pa_profile_enable(True)
+        binding.pa_set_option("no_small_q_route", 1)
+        try:
+            lse = torch.empty((w.total_q, Hq), device=DEV)
+            out = pa.paged_attention_prefill(w.k_cache, w.v_cache, w.q, cu, w.max_q_len, table, n, w.max_seq_len, w.scale, True,
+                                             lse=lse)
+            torch.cuda.synchronize()
+            counts = [binding.pa_profile_read(k)[0] for k in ("paged_prefill_mfma_kernel_live", "paged_prefill_mfma_kernel",
+                                                              "paged_attention_merge")]
+            assert counts == [live if cu is w.cu_q_lens else 0, 1, 0]
+        finally:
+            binding.pa_set_option("no_small_q_route", 0)
+            binding.pa_profile_enable(False)
+            binding.pa_profile_reset()
+        res.append((out, lse))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+    parity.assert_close(parity.to_f64(res[0][0]), parity.to_f64(_reference(w)), torch.bfloat16, f"{lens}")
+
+
+@pytest.mark.parametrize("window,cap,causal,d", [(0, 0.0, True, 128), (700, 0.0, True, 128), (700, 0.0, False, 64),
+                                                 (0, 0.0, False, 64), (0, 30.0, True, 256)])
+def test_the_two_term_rule_is_one_rule_in_both_grids(pa, window, cap, causal, d):
+    """Which rows carry two-term weights follows from the harmonic mean of the rows' keys, which the two grids' kernels each compute
+    for themselves: prompts around that mean, bit for bit."""
+    from paper_2506_07311_amd import binding
+    lens, q_lens = [1500, 1100, 700, 400], [1000, 1100, 300, 400]
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=16, num_kv_heads=8, head_dim=d, page_size=16,
+                        dtype=torch.bfloat16, causal=causal, seed=228, device=DEV)
+    pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
+    pad = torch.nn.functional.pad
+    more = (pad(w.cu_q_lens, (0, 61), value=w.total_q), pad(w.block_table, (0, 0, 0, 61)), pad(w.seq_lens, (0, 61)))
+    outs = []
+    for live, (cu, table, n) in ((1, (w.cu_q_lens, w.block_table, w.seq_lens)), (0, more)):
+        binding.pa_profile_reset()
+        binding.pa_profile_enable(True)
+        binding.pa_set_option("no_small_q_route", 1)
+        try:
+            outs.append(pa.paged_attention_prefill_mod(w.k_cache, w.v_cache, w.q, cu, w.max_q_len, table, n, w.max_seq_len, w.scale,
+                                                       causal, window=window, softcap=cap))
+            torch.cuda.synchronize()
+            counts = [binding.pa_profile_read(k)[0] for k in ("paged_prefill_mfma_kernel_live", "paged_attention_merge")]
+            assert counts == [live, 0]
+        finally:
+            binding.pa_set_option("no_small_q_route", 0)
+            binding.pa_profile_enable(False)
+            binding.pa_profile_reset()
+    assert torch.equal(outs[0], outs[1])
 
 
 @pytest.mark.parametrize("lens,q_lens,Hq,Hkv,d,P,dtype,causal,hooks", [
