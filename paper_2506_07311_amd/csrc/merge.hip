@@ -68,8 +68,8 @@ __device__ __forceinline__ void merge_rows(const RowMerge& p, int64_t o_idx, voi
     if (o_idx >= p.pairs) return;
     const int lane = threadIdx.x & 31;
     const int32_t row = (int32_t)(o_idx / num_q_heads);
-    if (cu_q_lens && row >= cu_q_lens[p.batch]) return;  // rows that pad the buffers: nobody left partials for them
     const RowInfo ri = locate_row(cu_q_lens, seq_lens, p.batch, row, p.causal);
+    if (ri.pos >= ri.len) return;                        // behind the last sequence: rows that pad the buffers
     const int32_t own = sequence_chunk(ri.len, p.chunk, p.nsplit, p.unit);
     if (p.final_group > 0 && (ri.q_len * p.final_group <= 16 || own >= ri.len)) return;
     const int32_t n = (ri.n_keys + own - 1) / own;       // chunks that hold keys
