@@ -227,6 +227,8 @@ inline bool goes_round(int64_t every, int64_t own)
     }
     return turns * own % 32 == 0;
 }
+// Are the chunks of a row tile neighbours in the grid of a call in `nsplit` chunks?
+bool prefill_chunks_by_tile(const AttnArgs& a, int32_t nsplit, int32_t cus);
 int32_t jagged_mfma_stream_wgs(const AttnArgs& a, int32_t cus);
 pa_status launch_jagged_mfma(const AttnArgs& a, const AttnArgs& s, int32_t cus, hipStream_t stream);
 // Its work-list mode (prefill_tiles.h): partial slots and floats per slot (plus 128 LSEs), the shortest context it may

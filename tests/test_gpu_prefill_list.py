@@ -550,3 +550,25 @@ def test_chunks_of_a_prompt_do_not_depend_on_the_workspace(pa, lens, q_lens, Hq,
         res.append((out, lse, int((ws.view(torch.int32) != -1).sum())))
     assert res[0][2] == res[1][2] > 0                         # as many words of partials
     assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+
+
+@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,d,P,causal,hooks,order", [
+    ([2366], [2366], 8, 1, 256, 16, True, dict(docs=True), "by_tile"),                         # three chunks, one head group
+    ([4589], [500], 64, 8, 128, 16, True, dict(window=256), "last_chunk_first"),               # four, most without keys
+    ([6000] * 2, [300] * 2, 8, 1, 128, 64, False, dict(window=700), "last_chunk_first"),        # windows to both sides
+    ([5000, 2100, 33], [64] * 2 + [33], 16, 8, 256, 16, True, dict(window=1024, softcap=30.0), "by_tile"),     # unequal queries
+    ([3500, 2100, 700], [130, 1, 70], 8, 8, 64, 16, True, dict(window=900, alibi=True), "by_tile")])           # some the stream's
+def test_orders_of_chunks(pa, oracle, lens, q_lens, Hq, Hkv, d, P, causal, hooks, order):
+    """The three orders in which a grid hands out row tiles and chunks; the fourth has the cases of prompts in chunks."""
+    from paper_2506_07311_amd import binding
+    from tests.test_gpu_parity import build_mods
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=P,
+                        dtype=torch.bfloat16, causal=causal, seed=229, device=DEV)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        parity.check_step(pa, oracle, w, f"{lens} {d}", mods=build_mods(hooks, Hq, lens) if hooks else None)
+        assert binding.pa_profile_read("paged_prefill_mfma_kernel_" + order)[0] == 1
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
