@@ -134,10 +134,10 @@ size_t paged_attention_workspace_bytes(int32_t batch, int32_t num_q_heads, int32
  * in the workspace too), and a captured HIP graph may be replayed like the call.
  * Results repeat bit for bit with the same arguments and workspace size.  How a
  * context is cut, and with it the last bits, can depend on what stands beside a
- * sequence: on batch and max_seq_len, for prefill also on total_q, max_q_len and
- * the hooks, for fp32 pools on workspace_bytes, and in jagged prefill calls on
- * the other sequences' lengths and on whether the workspace holds the whole
- * bound of paged_attention_workspace_bytes.
+ * sequence: on batch and max_seq_len, for prefill also on total_q, max_q_len,
+ * the hooks and whether the workspace holds the whole bound of
+ * paged_attention_workspace_bytes, for fp32 pools on workspace_bytes, and in
+ * jagged prefill calls on the other sequences' lengths.
  */
 pa_status paged_attention_decode(const pa_kv_cache_desc* cache, const void* q, void* out, float* lse,
                                  const int32_t* block_table, const int32_t* seq_lens, int32_t batch,

@@ -805,9 +805,12 @@ pa_status run_attention(const pa_kv_cache_desc* cache, const void* q, void* out,
             pp = even_prefill_split(pp, batch, tiles * (num_q_heads >> lg), (int64_t)total_q * num_q_heads, max_seq_len,
                                     cache->page_size, d);
         }
-        if (!may_have_small && list_items == 0 && g_opt.prefill_chunk_tokens == 0 && max_seq_len / 2 < max_q_len)
-            // (as many as a workspace of the required size holds, also in a larger one: the same call gives the same bits)
-            pp = prompt_split(a, lg, pp, required_workspace_bytes(batch, num_q_heads, d, total_q, max_seq_len));
+        if (!may_have_small && list_items == 0 && g_opt.prefill_chunk_tokens == 0 && max_seq_len / 2 < max_q_len) {
+            // (as many as the whole bound holds, or else what is required, also in a larger workspace: the same call gives the same
+            // bits.  Two prompts of 4200 tokens, 4 / 1 heads, head_dim 64, slopes: 5 chunks in the bound 75 us, 4 in what is required 81)
+            const size_t bound = paged_attention_workspace_bytes(batch, num_q_heads, d, total_q, max_seq_len);
+            pp = prompt_split(a, lg, pp, ws.bytes >= bound ? bound : required_workspace_bytes(batch, num_q_heads, d, total_q, max_seq_len));
+        }
         int32_t small_wgs = 0;
         if (may_have_small) {
             const int32_t head_groups = cache->num_kv_heads / decode_mfma_heads_per_wg(cache->num_kv_heads, d);

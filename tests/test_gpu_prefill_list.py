@@ -572,3 +572,23 @@ def test_orders_of_chunks(pa, oracle, lens, q_lens, Hq, Hkv, d, P, causal, hooks
     finally:
         binding.pa_profile_enable(False)
         binding.pa_profile_reset()
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d,causal,hooks,n", [
+    ([700, 4500], 4, 1, 64, True, dict(alibi=True), 8),       # more than what is required of a workspace holds
+    ([33, 4200], 4, 1, 128, True, dict(softcap=30.0), 6)])
+def test_the_number_of_chunks_of_prompts(pa, oracle, lens, Hq, Hkv, d, causal, hooks, n):
+    """How many chunks prompts get with the bound's workspace: the last row, which sees all of them, ends what is written to it."""
+    from tests.test_gpu_parity import alibi, build_mods
+    w = W.make_workload("t", seq_lens=lens, q_lens=lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=16,
+                        dtype=torch.bfloat16, causal=causal, seed=230, device=DEV)
+    parity.check_step(pa, oracle, w, f"{lens} {d}", mods=build_mods(hooks, Hq, lens))
+    kw = {k: v for k, v in hooks.items() if k != "alibi"}
+    if "alibi" in hooks:
+        kw["alibi_slopes"] = torch.tensor(alibi(Hq), dtype=torch.float32, device=DEV)
+    ws = torch.full((pa.paged_attention_workspace_bytes(w.batch, Hq, d, w.total_q, w.max_seq_len),), 0xFF, dtype=torch.uint8,
+                    device=DEV)
+    pa.paged_attention_prefill_mod(w.k_cache, w.v_cache, w.q, w.cu_q_lens, w.max_q_len, w.block_table, w.seq_lens, w.max_seq_len,
+                                   w.scale, causal, workspace=ws, **kw)
+    part_o = -(-w.total_q * Hq * n * d * 4 // 256) * 256
+    assert int((ws.view(torch.int32) != -1).nonzero().max()) + 1 == part_o // 4 + w.total_q * Hq * n
