@@ -501,7 +501,7 @@ SplitPlan prompt_split(const AttnArgs& a, int32_t log2_pack, const SplitPlan& gi
             const double all = wgs / cus * (walk * part * t1 * (slots > 1.0 ? 0.84 : 1.0) + start / slots);
             if (all > us) us = all;
         }
-        if (n > 1 && best.nsplit == 1) us *= 1.05;           // (not for an estimate's margin)
+        if (n > 1) us *= 1.05;                               // (not for an estimate's margin)
         if (us < best_us) {
             best_us = us;
             best.nsplit = n;
