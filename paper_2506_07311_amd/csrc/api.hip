@@ -473,13 +473,14 @@ SplitPlan prompt_split(const AttnArgs& a, int32_t log2_pack, const SplitPlan& gi
     if (tiles > bound) tiles = bound;
     const double cus = device_cus(), wgs = (double)tiles * heads;
     if (given.nsplit == 1 && wgs > cus) return given;
-    const bool windowed = a.mods.window > 0 && a.mods.window < a.max_seq_len;
+    const int64_t window = a.causal || a.mods.window <= 0 ? a.mods.window : 2LL * a.mods.window - 1;   // keys that a row sees
+    const bool windowed = window > 0 && window < a.max_seq_len;
     double t1 = d > 128 ? 2.25 : d == 128 ? 1.05 : d > 96 ? 1.5 : d > 80 ? 1.28 : d > 64 ? 1.05 : 0.75;
     if (a.mods.alibi_slopes || a.mods.user_mod) t1 *= 2.0;
     else if (a.mods.doc_ids) t1 *= 1.5;
     if (a.mods.softcap > 0.f) t1 += 0.65;
     const double start = d > 128 ? 7.0 : 6.0, part = a.causal ? 0.5 : 1.0;
-    const double walk = ((windowed ? a.mods.window : a.max_seq_len) + 63) / 64;      // key tiles of the longest row tile
+    const double walk = (double)(((windowed ? window : a.max_seq_len) + 63) / 64);      // key tiles of the longest row tile
     const double slots = d > 128 ? 1.0 : d > 64 ? 2.0 : 3.0;
     const int64_t unit = a.cache.page_size > 64 ? a.cache.page_size : 64;
     const double mb = (double)a.total_q * a.num_q_heads * d * 4e-6;

@@ -577,14 +577,22 @@ def test_orders_of_chunks(pa, oracle, lens, q_lens, Hq, Hkv, d, P, causal, hooks
 @pytest.mark.parametrize("lens,Hq,Hkv,d,causal,hooks,n", [
     ([700, 4500], 4, 1, 64, True, dict(alibi=True), 8),       # more than what is required of a workspace holds
     ([33, 4200], 4, 1, 128, True, dict(softcap=30.0), 6),
+    ([1000], 8, 1, 128, False, dict(window=700), 4),          # a window to both sides: all 1000 keys for most rows
+    ([900], 8, 1, 128, True, dict(prefix=True), 4),           # a user modification
     ([1025], 8, 1, 128, True, {}, 3)])                        # four are estimated within a margin behind three
 def test_the_number_of_chunks_of_prompts(pa, oracle, lens, Hq, Hkv, d, causal, hooks, n):
     """How many chunks prompts get with the bound's workspace: the last row, which sees all of them, ends what is written to it."""
+    from paper_2506_07311_amd import binding
     from tests.test_gpu_parity import alibi, build_mods
     w = W.make_workload("t", seq_lens=lens, q_lens=lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=16,
                         dtype=torch.bfloat16, causal=causal, seed=230, device=DEV)
-    parity.check_step(pa, oracle, w, f"{lens} {d}", mods=build_mods(hooks, Hq, lens) if hooks else None)
-    kw = {k: v for k, v in hooks.items() if k != "alibi"}
+    mods = build_mods(hooks, Hq, lens) if hooks else None
+    kw = {k: v for k, v in hooks.items() if k not in ("alibi", "prefix")}
+    if "prefix" in hooks:
+        mods = dict(prefix_lens=np.array([m // 2 for m in lens], dtype=np.int32), prefix_bias=0.5)
+        prefix = torch.tensor(mods["prefix_lens"], dtype=torch.int32, device=DEV)
+        kw = dict(user_mod=binding.PA_MOD_PREFIX_LM, user_data=binding.prefix_lm_data(prefix, mods["prefix_bias"]))
+    parity.check_step(pa, oracle, w, f"{lens} {d}", mods=mods)
     if "alibi" in hooks:
         kw["alibi_slopes"] = torch.tensor(alibi(Hq), dtype=torch.float32, device=DEV)
     ws = torch.full((pa.paged_attention_workspace_bytes(w.batch, Hq, d, w.total_q, w.max_seq_len),), 0xFF, dtype=torch.uint8,
