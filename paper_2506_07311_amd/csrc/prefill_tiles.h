@@ -263,15 +263,18 @@ template <bool SPLIT_TILES, bool BY_LENGTH = false>
 __device__ __forceinline__ bool list_locate(ListItem& it, const WorkList& w, const int32_t* __restrict__ cu_q_lens,
                                             const int32_t* __restrict__ seq_lens, int32_t idx, int lane)
 {
+    // whole chunks, then the shorter ones: an uncut list has none of the former, contexts cut by their own lengths none of the latter
+    const bool by_length = BY_LENGTH && w.unit > 0;
     int32_t items_before = 0;
-    for (int32_t part = 0; part < (SPLIT_TILES ? 1 : 2); ++part) {
+    for (int32_t part = !SPLIT_TILES && !by_length && w.chunk >= kListUncut ? 1 : 0; part < (SPLIT_TILES || by_length ? 1 : 2);
+         ++part) {
         int32_t slots_before = 0;
         for (int32_t blk = 0; blk < w.batch; blk += 64) {
             const ListSeq q = blk == 0 ? w.own : list_seq(cu_q_lens, seq_lens, w.batch, blk + lane, w.log2_pack, w.small_group);
             const int32_t chunk = list_chunk<BY_LENGTH>(w, q.len);
             const int32_t chunks = max((q.len + chunk - 1) / chunk, 1);
             const int32_t slots = chunks > 1 ? q.tiles * chunks : 0;
-            const int32_t whole = BY_LENGTH && w.unit > 0 ? chunks : q.len / chunk;
+            const int32_t whole = by_length ? chunks : q.len / chunk;
             const int32_t n = SPLIT_TILES ? (chunks > 1 ? q.tiles : 0) : q.tiles * (part == 0 ? whole : chunks - whole);
             const int32_t inc = wave_scan_moves(n), sinc = wave_scan_moves(slots);
             const uint64_t hit = __ballot(items_before + inc > idx);
