@@ -216,19 +216,6 @@ inline size_t arrival_bytes(int64_t units) { return ((size_t)units * kArrivalStr
 bool prefill_mfma_supported(const AttnArgs& a);
 int32_t prefill_mfma_log2_pack(int32_t num_q_heads, int32_t num_kv_heads);
 pa_status launch_prefill_mfma(const AttnArgs& a, int32_t cus, hipStream_t stream);
-// Workgroups go to the eight chiplets in turn and on each to its four shader engines in turn: do `own` workgroups in a row
-// that come every `every` fall on all of these alike?
-inline bool goes_round(int64_t every, int64_t own)
-{
-    int64_t turns = 32;                                      // places until they fall on the same again
-    while (turns > 1 && every % 2 == 0) {
-        turns /= 2;
-        every /= 2;
-    }
-    return turns * own % 32 == 0;
-}
-// Are the chunks of a row tile neighbours in the grid of a call in `nsplit` chunks?
-bool prefill_chunks_by_tile(const AttnArgs& a, int32_t nsplit, int32_t cus);
 int32_t jagged_mfma_stream_wgs(const AttnArgs& a, int32_t cus);
 pa_status launch_jagged_mfma(const AttnArgs& a, const AttnArgs& s, int32_t cus, hipStream_t stream);
 // Its work-list mode (prefill_tiles.h): partial slots and floats per slot (plus 128 LSEs), the shortest context it may

@@ -87,7 +87,7 @@ PrefillPlan prefill::make_plan(const AttnArgs& a)
     plan.group = a.num_q_heads / a.cache.num_kv_heads;
     plan.chunk = a.plan.chunk;
     plan.chunk_unit = a.plan.unit;
-    plan.order = kByChunk;
+    plan.order = kByTile;
     plan.nsplit = a.plan.nsplit;
     plan.skip_small = a.skip_small;
     plan.part_o = a.part_o;
@@ -96,15 +96,26 @@ PrefillPlan prefill::make_plan(const AttnArgs& a)
     return plan;
 }
 
+// Workgroups go to the eight chiplets in turn and on each to its four shader engines in turn: do `own` workgroups in a row
+// that come every `every` fall on all of these alike?
+static bool goes_round(int64_t every, int64_t own)
+{
+    int64_t turns = 32;                                      // places until they fall on the same again
+    while (turns > 1 && every % 2 == 0) {
+        turns /= 2;
+        every /= 2;
+    }
+    return turns * own % 32 == 0;
+}
+
 // Chunk after chunk, the first row tiles of causal prompts, which have no keys in the later chunks, leave no gaps among the others;
 // tile after tile the workgroups that are handed out last have the least to do.  The latter is better where the
 // gaps go round (as with an odd number of chunks on a sequence's one head group) and there is a queue at all.  us chunk after chunk /
 // tile after tile, three chunks, 8 / 1 heads: 4000 tokens at head_dim 64 47.4 / 42.4, with slopes 89 / 72.5, 5000 60 / 55, 2366 at
 // head_dim 256 with documents 83 / 68.5; without a queue 2700 with a cap 43.0 / 44.4, 2500 29.4 / 30.8; where the gaps stay, four
 // chunks of 4000 45 / 56, two of 3131 at head_dim 256 77 / 111.
-bool prefill_chunks_by_tile(const AttnArgs& a, int32_t nsplit, int32_t cus)
+static bool prefill_chunks_by_tile(const AttnArgs& a, int32_t nsplit, int32_t cus)
 {
-    if (a.mods.window > 0 && a.mods.window < a.max_seq_len) return false;
     const int32_t lg = prefill_mfma_log2_pack(a.num_q_heads, a.cache.num_kv_heads), heads = a.num_q_heads >> lg;
     const int64_t most = (((int64_t)a.total_q << lg) / kBM) + a.batch, tiles = plain_row_tiles(a) * a.batch;
     const double live = (double)(tiles < most ? tiles : most) * heads * (1.0 + (nsplit - 1) * (a.causal ? 0.5 : 1.0));
@@ -145,17 +156,23 @@ pa_status launch_prefill_mfma(const AttnArgs& a, int32_t cus, hipStream_t stream
         // chunk after chunk / from the last one on: 500 queries on 4589 keys, window 256, 64 / 8 heads 70 / 52 / 44.5, 1000 on 12406,
         // window 1024, 16 / 8 at head_dim 64 43.0 / 45.4 / 40.3, 256 on 30669 four times, window 256, 8 / 1 56 / 66 / 57 (40 calls in
         // the mean 1 / 0.97 / 0.89); two of 16 with 200 queries, 8 / 8 heads 60.5 / 60.8 / 64.8, one of five with 512 62 / 67 / 59.
-        if (window > 0 && window < a.max_seq_len)
-            plan.order = (int64_t)a.batch * a.max_q_len == a.total_q ? kLastChunkFirst : kByTile;
-        else if (prefill_chunks_by_tile(a, plan.nsplit, cus)) plan.order = kByTile;
+        if (window > 0 && window < a.max_seq_len) {
+            if ((int64_t)a.batch * a.max_q_len == a.total_q) plan.order = kLastChunkFirst;
+        } else if (!prefill_chunks_by_tile(a, plan.nsplit, cus)) {
+            plan.order = kByChunk;
+        }
+    } else if (plan.chunk_unit > 0) {
+        plan.order = kByLengths;
     }
     int64_t blocks = plan.list_items > 0 ? (int64_t)plan.list_items * heads : row_tiles * plan.nsplit * heads;
     if (plan.list_items > 0 && blocks > kListGrid) blocks = kListGrid;
     if (blocks > 0x7fffffffLL) return PA_ERR_UNSUPPORTED;
     {
-        static const char* const kNames[] = {"paged_prefill_mfma_kernel", "paged_prefill_mfma_kernel_live",
-                                             "paged_prefill_mfma_kernel_last_chunk_first", "paged_prefill_mfma_kernel_by_tile"};
-        ProfileScope prof(kNames[plan.order], stream);
+        const char* const name = plan.order == kLiveTiles        ? "paged_prefill_mfma_kernel_live"
+                                 : plan.order == kLastChunkFirst ? "paged_prefill_mfma_kernel_last_chunk_first"
+                                 : plan.order == kByTile && plan.nsplit > 1 ? "paged_prefill_mfma_kernel_by_tile"
+                                                                            : "paged_prefill_mfma_kernel";
+        ProfileScope prof(name, stream);
         pa_status st;
         switch (a.cache.head_dim) {
             case 64: st = launch_prefill_mfma_dim<64>(a, plan, blocks, tiles, stream); break;

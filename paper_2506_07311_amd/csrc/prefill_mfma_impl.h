@@ -1092,7 +1092,7 @@ __device__ __forceinline__ bool locate_live(WorkItem& own, int32_t& precise_keys
 
 // Both instantiations live in one kernel as two separate code paths (each with its own tile loop); a
 // workgroup runs exactly one of them, decided by its context length.
-// LIST: kSlotList, the work-list mode of prefill_tiles.h; kPlainGrid; or kLengthGrid (chunks or kLiveTiles; an instantiation of its own: deciding it
+// LIST: kSlotList, the work-list mode of prefill_tiles.h; kPlainGrid (kByTile); or kLengthGrid (the other orders; an instantiation of its own: deciding it
 // here scattered the first loads and cost a prompt of 128 tokens 0.4 us of 9).
 // Waves a SIMD: two, three at head_dim 64.  Hooks that keep more state spill under that bound: document masks and user
 // modifications 4 - 6 registers at head_dim 64, 12 and 24 at 256, slopes 7 at 256, and nothing at 128.  us for 4 x 2048, 2 x 1200 and
@@ -1127,8 +1127,8 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
         // backwards, so the whole grid is handed out heaviest (latest causal tiles) first.  With chunks (kLengthGrid) all row
         // tiles of a context chunk precede the next chunk's, whose first ones have no keys there: chunk beside chunk those would
         // recur at one place in every few workgroups (see locate_live; 3000 tokens in two chunks, 16 / 8 heads, head_dim 256, 169
-        // -> 145 us, 20 sequences of which two have 128 queries with a cap 231 -> 224; launch_prefill_mfma has the other two
-        // orders).  Where contexts are cut by their own lengths (kLengthGrid) they are much longer than the query
+        // -> 145 us, 20 sequences of which two have 128 queries with a cap 231 -> 224; launch_prefill_mfma says where
+        // another order is taken).  Where contexts are cut by their own lengths (kLengthGrid) they are much longer than the query
         // ranges and no tile is heavy: there the sequence is the slowest part, so that the workgroups with keys stand side by
         // side and get a compute unit each, whatever is empty between them (128 queries on 32768 keys and on 2000 three times
         // 206 -> 119 us, 256 on 32768 and on 16000 285 -> 224, 500 on 2048 in a call for up to 32768 65 -> 42).  In a
@@ -1166,10 +1166,9 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
                     own.split = batch == 1 ? rem : quot;
                     if (own.tile < 0) return;                    // (beyond a single sequence's chunks)
                 } else {
-                    const bool by_tile = plan.order == kByTile;
-                    const int32_t per = by_tile ? plan.nsplit : num_tiles, quot = of_all / per, rem = of_all - quot * per;
-                    own.split = by_tile ? rem : plan.order == kLastChunkFirst ? plan.nsplit - 1 - quot : quot;
-                    own.tile = num_tiles - 1 - (by_tile ? quot : rem);
+                    const int32_t quot = of_all / num_tiles;
+                    own.split = plan.order == kLastChunkFirst ? plan.nsplit - 1 - quot : quot;
+                    own.tile = num_tiles - 1 - (of_all - quot * num_tiles);
                 }
             }
         } else {
@@ -1204,7 +1203,7 @@ __global__ __launch_bounds__(RowGeo<D>::kThreads, D > 64 ? 2 : 3) void paged_pre
 
 // The plain grid's kernel in the order that the plan asks for.
 #define PA_GRID_KERNEL(UNIFORM, E, M)                                                                                  \
-    (plan.nsplit > 1 || plan.order == kLiveTiles ? paged_prefill_mfma_kernel<UNIFORM, E, M, D, kLengthGrid> : paged_prefill_mfma_kernel<UNIFORM, E, M, D>)
+    (plan.order != kByTile ? paged_prefill_mfma_kernel<UNIFORM, E, M, D, kLengthGrid> : paged_prefill_mfma_kernel<UNIFORM, E, M, D>)
 
 // Every kernel instantiation of one head_dim; defined in that head_dim's translation unit.
 template <int D>

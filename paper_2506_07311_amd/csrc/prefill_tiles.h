@@ -115,12 +115,13 @@ struct PrefillPlan {
     float* part_lse;      // [total_q, Hq, nsplit]
     ModArgs mods;         // mask / score hooks (used by the instantiations that have them)
     int32_t chunk_unit;   // > 0: chunks by each sequence's own length instead (sequence_chunk; kLengthGrid, kEitherList)
-    int32_t order;        // of the grid (kLengthGrid without chunk_unit): one of the four below
+    int32_t order;        // of the grid: one of the five below
 };
 
 // All row tiles of a context chunk, then the next chunk's; the row tiles that there are, in one piece (locate_live); chunk after
-// chunk from the last one on; the chunks of a row tile beside each other.
-constexpr int32_t kByChunk = 0, kLiveTiles = 1, kLastChunkFirst = 2, kByTile = 3;
+// chunk from the last one on; row tile after row tile, the chunks of one beside each other, and all that is in one piece; by each
+// sequence's own length (chunk_unit).
+constexpr int32_t kByChunk = 0, kLiveTiles = 1, kLastChunkFirst = 2, kByTile = 3, kByLengths = 4;
 
 PrefillPlan make_plan(const AttnArgs& a);
 
