@@ -140,16 +140,21 @@ pa_status launch_prefill_mfma(const AttnArgs& a, int32_t cus, hipStream_t stream
     // 64 / 8 heads 60 / 34; where they go round, 5 of up to 1359 at head_dim 64 29.1 / 30.9, 3 of up to 3519 with 16 / 2 80 / 84, 15
     // of up to 675 with 40 / 8 56 / 60.  Of 150 ragged calls 30 lost (1 % in the mean) where the gaps go round, and 56 gained 10 %
     // elsewhere; the rule still loses with 24 / 8 heads, 4 of up to 1261 at head_dim 64 22.9 / 24.3, and gives up 3 of up to 827 with
-    // 40 / 8 19.9 / 17.4.
+    // 40 / 8 19.9 / 17.4.  (Up to 64 sequences: a lane for each finds its row tiles.)
+    // Where most of the grid would be gaps, in a call that is mostly decode rows above all, leaving them out is worth it wherever they
+    // fall (queries fill as few sequences as the longest allows: `few` row tiles): 13 sequences, four with 512 queries, 16 / 2
+    // heads, head_dim 64, window and cap, 55 / 41, 49 of which 19 bring up to 512, 8 / 1 heads at 256, 152 / 125, 43 of which two bring
+    // 179, 40 / 8 heads with a cap 44 / 39; 60 such calls 0.973 in the mean, 1.02 at worst.
     int64_t window = a.mods.window;
     if (!a.causal && window > 0) window = 2 * window - 1;    // keys that a row sees
     const int64_t walk = window > 0 && window < a.max_seq_len ? window : a.max_seq_len;
-    const int64_t most = (((int64_t)a.total_q << plan.log2_pack) / kBM) + a.batch;
+    const int64_t full = ((int64_t)a.total_q << plan.log2_pack) / kBM, most = full + a.batch;
+    const int64_t few = full + (a.total_q + a.max_q_len - 1) / a.max_q_len;
     if (plan.list_items == 0 && plan.chunk_unit == 0 && plan.nsplit == 1 && a.batch > 1 && a.batch <= 64 &&
-        (int64_t)a.batch * a.max_q_len != a.total_q && most < row_tiles && !goes_round((int64_t)a.batch * heads, heads) &&
-        row_tiles * heads > cus && walk >= 8 * kBN) {
+        (int64_t)a.batch * a.max_q_len != a.total_q && row_tiles * heads > cus && walk >= 8 * kBN &&
+        (row_tiles > 2 * few || (most < row_tiles && !goes_round((int64_t)a.batch * heads, heads)))) {
         plan.order = kLiveTiles;
-        row_tiles = most;
+        if (row_tiles > most) row_tiles = most;
     } else if (plan.nsplit > 1 && plan.chunk_unit == 0) {
         // A window's keys are in the last chunks of most contexts, and the workgroups of all others end at once: in front of those
         // with keys they only cost their time.  Where query counts differ the chunks stay beside each other.  us tile after tile /

@@ -601,3 +601,23 @@ def test_the_number_of_chunks_of_prompts(pa, oracle, lens, Hq, Hkv, d, causal, h
                                    w.scale, causal, workspace=ws, **kw)
     part_o = -(-w.total_q * Hq * n * d * 4 // 256) * 256
     assert int((ws.view(torch.int32) != -1).nonzero().max()) + 1 == part_o // 4 + w.total_q * Hq * n
+
+
+@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,d,dtype,causal,hooks", [
+    ([300, 700, 90] * 3 + [650, 600, 400, 310], [1] * 9 + [300, 1, 33, 310], 16, 2, 64, torch.bfloat16, True, dict(window=600)),
+    ([600, 33, 5] * 9, [1, 3, 1] * 8 + [179, 33, 5], 40, 8, 128, torch.float16, True, dict(softcap=30.0)),
+    ([700] * 5, [1, 0, 700, 0, 2], 16, 2, 256, torch.bfloat16, False, None)])      # one sequence has them all
+def test_a_grid_of_mostly_gaps(pa, oracle, lens, q_lens, Hq, Hkv, d, dtype, causal, hooks):
+    """Gaps that go round the shader engines are left out all the same where most of the grid would be gaps."""
+    from paper_2506_07311_amd import binding
+    from tests.test_gpu_parity import build_mods
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=16,
+                        dtype=dtype, causal=causal, seed=231, device=DEV)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        parity.check_step(pa, oracle, w, f"{lens} {d}", mods=build_mods(hooks, Hq, lens) if hooks else None)
+        assert binding.pa_profile_read("paged_prefill_mfma_kernel_live")[0] == 1
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
