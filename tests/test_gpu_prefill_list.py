@@ -621,3 +621,22 @@ def test_a_grid_of_mostly_gaps(pa, oracle, lens, q_lens, Hq, Hkv, d, dtype, caus
     finally:
         binding.pa_profile_enable(False)
         binding.pa_profile_reset()
+
+
+@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,d,kernel", [
+    ([769], [769], 8, 1, 256, "paged_attention_merge_kernel"),                     # a prompt in chunks of 256 keys
+    ([4097, 300], [130, 1], 8, 4, 128, "paged_attention_merge_list_kernel"),      # the list: of 1024 keys
+    ([4097, 4097], [64, 64], 8, 2, 64, "paged_attention_merge_kernel")])
+def test_a_last_chunk_of_one_key(pa, oracle, lens, q_lens, Hq, Hkv, d, kernel):
+    """Contexts one key longer than their chunks are."""
+    from paper_2506_07311_amd import binding
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=16,
+                        dtype=torch.bfloat16, causal=True, seed=232, device=DEV)
+    binding.pa_profile_reset()
+    binding.pa_profile_enable(True)
+    try:
+        parity.check_step(pa, oracle, w, f"{lens} {d}")
+        assert binding.pa_profile_read(kernel)[0] == 1
+    finally:
+        binding.pa_profile_enable(False)
+        binding.pa_profile_reset()
