@@ -230,7 +230,8 @@ __global__ __launch_bounds__(kThreads) void paged_attention_generic_kernel(
             if (M::kDoc && doc && doc[j] != my_doc) sj = -INFINITY;
             if (M::kUser) sj = user_score<M>(uc, j, sj);   // in the score type: fp64 for fp32 pools
             sc[jj] = sj;
-            lmax = sj > lmax ? sj : lmax;
+            // (with masks a NaN counts as +inf, which makes the row NaN: nothing but -inf is a row without a visible key)
+            lmax = sj > lmax ? sj : M::kDoc && sj != sj ? (score_t)INFINITY : lmax;
         }
         const score_t m_new = block_max_t(m > lmax ? m : lmax, red_t);
         if (M::kDoc && m_new == -INFINITY) {       // no visible key so far (uniform over the workgroup)
@@ -281,7 +282,7 @@ __global__ __launch_bounds__(kThreads) void paged_attention_generic_kernel(
             part_o[(o_idx * nsplit + split) * d + e] = o;
     }
     if (tid == 0) {
-        const float r = (!M::kDoc || l > 0.f) ? (float)(m + (score_t)logf(l)) : -INFINITY;
+        const float r = M::kDoc && l <= 0.f ? -INFINITY : (float)(m + (score_t)logf(l));
         if (nsplit == 1) { if (lse) lse[o_idx] = r; }
         else part_lse[o_idx * nsplit + split] = r;
     }

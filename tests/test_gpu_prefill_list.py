@@ -640,3 +640,32 @@ def test_a_last_chunk_of_one_key(pa, oracle, lens, q_lens, Hq, Hkv, d, kernel):
     finally:
         binding.pa_profile_enable(False)
         binding.pa_profile_reset()
+
+
+@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,d,dtype", [
+    ([3000, 70], [1, 1], 8, 8, 64, torch.float32),
+    ([600, 70], [600, 70], 8, 8, 64, torch.float32),
+    ([3000, 70], [1, 1], 8, 2, 96, torch.bfloat16),
+    ([700, 70], [64, 1], 8, 2, 96, torch.float16),
+    ([3000, 70], [1, 1], 8, 2, 128, torch.bfloat16),
+    ([3000, 70], [130, 1], 8, 2, 128, torch.bfloat16),
+    ([1000], [1000], 8, 1, 64, torch.float16),
+    ([1000], [1000], 8, 1, 256, torch.bfloat16)])
+@pytest.mark.parametrize("docs", [True, False])
+def test_a_nan_in_a_query_beside_document_masks(pa, lens, q_lens, Hq, Hkv, d, dtype, docs):
+    """Scores that are all NaN or hidden are not taken for a row without a visible key, by any of the kernels."""
+    from tests.test_gpu_parity import doc_ids
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=16,
+                        dtype=dtype, causal=True, seed=233, device=DEV)
+    bad = torch.zeros((w.total_q, Hq), dtype=torch.bool, device=DEV)
+    for r in (0, w.total_q - 1):
+        w.q[r, Hq - 1, 5] = float("nan")
+        bad[r, Hq - 1] = True
+    pa.paged_kv_append(w.k_cache, w.v_cache, w.k_new, w.v_new, w.seq_ids, w.positions, w.block_table)
+    lse = torch.zeros((w.total_q, Hq), device=DEV)
+    ids = torch.tensor(doc_ids(lens, 7), dtype=torch.int32, device=DEV) if docs else None
+    out = pa.paged_attention_prefill_mod(w.k_cache, w.v_cache, w.q, w.cu_q_lens, w.max_q_len, w.block_table, w.seq_lens,
+                                         w.max_seq_len, w.scale, True, lse=lse, doc_ids=ids)
+    assert torch.equal(lse.isnan(), bad)
+    assert torch.equal(out.isnan(), bad[..., None].expand_as(out))
+    assert torch.isfinite(lse[~bad]).all()
