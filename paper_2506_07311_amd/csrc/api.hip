@@ -461,10 +461,12 @@ size_t part_lse_bytes(int64_t rows, int32_t hq, int32_t nsplit)
 // lasts as long as the longest row tile's walk while most of the machine stands by, which costs more than partials and their merge
 // do.  Estimated from the sizes: t1 us for 64 keys of a workgroup alone on its compute unit, up to 1.67 times that beside another,
 // `start` for its start and end, and of the row tiles of causal prompts half a walk on average; the merge 5.5 us and its partials at
-// 3.3 MB a us.  us a call in one piece / in so many, 8 / 1 heads, head_dim 128: 600 tokens 16.4 / 17.2 (2), 1000 22.9 / 19.6 (4),
-// 2000 39.2 / 31.5 (2: as many as the workspace holds), 4000 73.7 / 58.7 (3), 69.0 (4); with slopes 600 28.4 / 21.5 (6), 1000
-// 41.9 / 24.7 (4); 600 and 1195 with a cap 39.3 / 32.4 (2); head_dim 256 1000 42.9 / 30.0 (4), 32 / 8 heads and 500 26.9 / 30.5 (2), 16
-// / 8 and 3000 111.6 / 145.3 (2); the estimates are within 10 % of these and of 30 others.
+// 3.3 MB a us.  us a call in one piece / in so many, 8 / 1 heads, head_dim 128: 1000 tokens 23.1 / 21.2 (4), 2000 40.0 / 34.2 (2: as
+// many as the workspace holds), 4000 73.5 / 60.1 (3); with slopes 600 28.2 / 22.3 (3), 1000 42.0 / 26.2 (4); 600 and 1195 with a cap
+// 39.1 / 32.9 (2); head_dim 256 1000 42.8 / 32.6 (4), 3000 110 / 75 (2).  One piece stays with 600 tokens (16.5), 32 / 8 heads and 500 at
+// 256 (26.3) and 16 / 8 and 3000 (112).  With every number of chunks measured for 100 calls the one chosen is 0.9 % behind the best that
+// the workspace holds, 16 % at worst (443 tokens, 4 / 1 heads, head_dim 256, documents 24.0 / 27.7); of 294 estimates eight in ten are
+// within -14 .. 20 %.
 SplitPlan prompt_split(const AttnArgs& a, int32_t log2_pack, const SplitPlan& given, size_t room)
 {
     const int32_t d = a.cache.head_dim, heads = a.num_q_heads >> log2_pack;
