@@ -63,7 +63,11 @@ void profile_end(hipStream_t stream);
 
 struct ProfileScope {
     hipStream_t s;
-    ProfileScope(const char* kernel, hipStream_t stream) : s(stream) { profile_begin(kernel, stream); }
+    // variant: the kernel's name and what tells this launch of it apart (a reader of the kernel's times asks for its name's prefix)
+    ProfileScope(const char* kernel, hipStream_t stream, const char* variant = nullptr) : s(stream)
+    {
+        profile_begin(variant ? variant : kernel, stream);
+    }
     ~ProfileScope() { profile_end(s); }
 };
 

@@ -173,11 +173,10 @@ pa_status launch_prefill_mfma(const AttnArgs& a, int32_t cus, hipStream_t stream
     if (plan.list_items > 0 && blocks > kListGrid) blocks = kListGrid;
     if (blocks > 0x7fffffffLL) return PA_ERR_UNSUPPORTED;
     {
-        const char* const name = plan.order == kLiveTiles        ? "paged_prefill_mfma_kernel_live"
-                                 : plan.order == kLastChunkFirst ? "paged_prefill_mfma_kernel_last_chunk_first"
-                                 : plan.order == kByTile && plan.nsplit > 1 ? "paged_prefill_mfma_kernel_by_tile"
-                                                                            : "paged_prefill_mfma_kernel";
-        ProfileScope prof(name, stream);
+        static const char* const kOrders[] = {nullptr, "paged_prefill_mfma_kernel_live", "paged_prefill_mfma_kernel_last_chunk_first",
+                                              "paged_prefill_mfma_kernel_by_tile", nullptr};
+        const char* const variant = plan.order == kByTile && plan.nsplit == 1 ? nullptr : kOrders[plan.order];
+        ProfileScope prof("paged_prefill_mfma_kernel", stream, variant);
         pa_status st;
         switch (a.cache.head_dim) {
             case 64: st = launch_prefill_mfma_dim<64>(a, plan, blocks, tiles, stream); break;
