@@ -322,6 +322,22 @@ def test_the_few_query_launches_are_left_out_of_ragged_prompts(pa, oracle, q_len
 @pytest.mark.parametrize("lens,q_lens,Hq,Hkv,d,P,dtype,causal,hooks", [
     # prompts of all tiles, of one row, of none, one row beyond a tile; a lane for every tile index
     ([700, 33, 0, 545, 129, 1], [700, 33, 0, 513, 129, 1], 32, 8, 128, 16, torch.bfloat16, True, None),
+    ([700, 600, 520], [641, 64, 65], 16, 8, 256, 32, torch.float16, True, dict(window=520, softcap=30.0)),
+    ([600] * 3 + [90] * 20, [257] * 3 + [70] * 20, 16, 8, 64, 16, torch.bfloat16, False, None),   # more than 16 sequences
+    ([1100, 600, 70], [1100, 33, 64], 16, 2, 64, 16, torch.float16, True, dict(alibi=True)),      # more than 64 tile indexes
+    ([900, 800, 700, 600], [180, 1, 2, 150], 32, 8, 128, 64, torch.bfloat16, True, dict(window=600)),  # some are the stream's
+    ([600, 700, 70, 650], [600, 20, 70, 300], 12, 12, 128, 16, torch.bfloat16, True, dict(docs=True))])
+def test_a_grid_of_the_row_tiles_that_there_are(pa, oracle, lens, q_lens, Hq, Hkv, d, P, dtype, causal, hooks):
+    """Ragged batches whose grid leaves out what shorter sequences do not have, in the order of the full grid."""
+    from tests.test_gpu_parity import build_mods
+    w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=P,
+                        dtype=dtype, causal=causal, seed=221, device=DEV)
+    parity.check_step(pa, oracle, w, f"{lens} {q_lens} {d}", mods=build_mods(hooks, Hq, lens) if hooks else None)
+
+
+@pytest.mark.parametrize("lens,q_lens,Hq,Hkv,d,P,dtype,causal,hooks", [
+    # prompts of all tiles, of one row, of none, one row beyond a tile; a lane for every tile index
+    ([700, 33, 0, 545, 129, 1], [700, 33, 0, 513, 129, 1], 32, 8, 128, 16, torch.bfloat16, True, None),
     ([700, 600, 520, 9], [641, 64, 65, 0], 16, 8, 256, 32, torch.float16, True, dict(window=520, softcap=30.0)),
     ([600] * 3 + [90] * 21, [257] * 3 + [70] * 21, 16, 8, 64, 16, torch.bfloat16, False, None),   # more than 16 sequences
     ([1100, 600, 70, 5], [1100, 33, 64, 1], 16, 2, 64, 16, torch.float16, True, dict(alibi=True)),      # more than 64 tile indexes
@@ -330,8 +346,8 @@ def test_the_few_query_launches_are_left_out_of_ragged_prompts(pa, oracle, q_len
     ([700, 700, 70, 650], [700, 20, 70, 300], 12, 12, 128, 16, torch.bfloat16, True, dict(docs=True)),
     ([700, 133, 600, 1], [700, 133, 600, 1], 32, 8, 96, 16, torch.bfloat16, True, None),
     ([700, 133, 600, 64], [700, 133, 600, 64], 32, 8, 128, 16, torch.bfloat16, True, dict(prefix=True))])
-def test_a_grid_of_the_row_tiles_that_there_are(pa, oracle, lens, q_lens, Hq, Hkv, d, P, dtype, causal, hooks):
-    """Ragged batches whose grid leaves out what shorter sequences do not have, in the order of the full grid."""
+def test_a_grid_without_gaps_by_its_name(pa, oracle, lens, q_lens, Hq, Hkv, d, P, dtype, causal, hooks):
+    """Ragged batches whose grid leaves out what shorter sequences do not have, which its launch says."""
     from paper_2506_07311_amd import binding
     from tests.test_gpu_parity import build_mods
     w = W.make_workload("t", seq_lens=lens, q_lens=q_lens, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, page_size=P,
