@@ -145,6 +145,11 @@ pa_status launch_prefill_mfma(const AttnArgs& a, int32_t cus, hipStream_t stream
     // fall (queries fill as few sequences as the longest allows: `few` row tiles): 13 sequences, four with 512 queries, 16 / 2
     // heads, head_dim 64, window and cap, 55 / 41, 49 of which 19 bring up to 512, 8 / 1 heads at 256, 152 / 125, 43 of which two bring
     // 179, 40 / 8 heads with a cap 44 / 39; 60 such calls 0.973 in the mean, 1.02 at worst.
+    // So it is where a row tile's keys take long (head_dim 256, a score hook, document masks) unless a sequence has all 32 places: 11 prompts
+    // of up to 989 tokens, 8 / 2 heads, head_dim 256, 69 / 61, 5 of up to 786 with 24 / 8 and a cap 35 / 32, 15 of up to 587 with 8 / 8,
+    // slopes, 256 55 / 50; 48 such calls 0.970 in the mean, 1.02 at worst, 42 others where gaps go round 1.013.
+    const bool costly = (a.cache.head_dim > 128 || a.mods.alibi_slopes || a.mods.user_mod || a.mods.softcap > 0.f ||
+                         a.mods.doc_ids) && heads % 32 != 0;
     int64_t window = a.mods.window;
     if (!a.causal && window > 0) window = 2 * window - 1;    // keys that a row sees
     const int64_t walk = window > 0 && window < a.max_seq_len ? window : a.max_seq_len;
@@ -152,7 +157,7 @@ pa_status launch_prefill_mfma(const AttnArgs& a, int32_t cus, hipStream_t stream
     const int64_t few = full + (a.total_q + a.max_q_len - 1) / a.max_q_len;
     if (plan.list_items == 0 && plan.chunk_unit == 0 && plan.nsplit == 1 && a.batch > 1 && a.batch <= 64 &&
         (int64_t)a.batch * a.max_q_len != a.total_q && row_tiles * heads > cus && walk >= 8 * kBN &&
-        (row_tiles > 2 * few || (most < row_tiles && !goes_round((int64_t)a.batch * heads, heads)))) {
+        (row_tiles > 2 * few || (most < row_tiles && (!goes_round((int64_t)a.batch * heads, heads) || costly)))) {
         plan.order = kLiveTiles;
         if (row_tiles > most) row_tiles = most;
     } else if (plan.nsplit > 1 && plan.chunk_unit == 0) {

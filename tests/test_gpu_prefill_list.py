@@ -345,7 +345,10 @@ def test_a_grid_of_the_row_tiles_that_there_are(pa, oracle, lens, q_lens, Hq, Hk
     ([900, 600], [900, 300], 32, 8, 128, 16, torch.float16, False, dict(window=400)),    # a window to both sides: 799 keys
     ([700, 700, 70, 650], [700, 20, 70, 300], 12, 12, 128, 16, torch.bfloat16, True, dict(docs=True)),
     ([700, 133, 600, 1], [700, 133, 600, 1], 32, 8, 96, 16, torch.bfloat16, True, None),
-    ([700, 133, 600, 64], [700, 133, 600, 64], 32, 8, 128, 16, torch.bfloat16, True, dict(prefix=True))])
+    ([700, 133, 600, 64], [700, 133, 600, 64], 32, 8, 128, 16, torch.bfloat16, True, dict(prefix=True)),
+    # gaps that go round, where a row tile takes long
+    ([900, 400, 300], [900, 400, 300], 32, 8, 64, 16, torch.float16, True, dict(softcap=30.0)),
+    ([900, 700, 1, 400, 300], [900, 700, 1, 400, 300], 16, 8, 256, 16, torch.bfloat16, True, None)])
 def test_a_grid_without_gaps_by_its_name(pa, oracle, lens, q_lens, Hq, Hkv, d, P, dtype, causal, hooks):
     """Ragged batches whose grid leaves out what shorter sequences do not have, which its launch says."""
     from paper_2506_07311_amd import binding
