@@ -96,17 +96,19 @@ PrefillPlan prefill::make_plan(const AttnArgs& a)
     return plan;
 }
 
-// Workgroups go to the eight chiplets in turn and on each to its four shader engines in turn: do `own` workgroups in a row
-// that come every `every` fall on all of these alike?
-static bool goes_round(int64_t every, int64_t own)
+// Workgroups go to the eight chiplets in turn and on each to its four shader engines in turn, 32 places in all.  How often do
+// workgroups that come every `every` of them fall on another place before they are back at the first?
+static int64_t turns(int64_t every)
 {
-    int64_t turns = 32;                                      // places until they fall on the same again
-    while (turns > 1 && every % 2 == 0) {
-        turns /= 2;
+    int64_t n = 32;
+    while (n > 1 && every % 2 == 0) {
+        n /= 2;
         every /= 2;
     }
-    return turns * own % 32 == 0;
+    return n;
 }
+// Do `own` workgroups in a row that come every `every` fall on all places alike?
+static bool goes_round(int64_t every, int64_t own) { return turns(every) * own % 32 == 0; }
 
 // Chunk after chunk, the first row tiles of causal prompts, which have no keys in the later chunks, leave no gaps among the others;
 // tile after tile the workgroups that are handed out last have the least to do.  The latter is better where the
@@ -161,13 +163,17 @@ pa_status launch_prefill_mfma(const AttnArgs& a, int32_t cus, hipStream_t stream
         plan.order = kLiveTiles;
         if (row_tiles > most) row_tiles = most;
     } else if (plan.nsplit > 1 && plan.chunk_unit == 0) {
-        // A window's keys are in the last chunks of most contexts, and the workgroups of all others end at once: in front of those
-        // with keys they only cost their time.  Where query counts differ the chunks stay beside each other.  us tile after tile /
-        // chunk after chunk / from the last one on: 500 queries on 4589 keys, window 256, 64 / 8 heads 70 / 52 / 44.5, 1000 on 12406,
-        // window 1024, 16 / 8 at head_dim 64 43.0 / 45.4 / 40.3, 256 on 30669 four times, window 256, 8 / 1 56 / 66 / 57 (40 calls in
-        // the mean 1 / 0.97 / 0.89); two of 16 with 200 queries, 8 / 8 heads 60.5 / 60.8 / 64.8, one of five with 512 62 / 67 / 59.
+        // A window's keys are in one or two chunks, most of them the last ones of contexts, and the workgroups of all others end at
+        // once: in front of those with keys they only cost their time.  us tile after tile / chunk after chunk / from the last one
+        // on: 500 queries on 4589 keys, window 256, 64 / 8 heads 70 / 52 / 44.5, 1000 on 12406, window 1024, 16 / 8 at head_dim 64
+        // 43.0 / 45.4 / 40.3, 256 on 30669 four times, window 256, 8 / 1 56 / 66 / 57 (40 calls in the mean 1 / 0.97 / 0.89).  Where
+        // query counts differ the chunks stay beside each other while a sequence's row tiles then meet half of the 32 places: eight
+        // sequences of up to 13760 keys, 8 / 1 heads, window 1000, one place, 155 / 68 / 82, four of up to 11738 with 32 / 8 at head_dim
+        // 256, window 2000, cap, eight, 189 / 225 / 147; five of up to 7824 with 8 / 1, window 128, all, 37.3 / 39.9 / 40.6, five of up to
+        // 8838 with 16 / 8, all, 40.6 / 43.9 / 43.0.  50 such calls with fewer places 1 / 0.95 / 0.92, 57 with more 1 / 1.02 / 1.01.
         if (window > 0 && window < a.max_seq_len) {
-            if ((int64_t)a.batch * a.max_q_len == a.total_q) plan.order = kLastChunkFirst;
+            if ((int64_t)a.batch * a.max_q_len == a.total_q || turns((int64_t)a.batch * heads * plan.nsplit) * heads < 16)
+                plan.order = kLastChunkFirst;
         } else if (!prefill_chunks_by_tile(a, plan.nsplit, cus)) {
             plan.order = kByChunk;
         }

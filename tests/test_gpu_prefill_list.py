@@ -575,7 +575,7 @@ def test_chunks_of_a_prompt_do_not_depend_on_the_workspace(pa, lens, q_lens, Hq,
     ([2366], [2366], 8, 1, 256, 16, True, dict(docs=True), "by_tile"),                         # three chunks, one head group
     ([4589], [500], 64, 8, 128, 16, True, dict(window=256), "last_chunk_first"),               # four, most without keys
     ([6000] * 2, [300] * 2, 8, 1, 128, 64, False, dict(window=700), "last_chunk_first"),        # windows to both sides
-    ([5000, 2100, 33], [64] * 2 + [33], 16, 8, 256, 16, True, dict(window=1024, softcap=30.0), "by_tile"),     # unequal queries
+    ([5000, 2100, 33], [64] * 2 + [33], 16, 8, 256, 16, True, dict(window=1024, softcap=30.0), "last_chunk_first"),     # unequal queries, few places
     ([3500, 2100, 700], [130, 1, 70], 8, 8, 64, 16, True, dict(window=900, alibi=True), "by_tile")])           # some the stream's
 def test_orders_of_chunks(pa, oracle, lens, q_lens, Hq, Hkv, d, P, causal, hooks, order):
     """The three orders in which a grid hands out row tiles and chunks; the fourth has the cases of prompts in chunks."""
